@@ -420,8 +420,8 @@ def measure(k: int, steps: int, warmup: int, order: str, calib: Calibration | No
         "llc_resident_bytes_per_step": resident,
         "hbm_frac": round((total_b - resident * steps) / kern_s / 1e9 / HBM_PEAK_GBS, 4),
         "cache_resident": resident >= step_b,
-        "kernels_per_round": ("slot_kernel (one fused pass)" if cfg.grad_dtype == "bf16" else
-                              "slot_kernel; in rounds the library splits, slot_kernel (reduction + "
+        "kernels_per_round": ("chunk_kernel (a small model: everything at once)" if resident >= step_b else
+                              "burst_kernel; in rounds the library splits, burst_kernel (reduction + "
                               "update) then carry_kernel (late gradients into the send buffers)"),
     }
     plain = not (kw.pop("no_exchange", False) or kw.get("stats") or kw.get("unfused") or
@@ -524,7 +524,7 @@ def record_traffic(spec: str) -> int:
         agg = {}
         for r in csv.DictReader(open(path)):
             if r["Counter_Name"] == counter and "eager::" in r["Kernel_Name"]:
-                for tag in ("slot_kernel", "carry_kernel", "copy_kernel"):
+                for tag in ("burst_kernel", "carry_kernel", "copy_kernel"):
                     if tag in r["Kernel_Name"]:
                         agg.setdefault(tag, []).append(float(r["Counter_Value"]))
         return agg
@@ -535,9 +535,9 @@ def record_traffic(spec: str) -> int:
         gib_kib = float(1 << 20)
         fs = gib_kib / (sum(f["copy_kernel"]) / len(f["copy_kernel"]))
         ws = gib_kib / (sum(w["copy_kernel"]) / len(w["copy_kernel"]))
-        rounds = len(f["slot_kernel"])
+        rounds = len(f["burst_kernel"])
         total = 0.0
-        for tag in ("slot_kernel", "carry_kernel"):
+        for tag in ("burst_kernel", "carry_kernel"):
             total += sum(f.get(tag, [])) * fs * 1024 + sum(w.get(tag, [])) * ws * 1024
         # algorithmic bytes of the same rounds (0 .. rounds-1 of the configuration)
         from paper_1908_04207_amd import binding as eb

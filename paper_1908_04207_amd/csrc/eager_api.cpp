@@ -100,18 +100,20 @@ bool use_split(const eager::Launch &l, int P, uint64_t mask, uint64_t valid, int
 {
     if (l.split == 1) return false;
     if (l.split == 2) return true;
-    // Measured on MI355X: a copy that streams one source and one destination at a time
-    // reaches 6.7 TB/s, whereas the same bytes written as several interleaved streams next
-    // to the reduction's reads cost 5-10 % of the round (P = 8, 7 late: 6.1 fused, 6.7 split).
-    // The fused pass wins while few processes are late and all of its streams fit one chunk
-    // of 16 loads, and on short runs, where the second launch costs more than it saves
-    // (25 M elements, P = 8: 7.03 fused against 6.82 TB/s split).  The same holds with bf16
-    // gradients (P = 16, 15 late: 6.43 split against 5.91 TB/s fused on 67 M elements, 6.31
-    // against 6.19 on 1.56e9; P = 16, 2 late, 16 M elements: 6.68 split against 6.71 fused).
+    // Measured on MI355X: a copy that streams one source and one destination at a time reaches
+    // 6.7 TB/s, whereas the same bytes written as several interleaved streams next to the
+    // reduction's reads cost 5-10 % of the round (P = 16, 15 late, 67 M elements: 2.04 ms split, 2.25
+    // fused).  The fused pass wins while few processes are late (P = 8, 4 late: 101 against 104 us on
+    // 8 M elements, 211 against 212 on 17 M, 410 against 403 on 34 M) and on short rounds, where
+    // the second launch costs more than it saves (P = 16: 11.8 against 15.5 us on 262 k elements
+    // with 15 late, 49 against 53 on 2 M with 8 late = 300 MB, but 142 against 132 on 4 M with 15
+    // late = 840 MB).  The same holds with bf16 gradients.
     const uint64_t late = ~mask & low_bits(P);
     const int n_late = popcount64(late);
     if (n_late == 0) return false;
     const int fused_streams = P + popcount64(valid);   // every G_p, every non-empty R_p
+    const int64_t moved = n * 4 * (fused_streams + n_late + 4);
+    if (moved < (int64_t{512} << 20)) return false;
     return fused_streams > 16 || n_late >= 8 || (n_late >= 3 && n >= (int64_t{1} << 25));
 }
 
@@ -201,6 +203,7 @@ int partial_allreduce(eager_ctx *ctx, int want_mode, const eager_plan *plan, uin
     a.w = opt ? opt->params : nullptr;
     a.v = opt ? opt->momentum : nullptr;
     a.recv = recv;
+    a.model = ctx->offset.back() + ctx->numel.back() - ctx->offset.front();
     a.P = P;
     a.elem_bytes = ctx->bf16 ? 2 : 4;
     a.inv_P = 1.0f / static_cast<float>(P);

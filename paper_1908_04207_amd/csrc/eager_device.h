@@ -216,19 +216,23 @@ __device__ __forceinline__ void stats_commit(StatsRecord *records, StatsRecord *
     if ((threadIdx.x & 63u) == 0u) records[wave_index] = rec;
 }
 
-// LDS is not used by the kernel; a dynamic allocation only caps how many workgroups a CU
-// holds at once.  A stream that mixes reads with 30-35 % writes runs 5-10 % faster on
-// MI355X with a few wavefronts per CU, each with 12-16 KiB of loads in flight, than at
-// full occupancy (measured: about 64-110 KiB in flight per CU is the optimum; beyond it
-// HBM throughput falls again).
+// LDS is not used by the kernels; a dynamic allocation only caps how many workgroups a CU
+// holds at once.  A stream that mixes reads and writes is fastest on MI355X with about 26 KiB
+// of loads in flight per CU; beyond it HBM throughput falls again.  LDS is handed out in units of
+// 1280 bytes.
 constexpr int kLdsPerCu = 160 * 1024;
+constexpr int kLdsUnit = 1280;
+constexpr int kCus = 256;
 
 // A grid must hold fewer than 2^32 threads in total; a launch beyond that is not refused
 // by the runtime, its thread count wraps.  Every launcher stays at or below 2^31.
 constexpr long long kMaxGridThreads = 1ll << 31;
 
-// Parameters and momentum above this size are streamed past the caches (see slot_vectors).
+// Parameters and momentum above this size are streamed past the caches (see finish_tile).
 constexpr long long kStateCacheBytes = 256ll << 20;
+
+// A round that moves no more than this works out of the last-level cache (see launch_slots).
+constexpr long long kSmallRoundBytes = 96ll << 20;
 
 template <typename K, typename A, typename... Extra>
 hipError_t launch_capped(K kernel, const A &a, int bpc, const Launch &cfg, dim3 grid,
@@ -236,7 +240,7 @@ hipError_t launch_capped(K kernel, const A &a, int bpc, const Launch &cfg, dim3 
 {
     unsigned lds = 0;
     if (bpc > 0) {
-        lds = static_cast<unsigned>(kLdsPerCu / bpc) & ~2047u;
+        lds = static_cast<unsigned>(kLdsPerCu / bpc / kLdsUnit * kLdsUnit);
         // Kernels of one signature share this function, so the flag is kept per kernel
         // address (a handful of entries; a context is not used from several threads, the
         // mutex covers several contexts).

@@ -91,6 +91,7 @@ struct RoundArgs {
     float *recv;                 // receive buffer (NULL: not wanted)
     long long e0;                // first element of the run (arena index)
     long long n;                 // elements in the run
+    long long model;             // elements of the whole model (first bucket start to last end)
     int P;
     int elem_bytes;              // bytes per gradient element: 4 (fp32) or 2 (bf16)
     float inv_P;                 // 1.0f / (float)P
@@ -101,31 +102,39 @@ struct RoundArgs {
     StatsArgs stats;             // stats.stats == NULL: no by-products
 };
 
-// The same round as the kernel takes it: a list of streams.  Slot k is one stream and one
+// The same round as the kernels take it: a list of streams.  Slot k is one stream and one
 // action; slots are listed in the order in which they enter the sum (ascending rank, send
 // buffer before gradient):
 //   ADD    s = s + x                       (a pending R_p of a late process, or the G_p
 //                                           of an on-time process with an empty buffer)
 //   HOLD   c = x                           (R_p of an on-time process ...)
 //   PAIR   s = s + (c + x)                 (... followed by its G_p)
-//   STORE  dst <- x, nothing added         (G_p of a late process, fused mode only)
+//   SKIP   nothing                         (fills the list up)
 // Streams that need not be read do not appear at all, so no load is wasted.  A stream is
 // fp32 (send buffers; fp32 gradients) or bf16 (bf16 gradients); a lane owns 4 consecutive
-// elements of every stream either way.
+// elements of every stream either way.  The list goes on with the late gradients that the launch
+// copies into their send buffers (COPY, fused rounds; the destinations are listed apart) and
+// ends in SKIPs.  A slot is ONE scalar load for the kernel: the arena base, whose low four bits are
+// zero, with the action and the type in those bits.  What every wavefront reads first stands first.
 constexpr int kMaxSlots = 2 * kMaxP;
-enum SlotKind { kAdd = 0, kHold = 1, kPair = 2, kStore = 3 };
+constexpr int kSlotChunk = 16;
+constexpr int kBurst = 2;              // slots in flight per wavefront of the burst kernel
+enum SlotKind : unsigned {
+    kAdd = 0, kHold = 1, kPair = 2, kSkip = 3, kKindMask = 3,
+    kSlotBf16 = 4,                     // the stream is bf16
+    kSlotCopy = 8,                     // with kSkip: a copy
+    kSlotTag = 15
+};
 struct SlotArgs {
-    const void *src[kMaxSlots];        // arena bases
-    float *dst[kMaxSlots];             // meaningful for STORE slots only
-    unsigned long long kind0[2];       // bit k: low bit of the kind of slot k
-    unsigned long long kind1[2];       // bit k: high bit
-    unsigned long long bf[2];          // bit k: the stream of slot k is bf16
-    int n_slots;
-    float *w, *v, *recv;
     long long e0, n;
+    int n_sum, n_copy;                 // slots of the sum (a multiple of kBurst), copies
+    int waves_per_block, xcd_blocks;   // xcd_blocks: 0, or workgroups per XCD when every XCD takes
+                                       // a contiguous eighth of the run
+    float *w, *v, *recv;
     float inv_P, neg_lr, mu, wd;
     int nesterov;
-    int xcd_map;                       // 1: every XCD takes a contiguous eighth of the run
+    unsigned long long slot[kMaxSlots + kSlotChunk + kBurst];   // a process has at most two slots
+    float *dst[kMaxP];                 // of the copies, in order
     StatsArgs stats;
 };
 
@@ -174,12 +183,12 @@ struct SgdArgs {
 
 struct Launch {
     int block = 64;        // threads per workgroup
-    int chunk = 0;         // streams whose loads are in flight together; 0: 16
+    int chunk = 0;         // slots whose loads are in flight together; 0: chosen from the run
     int split = 0;         // 0: chosen from the round; 1: one fused kernel; 2: reduce+update
                            // kernel followed by a carry (copy) kernel
     int blocks_per_cu = 0; // 0: chosen from the round; -1: no cap; else max workgroups resident per CU
     int nt_state = -1;     // w, v, recv nontemporal: -1 chosen from their size, 0 no, 1 yes
-    int xcd_map = 0;       // slot kernel: 1 = contiguous eighth of the run per XCD
+    int xcd_map = 0;       // round kernels: 1 = contiguous eighth of the run per XCD
     int carry_block = 64;  // carry kernel: threads per workgroup
     int carry_vec = 1;     // carry kernel: lane-vectors per thread and iteration (1, 2, 4)
     int round_stats = 1;           // 0: rounds skip the by-products although statistics are attached
@@ -190,7 +199,7 @@ hipError_t launch_round(const RoundArgs &a, bool bf16, bool fast, const Launch &
                         hipStream_t stream);
 hipError_t launch_carry(const CarryArgs &a, bool bf16, const Launch &cfg, hipStream_t stream);
 hipError_t launch_stats_finish(const StatsArgs &a, hipStream_t stream);
-long long slot_records(long long n, bool bf16, int block);   // wavefronts of a slot launch
+long long slot_records(long long n, bool bf16, int block);   // tiles of a round, one record each
 int slot_tail(long long n, bool bf16);                       // elements of its ragged tail
 hipError_t launch_stash(const StashArgs &a, bool bf16, hipStream_t stream);
 hipError_t launch_views_sgd(const ViewsArgs &a, bool fast, const Launch &cfg, hipStream_t stream);

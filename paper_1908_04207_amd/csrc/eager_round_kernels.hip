@@ -5,12 +5,13 @@
 // The path is a pure stream: per element <= 2P adds, one multiply and two FMAs against
 // >= 4P bytes, so HBM bandwidth is the only roofline that matters and there is no
 // contraction for the matrix cores.  Design for CDNA4:
-//   * slot_kernel: the host compacts the round into a list of streams that
-//     must be read, in summation order; a lane owns 4 consecutive elements of every stream,
-//     so a 64-lane wavefront reads or writes one contiguous KiB per fp32 stream and
-//     instruction; the loads of a chunk of 16 streams are all issued before the first add,
-//     which keeps 16-18 x 16 B per lane in flight - that, together with a deliberately
-//     capped occupancy, is what suits HBM with mixed reads and writes;
+//   * the host compacts the round into a list of streams ("slots") that must be read, in
+//     summation order, each with one action; a wavefront takes one tile of 256 elements, a lane
+//     4 consecutive elements of every stream, so a 64-lane wavefront reads or writes one
+//     contiguous KiB per fp32 stream and instruction;
+//   * burst_kernel, for runs that stream from HBM: many wavefronts per CU, two loads in flight
+//     in each; occupancy is capped so that the bytes in flight match what the memory side holds;
+//   * chunk_kernel, for runs that latency bounds: up to 16 loads in flight per lane, no cap;
 //   * which streams exist and what is done with each is decided on the host and applied in
 //     the kernel with scalar bit masks: no branch around a load, empty send buffers cost
 //     no bytes, the send buffer of an on-time process is "cleared" by a flag on the host,
@@ -21,7 +22,7 @@
 //   * carry_kernel: the send-buffer rewrite of late processes as a plain pair-by-pair
 //     copy, when a round is split;
 //   * optional per-bucket norms as by-products of the same pass: DPP sums inside wavefronts,
-//     one record per wavefront (the helpers live in eager_device.h, the kernels that finish
+//     one record per tile (the helpers live in eager_device.h, the kernels that finish
 //     them in eager_aux_kernels.hip).
 #include "eager_device.h"
 
@@ -30,28 +31,65 @@
 namespace eager {
 namespace {
 
-// The round as a list of streams ("slots"), each with one action, in summation order.  A
-// chunk of C slots is C loads issued back to back, then the adds, then the stores; the list
-// is consumed in chunks of CH and one remainder chunk of its exact size, so that no load is
-// issued for a stream the round does not need.
+// A wavefront owns one tile of 64 lane-vectors (a lane-vector = 4 elements), so that each load or
+// store instruction covers one contiguous kilobyte of an fp32 stream.  With bf16 gradients (BF16)
+// a lane's 4 gradient elements are 8 bytes, one half of an aligned 16-byte piece: lanes 2k and
+// 2k+1 load the same piece and each keeps its half.  That way every load is the same 16-byte
+// instruction whatever the type of its stream - the type, like the action, is a scalar select and
+// never a branch around a load.
 //
-// A lane owns 4 consecutive elements of every stream, so that each load or store instruction
-// of a wavefront covers one contiguous kilobyte of an fp32 stream.  With bf16 gradients
-// (BF16) the lane's 4 gradient elements are 8 bytes, one half of an aligned 16-byte piece:
-// lanes 2k and 2k+1 load the same piece and each keeps its half.  That way every load of a
-// chunk is the same 16-byte instruction whatever the type of its stream - the type, like the
-// action, is a scalar select and never a branch around a load.
-struct LaneVec {
-    long long e;        // first of the lane's 4 elements (arena index)
-    long long off_bf;   // byte offset of the 16-byte piece of a bf16 stream that holds them
-    bool odd;           // the lane's elements are the upper half of that piece
+// Addresses are a uniform base (stream + first element of the tile) plus a 32-bit offset of the
+// lane.  Lanes beyond the last lane-vector repeat it: their loads stay inside the run and their
+// results are never stored.
+struct Lanes {
+    long long e0;          // first element of the tile (arena index), uniform
+    unsigned off;          // byte offset of the lane-vector in an fp32 stream
+    unsigned off_bf;       // byte offset of the 16-byte piece of a bf16 stream that holds it
+    bool odd;              // the lane-vector is the upper half of that piece
+    bool in;               // the lane-vector belongs to the run
 };
 
-template <bool BF16>
-__device__ __forceinline__ f32x4 slot_value(u32x4 raw, bool is_bf, bool odd)
+typedef const f32x4 __attribute__((address_space(1))) GF4;
+typedef f32x4 __attribute__((address_space(1))) GF4w;
+
+// (the empty statement keeps the widening of the offset next to the access, where it folds into
+// the instruction's scalar-base form; hoisted out of it, every stream would hold a 64-bit address
+// per lane)
+template <bool NT>
+__device__ __forceinline__ f32x4 ld_at(const char *base, unsigned off)
 {
-    const f32x4 plain = __builtin_bit_cast(f32x4, raw);
+    asm("" : "+v"(off));
+    GF4 *p = (GF4 *)(base + off);
+    if (NT) return __builtin_nontemporal_load(p);
+    return *p;
+}
+template <bool NT>
+__device__ __forceinline__ void st_at(char *base, unsigned off, f32x4 x)
+{
+    asm("" : "+v"(off));
+    GF4w *p = (GF4w *)(base + off);
+    if (NT) __builtin_nontemporal_store(x, p);
+    else *p = x;
+}
+
+// 16 bytes of a slot's stream (raw: a bf16 stream is widened by slot_value).  For a SKIP every
+// lane loads one and the same piece: hardly any traffic.
+template <bool BF16, bool NT = true>
+__device__ __forceinline__ f32x4 ld_slot_or_skip(unsigned long long slot, const Lanes &L)
+{
+    const bool skip = (slot & (kKindMask | kSlotCopy)) == kSkip;
+    const bool is_bf = BF16 && (slot & kSlotBf16);
+    const char *base = reinterpret_cast<const char *>(slot & ~static_cast<unsigned long long>(kSlotTag)) +
+                       L.e0 * (is_bf ? 2 : 4);
+    const unsigned off = L.off, off_bf = L.off_bf;
+    return ld_at<NT>(base, (is_bf ? off_bf : off) & (skip ? 0u : ~0u));
+}
+
+template <bool BF16>
+__device__ __forceinline__ f32x4 slot_value(f32x4 plain, bool is_bf, bool odd)
+{
     if (!BF16) return plain;
+    const u32x4 raw = __builtin_bit_cast(u32x4, plain);
     const unsigned a = odd ? raw.z : raw.x, b = odd ? raw.w : raw.y;
     f32x4 wide;
     wide.x = __uint_as_float(a << 16);
@@ -66,162 +104,110 @@ __device__ __forceinline__ f32x4 masked(f32x4 x, unsigned m)
     return __builtin_bit_cast(f32x4, __builtin_bit_cast(u32x4, x) & m);
 }
 
-template <bool BF16, bool FAST, bool NT, int U, int C>
-__device__ __forceinline__ void slot_chunk(KSlotArgs &a, int k0, const LaneVec (&lv)[U],
-                                           f32x4 (&s)[U][2], f32x4 (&hold)[U])
+// The partial sums of a wavefront.  term: what the slot before would add (a HOLD is always
+// directly followed by its PAIR).
+struct Sums {
+    f32x4 s, s2, term;     // s2: the second partial sum of fast mode
+};
+
+// Add one slot's values.  The action is applied with bit masks built from scalar conditions,
+// never with a branch: if a path existed on which a load is not consumed, the compiler would
+// have to drain all memory operations before its registers could be reused.
+//   fixed order:  term = x + (term & pair) ;  s = s + (term & adds)
+// pair = all ones for a PAIR slot, adds = all ones for ADD and PAIR.  A masked-out term is +0.0f,
+// and adding +0.0f changes nothing here: s starts at +0.0f and a sum of two floats is -0.0f only
+// if both are, so s is never -0.0f; and x + 0.0f differs from x only for x = -0.0f, which adds
+// the same as +0.0f to an s that is not -0.0f, directly or as a part of a pair.
+template <bool BF16, bool FAST>
+__device__ __forceinline__ void add_slot(unsigned long long slot, f32x4 raw, const Lanes &L, Sums &S,
+                                         bool second)
 {
-    // a chunk starts at a multiple of its size (8, 16 or 32): its bits never straddle a
-    // mask word
-    const unsigned long long b0 = a.kind0[k0 >> 6] >> (k0 & 63);
-    const unsigned long long b1 = a.kind1[k0 >> 6] >> (k0 & 63);
-    const unsigned long long bf = BF16 ? a.bf[k0 >> 6] >> (k0 & 63) : 0ull;
-    u32x4 raw[U][C];
-#pragma unroll
-    for (int j = 0; j < C; ++j) {
-        const char *sp = static_cast<const char *>(a.src[k0 + j]);
-        const bool is_bf = BF16 && ((bf >> j) & 1ull);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            raw[u][j] = ld_u4<NT>(sp + (is_bf ? lv[u].off_bf : lv[u].e * 4));
-    }
-    // Every loaded value is used unconditionally and the action of a slot is applied with
-    // bit masks built from scalar conditions, never with a branch: if a path existed on
-    // which a load is not consumed, the compiler would have to drain all memory operations
-    // before its registers could be reused.
-    //   fixed order:  c = x + (prev & pair) ;  s = s + (c & adds)
-    // where prev is the value of the slot before (a HOLD is always directly followed by its
-    // PAIR; `hold` carries the last value of the previous chunk), pair = all ones for a PAIR
-    // slot, adds = all ones for ADD and PAIR.  A masked-out term is +0.0f, and adding +0.0f
-    // changes nothing here: s starts at +0.0f and a sum of two floats is -0.0f only if both
-    // are, so s is never -0.0f; and c = x + 0.0f differs from x only for x = -0.0f, which
-    // adds the same as +0.0f to an s that is not -0.0f.
-    f32x4 x[U][C];
-#pragma unroll
-    for (int j = 0; j < C; ++j) {
-        const unsigned lo = static_cast<unsigned>(b0 >> j) & 1u;
-        const unsigned hi = static_cast<unsigned>(b1 >> j) & 1u;
-        const unsigned m_pair = 0u - (hi & ~lo & 1u);          // PAIR
-        const unsigned m_adds = 0u - (~lo & 1u);               // ADD or PAIR
-        const unsigned m_sum = ~(0u - (lo & hi));              // everything but STORE
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            x[u][j] = slot_value<BF16>(raw[u][j], (bf >> j) & 1ull, lv[u].odd);
-            if (FAST) {
-                // any order: two interleaved partial sums
-                s[u][j & 1] = s[u][j & 1] + masked(x[u][j], m_sum);
-            } else {
-                const f32x4 prev = j == 0 ? hold[u] : x[u][j - 1];
-                const f32x4 c = x[u][j] + masked(prev, m_pair);
-                s[u][0] = s[u][0] + masked(c, m_adds);
-            }
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) hold[u] = x[u][C - 1];
-    // Stores stay behind the adds: moved ahead of them (the compiler likes to sink the add
-    // chain below the store branches), the in-order memory counter would make every add
-    // wait for the acknowledgement of a store instead of for its load.  The empty
-    // statement pins the sums here and orders the stores after it.
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-        asm volatile("" : "+v"(s[u][0]), "+v"(s[u][1]), "+v"(hold[u]) : : "memory");
-#pragma unroll
-    for (int j = 0; j < C; ++j) {
-        if (((b0 >> j) & 1ull) && ((b1 >> j) & 1ull)) {          // STORE
-            float *dp = a.dst[k0 + j];
-#pragma unroll
-            for (int u = 0; u < U; ++u) st_f4<NT>(dp + lv[u].e, x[u][j]);
-        }
+    const unsigned tag = static_cast<unsigned>(slot);
+    const unsigned lo = tag & 1u, hi = (tag >> 1) & 1u;
+    const f32x4 x = slot_value<BF16>(raw, BF16 && (tag & kSlotBf16), L.odd);
+    if (FAST) {
+        // any order: two interleaved partial sums; everything but SKIP
+        f32x4 &s = second ? S.s2 : S.s;
+        s = s + masked(x, ~(0u - (lo & hi)));
+    } else {
+        S.term = x + masked(S.term, 0u - (hi & ~lo & 1u));       // PAIR
+        S.s = S.s + masked(S.term, 0u - (~lo & 1u));             // ADD or PAIR
     }
 }
 
-template <bool BF16, bool FAST, bool NT, int U, int R>
-__device__ __forceinline__ void slot_remainder(KSlotArgs &a, int k0, int rem,
-                                               const LaneVec (&lv)[U], f32x4 (&s)[U][2],
-                                               f32x4 (&hold)[U])
-{
-    if constexpr (R >= 1) {
-        if (rem == R) slot_chunk<BF16, FAST, NT, U, R>(a, k0, lv, s, hold);
-        else slot_remainder<BF16, FAST, NT, U, R - 1>(a, k0, rem, lv, s, hold);
-    }
-}
-
+// What follows the sum: average, receive buffer, by-products, update rule.
 // NTS: parameters, momentum and the receive buffer are streamed with the nontemporal hint
 // too (right when they are too large to stay in the last-level cache until the next round).
-template <bool BF16, bool FAST, bool NT, bool NTS, int U, int CH, bool STATS>
-__device__ __forceinline__ void slot_vectors(KSlotArgs &a, const LaneVec (&lv)[U], int n_valid,
-                                             LaneStats &ls)
+template <bool FAST, bool NTS, bool OPT, bool STATS>
+__device__ __forceinline__ void finish_tile(KSlotArgs &a, const Lanes &L, const Sums &S, f32x4 vo,
+                                            f32x4 wo, int n_valid, LaneStats &ls)
 {
-    f32x4 s[U][2], hold[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        s[u][0] = (f32x4)(0.0f);
-        s[u][1] = (f32x4)(0.0f);
-        hold[u] = (f32x4)(0.0f);
+    const long long base = L.e0 * 4;
+    f32x4 sum = S.s;
+    if (FAST) sum = sum + S.s2;
+    const f32x4 avg = sum * a.inv_P;
+    if (STATS) {
+        // n_valid: how many of the lane's 4 elements lie inside their bucket (the rest
+        // is padding between buckets)
+        const f32x4 w_old = OPT ? wo : (f32x4)(0.0f);
+        if (n_valid > 0) stats_add(ls, avg.x, w_old.x, OPT);
+        if (n_valid > 1) stats_add(ls, avg.y, w_old.y, OPT);
+        if (n_valid > 2) stats_add(ls, avg.z, w_old.z, OPT);
+        if (n_valid > 3) stats_add(ls, avg.w, w_old.w, OPT);
     }
-    f32x4 vo[U], wo[U];
-    if (a.w) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            vo[u] = ld_f4<NTS>(a.v + lv[u].e);
-            wo[u] = ld_f4<NTS>(a.w + lv[u].e);
-        }
+    f32x4 vn, wn;
+    if (OPT) {
+        const UpdateRule rule = {a.neg_lr, a.mu, a.wd, a.nesterov};
+        update_rule<FAST>(rule, avg, vo, wo, vn, wn);
     }
-    // The chunk sequence is unrolled to its maximum length with forward exits only: in a
-    // real loop the compiler drains every outstanding store at the loop head before the
-    // next chunk's loads may issue, which puts a store round trip between chunks.
-    const int n = a.n_slots;
-#pragma unroll
-    for (int c = 0; c < kMaxSlots / CH; ++c)
-        if ((c + 1) * CH <= n) slot_chunk<BF16, FAST, NT, U, CH>(a, c * CH, lv, s, hold);
-    // the remainder is ONE chunk of its exact size: every chunk costs a memory round
-    // trip per wavefront, so a cascade of smaller and smaller chunks would be slow
-    slot_remainder<BF16, FAST, NT, U, CH - 1>(a, n / CH * CH, n % CH, lv, s, hold);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const long long e = lv[u].e;
-        f32x4 sum = s[u][0];
-        if (FAST) sum = sum + s[u][1];
-        const f32x4 avg = sum * a.inv_P;
-        if (a.recv) st_f4<NTS>(a.recv + e, avg);
-        if (STATS) {
-            // n_valid: how many of the lane's 4 elements lie inside their bucket (the rest
-            // is padding between buckets)
-            const bool has_w = a.w != nullptr;
-            const f32x4 w_old = has_w ? wo[u] : (f32x4)(0.0f);
-            if (n_valid > 0) stats_add(ls, avg.x, w_old.x, has_w);
-            if (n_valid > 1) stats_add(ls, avg.y, w_old.y, has_w);
-            if (n_valid > 2) stats_add(ls, avg.z, w_old.z, has_w);
-            if (n_valid > 3) stats_add(ls, avg.w, w_old.w, has_w);
-        }
-        if (a.w) {
-            f32x4 vn, wn;
-            const UpdateRule rule = {a.neg_lr, a.mu, a.wd, a.nesterov};
-            update_rule<FAST>(rule, avg, vo[u], wo[u], vn, wn);
-            st_f4<NTS>(a.v + e, vn);
-            st_f4<NTS>(a.w + e, wn);
+    if (L.in) {
+        if (a.recv) st_at<NTS>(reinterpret_cast<char *>(a.recv) + base, L.off, avg);
+        if (OPT) {
+            st_at<NTS>(reinterpret_cast<char *>(a.v) + base, L.off, vn);
+            st_at<NTS>(reinterpret_cast<char *>(a.w) + base, L.off, wn);
         }
     }
 }
 
-// ragged tail: at most 3 (7 with bf16 gradients) elements per launch, fixed order in both
-// modes
-template <bool BF16, bool STATS>
-__device__ __forceinline__ void slot_scalar(KSlotArgs &a, long long i)
+// one element of a slot's stream (a SKIP without a stream, in a list that has none: 0)
+template <bool BF16>
+__device__ __forceinline__ float ld_slot_element(unsigned long long slot, long long i)
 {
-    float s = 0.0f, hold = 0.0f;
-    for (int k = 0; k < a.n_slots; ++k) {
-        const int kind = static_cast<int>((a.kind0[k >> 6] >> (k & 63)) & 1ull) |
-                         static_cast<int>(((a.kind1[k >> 6] >> (k & 63)) & 1ull) << 1);
-        float x;
-        if (BF16 && ((a.bf[k >> 6] >> (k & 63)) & 1ull))
-            x = load_grad_scalar<true>(a.src[k], i);
-        else
-            x = load_grad_scalar<false>(a.src[k], i);
-        if (kind == kAdd) s = s + x;
-        else if (kind == kHold) hold = x;
-        else if (kind == kPair) { const float c = hold + x; s = s + c; }
-        else a.dst[k][i] = x;
+    typedef const float __attribute__((address_space(1))) GF;
+    typedef const unsigned short __attribute__((address_space(1))) GH;
+    const unsigned long long base = slot & ~static_cast<unsigned long long>(kSlotTag);
+    if (base == 0) return 0.0f;
+    if (BF16 && (slot & kSlotBf16))
+        return __uint_as_float(static_cast<unsigned>(((GH *)base)[i]) << 16);
+    return ((GF *)base)[i];
+}
+
+// Ragged tail: at most 3 (7 with bf16 gradients) elements per launch, one lane each, by a
+// wavefront that has nothing else to do; fixed order in both modes.  The loads of 8 slots are
+// issued together: one at a time, a round of 16 streams waited 16 times for memory.
+template <bool BF16, bool STATS>
+__device__ __forceinline__ void slot_tail_element(KSlotArgs &a, long long i)
+{
+    float s = 0.0f, term = 0.0f;
+    constexpr int C = 8;                  // the list ends in at least 16 SKIPs
+    for (int k0 = 0; k0 < a.n_sum; k0 += C) {
+        float x[C];
+#pragma unroll
+        for (int j = 0; j < C; ++j) x[j] = ld_slot_element<BF16>(a.slot[k0 + j], i);
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            const int kind = static_cast<int>(a.slot[k0 + j] & kKindMask);
+            term = kind == kPair ? term + x[j] : x[j];
+            s = kind == kAdd || kind == kPair ? s + term : s;
+        }
+    }
+    for (int c0 = 0; c0 < a.n_copy; c0 += C) {
+        float x[C];
+#pragma unroll
+        for (int j = 0; j < C; ++j) x[j] = ld_slot_element<BF16>(a.slot[a.n_sum + c0 + j], i);
+#pragma unroll
+        for (int j = 0; j < C; ++j)
+            if (c0 + j < a.n_copy) a.dst[c0 + j][i] = x[j];
     }
     const float avg = s * a.inv_P;
     if (a.recv) a.recv[i] = avg;
@@ -233,7 +219,7 @@ __device__ __forceinline__ void slot_scalar(KSlotArgs &a, long long i)
         if (i < tbl[2 * ls.bucket + 1]) stats_add(ls, avg, a.w ? a.w[i] : 0.0f, a.w != nullptr);
         else ls.bucket = -2;                                   // padding
         const StatsRecord mine = {ls.ssu, ls.ssw, ls.bucket, ls.nf, 0};
-        a.stats.lane_records[static_cast<long long>(a.stats.n_buckets) * 64 + threadIdx.x] = mine;
+        a.stats.lane_records[static_cast<long long>(a.stats.n_buckets) * 64 + (threadIdx.x & 63u)] = mine;
     }
     if (a.w) {
         const UpdateRule rule = {a.neg_lr, a.mu, a.wd, a.nesterov};
@@ -253,57 +239,192 @@ __host__ __device__ __forceinline__ long long slot_nvec(long long n)
     return BF16 ? (n / 8) * 2 : n / 4;
 }
 
-// One lane-vector per lane and no loop over tiles: inside a loop every scalar condition of
-// every slot is loop invariant, the compiler hoists hundreds of them out of it and then
-// spills scalar registers.  The grid always covers the run.  (Two consecutive tiles per
-// wavefront, every stream requested 2 KiB at a time, were measured as well: 3-6 % faster in a
-// plain kernel of 16-34 read and 2 write streams, but on the rounds themselves the same with
-// 18 streams and 2-5 % slower with 13 or 28.)
-template <bool BF16, bool FAST, bool NT, bool NTS, int CH, bool STATS>
-__global__ __launch_bounds__(256) void slot_kernel(const SlotArgs)
+// Index of the wavefront in the grid.  Workgroups are dealt to the 8 XCDs round robin; xcd_blocks
+// gives every XCD one contiguous eighth of the run instead of every eighth tile (a launch
+// option, for A/B).  (The grid's shape comes with the arguments: the built-in blockDim is a load
+// from memory that every wavefront would have to wait for.)
+__device__ __forceinline__ long long wave_index(KSlotArgs &a)
+{
+    unsigned bid = blockIdx.x;
+    const unsigned per = static_cast<unsigned>(a.xcd_blocks);
+    if (per && bid < per * 8u) bid = (bid % 8u) * per + bid / 8u;
+    const unsigned wave = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
+    return static_cast<long long>(bid) * a.waves_per_block + wave;
+}
+
+__device__ __forceinline__ Lanes place_lanes(KSlotArgs &a, long long tile, long long nvec)
+{
+    const unsigned lane = threadIdx.x & 63u;
+    const long long left = nvec - tile * 64;                   // uniform, > 0
+    const unsigned last = left > 64 ? 63u : static_cast<unsigned>(left) - 1u;
+    const unsigned lv = lane < last ? lane : last;
+    Lanes L;
+    L.e0 = a.e0 + tile * 256;
+    L.in = lane <= last;
+    L.off = lv * 16u;
+    L.off_bf = (lv >> 1) * 16u;
+    L.odd = (lv & 1u) != 0;
+    return L;
+}
+
+// By-products: bucket of the lane-vector (it never straddles a bucket start, starts are multiples
+// of 4) and how many of its elements lie inside.  Everything that is looked up is uniform over the
+// wavefront: the table is read with scalar loads, which do not wait behind the streams.
+__device__ __forceinline__ int place_stats(KSlotArgs &a, const Lanes &L, LaneStats &ls)
+{
+    typedef const long long __attribute__((address_space(4))) KLong;
+    KLong *tbl = (KLong *)reinterpret_cast<unsigned long long>(a.stats.table);
+    int lo = a.stats.b_lo, hi = a.stats.b_hi;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (tbl[2 * mid] <= L.e0) lo = mid;
+        else hi = mid;
+    }
+    const long long e = L.e0 + (L.off >> 2);
+    int b = lo;
+    long long end = tbl[2 * lo + 1];
+    for (int k = lo + 1; k < a.stats.b_hi; ++k) {
+        const long long start = tbl[2 * k];
+        if (start >= L.e0 + 256) break;
+        if (e >= start) {
+            b = k;
+            end = tbl[2 * k + 1];
+        }
+    }
+    ls = {0.0, 0.0, 0u, L.in ? b : -1};
+    const long long left = end - e;
+    return !L.in ? 0 : left >= 4 ? 4 : left > 0 ? static_cast<int>(left) : 0;
+}
+
+// The round as a stream of bursts: a wavefront (one tile) requests kBurst = 2 slots, waits for both,
+// adds them, and goes on to the next two; w and v come last.  What bounds it is the memory
+// side, and the memory side wants FEW bytes in flight: about 26 KiB per CU is the product of its
+// latency and its rate, more only queues up and loses row locality.  Many wavefronts with little
+// in flight each do that best: with 16 streams of 268 MB, w and v updated, 2 loads by 12 wavefronts
+// move 6.4-6.6 TB/s where 16 loads by 8 wavefronts move 6.0-6.2 (32 streams: 6.2-6.3 and 5.7-5.9;
+// both depend on where the arenas lie).  Two or four tiles per wavefront reach 6.7 with some
+// placements and 5.2 with others, a rolling window of 2-4 loads is 2 % slower than bursts.
+// Copies (late gradients of a fused round) follow the sum in the same way.  Whole rounds, before
+// (16 loads at once) and now: 16 processes, 67 M elements, everybody on time 882 -> 841 us; 2
+// processes, 20 M: 84.5 -> 78.5; 16 processes, 1 M, 15 late: 38.9 -> 34.8.
+template <bool BF16, bool FAST, bool NTS, bool OPT, bool STATS>
+__global__ __launch_bounds__(256) void burst_kernel(const SlotArgs)
+{
+    constexpr int D = kBurst;
+    KSlotArgs &a = kernarg<SlotArgs>();
+    const long long nvec = slot_nvec<BF16>(a.n);
+    const long long tile = wave_index(a);
+    if (tile * 64 >= nvec) {
+        // the grid's last wavefront: the ragged tail
+        const long long rem = a.n - nvec * 4, t = threadIdx.x & 63u;
+        if (tile * 64 < nvec + 64 && t < rem) slot_tail_element<BF16, STATS>(a, a.e0 + nvec * 4 + t);
+        return;
+    }
+    const Lanes L = place_lanes(a, tile, nvec);
+    Sums S;
+    S.s = S.s2 = S.term = (f32x4)(0.0f);
+    const int n_sum = a.n_sum, n = n_sum + a.n_copy;
+    unsigned long long slot[D];
+    f32x4 x[D];
+    auto request = [&](int k) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) slot[j] = a.slot[k + j];
+#pragma unroll
+        for (int j = 0; j < D; ++j) x[j] = ld_slot_or_skip<BF16>(slot[j], L);
+    };
+    // Everything in flight has arrived before it is used and before the next burst is requested:
+    // the empty statements hold the compiler to that order.
+    auto arrived = [&]() {
+#pragma unroll
+        for (int j = 0; j < D; ++j) asm volatile("" : "+v"(x[j]) : : "memory");
+    };
+    LaneStats ls;
+    int n_valid = 0;
+    if (n_sum > 0) {
+        request(0);
+        if (STATS) n_valid = place_stats(a, L, ls);
+        for (int k = D;; k += D) {
+            arrived();
+#pragma unroll
+            for (int j = 0; j < D; ++j) add_slot<BF16, FAST>(slot[j], x[j], L, S, j & 1);
+            asm volatile("" : "+v"(S.s), "+v"(S.s2), "+v"(S.term) : : "memory");
+            if (k >= n_sum) break;
+            request(k);
+        }
+    } else if (STATS) {
+        n_valid = place_stats(a, L, ls);
+    }
+    f32x4 vo = (f32x4)(0.0f), wo = vo;
+    if (OPT) {
+        vo = ld_at<NTS>(reinterpret_cast<const char *>(a.v) + L.e0 * 4, L.off);
+        wo = ld_at<NTS>(reinterpret_cast<const char *>(a.w) + L.e0 * 4, L.off);
+    }
+    finish_tile<FAST, NTS, OPT, STATS>(a, L, S, vo, wo, n_valid, ls);
+    for (int k = n_sum; k < n; k += D) {
+        request(k);
+        arrived();
+#pragma unroll
+        for (int j = 0; j < D; ++j)
+            if (k + j < n) {
+                char *dst = reinterpret_cast<char *>(a.dst[k + j - n_sum]) + L.e0 * 4;
+                if (L.in) st_at<true>(dst, L.off, slot_value<BF16>(x[j], BF16, L.odd));
+            }
+    }
+    if (STATS) stats_commit(a.stats.records, a.stats.lane_records, ls, tile);
+}
+
+// The round for small runs: what counts there is the time from launch to the last store, so a
+// wavefront (one tile) requests w and v and CH slots at once and waits for all of it together; with
+// more slots than CH it does so again.  One body of code whatever the number of slots (the list
+// ends in SKIPs, which are nearly free): a body for every remainder has to be fetched before it
+// runs.  NT: as for the streams of the burst kernel, or plain.  Kernel time, before and now:
+// 8193 elements, 8 processes solo 7.0 -> 4.5 us; 1 M elements, 4 processes solo 12.1 -> 10.6
+// us a round; 1 M, 8 processes, 4 late 17.2 -> 14.1.
+template <bool BF16, bool FAST, bool NT, bool NTS, bool OPT, bool STATS, int CH>
+__global__ __launch_bounds__(256) void chunk_kernel(const SlotArgs)
 {
     KSlotArgs &a = kernarg<SlotArgs>();
     const long long nvec = slot_nvec<BF16>(a.n);
-    // Workgroups are dealt to the 8 XCDs round robin.  xcd_map = 1 gives every XCD one
-    // contiguous eighth of the run instead of every eighth tile (a launch option, for A/B).
-    unsigned bid = blockIdx.x;
-    if (a.xcd_map) {
-        const unsigned per = gridDim.x / 8u;
-        if (bid < per * 8u) bid = (bid % 8u) * per + bid / 8u;
+    const long long tile = wave_index(a);
+    if (tile * 64 >= nvec) {
+        // the grid's last wavefront: the ragged tail
+        const long long rem = a.n - nvec * 4, t = threadIdx.x & 63u;
+        if (tile * 64 < nvec + 64 && t < rem) slot_tail_element<BF16, STATS>(a, a.e0 + nvec * 4 + t);
+        return;
     }
-    const long long vi = static_cast<long long>(bid) * blockDim.x + threadIdx.x;
-    LaneStats ls = {0.0, 0.0, 0u, -1};
-    int n_valid = 0;
-    int wave_bucket = 0;
-    if (STATS) {
-        // bucket of the wavefront's first element: a uniform search (scalar loads), started
-        // before the streams are requested
-        const long long v0 = vi - (threadIdx.x & 63u);
-        const long long e_wave =
-            a.e0 + 4 * ((static_cast<long long>(__builtin_amdgcn_readfirstlane(
-                             static_cast<int>(v0 >> 32))) << 32) |
-                        static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(v0))));
-        wave_bucket = find_bucket(a.stats.table, a.stats.n_buckets, e_wave);
+    const Lanes L = place_lanes(a, tile, nvec);
+    Sums S;
+    S.s = S.s2 = S.term = (f32x4)(0.0f);
+    f32x4 vo = (f32x4)(0.0f), wo = vo;
+    if (OPT) {
+        vo = ld_at<NTS>(reinterpret_cast<const char *>(a.v) + L.e0 * 4, L.off);
+        wo = ld_at<NTS>(reinterpret_cast<const char *>(a.w) + L.e0 * 4, L.off);
     }
-    if (vi < nvec) {
-        // bucket starts are multiples of 8 elements with bf16 gradients, so e0 * 2 is a
-        // multiple of 16 bytes
-        const LaneVec lv[1] = {{a.e0 + vi * 4, a.e0 * 2 + (vi >> 1) * 16, (vi & 1) != 0}};
-        if (STATS) {
-            // a lane's 4 elements never straddle a bucket start (starts are multiples of 4)
-            const long long *tbl = a.stats.table;
-            int b = wave_bucket;
-            while (b + 1 < a.stats.n_buckets && tbl[2 * (b + 1)] <= lv[0].e) ++b;
-            const long long left = tbl[2 * b + 1] - lv[0].e;
-            n_valid = left >= 4 ? 4 : left > 0 ? static_cast<int>(left) : 0;
-            ls.bucket = b;
+    const int n_sum = a.n_sum, n = n_sum + a.n_copy;
+    LaneStats ls;
+    const int n_valid = STATS ? place_stats(a, L, ls) : 0;
+    for (int k0 = 0; k0 < n; k0 += CH) {
+        f32x4 x[CH];
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            x[j] = ld_slot_or_skip<BF16, NT>(a.slot[k0 + j], L);
         }
-        slot_vectors<BF16, FAST, NT, NTS, 1, CH, STATS>(a, lv, n_valid, ls);
+#pragma unroll
+        for (int j = 0; j < CH; ++j) add_slot<BF16, FAST>(a.slot[k0 + j], x[j], L, S, j & 1);
+        // Stores stay behind the adds: moved ahead of them, the in-order memory counter would make
+        // every add wait for the acknowledgement of a store instead of for its load.
+        asm volatile("" : "+v"(S.s), "+v"(S.s2), "+v"(S.term) : : "memory");
+        if (k0 + CH > n_sum) {
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                if (a.slot[k0 + j] & kSlotCopy) {
+                    char *dst = reinterpret_cast<char *>(a.dst[k0 + j - n_sum]) + L.e0 * 4;
+                    if (L.in) st_at<NT>(dst, L.off, slot_value<BF16>(x[j], BF16, L.odd));
+                }
+        }
     }
-    if (STATS) stats_commit(a.stats.records, a.stats.lane_records, ls, vi >> 6);
-    const long long rem = a.n - nvec * 4;
-    if (blockIdx.x == 0 && static_cast<long long>(threadIdx.x) < rem)
-        slot_scalar<BF16, STATS>(a, a.e0 + nvec * 4 + threadIdx.x);
+    finish_tile<FAST, NTS, OPT, STATS>(a, L, S, vo, wo, n_valid, ls);
+    if (STATS) stats_commit(a.stats.records, a.stats.lane_records, ls, tile);
 }
 
 // R_p <- G_p for the late processes, as a plain copy: pair after pair (blockIdx.y is the
@@ -354,35 +475,35 @@ __global__ __launch_bounds__(256) void carry_kernel(const CarryArgs a)
     }
 }
 
-// ---- slot kernel: build the stream list from the rank masks, pick the instantiation
+// ---- the stream list of a round from the rank masks
 void build_slots(const RoundArgs &a, SlotArgs &s)
 {
-    s.n_slots = 0;
-    s.kind0[0] = s.kind0[1] = s.kind1[0] = s.kind1[1] = s.bf[0] = s.bf[1] = 0;
     const bool bf16 = a.elem_bytes == 2;
-    auto push = [&s](const void *src, float *dst, int kind, bool is_bf) {
-        const int k = s.n_slots++;
-        s.src[k] = src;
-        s.dst[k] = dst;
-        if (kind & 1) s.kind0[k >> 6] |= 1ull << (k & 63);
-        if (kind & 2) s.kind1[k >> 6] |= 1ull << (k & 63);
-        if (is_bf) s.bf[k >> 6] |= 1ull << (k & 63);
+    int n = 0;
+    auto push = [&](const void *src, unsigned kind, bool is_bf) {
+        s.slot[n++] = reinterpret_cast<unsigned long long>(src) | kind |
+                      (is_bf ? kSlotBf16 : 0u);
     };
     for (int p = 0; p < a.P; ++p) {
         const bool on_time = (a.active >> p) & 1ull, has_stale = (a.valid >> p) & 1ull;
-        const void *g = a.g[p];
-        if (on_time) {
-            if (has_stale) {
-                push(a.r[p], nullptr, kHold, false);
-                push(g, nullptr, kPair, bf16);
-            } else {
-                push(g, nullptr, kAdd, bf16);
-            }
-        } else {
-            if (has_stale) push(a.r[p], nullptr, kAdd, false);
-            if ((a.store >> p) & 1ull) push(g, a.r[p], kStore, bf16);
-        }
+        if (has_stale) push(a.r[p], on_time ? kHold : kAdd, false);
+        if (on_time) push(a.g[p], has_stale ? kPair : kAdd, bf16);
     }
+    // A SKIP is the last stream again (or, where there is none, any readable memory of the run):
+    // loaded where slots are taken several at a time, and not added.
+    const void *any = a.w ? a.w : a.recv;
+    const unsigned long long none = (n > 0 ? s.slot[n - 1] & ~static_cast<unsigned long long>(kKindMask)
+                                           : reinterpret_cast<unsigned long long>(any)) | kSkip;
+    while (n % kBurst) s.slot[n++] = none;
+    s.n_sum = n;
+    s.n_copy = 0;
+    for (int p = 0; p < a.P; ++p)
+        if ((a.store >> p) & 1ull) {
+            push(a.g[p], kSkip | kSlotCopy, bf16);
+            s.dst[s.n_copy++] = a.r[p];
+        }
+    const unsigned long long skip = s.n_copy ? s.slot[n - 1] & ~static_cast<unsigned long long>(kSlotCopy) : none;
+    for (int k = 0; k < kSlotChunk; ++k) s.slot[n + k] = skip;
     s.w = a.w;
     s.v = a.v;
     s.recv = a.recv;
@@ -394,33 +515,81 @@ void build_slots(const RoundArgs &a, SlotArgs &s)
     s.wd = a.wd;
     s.nesterov = a.nesterov;
     s.stats = a.stats;
-    s.xcd_map = 0;
 }
 
-// Resident 64-lane wavefronts per CU for the slot kernel (measured optima): with stores of
-// late gradients in the same pass few wavefronts are best once there are many streams; a
-// pass that only reads (apart from w and v) likes more while one chunk holds all streams.
-// What counts is the bytes in flight per CU: a bf16 stream carries half as many per load, so
-// the count grows with the share of bf16 streams (all bf16: twice as many wavefronts).
-int auto_waves_for_slots(const SlotArgs &s, bool has_stores)
+// Resident wavefronts per CU of the burst kernel: 14, or 12 where it also copies, for fp32 streams
+// (26 KiB in flight), up to half as many again with bf16 streams, whose bursts are half as large
+// (16 of 16 streams bf16, 64 M elements: 486 us with 20, 552 with 16, 498 with 28; 15 fp32 and 1 bf16
+// streams, 451 M elements: 5.6 ms with 14, 5.7 with 12 or 16).  A run of few generations of
+// wavefronts takes the neighbouring count that fills them best (2 M elements, 32 tiles per CU:
+// 49.3 us with 16, 52.1 with 14); one that fits the chip at once needs no cap (1 M elements, 16
+// processes: 34.8 us, 42.7 with 14).
+int burst_waves(const SlotArgs &s, long long tiles)
 {
-    const int n = s.n_slots;
-    const int n_bf = __builtin_popcountll(s.bf[0]) + __builtin_popcountll(s.bf[1]);
-    if (has_stores && n <= 16) {
-        // One chunk with stores: about 84 KiB of loads in flight per CU, between 8 and 12
-        // wavefronts.  A wavefront requests a KiB per fp32 stream (w and v included), half of
-        // that per bf16 stream.  Measured, 2e8 elements: 3 fp32 streams 6.64 TB/s with 12
-        // against 6.17 with 8; 4 bf16 + 1 fp32 streams 6.64 against 5.72; 8 bf16 + 1 fp32
-        // (2.6e7 elements) 6.94 against 6.43; from 9 fp32 streams on 8 stays the best count.
-        const int half_kib = 2 * (n - n_bf) + n_bf + 4;
-        const int waves = (2 * 84 + half_kib / 2) / half_kib;
-        return waves < 8 ? 8 : waves > 12 ? 12 : waves;
+    const int n = s.n_sum + s.n_copy;
+    int n_bf = 0;
+    for (int k = 0; k < n; ++k)
+        n_bf += (s.slot[k] & kSlotBf16) && (s.slot[k] & (kKindMask | kSlotCopy)) != kSkip;
+    const int base = s.n_copy ? 12 : 14;
+    const int w0 = n > 0 ? base + base * n_bf / (2 * n) : base;
+    const long long per_cu = (tiles + kCus - 1) / kCus;
+    if (per_cu <= w0 + 6) return -1;
+    int best = w0;
+    double least = 1e9;
+    for (int w = w0 - 2; w <= w0 + 4; ++w) {
+        const long long generations = (per_cu + w - 1) / w;
+        const double cost = static_cast<double>(generations * w) / static_cast<double>(per_cu) +
+                            0.01 * (w > w0 ? w - w0 : w0 - w);
+        if (cost < least) {
+            least = cost;
+            best = w;
+        }
     }
-    const int base = has_stores ? 5 : (n <= 20 ? 10 : 5);
-    if (n_bf == 0 || n == 0) return base;
-    // base / (1 - share/2), rounded
-    const int waves = (2 * base * n + (2 * n - n_bf) / 2) / (2 * n - n_bf);
-    return waves > 16 ? 16 : waves;
+    return best;
+}
+
+template <bool BF16, bool FAST, bool NTS, bool OPT>
+hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStream_t st)
+{
+    const long long tiles = (slot_nvec<BF16>(s.n) + 63) / 64;
+    const long long waves = tiles + (slot_nvec<BF16>(s.n) * 4 < s.n ? 1 : 0);   // and the tail
+    const int per = cfg.block / 64;                    // wavefronts per workgroup
+    const long long g = (waves + per - 1) / per;
+    // these kernels do not stride: a run beyond the thread limit of a grid (more than
+    // 2^33 elements) is refused
+    if (g * cfg.block > kMaxGridThreads) return hipErrorInvalidValue;
+    const dim3 grid(static_cast<unsigned>(g));
+    s.waves_per_block = per;
+    s.xcd_blocks = cfg.xcd_map ? static_cast<int>(g / 8) : 0;
+    // A run that moves at most 96 MB is bound by latency: everything at once, no cap.  Beyond that
+    // it is a stream.  (Both sides at the line: 1 M elements, 16 processes, 15 late = 210 MB: 41 us
+    // at once, 34.8 in bursts; 262 k = 52 MB: 11.8 and 14.7.)  Accesses are plain where the whole model
+    // moves no more than that in a round: its arrays then stay in the last-level cache from
+    // round to round (1 M elements, 8 processes: 14.1 us, 16.6 with the nontemporal hint); small runs
+    // of a larger model are streamed (1 M elements, 16 processes, cold: 41.9 us, 44.2 plain).
+    const long long per_element = 4ll * (s.n_sum + 2 * s.n_copy + (OPT ? 4 : 1));
+    const bool small = s.n * per_element <= kSmallRoundBytes;
+    const bool plain = model * per_element <= kSmallRoundBytes;
+    int bpc = cfg.blocks_per_cu;
+    if (bpc == 0) {
+        const int w = small || cfg.chunk != 0 ? -1 : burst_waves(s, tiles);
+        bpc = w < 0 ? -1 : (w + per - 1) / per;
+    }
+    const bool stats = s.stats.stats != nullptr;
+    if (cfg.chunk == 0 && !small)
+        return stats ? launch_capped(burst_kernel<BF16, FAST, NTS, OPT, true>, s, bpc, cfg, grid, st)
+                     : launch_capped(burst_kernel<BF16, FAST, NTS, OPT, false>, s, bpc, cfg, grid, st);
+    // the by-products exist for the default chunk size only
+    if (stats) {
+        if (cfg.chunk == 8) return hipErrorInvalidValue;
+        return plain ? launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, true, 16>, s, bpc, cfg, grid, st)
+                     : launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, true, 16>, s, bpc, cfg, grid, st);
+    }
+    if (cfg.chunk == 8 || (cfg.chunk == 0 && s.n_sum + s.n_copy <= 8))
+        return plain ? launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, false, 8>, s, bpc, cfg, grid, st)
+                     : launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, false, 8>, s, bpc, cfg, grid, st);
+    return plain ? launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, false, 16>, s, bpc, cfg, grid, st)
+                 : launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, false, 16>, s, bpc, cfg, grid, st);
 }
 
 template <bool BF16, bool FAST>
@@ -428,50 +597,14 @@ hipError_t launch_slots(const RoundArgs &a, const Launch &cfg, hipStream_t st)
 {
     SlotArgs s;
     build_slots(a, s);
-    int bpc = cfg.blocks_per_cu;
-    if (bpc == 0) {
-        int waves = auto_waves_for_slots(s, a.store != 0);
-        // With the by-products a wavefront ends in arithmetic (fp64 squares, DPP sums) during
-        // which it has nothing in flight; a little more occupancy covers that (measured: 355 M
-        // elements, P = 32, 6 instead of 5: 15.28 against 15.78 ms, 15.08 without by-products;
-        // 25.6 M elements, P = 8, 12 instead of 8: 0.287 against 0.296 ms, 0.271 without).
-        if (s.stats.stats) waves = waves <= 7 ? waves + 1 : waves == 8 ? 12 : waves;
-        bpc = (waves * 64 + cfg.block - 1) / cfg.block;
-        if (bpc < 1) bpc = 1;
-        // A run whose streams all fit the last-level cache is not an HBM stream: it is bound
-        // by latency, and full occupancy is fastest (1 M elements, P = 4: 8.9 against 10 us).
-        const long long run_bytes = s.n * (4ll * s.n_slots + 16);
-        if (run_bytes < kStateCacheBytes / 2) bpc = -1;
-    }
-    // one vector per lane, the grid covers the run; always nontemporal
-    const long long nvec = slot_nvec<BF16>(s.n);
-    long long g = (nvec + cfg.block - 1) / cfg.block;
-    if (g < 1) g = 1;
-    // this kernel does not stride: a run beyond the thread limit of a grid (more than
-    // 2^33 elements) is refused
-    if (g * cfg.block > kMaxGridThreads) return hipErrorInvalidValue;
-    const unsigned grid = static_cast<unsigned>(g);
-    int ch = cfg.chunk;
-    if (ch == 0) ch = 16;
     // w, v (and recv) of a run that cannot stay in the 256 MiB last-level cache until the
     // next round are streamed; smaller ones are left to the cache
     const long long state_bytes = s.n * 4 * ((s.w ? 2 : 0) + (s.recv ? 1 : 0));
     const bool nts = cfg.nt_state < 0 ? state_bytes > kStateCacheBytes : cfg.nt_state != 0;
-    s.xcd_map = cfg.xcd_map;
-    if (s.stats.stats) {
-        // the by-products exist for the default chunk size only
-        if (ch != 16) return hipErrorInvalidValue;
-        s.stats.n_records = (static_cast<long long>(grid) * cfg.block + 63) / 64;
-        return nts ? launch_capped(slot_kernel<BF16, FAST, true, true, 16, true>, s, bpc, cfg, grid, st)
-                   : launch_capped(slot_kernel<BF16, FAST, true, false, 16, true>, s, bpc, cfg, grid, st);
-    }
-    switch (ch * 2 + (nts ? 1 : 0)) {
-    case 16: return launch_capped(slot_kernel<BF16, FAST, true, false, 8, false>, s, bpc, cfg, grid, st);
-    case 17: return launch_capped(slot_kernel<BF16, FAST, true, true, 8, false>, s, bpc, cfg, grid, st);
-    case 32: return launch_capped(slot_kernel<BF16, FAST, true, false, 16, false>, s, bpc, cfg, grid, st);
-    case 33: return launch_capped(slot_kernel<BF16, FAST, true, true, 16, false>, s, bpc, cfg, grid, st);
-    default: return hipErrorInvalidValue;   // more streams per chunk exceed the scalar registers
-    }
+    if (s.w) return nts ? launch_slots<BF16, FAST, true, true>(s, a.model, cfg, st)
+                        : launch_slots<BF16, FAST, false, true>(s, a.model, cfg, st);
+    return nts ? launch_slots<BF16, FAST, true, false>(s, a.model, cfg, st)
+               : launch_slots<BF16, FAST, false, false>(s, a.model, cfg, st);
 }
 
 }  // namespace
@@ -536,10 +669,9 @@ hipError_t launch_carry(const CarryArgs &a, bool bf16, const Launch &cfg, hipStr
 
 long long slot_records(long long n, bool bf16, int block)
 {
+    (void)block;
     const long long nvec = bf16 ? slot_nvec<true>(n) : slot_nvec<false>(n);
-    long long g = (nvec + block - 1) / block;
-    if (g < 1) g = 1;
-    return (g * block + 63) / 64;
+    return (nvec + 63) / 64;
 }
 
 int slot_tail(long long n, bool bf16)
