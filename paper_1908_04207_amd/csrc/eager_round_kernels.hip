@@ -410,7 +410,11 @@ __global__ __launch_bounds__(256) void chunk_kernel(const SlotArgs)
             x[j] = ld_slot_or_skip<BF16, NT>(a.slot[k0 + j], L);
         }
 #pragma unroll
-        for (int j = 0; j < CH; ++j) add_slot<BF16, FAST>(a.slot[k0 + j], x[j], L, S, j & 1);
+        for (int g = 0; g < CH; g += 4)
+            if (k0 + g < n_sum) {           // (what follows the sum costs no arithmetic)
+#pragma unroll
+                for (int j = g; j < g + 4; ++j) add_slot<BF16, FAST>(a.slot[k0 + j], x[j], L, S, j & 1);
+            }
         // Stores stay behind the adds: moved ahead of them, the in-order memory counter would make
         // every add wait for the acknowledgement of a store instead of for its load.
         asm volatile("" : "+v"(S.s), "+v"(S.s2), "+v"(S.term) : : "memory");
@@ -580,16 +584,18 @@ hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStre
         return stats ? launch_capped(burst_kernel<BF16, FAST, NTS, OPT, true>, s, bpc, cfg, grid, st)
                      : launch_capped(burst_kernel<BF16, FAST, NTS, OPT, false>, s, bpc, cfg, grid, st);
     // the by-products exist for the default chunk size only
-    if (stats) {
-        if (cfg.chunk == 8) return hipErrorInvalidValue;
-        return plain ? launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, true, 16>, s, bpc, cfg, grid, st)
-                     : launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, true, 16>, s, bpc, cfg, grid, st);
+    if (stats && cfg.chunk == 8) return hipErrorInvalidValue;
+    const bool few = cfg.chunk == 8 || (cfg.chunk == 0 && s.n_sum + s.n_copy <= 8);
+    switch ((stats ? 4 : 0) | (few ? 2 : 0) | (plain ? 1 : 0)) {
+    case 0: return launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, false, 16>, s, bpc, cfg, grid, st);
+    case 1: return launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, false, 16>, s, bpc, cfg, grid, st);
+    case 2: return launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, false, 8>, s, bpc, cfg, grid, st);
+    case 3: return launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, false, 8>, s, bpc, cfg, grid, st);
+    case 4: return launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, true, 16>, s, bpc, cfg, grid, st);
+    case 5: return launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, true, 16>, s, bpc, cfg, grid, st);
+    case 6: return launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, true, 8>, s, bpc, cfg, grid, st);
+    default: return launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, true, 8>, s, bpc, cfg, grid, st);
     }
-    if (cfg.chunk == 8 || (cfg.chunk == 0 && s.n_sum + s.n_copy <= 8))
-        return plain ? launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, false, 8>, s, bpc, cfg, grid, st)
-                     : launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, false, 8>, s, bpc, cfg, grid, st);
-    return plain ? launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, false, 16>, s, bpc, cfg, grid, st)
-                 : launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, false, 16>, s, bpc, cfg, grid, st);
 }
 
 template <bool BF16, bool FAST>
