@@ -9,27 +9,48 @@
 namespace eager {
 namespace {
 
-// Adds the plain records (one per wavefront whose elements all lie in one bucket) with index in
+constexpr int kStatsThreads = 1024, kStatsWaves = kStatsThreads / 64;
+
+// Adds the plain records (one per tile whose elements all lie in one bucket) with index in
 // [lo, hi) that belong to bucket b: 8 independent loads per thread in flight, wavefront sums by
-// DPP, the 4 wavefronts of the workgroup through LDS.  The totals arrive in thread 0.
+// DPP, the 16 wavefronts of the workgroup through LDS.  The totals arrive in wavefront 0.  What
+// bounds it is latency: 1024 threads take 8192 records (2 M elements) in one trip, so a first stage
+// is launched for larger buckets only (see launch_stats_finish).
+// Records of norms_kernel come in groups of kNormsTiles: the first of a group holds the sums of
+// all, unless it is flagged - then every tile of the group has a record of its own.
+constexpr int kNormsTiles = 8;
+
+template <int THREADS, bool GROUPED>
 __device__ __forceinline__ void add_records(const StatsRecord *records, long long lo, long long hi,
                                             int b, double &su, double &sw, double &nf)
 {
-    constexpr int K = 8;
-    for (long long wb = lo + threadIdx.x; wb < hi; wb += static_cast<long long>(blockDim.x) * K) {
+    constexpr int K = GROUPED ? 4 : 8, G = GROUPED ? kNormsTiles : 1;
+    auto add = [&](const StatsRecord &r) {
+        if (r.bucket == b) {
+            su += r.ssu;
+            sw += r.ssw;
+            nf += r.nf;
+        }
+    };
+    const long long g0 = lo / G, g1 = (hi + G - 1) / G;
+    for (long long gb = g0 + threadIdx.x; gb < g1; gb += static_cast<long long>(THREADS) * K) {
         StatsRecord r[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const long long w = wb + static_cast<long long>(k) * blockDim.x;
-            if (w < hi) r[k] = records[w];
+            const long long g = gb + static_cast<long long>(k) * THREADS;
+            r[k].flag = 0;
+            if (g < g1) r[k] = records[g * G];
             else r[k].bucket = -2;
         }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            if (r[k].bucket == b) {
-                su += r[k].ssu;
-                sw += r[k].ssw;
-                nf += r[k].nf;
+            if (GROUPED && r[k].flag) {
+                const long long t = (gb + static_cast<long long>(k) * THREADS) * G;
+#pragma unroll
+                for (int j = 0; j < G; ++j)
+                    if (t + j >= lo && t + j < hi) add(records[t + j]);
+            } else {
+                add(r[k]);
             }
         }
     }
@@ -39,20 +60,23 @@ __device__ __forceinline__ void add_records(const StatsRecord *records, long lon
 // overflow on a bucket of billions of elements)
 __device__ __forceinline__ void workgroup_sum(double &su, double &sw, double &nf)
 {
-    __shared__ double part_u[4], part_w[4], part_n[4];
+    __shared__ double part[3][kStatsWaves];
     su = wave_sum(su);
     sw = wave_sum(sw);
     nf = wave_sum(nf);
-    const unsigned wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63u) == 0u) {
-        part_u[wave] = su;
-        part_w[wave] = sw;
-        part_n[wave] = nf;
+    const unsigned wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+    if (lane == 0u) {
+        part[0][wave] = su;
+        part[1][wave] = sw;
+        part[2][wave] = nf;
     }
     __syncthreads();
-    su = (part_u[0] + part_u[1]) + (part_u[2] + part_u[3]);
-    sw = (part_w[0] + part_w[1]) + (part_w[2] + part_w[3]);
-    nf = (part_n[0] + part_n[1]) + (part_n[2] + part_n[3]);
+    if (wave == 0) {                     // the totals are needed there
+        const bool has = lane < kStatsWaves;
+        su = wave_sum(has ? part[0][lane] : 0.0);
+        sw = wave_sum(has ? part[1][lane] : 0.0);
+        nf = wave_sum(has ? part[2][lane] : 0.0);
+    }
 }
 
 // records of bucket b: [w0, w1)
@@ -66,16 +90,20 @@ __device__ __forceinline__ void bucket_records(const StatsArgs &a, int b, long l
 
 // First stage for buckets with many records (a flat model is ONE bucket: millions of records):
 // workgroup (bucket, slice) adds one slice of the bucket's plain records and leaves a partial.
-__global__ __launch_bounds__(256) void stats_slice_kernel(const StatsArgs a)
+template <bool GROUPED>
+__global__ __launch_bounds__(kStatsThreads) void stats_slice_kernel(const StatsArgs a)
 {
     const int b = a.b_lo + static_cast<int>(blockIdx.x);
     const int s = static_cast<int>(blockIdx.y);
     long long w0, w1;
     bucket_records(a, b, w0, w1);
-    const long long len = (w1 - w0 + a.slices - 1) / a.slices;
-    const long long lo = w0 + s * len, hi = lo + len < w1 ? lo + len : w1;
+    // slices begin at whole groups of records
+    const long long len = ((w1 - w0 + a.slices - 1) / a.slices + kNormsTiles - 1) / kNormsTiles * kNormsTiles;
+    const long long first = w0 / kNormsTiles * kNormsTiles;
+    const long long lo = s == 0 ? w0 : first + s * len;
+    const long long hi = s + 1 == a.slices || first + (s + 1) * len > w1 ? w1 : first + (s + 1) * len;
     double su = 0.0, sw = 0.0, nf = 0.0;
-    add_records(a.records, lo, hi, b, su, sw, nf);
+    add_records<kStatsThreads, GROUPED>(a.records, lo, hi, b, su, sw, nf);
     workgroup_sum(su, sw, nf);
     if (threadIdx.x == 0) {
         // a slice holds at most 2^33 / 256 / slices records of 256 elements: the count fits
@@ -88,43 +116,48 @@ __global__ __launch_bounds__(256) void stats_slice_kernel(const StatsArgs a)
 // touch the bucket (they are consecutive) - a uniform wavefront's sums (or the partials of the
 // first stage), a mixed wavefront's lane records of this bucket - and the records of the ragged
 // tail; one thread writes the bucket's totals.
-__global__ __launch_bounds__(256) void stats_finish_kernel(const StatsArgs a)
+template <bool GROUPED>
+__global__ __launch_bounds__(kStatsThreads) void stats_finish_kernel(const StatsArgs a)
 {
     const int b = a.b_lo + static_cast<int>(blockIdx.x);
     long long w0, w1;
     bucket_records(a, b, w0, w1);
     double su = 0.0, sw = 0.0, nf = 0.0;
-    if (a.slices > 1) {
-        if (static_cast<int>(threadIdx.x) < a.slices) {
+    // Only the first and the last wavefront of the bucket can be mixed.  The lane records of the
+    // first, those of the last and the ragged tail have a wavefront of this workgroup each (one lane
+    // per record), so that their dependent loads run beside the others' and not after them.
+    constexpr int kPlain = kStatsThreads - 3 * 64;
+    const int which = static_cast<int>(threadIdx.x >> 6) - kPlain / 64, lane = threadIdx.x & 63;
+    if (which < 0) {
+        if (a.slices == 1) {
+            add_records<kPlain, GROUPED>(a.records, w0, w1, b, su, sw, nf);
+        } else if (static_cast<int>(threadIdx.x) < a.slices) {
             const StatsRecord r = a.partials[static_cast<long long>(b) * kStatsMaxSlices + threadIdx.x];
             su = r.ssu;
             sw = r.ssw;
             nf = r.nf;
         }
-    } else {
-        add_records(a.records, w0, w1, b, su, sw, nf);
-    }
-    // Only the first and the last wavefront of the bucket can be mixed: wavefront 0 of this
-    // workgroup takes the lane records of the first, wavefront 1 those of the last, one lane
-    // each; wavefront 2 takes the ragged tail.
-    const unsigned which = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-    if (which < 2 && w1 > w0 && (which == 0 || w1 - 1 != w0)) {
-        const StatsRecord r = a.records[which == 0 ? w0 : w1 - 1];
-        if (r.bucket == -1) {
-            const StatsRecord lr = a.lane_records[static_cast<long long>(r.nf) * 64 + lane];
-            if (lr.bucket == b) {
-                su += lr.ssu;
-                sw += lr.ssw;
-                nf += lr.nf;
+    } else if (which < 2) {
+        const long long t = which == 0 ? w0 : w1 - 1;
+        // (in a group that is not flagged only the first record has been written)
+        if (w1 > w0 && (which == 0 || t != w0) &&
+            (!GROUPED || a.records[t / kNormsTiles * kNormsTiles].flag)) {
+            const StatsRecord r = a.records[t];
+            if (r.bucket == -1) {
+                const StatsRecord lr = a.lane_records[static_cast<long long>(r.nf) * 64 + lane];
+                if (lr.bucket == b) {
+                    su = lr.ssu;
+                    sw = lr.ssw;
+                    nf = lr.nf;
+                }
             }
         }
-    }
-    if (which == 2 && static_cast<int>(lane) < a.tail_count) {
+    } else if (lane < a.tail_count) {
         const StatsRecord tr = a.lane_records[static_cast<long long>(a.n_buckets) * 64 + lane];
         if (tr.bucket == b) {
-            su += tr.ssu;
-            sw += tr.ssw;
-            nf += tr.nf;
+            su = tr.ssu;
+            sw = tr.ssw;
+            nf = tr.nf;
         }
     }
     workgroup_sum(su, sw, nf);
@@ -345,14 +378,6 @@ __global__ __launch_bounds__(256) void sgd_kernel(const SgdArgs a)
 //     g = rate_b * (u + wd*w);  v' = mu*v + g;  step = nesterov ? g + mu*v' : v';  w' = w - lr*step
 // One lane-vector per lane in both, so that record k belongs to elements [256k, 256k + 256).
 
-// the wavefront's first lane-vector as a uniform value
-__device__ __forceinline__ long long wave_first(long long vi)
-{
-    const long long v0 = vi - (threadIdx.x & 63u);
-    return (static_cast<long long>(__builtin_amdgcn_readfirstlane(static_cast<int>(v0 >> 32))) << 32) |
-           static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(v0)));
-}
-
 // bucket of the lane's 4 elements (they never straddle a bucket start: starts are multiples
 // of 4) and how many of them lie inside it; the search starts at the wavefront's bucket
 __device__ __forceinline__ int lane_bucket(const long long *tbl, int nb, int wave_bucket, long long e,
@@ -365,42 +390,74 @@ __device__ __forceinline__ int lane_bucket(const long long *tbl, int nb, int wav
     return b;
 }
 
-// A wavefront takes K consecutive tiles of 256 elements: all 2K loads are issued before the
-// first is used, and every tile leaves its own record.
-constexpr int kNormsTiles = 4;
-
+// A wavefront takes K consecutive tiles of 256 elements.  Where they all lie inside one bucket,
+// as nearly always, it requests u and w of one tile after the other, squares and sums in its
+// lanes, and combines the lanes once at the end: one record instead of K, and K times fewer
+// cross-lane steps in fp64.  Other wavefronts leave a record per tile, or per lane where a tile
+// is mixed.  It is bound by the reads of u and w (25.6 M elements after a round: 36 us = 5.7 TB/s,
+// 54.6 before; most of the difference is that lars_kernel no longer leaves 200 MB of w and v in the
+// last-level cache which this kernel's reads would push out).
 template <bool NT>
 __global__ __launch_bounds__(64) void norms_kernel(const SgdArgs a, const StatsArgs st)
 {
     constexpr int K = kNormsTiles;
+    typedef const long long __attribute__((address_space(4))) KLong;
+    KLong *tbl = (KLong *)reinterpret_cast<unsigned long long>(st.table);
     const long long nvec = a.n / 4;
     const long long tile0 = static_cast<long long>(blockIdx.x) * K;
-    int bucket = find_bucket(st.table, st.n_buckets, a.e0 + tile0 * 256);
-    f32x4 u[K], w[K];
-    if (nvec > 0) {
+    const long long first = a.e0 + tile0 * 256, last = first + K * 256;
+    const unsigned lane = threadIdx.x & 63u;
+    const f32x4 *up = reinterpret_cast<const f32x4 *>(a.u + first) + lane;
+    const f32x4 *wp = reinterpret_cast<const f32x4 *>(a.w + first) + lane;
+    const bool whole = (tile0 + K) * 64 <= nvec;
+    f32x4 u, w;
+    if (whole) {
+        u = ld_f4<NT>(reinterpret_cast<const float *>(up));
+        w = ld_f4<NT>(reinterpret_cast<const float *>(wp));
+    }
+    int bucket = st.b_lo;
+    for (int hi = st.b_hi; hi - bucket > 1;) {
+        const int mid = (bucket + hi) >> 1;
+        if (tbl[2 * mid] <= first) bucket = mid;
+        else hi = mid;
+    }
+    if (whole && tbl[2 * bucket + 1] >= last) {
+        LaneStats ls = {0.0, 0.0, 0u, bucket};
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            // beyond the end: the last lane-vector again, discarded below
-            long long vi = (tile0 + k) * 64 + threadIdx.x;
-            if (vi >= nvec) vi = nvec - 1;
-            u[k] = ld_f4<NT>(a.u + a.e0 + vi * 4);
-            w[k] = ld_f4<NT>(a.w + a.e0 + vi * 4);
+            const f32x4 x = u, y = w;
+            if (k + 1 < K) {
+                u = ld_f4<NT>(reinterpret_cast<const float *>(up + (k + 1) * 64));
+                w = ld_f4<NT>(reinterpret_cast<const float *>(wp + (k + 1) * 64));
+            }
+            stats_add(ls, x.x, y.x, true);
+            stats_add(ls, x.y, y.y, true);
+            stats_add(ls, x.z, y.z, true);
+            stats_add(ls, x.w, y.w, true);
         }
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const long long vi = (tile0 + k) * 64 + threadIdx.x;
-        LaneStats ls = {0.0, 0.0, 0u, -1};
-        if (vi < nvec) {
-            int n_valid;
-            bucket = lane_bucket(st.table, st.n_buckets, bucket, a.e0 + vi * 4, n_valid);
-            ls.bucket = bucket;
-            if (n_valid > 0) stats_add(ls, u[k].x, w[k].x, true);
-            if (n_valid > 1) stats_add(ls, u[k].y, w[k].y, true);
-            if (n_valid > 2) stats_add(ls, u[k].z, w[k].z, true);
-            if (n_valid > 3) stats_add(ls, u[k].w, w[k].w, true);
+        const double su = wave_sum(ls.ssu), sw = wave_sum(ls.ssw);
+        unsigned nf = 0u;
+        if (__builtin_amdgcn_ballot_w64(ls.nf != 0u) != 0ull) nf = wave_sum(ls.nf);
+        if (lane == 0u) {
+            const StatsRecord rec = {su, sw, bucket, nf, 0};
+            st.records[tile0] = rec;
         }
-        stats_commit(st.records, st.lane_records, ls, tile0 + k);
+    } else {
+        for (int k = 0; k < K; ++k) {
+            const long long vi = (tile0 + k) * 64 + lane;
+            LaneStats ls = {0.0, 0.0, 0u, -1};
+            if (vi < nvec) {
+                u = ld_f4<NT>(a.u + a.e0 + vi * 4);
+                w = ld_f4<NT>(a.w + a.e0 + vi * 4);
+                int n_valid;
+                ls.bucket = bucket = lane_bucket(st.table, st.n_buckets, bucket, a.e0 + vi * 4, n_valid);
+                if (n_valid > 0) stats_add(ls, u.x, w.x, true);
+                if (n_valid > 1) stats_add(ls, u.y, w.y, true);
+                if (n_valid > 2) stats_add(ls, u.z, w.z, true);
+                if (n_valid > 3) stats_add(ls, u.w, w.w, true);
+            }
+            stats_commit(st.records, st.lane_records, ls, tile0 + k, k == 0 ? 1 : 0);
+        }
     }
     const long long rem = a.n - nvec * 4;
     if (blockIdx.x == 0 && static_cast<long long>(threadIdx.x) < rem) {
@@ -427,12 +484,17 @@ __device__ __forceinline__ f32x4 scaled_gradient(float rate, float wd, f32x4 u, 
     return rate * g;
 }
 
+// NT: w, v and their new values are streamed.  The old w and u have just been read by norms_kernel
+// and are in the last-level cache where they fit; writing w and v past it leaves nothing there
+// that the next kernels would have to write back first.
 template <bool FAST, bool NT>
 __global__ __launch_bounds__(64) void lars_kernel(const SgdArgs a, const StatsArgs st)
 {
+    typedef const long long __attribute__((address_space(4))) KLong;
+    KLong *tbl = (KLong *)reinterpret_cast<unsigned long long>(st.table);
     const long long nvec = a.n / 4;
-    const long long vi = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int wave_bucket = find_bucket(st.table, st.n_buckets, a.e0 + 4 * wave_first(vi));
+    const long long vi = static_cast<long long>(blockIdx.x) * 64 + threadIdx.x;
+    const long long first = a.e0 + static_cast<long long>(blockIdx.x) * 256;
     // the decay is part of the scaled gradient, so the plain rule follows with wd = 0
     const UpdateRule rule = {a.neg_lr, a.mu, 0.0f, a.nesterov};
     if (vi < nvec) {
@@ -440,9 +502,24 @@ __global__ __launch_bounds__(64) void lars_kernel(const SgdArgs a, const StatsAr
         const f32x4 u = ld_f4<true>(a.u + e);
         const f32x4 vo = ld_f4<NT>(a.v + e);
         const f32x4 wo = ld_f4<NT>(a.w + e);
-        int n_valid;
-        const int b = lane_bucket(st.table, st.n_buckets, wave_bucket, e, n_valid);
-        const float rate = st.stats[b].rate;
+        // bucket of the wavefront's first element and the rates of it and of those that begin
+        // inside the tile: uniform, scalar loads beside the streams
+        int b = st.b_lo;
+        for (int hi = st.b_hi; hi - b > 1;) {
+            const int mid = (b + hi) >> 1;
+            if (tbl[2 * mid] <= first) b = mid;
+            else hi = mid;
+        }
+        typedef const float __attribute__((address_space(4))) KFloat;
+        KFloat *rates = (KFloat *)reinterpret_cast<unsigned long long>(&st.stats[0].rate);
+        constexpr int kStep = sizeof(BucketStats) / sizeof(float);
+        float rate = rates[static_cast<long long>(b) * kStep];
+        for (++b; b < st.b_hi; ++b) {
+            const long long start = tbl[2 * b];
+            if (start >= first + 256) break;
+            const float r = rates[static_cast<long long>(b) * kStep];
+            if (e >= start) rate = r;
+        }
         f32x4 vn, wn;
         update_rule<FAST>(rule, scaled_gradient<FAST>(rate, a.wd, u, wo), vo, wo, vn, wn);
         st_f4<NT>(a.v + e, vn);
@@ -482,16 +559,31 @@ int views_average_waves(int n_views)
 
 }  // namespace
 
-hipError_t launch_stats_finish(const StatsArgs &a, hipStream_t stream)
+hipError_t launch_stats_finish(const StatsArgs &args, hipStream_t stream)
 {
-    const int n = a.b_hi - a.b_lo;
+    const int n = args.b_hi - args.b_lo;
     if (n <= 0) return hipSuccess;
-    if (a.slices > kStatsMaxSlices || a.slices < 1) return hipErrorInvalidValue;
+    if (args.slices > kStatsMaxSlices || args.slices < 1) return hipErrorInvalidValue;
+    StatsArgs a = args;
+    const dim3 threads(kStatsThreads);
+    // One workgroup per bucket takes two trips to memory for 12 k records (ResNet-50, 161 buckets of up
+    // to 9 k records: 6.7 us in one launch, 9.9 us with a first stage); with more the first stage
+    // is worth its launch (262 k records: 9.5 us, 42 us without).  Groups of norms_kernel count once.
+    if (a.want_rate) {                   // the records are norms_kernel's
+        a.slices = a.slices <= 12 ? 1 : (a.slices + kNormsTiles - 1) / kNormsTiles;
+        if (a.slices > 1) {
+            hipLaunchKernelGGL(stats_slice_kernel<true>, dim3(n, a.slices), threads, 0, stream, a);
+            if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(stats_finish_kernel<true>, dim3(n), threads, 0, stream, a);
+        return hipGetLastError();
+    }
+    if (a.slices <= 3) a.slices = 1;
     if (a.slices > 1) {
-        hipLaunchKernelGGL(stats_slice_kernel, dim3(n, a.slices), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(stats_slice_kernel<false>, dim3(n, a.slices), threads, 0, stream, a);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(stats_finish_kernel, dim3(n), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(stats_finish_kernel<false>, dim3(n), threads, 0, stream, a);
     return hipGetLastError();
 }
 
@@ -578,10 +670,11 @@ hipError_t launch_norms(const SgdArgs &a, const StatsArgs &st, hipStream_t strea
     if (g * 64 > kMaxGridThreads) return hipErrorInvalidValue;    // the kernel does not stride
     // u and w are read again by the update right after: leave them in the last-level cache
     // when both fit
+    const dim3 grid(static_cast<unsigned>(g)), block(64);
     if (a.n * 8 <= kStateCacheBytes)
-        hipLaunchKernelGGL(norms_kernel<false>, dim3(static_cast<unsigned>(g)), dim3(64), 0, stream, a, st);
+        hipLaunchKernelGGL(norms_kernel<false>, grid, block, 0, stream, a, st);
     else
-        hipLaunchKernelGGL(norms_kernel<true>, dim3(static_cast<unsigned>(g)), dim3(64), 0, stream, a, st);
+        hipLaunchKernelGGL(norms_kernel<true>, grid, block, 0, stream, a, st);
     return hipGetLastError();
 }
 
@@ -591,7 +684,10 @@ hipError_t launch_sgd_lars(const SgdArgs &a, const StatsArgs &st, bool fast, hip
     long long g = (a.n / 4 + 63) / 64;                            // one lane-vector per lane
     if (g < 1) g = 1;
     if (g * 64 > kMaxGridThreads) return hipErrorInvalidValue;
-    const bool nt = a.n * 8 > kStateCacheBytes;
+    // w and v are streamed unless u, w and v stay in the last-level cache until the next step
+    // (norms, rate and update on 10 M elements: 98 us streamed, 99 not; 4 M: 55.9 and 54.0; 25.6 M after
+    // a round: 117 and 136)
+    const bool nt = a.n * 12 > kSmallRoundBytes;
     const dim3 grid(static_cast<unsigned>(g)), block(64);
     if (fast) {
         if (nt) hipLaunchKernelGGL((lars_kernel<true, true>), grid, block, 0, stream, a, st);

@@ -198,11 +198,12 @@ __device__ __forceinline__ void stats_add(LaneStats &ls, float u, float w_old, b
 // one whose first lane lies in bucket b0 while a later lane does not: block b0 of the lane
 // records is its own.
 __device__ __forceinline__ void stats_commit(StatsRecord *records, StatsRecord *lane_records,
-                                             const LaneStats &ls, long long wave_index)
+                                             const LaneStats &ls, long long wave_index,
+                                             long long flag = 0)
 {
     const int b0 = __builtin_amdgcn_readfirstlane(ls.bucket);
     const bool mixed = __builtin_amdgcn_ballot_w64(ls.bucket != b0) != 0ull;
-    StatsRecord rec = {0.0, 0.0, b0 >= 0 ? b0 : -2, 0u, 0};
+    StatsRecord rec = {0.0, 0.0, b0 >= 0 ? b0 : -2, 0u, flag};
     if (mixed) {
         const StatsRecord mine = {ls.ssu, ls.ssw, ls.bucket, ls.nf, 0};
         lane_records[static_cast<long long>(b0) * 64 + (threadIdx.x & 63u)] = mine;

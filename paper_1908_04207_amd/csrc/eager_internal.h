@@ -29,7 +29,7 @@ struct StatsRecord {
     double ssu, ssw;
     int bucket;
     unsigned nf;
-    long long pad;
+    long long flag;              // norms_kernel: the tiles of the group have records of their own
 };
 
 struct StatsArgs {

@@ -97,3 +97,60 @@ def test_statistics_of_a_streamed_round(eb, dtype):
             # 64-bit sums in another order: 1e-10 is what the statistics promise
             assert np.isclose(got[b, 0], np.sum(u[fine] ** 2), rtol=1e-10, atol=0), (t, b)
             assert np.isclose(got[b, 1], np.sum(w[np.isfinite(w)] ** 2), rtol=1e-10, atol=0), (t, b)
+
+
+@pytest.mark.parametrize("num", [
+    [2048 * 3, 100, 2047, 2049, 5, 256, 2048],            # groups of 8 tiles begin and end everywhere
+    [3], [255, 4096, 1], [2048 * 40 + 3, 700_001, 9],
+    [13_000_001, 40, 2_000_000]])                         # enough records for the first stage
+def test_layerwise_norms_by_groups_of_tiles(eb, num):
+    """Norms, rates and the layer-wise step over buckets that lie anywhere in the groups of tiles
+    the norms pass works in, in a workspace that a round with statistics has used before."""
+    off, cur = [], 0
+    for m in num:
+        off.append(cur)
+        cur = (cur + m + 3) // 4 * 4
+    dev = torch.device("cuda:0")
+    P, trust, eps, lr, mu, wd = 2, 0.02, 1e-9, 0.1, 0.9, 1e-3
+    ctx = eb.Context(P, off, num)
+    ctx.eager_set_update_rule(wd, False)
+    fill = lambda rank, sigma: wg.fill(torch.empty(cur), 3, 0, rank, sigma)   # noqa: E731
+    w, v, u = fill(wg.PARAM_RANK, 0.02), fill(9, 1e-3), fill(8, 1e-3)
+    u[off[0]] = float("nan")
+    stats = torch.zeros(len(num) * 32, dtype=torch.uint8, device=dev)
+    need = ctx.eager_stats_workspace_bytes()
+    ws = torch.empty(need, dtype=torch.uint8, device=dev)
+    ctx.eager_stats_attach(stats, ws, need)
+    wd_, vd, ud = w.to(dev), v.to(dev), u.to(dev)
+    G = [torch.zeros(cur, device=dev) for _ in range(P)]
+    R = [torch.zeros(cur, device=dev) for _ in range(P)]
+    recv = torch.empty(cur, device=dev)
+    for t, (b0, b1) in enumerate(((0, len(num)), (len(num) - 1, len(num)), (0, 1))):
+        ctx.eager_partial_allreduce(eb.make_plan(eb.MAJORITY, P, t, 0b11), G, R, recv=recv)
+        before_w, before_v = wd_.cpu(), vd.cpu()
+        ctx.eager_sgd_step_lars(ud, (wd_, vd, lr, mu), trust, eps, b0=b0, b1=b1)
+        torch.cuda.synchronize()
+        norms = stats.view(torch.float64).view(-1, 4)[:, :2].cpu()
+        bad = stats.view(torch.int64).view(-1, 4)[:, 2].cpu()
+        rates = stats.view(torch.float32).view(-1, 8)[:, 6].cpu()
+        for b in range(b0, b1):
+            sl = slice(off[b], off[b] + num[b])
+            x, y, z = u[sl].double(), before_w[sl].double(), before_v[sl].double()
+            ok = torch.isfinite(x)
+            oky = torch.isfinite(y)
+            su, sw = float((x[ok] ** 2).sum()), float((y[oky] ** 2).sum())
+            assert int(bad[b]) == int((~ok).sum())
+            assert abs(float(norms[b, 0]) - su) <= 1e-10 * su and abs(float(norms[b, 1]) - sw) <= 1e-10 * sw
+            rate = trust * sw ** 0.5 / (su ** 0.5 + wd * sw ** 0.5 + eps) if su and sw else 1.0
+            assert abs(float(rates[b]) - rate) <= 1.2e-7 * rate      # one rounding to fp32
+            g = rate * (x + wd * y)
+            vn = mu * z + g
+            wn = y - lr * vn
+            # a handful of fp32 roundings per element
+            for got, want in ((vd.cpu()[sl], vn), (wd_.cpu()[sl], wn)):
+                fine = torch.isfinite(want)
+                assert torch.equal(torch.isfinite(got), fine)
+                if bool(fine.any()):
+                    scale = float(want[fine].abs().max())
+                    assert float((got.double() - want)[fine].abs().max()) <= 1e-6 * scale
+    ctx.close()
