@@ -1,9 +1,14 @@
-"""ctypes binding of libeager.so: argument marshalling only.
+"""Binding of libeager.so: argument marshalling only.
 
 Every step of a round runs in the library's HIP kernels; nothing here computes.  There
 is no fallback: if the shared library is missing the import of this module fails.
 PyTorch tensors are accepted as device buffers (their data_ptr is passed on) and the
 current torch stream is used unless a stream is given.
+
+ctypes defines every call and what it accepts.  The calls of a training step hand their
+arguments to the extension module _marshal first, which knows the usual forms (lists of
+tensors, pointer tables, tuples of floats) and calls the same entry points without a ctypes
+object per argument; it returns NotImplemented for everything else.
 """
 from __future__ import annotations
 
@@ -120,6 +125,19 @@ def _load() -> ctypes.CDLL:
 
 
 lib = _load()
+try:
+    from . import _marshal
+except ImportError as e:
+    raise ImportError(f"the argument marshalling module is missing ({e}): build it with "
+                      "`python -m paper_1908_04207_amd.build`") from e
+_marshal.bind(tuple(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in (
+    "eager_plan_participation", "eager_plan_quorum", "eager_partial_allreduce_solo",
+    "eager_partial_allreduce_majority", "eager_partial_allreduce_quorum",
+    "eager_partial_allreduce_lagging", "eager_partial_allreduce_exchange", "eager_sgd_step",
+    "eager_sgd_step_lars", "eager_stash", "eager_sgd_step_views", "eager_average_views")),
+    Plan, ctypes.Array)
+# a child process has no current stream before torch says so again
+os.register_at_fork(after_in_child=lambda: _marshal.streams(None, None))
 
 
 def _ptr(x) -> Optional[int]:
@@ -133,7 +151,10 @@ def _ptr(x) -> Optional[int]:
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        current = torch.cuda.current_stream().cuda_stream
+        # initialised by now: from here on _marshal asks the two functions behind that call
+        _marshal.streams(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        return current
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -150,6 +171,9 @@ def status_string(status: int) -> str:
 
 def eager_plan_participation(mode: int, arrival_ms: Sequence[float], seed: int, step: int,
                              window_ms: float = 0.0, flags: int = 0) -> Plan:
+    plan = _marshal.plan_participation(mode, arrival_ms, seed, step, window_ms, flags)
+    if type(plan) is Plan:
+        return plan
     P = len(arrival_ms)
     arr = (ctypes.c_double * max(P, 1))(*arrival_ms)
     plan = Plan()
@@ -162,6 +186,9 @@ def eager_plan_participation(mode: int, arrival_ms: Sequence[float], seed: int, 
 
 def eager_plan_quorum(arrival_ms: Sequence[float], quorum: int, step: int,
                       window_ms: float = 0.0) -> Plan:
+    plan = _marshal.plan_quorum(arrival_ms, quorum, step, window_ms)
+    if type(plan) is Plan:
+        return plan
     P = len(arrival_ms)
     arr = (ctypes.c_double * max(P, 1))(*arrival_ms)
     plan = Plan()
@@ -198,6 +225,10 @@ def make_plan(mode: int, P: int, step: int, mask: int, initiator: Optional[int] 
     return Plan(mode, P, step, mask, initiator, bin(mask).count("1"), flags, 0)
 
 
+_ALLREDUCE = {SOLO: "eager_partial_allreduce_solo", MAJORITY: "eager_partial_allreduce_majority",
+              QUORUM: "eager_partial_allreduce_quorum"}
+
+
 class Context:
     """Owns one eager_ctx.  Buffers are passed per call and stay owned by the caller."""
 
@@ -213,12 +244,14 @@ class Context:
         if st != OK:
             raise EagerError(st, f"eager_create: {status_string(st)}")
         self._h = h
+        self._addr = h.value
         self.P, self.n_buckets = P, n
 
     def close(self) -> None:
         if getattr(self, "_h", None) and lib is not None:   # lib is None at interpreter exit
             lib.eager_destroy(self._h)
             self._h = None
+            self._addr = 0
 
     __del__ = close
 
@@ -233,7 +266,13 @@ class Context:
         of the list to the partial allreduce calls of a tight loop."""
         return (ctypes.c_void_p * max(len(buffers), 1))(*[_ptr(x) for x in buffers])
 
-    def _allreduce(self, fn, what, plan, grads, resid, recv, opt, b0, b1, stream):
+    def _allreduce(self, kind, fn, what, plan, grads, resid, recv, opt, b0, b1, stream, absent=0):
+        st = _marshal.round(kind, self._addr, self.P, self.n_buckets, plan, absent, b0, b1, grads,
+                            resid, recv, opt, stream)
+        if st is not NotImplemented:
+            if st != OK:
+                self._check(st, what)
+            return
         b1 = self.n_buckets if b1 is None else b1
         P = len(grads)
         g = grads if isinstance(grads, ctypes.Array) else self.pointers(grads)
@@ -249,17 +288,17 @@ class Context:
 
     def eager_partial_allreduce_solo(self, plan: Plan, grads, resid, recv=None, opt=None,
                                      b0: int = 0, b1: Optional[int] = None, stream=None):
-        self._allreduce(lib.eager_partial_allreduce_solo, "eager_partial_allreduce_solo", plan,
+        self._allreduce(0, lib.eager_partial_allreduce_solo, "eager_partial_allreduce_solo", plan,
                         grads, resid, recv, opt, b0, b1, stream)
 
     def eager_partial_allreduce_majority(self, plan: Plan, grads, resid, recv=None, opt=None,
                                          b0: int = 0, b1: Optional[int] = None, stream=None):
-        self._allreduce(lib.eager_partial_allreduce_majority, "eager_partial_allreduce_majority",
+        self._allreduce(1, lib.eager_partial_allreduce_majority, "eager_partial_allreduce_majority",
                         plan, grads, resid, recv, opt, b0, b1, stream)
 
     def eager_partial_allreduce_quorum(self, plan: Plan, grads, resid, recv=None, opt=None,
                                        b0: int = 0, b1: Optional[int] = None, stream=None):
-        self._allreduce(lib.eager_partial_allreduce_quorum, "eager_partial_allreduce_quorum",
+        self._allreduce(2, lib.eager_partial_allreduce_quorum, "eager_partial_allreduce_quorum",
                         plan, grads, resid, recv, opt, b0, b1, stream)
 
     def eager_partial_allreduce_lagging(self, plan: Plan, absent: int, grads, resid, recv=None,
@@ -267,14 +306,18 @@ class Context:
                                         stream=None):
         """grads[p] may be None for the processes in `absent`."""
         fn = lambda h, pl, *rest: lib.eager_partial_allreduce_lagging(h, pl, absent, *rest)  # noqa: E731
-        self._allreduce(fn, "eager_partial_allreduce_lagging", plan, grads, resid, recv, opt, b0,
-                        b1, stream)
+        self._allreduce(3, fn, "eager_partial_allreduce_lagging", plan, grads, resid, recv, opt, b0,
+                        b1, stream, absent)
 
     def eager_partial_allreduce_exchange(self, plan: Plan, grads, resid, recv=None, opt=None,
                                          stream=None) -> None:
         """`grads` and `resid` are pointer tables from Context.pointers (the library exchanges
         the entries of late processes in them), or lists of device buffers - then the two lists
         are permuted in place the way the library permuted their pointers."""
+        st = _marshal.round(4, self._addr, self.P, self.n_buckets, plan, 0, 0, None, grads, resid,
+                            recv, opt, stream)
+        if st is not NotImplemented:
+            return self._check(st, "eager_partial_allreduce_exchange")
         tables = isinstance(grads, ctypes.Array)
         g = grads if tables else self.pointers(grads)
         r = resid if tables else self.pointers(resid)
@@ -295,6 +338,9 @@ class Context:
 
     def eager_stash(self, process: int, grad, resid, b0: int = 0, b1: Optional[int] = None,
                     stream=None) -> None:
+        st = _marshal.stash(self._addr, self.n_buckets, process, b0, b1, grad, resid, stream)
+        if st is not NotImplemented:
+            return self._check(st, "eager_stash")
         b1 = self.n_buckets if b1 is None else b1
         self._check(lib.eager_stash(self._h, process, b0, b1, _ptr(grad), _ptr(resid),
                                     _stream(stream)), "eager_stash")
@@ -312,12 +358,12 @@ class Context:
 
     def eager_partial_allreduce(self, plan: Plan, *a, **kw):
         """Dispatch on plan.mode to the entry point of that name."""
-        fn = {SOLO: self.eager_partial_allreduce_solo,
-              MAJORITY: self.eager_partial_allreduce_majority,
-              QUORUM: self.eager_partial_allreduce_quorum}[plan.mode]
-        fn(plan, *a, **kw)
+        getattr(self, _ALLREDUCE[plan.mode])(plan, *a, **kw)
 
     def eager_sgd_step(self, update, opt, b0: int = 0, b1: Optional[int] = None, stream=None):
+        st = _marshal.step(self._addr, self.n_buckets, b0, b1, update, opt, None, None, stream)
+        if st is not NotImplemented:
+            return self._check(st, "eager_sgd_step")
         b1 = self.n_buckets if b1 is None else b1
         params, momentum, lr, mu = opt
         o = Opt(_ptr(params), _ptr(momentum), lr, mu)
@@ -326,6 +372,10 @@ class Context:
 
     def eager_sgd_step_lars(self, update, opt, trust: float, eps: float = 0.0, b0: int = 0,
                             b1: Optional[int] = None, stream=None) -> None:
+        if type(trust) is float:           # (the extension reads None as: the plain rule)
+            st = _marshal.step(self._addr, self.n_buckets, b0, b1, update, opt, trust, eps, stream)
+            if st is not NotImplemented:
+                return self._check(st, "eager_sgd_step_lars")
         b1 = self.n_buckets if b1 is None else b1
         params, momentum, lr, mu = opt
         o = Opt(_ptr(params), _ptr(momentum), lr, mu)
@@ -345,6 +395,11 @@ class Context:
 
     def eager_sgd_step_views(self, update, params, momentum, lr: float, mu: float, b0: int = 0,
                              b1: Optional[int] = None, stream=None) -> None:
+        if momentum is not None:           # (the extension reads None as: the average)
+            st = _marshal.views(self._addr, self.n_buckets, b0, b1, update, params, momentum, lr, mu,
+                                stream)
+            if st is not NotImplemented:
+                return self._check(st, "eager_sgd_step_views")
         b1 = self.n_buckets if b1 is None else b1
         tab = lambda x: x if isinstance(x, ctypes.Array) else self.pointers(x)  # noqa: E731
         self._check(lib.eager_sgd_step_views(self._h, b0, b1, _ptr(update), len(params),
@@ -352,6 +407,10 @@ class Context:
                                              lr, mu, _stream(stream)), "eager_sgd_step_views")
 
     def eager_average_views(self, views, b0: int = 0, b1: Optional[int] = None, stream=None) -> None:
+        if type(views) in (list, tuple):
+            st = _marshal.views(self._addr, self.n_buckets, b0, b1, None, views, None, None, None, stream)
+            if st is not NotImplemented:
+                return self._check(st, "eager_average_views")
         b1 = self.n_buckets if b1 is None else b1
         self._check(lib.eager_average_views(self._h, b0, b1, len(views), self.pointers(views),
                                             _stream(stream)), "eager_average_views")

@@ -11,6 +11,7 @@ import hashlib
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -19,6 +20,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libeager.so")
 STAMP = LIB + ".srchash"
+MARSHAL = os.path.join(HERE, "_marshal.so")
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ["eager_round_kernels.hip", "eager_aux_kernels.hip", "eager_static_kernels.hip",
            "eager_calib_kernels.hip", "eager_api.cpp"]
@@ -99,6 +101,7 @@ def build(verbose: bool = False, extra=(), force: bool = True) -> str:
         objs = list(pool.map(compile_one, SOURCES))
     if os.path.exists(STAMP):
         os.remove(STAMP)
+    build_marshal(verbose)
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -108,9 +111,19 @@ def build(verbose: bool = False, extra=(), force: bool = True) -> str:
     return LIB
 
 
+def build_marshal(verbose: bool = False) -> str:
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "eager_marshal.cpp"),
+           "-o", MARSHAL]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    _run(cmd)
+    return MARSHAL
+
+
 def is_current() -> bool:
     """Whether the built library was compiled from the sources as they are now."""
-    if not (os.path.exists(LIB) and os.path.exists(STAMP)):
+    if not (os.path.exists(LIB) and os.path.exists(MARSHAL) and os.path.exists(STAMP)):
         return False
     with open(STAMP) as f:
         return f.read().strip() == source_hash()

@@ -1,0 +1,144 @@
+"""The native argument marshalling against the ctypes path, which defines what a call accepts and
+how it refuses: every form of argument goes through both, and the outcome - status, message, type
+of exception, plan - must be the same.  All calls are refused by the library's own checks before
+anything is launched, so this runs without a GPU.
+"""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_1908_04207_amd import binding as eb
+
+
+class _Absent:
+    """Stands in for the extension module: knows no form at all."""
+    def __getattr__(self, name):
+        return lambda *a: NotImplemented
+
+
+class _Buffer:
+    def __init__(self, p):
+        self.p = p
+
+    def data_ptr(self):
+        return self.p
+
+
+class _Broken:
+    def data_ptr(self):
+        raise KeyError("gone")
+
+
+class _Stream:
+    cuda_stream = 0
+
+
+class _OtherPlan(eb.Plan):
+    pass
+
+
+def _outcome(call):
+    try:
+        return "returned", call()
+    except Exception as e:                                  # noqa: BLE001
+        return type(e), getattr(e, "status", None), str(e)
+
+
+def _both(monkeypatch, call):
+    """What a call does through the extension where it knows the form, and without it."""
+    native = _outcome(call)
+    with monkeypatch.context() as m:
+        m.setattr(eb, "_marshal", _Absent())
+        plain = _outcome(call)
+    return native, plain
+
+
+P, A = 3, 0x10000
+G, R = [A * (i + 1) for i in range(P)], [A * (i + 9) for i in range(P)]
+OPT = (A * 20, A * 21, 0.1, 0.9)
+BAD = A * 22 + 4                                            # misaligned: refused before any launch
+TABLE = eb.Context.pointers
+
+ROUNDS = [
+    dict(), dict(grads=tuple(G), resid=tuple(R)), dict(grads=TABLE(G), resid=TABLE(R)),
+    dict(grads=TABLE(G), resid=R), dict(grads=[_Buffer(p) for p in G]), dict(grads=[None] + G[1:]),
+    dict(grads=[np.int64(1)] + G[1:]), dict(grads=[-16] + G[1:]), dict(grads=[1 << 70] + G[1:]),
+    dict(grads=[_Broken()] + G[1:]), dict(grads=G[:2]), dict(resid=R + R), dict(grads=TABLE(G[:2])),
+    dict(grads=(ctypes.c_int64 * 3)(*G)), dict(grads=iter(G)), dict(grads=None), dict(recv=None, opt=None),
+    dict(opt=list(OPT)), dict(opt=OPT[:3]), dict(opt=(*OPT[:2], 1, 0)), dict(opt=(None, *OPT[1:])),
+    dict(opt=(_Buffer(A), *OPT[1:])), dict(opt=(BAD, *OPT[1:]), recv=A), dict(opt=None),
+    dict(recv=_Buffer(BAD)), dict(recv=-4), dict(b0=1, b1=1), dict(b0=-1), dict(b1=7), dict(b0=True),
+    dict(b0=0.0), dict(b1=1 << 40), dict(b0=None), dict(stream=_Stream()), dict(stream=True),
+    dict(stream="x"), dict(plan="x"), dict(plan=_OtherPlan(0, P, 0, 1, 0, 1, 0, 0)),
+    dict(plan=eb.make_plan(eb.QUORUM, P, 0, 1)), dict(plan=eb.make_plan(eb.SOLO, 4, 0, 1)),
+    dict(plan=eb.make_plan(eb.SOLO, P, 0, 0b1001)),
+]
+
+
+@pytest.mark.parametrize("i", range(len(ROUNDS)))
+def test_rounds(monkeypatch, i):
+    ctx = eb.Context(P, [0, 64], [60, 64])
+    kw = dict(plan=eb.make_plan(eb.SOLO, P, 0, 1), grads=G, resid=R, recv=BAD, opt=OPT, b0=0, b1=None,
+              stream=0)
+    kw.update(ROUNDS[i])
+    plan = kw.pop("plan")
+    for name in ("solo", "majority", "quorum"):
+        fn = getattr(ctx, "eager_partial_allreduce_" + name)
+        native, plain = _both(monkeypatch, lambda: fn(plan, **kw))
+        assert native == plain and native[0] != "returned", (name, native, plain)
+    native, plain = _both(monkeypatch, lambda: ctx.eager_partial_allreduce_lagging(plan, 0b110, **kw))
+    assert native == plain and native[0] != "returned", (native, plain)
+    kw.pop("b0"), kw.pop("b1")
+    # (a range is not part of this call, so a bad one is not in it either: recv stays bad)
+    native, plain = _both(monkeypatch, lambda: ctx.eager_partial_allreduce_exchange(plan, **dict(kw, recv=BAD)))
+    assert native == plain and native[0] != "returned", (native, plain)
+    ctx.close()
+    native, plain = _both(monkeypatch, lambda: ctx.eager_partial_allreduce_solo(plan, G, R, opt=OPT, stream=0))
+    assert native == plain and native[0] != "returned"
+
+
+@pytest.mark.parametrize("kw", [
+    {}, dict(opt=list(OPT)), dict(opt=(A, A, 1, 0.5)), dict(opt=(None, A, 0.1, 0.9)), dict(update=None),
+    dict(update=_Buffer(BAD)), dict(update=_Broken()), dict(b0=2), dict(b0=1.5), dict(b1=-3), dict(stream=_Stream())])
+def test_steps_stash_and_views(monkeypatch, kw):
+    ctx = eb.Context(P, [0], [64])
+    a = dict(update=BAD, opt=OPT, b0=0, b1=None, stream=0)
+    a.update(kw)
+    u, opt = a.pop("update"), a.pop("opt")
+    calls = [lambda: ctx.eager_sgd_step(u, opt, **a)]
+    for trust, eps in ((0.02, 1e-9), (0.02, 0), (1, 0.0), (None, 0.0), (-1.0, 0.0)):
+        calls.append(lambda t=trust, e=eps: ctx.eager_sgd_step_lars(u, opt, t, e, **a))
+    for p in (0, 5, -1, 0.5):
+        calls.append(lambda p=p: ctx.eager_stash(p, BAD, u, **a))
+    for w, v in ((G, R), (tuple(G), R), (TABLE(G), TABLE(R)), (G, R[:2]), ([], []), (G, None), ([A] * 65, [A] * 65),
+                 (G, [_Broken()] * 3)):
+        for lr in (0.1, 1):
+            calls.append(lambda w=w, v=v, lr=lr: ctx.eager_sgd_step_views(BAD, w, v, lr, 0.9, **a))
+    for views in ([A, A], (A, A), [BAD], [], [None], [A] * 65, [_Broken()], iter([A])):
+        calls.append(lambda views=views: ctx.eager_average_views(views, **a))
+    for k, call in enumerate(calls):
+        native, plain = _both(monkeypatch, call)
+        assert native == plain and native[0] != "returned", (k, native, plain)
+    ctx.close()
+
+
+@pytest.mark.parametrize("times", [
+    [3.0, 1.0, 2.0], (3.0, 1.0, 2.0), [3, 1, 2], np.array([3.0, 1.0, 2.0]), [1.0], [], [1.0] * 65, [float("nan"), 1.0],
+    [float("inf"), 1.0], ["x"], [1.0] * 64])
+def test_plans(monkeypatch, times):
+    calls = []
+    for mode in (eb.SOLO, eb.MAJORITY, 7, 1.0):
+        for seed, step in ((1, 0), (-5, 3), (1 << 70, 1 << 65), (2, -1)):
+            for window, flags in ((0.0, 0), (1, 0), (0.5, eb.FLAG_STRICT_QUORUM), (-1.0, 0), (0.0, 8)):
+                calls.append(lambda a=(mode, times, seed, step, window, flags): eb.eager_plan_participation(*a))
+    for q in (0, 1, 2, 65, 1.0):
+        for window in (0.0, 1, 0.5, float("nan")):
+            calls.append(lambda a=(times, q, 4, window): eb.eager_plan_quorum(*a))
+    for call in calls:
+        native, plain = _both(monkeypatch, call)
+        if native[0] == "returned":
+            assert type(native[1]) is eb.Plan and plain[0] == "returned"
+            assert bytes(native[1]) == bytes(plain[1])
+        else:
+            assert native == plain
