@@ -183,6 +183,40 @@ __device__ __forceinline__ int find_bucket(const long long *tbl, int nb, long lo
     return lo;
 }
 
+// The bucket of a lane's 4 elements e .. e+3 inside the tile of 256 elements that begins at `first`
+// (starts are multiples of 4, so they never straddle one), and where it ends.  Everything looked
+// up is uniform over the wavefront: the table is read with scalar loads, which do not wait behind
+// the streams; buckets that begin inside the tile are gone through one by one.
+typedef const long long __attribute__((address_space(4))) KLong;
+__device__ __forceinline__ int tile_bucket(const long long *table, int b_lo, int b_hi, long long first,
+                                           long long e, long long &end)
+{
+    KLong *tbl = (KLong *)reinterpret_cast<unsigned long long>(table);
+    int lo = b_lo, hi = b_hi;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (tbl[2 * mid] <= first) lo = mid;
+        else hi = mid;
+    }
+    int b = lo;
+    end = tbl[2 * lo + 1];
+    for (int k = lo + 1; k < b_hi; ++k) {
+        const long long k_start = tbl[2 * k], k_end = tbl[2 * k + 1];
+        if (k_start >= first + 256) break;
+        if (e >= k_start) {
+            b = k;
+            end = k_end;
+        }
+    }
+    return b;
+}
+// how many of the lane's 4 elements lie inside the bucket (the rest is padding)
+__device__ __forceinline__ int inside(long long e, long long end)
+{
+    const long long left = end - e;
+    return left >= 4 ? 4 : left > 0 ? static_cast<int>(left) : 0;
+}
+
 __device__ __forceinline__ void stats_add(LaneStats &ls, float u, float w_old, bool has_w)
 {
     // the square of an fp32 value is exact in fp64, so the fused form rounds exactly like a

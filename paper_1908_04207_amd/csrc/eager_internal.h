@@ -125,7 +125,7 @@ enum SlotKind : unsigned {
     kSlotCopy = 8,                     // with kSkip: a copy
     kSlotTag = 15
 };
-struct SlotArgs {
+struct SlotHead {
     long long e0, n;
     int n_sum, n_copy;                 // slots of the sum (a multiple of kBurst), copies
     int waves_per_block, xcd_blocks;   // xcd_blocks: 0, or workgroups per XCD when every XCD takes
@@ -133,8 +133,11 @@ struct SlotArgs {
     float *w, *v, *recv;
     float inv_P, neg_lr, mu, wd;
     int nesterov;
+};
+struct SlotArgs {
+    SlotHead h;
     unsigned long long slot[kMaxSlots + kSlotChunk + kBurst];   // a process has at most two slots
-    float *dst[kMaxP];                 // of the copies, in order
+    float *dst[kMaxSlots + kSlotChunk + kBurst];                // of slot k where it is a copy
     StatsArgs stats;
 };
 

@@ -139,13 +139,13 @@ __device__ __forceinline__ void add_slot(unsigned long long slot, f32x4 raw, con
 // NTS: parameters, momentum and the receive buffer are streamed with the nontemporal hint
 // too (right when they are too large to stay in the last-level cache until the next round).
 template <bool FAST, bool NTS, bool OPT, bool STATS>
-__device__ __forceinline__ void finish_tile(KSlotArgs &a, const Lanes &L, const Sums &S, f32x4 vo,
+__device__ __forceinline__ void finish_tile(const SlotHead &h, const Lanes &L, const Sums &S, f32x4 vo,
                                             f32x4 wo, int n_valid, LaneStats &ls)
 {
     const long long base = L.e0 * 4;
     f32x4 sum = S.s;
     if (FAST) sum = sum + S.s2;
-    const f32x4 avg = sum * a.inv_P;
+    const f32x4 avg = sum * h.inv_P;
     if (STATS) {
         // n_valid: how many of the lane's 4 elements lie inside their bucket (the rest
         // is padding between buckets)
@@ -157,26 +157,25 @@ __device__ __forceinline__ void finish_tile(KSlotArgs &a, const Lanes &L, const 
     }
     f32x4 vn, wn;
     if (OPT) {
-        const UpdateRule rule = {a.neg_lr, a.mu, a.wd, a.nesterov};
+        const UpdateRule rule = {h.neg_lr, h.mu, h.wd, h.nesterov};
         update_rule<FAST>(rule, avg, vo, wo, vn, wn);
     }
     if (L.in) {
-        if (a.recv) st_at<NTS>(reinterpret_cast<char *>(a.recv) + base, L.off, avg);
+        if (h.recv) st_at<NTS>(reinterpret_cast<char *>(h.recv) + base, L.off, avg);
         if (OPT) {
-            st_at<NTS>(reinterpret_cast<char *>(a.v) + base, L.off, vn);
-            st_at<NTS>(reinterpret_cast<char *>(a.w) + base, L.off, wn);
+            st_at<NTS>(reinterpret_cast<char *>(h.v) + base, L.off, vn);
+            st_at<NTS>(reinterpret_cast<char *>(h.w) + base, L.off, wn);
         }
     }
 }
 
-// one element of a slot's stream (a SKIP without a stream, in a list that has none: 0)
+// one element of a slot's stream
 template <bool BF16>
 __device__ __forceinline__ float ld_slot_element(unsigned long long slot, long long i)
 {
     typedef const float __attribute__((address_space(1))) GF;
     typedef const unsigned short __attribute__((address_space(1))) GH;
     const unsigned long long base = slot & ~static_cast<unsigned long long>(kSlotTag);
-    if (base == 0) return 0.0f;
     if (BF16 && (slot & kSlotBf16))
         return __uint_as_float(static_cast<unsigned>(((GH *)base)[i]) << 16);
     return ((GF *)base)[i];
@@ -186,11 +185,11 @@ __device__ __forceinline__ float ld_slot_element(unsigned long long slot, long l
 // wavefront that has nothing else to do; fixed order in both modes.  The loads of 8 slots are
 // issued together: one at a time, a round of 16 streams waited 16 times for memory.
 template <bool BF16, bool STATS>
-__device__ __forceinline__ void slot_tail_element(KSlotArgs &a, long long i)
+__device__ __forceinline__ void slot_tail_element(KSlotArgs &a, const SlotHead &h, long long i)
 {
     float s = 0.0f, term = 0.0f;
     constexpr int C = 8;                  // the list ends in at least 16 SKIPs
-    for (int k0 = 0; k0 < a.n_sum; k0 += C) {
+    for (int k0 = 0; k0 < h.n_sum; k0 += C) {
         float x[C];
 #pragma unroll
         for (int j = 0; j < C; ++j) x[j] = ld_slot_element<BF16>(a.slot[k0 + j], i);
@@ -201,32 +200,32 @@ __device__ __forceinline__ void slot_tail_element(KSlotArgs &a, long long i)
             s = kind == kAdd || kind == kPair ? s + term : s;
         }
     }
-    for (int c0 = 0; c0 < a.n_copy; c0 += C) {
+    for (int c0 = 0; c0 < h.n_copy; c0 += C) {
         float x[C];
 #pragma unroll
-        for (int j = 0; j < C; ++j) x[j] = ld_slot_element<BF16>(a.slot[a.n_sum + c0 + j], i);
+        for (int j = 0; j < C; ++j) x[j] = ld_slot_element<BF16>(a.slot[h.n_sum + c0 + j], i);
 #pragma unroll
         for (int j = 0; j < C; ++j)
-            if (c0 + j < a.n_copy) a.dst[c0 + j][i] = x[j];
+            if (c0 + j < h.n_copy) a.dst[h.n_sum + c0 + j][i] = x[j];
     }
-    const float avg = s * a.inv_P;
-    if (a.recv) a.recv[i] = avg;
+    const float avg = s * h.inv_P;
+    if (h.recv) h.recv[i] = avg;
     if (STATS) {
         // a handful of single elements per launch: one record each, in the block after the
         // last bucket's
         const long long *tbl = a.stats.table;
         LaneStats ls = {0.0, 0.0, 0u, find_bucket(tbl, a.stats.n_buckets, i)};
-        if (i < tbl[2 * ls.bucket + 1]) stats_add(ls, avg, a.w ? a.w[i] : 0.0f, a.w != nullptr);
+        if (i < tbl[2 * ls.bucket + 1]) stats_add(ls, avg, h.w ? h.w[i] : 0.0f, h.w != nullptr);
         else ls.bucket = -2;                                   // padding
         const StatsRecord mine = {ls.ssu, ls.ssw, ls.bucket, ls.nf, 0};
         a.stats.lane_records[static_cast<long long>(a.stats.n_buckets) * 64 + (threadIdx.x & 63u)] = mine;
     }
-    if (a.w) {
-        const UpdateRule rule = {a.neg_lr, a.mu, a.wd, a.nesterov};
-        float v = a.v[i], w = a.w[i];
+    if (h.w) {
+        const UpdateRule rule = {h.neg_lr, h.mu, h.wd, h.nesterov};
+        float v = h.v[i], w = h.w[i];
         update_rule_scalar(rule, avg, v, w);
-        a.v[i] = v;
-        a.w[i] = w;
+        h.v[i] = v;
+        h.w[i] = w;
     }
 }
 
@@ -239,27 +238,40 @@ __host__ __device__ __forceinline__ long long slot_nvec(long long n)
     return BF16 ? (n / 8) * 2 : n / 4;
 }
 
+// The head of the arguments, all of it requested at once and waited for here: read where it is
+// used, one field after the other, a wavefront starts with four or five trips to the argument
+// segment in a row.
+__device__ __forceinline__ SlotHead read_head(KSlotArgs &a)
+{
+    SlotHead h;
+    __builtin_memcpy(&h, (const void __attribute__((address_space(4))) *)&a.h, sizeof h);
+    asm volatile("" : "+s"(h.e0), "+s"(h.n), "+s"(h.n_sum), "+s"(h.n_copy), "+s"(h.waves_per_block),
+                 "+s"(h.xcd_blocks), "+s"(h.w), "+s"(h.v), "+s"(h.recv), "+s"(h.inv_P), "+s"(h.neg_lr),
+                 "+s"(h.mu), "+s"(h.wd), "+s"(h.nesterov));
+    return h;
+}
+
 // Index of the wavefront in the grid.  Workgroups are dealt to the 8 XCDs round robin; xcd_blocks
 // gives every XCD one contiguous eighth of the run instead of every eighth tile (a launch
 // option, for A/B).  (The grid's shape comes with the arguments: the built-in blockDim is a load
 // from memory that every wavefront would have to wait for.)
-__device__ __forceinline__ long long wave_index(KSlotArgs &a)
+__device__ __forceinline__ long long wave_index(const SlotHead &h)
 {
     unsigned bid = blockIdx.x;
-    const unsigned per = static_cast<unsigned>(a.xcd_blocks);
+    const unsigned per = static_cast<unsigned>(h.xcd_blocks);
     if (per && bid < per * 8u) bid = (bid % 8u) * per + bid / 8u;
     const unsigned wave = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
-    return static_cast<long long>(bid) * a.waves_per_block + wave;
+    return static_cast<long long>(bid) * h.waves_per_block + wave;
 }
 
-__device__ __forceinline__ Lanes place_lanes(KSlotArgs &a, long long tile, long long nvec)
+__device__ __forceinline__ Lanes place_lanes(const SlotHead &h, long long tile, long long nvec)
 {
     const unsigned lane = threadIdx.x & 63u;
     const long long left = nvec - tile * 64;                   // uniform, > 0
     const unsigned last = left > 64 ? 63u : static_cast<unsigned>(left) - 1u;
     const unsigned lv = lane < last ? lane : last;
     Lanes L;
-    L.e0 = a.e0 + tile * 256;
+    L.e0 = h.e0 + tile * 256;
     L.in = lane <= last;
     L.off = lv * 16u;
     L.off_bf = (lv >> 1) * 16u;
@@ -267,33 +279,14 @@ __device__ __forceinline__ Lanes place_lanes(KSlotArgs &a, long long tile, long 
     return L;
 }
 
-// By-products: bucket of the lane-vector (it never straddles a bucket start, starts are multiples
-// of 4) and how many of its elements lie inside.  Everything that is looked up is uniform over the
-// wavefront: the table is read with scalar loads, which do not wait behind the streams.
+// By-products: bucket of the lane-vector and how many of its elements lie inside.
 __device__ __forceinline__ int place_stats(KSlotArgs &a, const Lanes &L, LaneStats &ls)
 {
-    typedef const long long __attribute__((address_space(4))) KLong;
-    KLong *tbl = (KLong *)reinterpret_cast<unsigned long long>(a.stats.table);
-    int lo = a.stats.b_lo, hi = a.stats.b_hi;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (tbl[2 * mid] <= L.e0) lo = mid;
-        else hi = mid;
-    }
     const long long e = L.e0 + (L.off >> 2);
-    int b = lo;
-    long long end = tbl[2 * lo + 1];
-    for (int k = lo + 1; k < a.stats.b_hi; ++k) {
-        const long long start = tbl[2 * k];
-        if (start >= L.e0 + 256) break;
-        if (e >= start) {
-            b = k;
-            end = tbl[2 * k + 1];
-        }
-    }
+    long long end;
+    const int b = tile_bucket(a.stats.table, a.stats.b_lo, a.stats.b_hi, L.e0, e, end);
     ls = {0.0, 0.0, 0u, L.in ? b : -1};
-    const long long left = end - e;
-    return !L.in ? 0 : left >= 4 ? 4 : left > 0 ? static_cast<int>(left) : 0;
+    return L.in ? inside(e, end) : 0;
 }
 
 // The round as a stream of bursts: a wavefront (one tile) requests kBurst = 2 slots, waits for both,
@@ -312,18 +305,19 @@ __global__ __launch_bounds__(256) void burst_kernel(const SlotArgs)
 {
     constexpr int D = kBurst;
     KSlotArgs &a = kernarg<SlotArgs>();
-    const long long nvec = slot_nvec<BF16>(a.n);
-    const long long tile = wave_index(a);
+    const SlotHead h = read_head(a);
+    const long long nvec = slot_nvec<BF16>(h.n);
+    const long long tile = wave_index(h);
     if (tile * 64 >= nvec) {
         // the grid's last wavefront: the ragged tail
-        const long long rem = a.n - nvec * 4, t = threadIdx.x & 63u;
-        if (tile * 64 < nvec + 64 && t < rem) slot_tail_element<BF16, STATS>(a, a.e0 + nvec * 4 + t);
+        const long long rem = h.n - nvec * 4, t = threadIdx.x & 63u;
+        if (tile * 64 < nvec + 64 && t < rem) slot_tail_element<BF16, STATS>(a, h, h.e0 + nvec * 4 + t);
         return;
     }
-    const Lanes L = place_lanes(a, tile, nvec);
+    const Lanes L = place_lanes(h, tile, nvec);
     Sums S;
     S.s = S.s2 = S.term = (f32x4)(0.0f);
-    const int n_sum = a.n_sum, n = n_sum + a.n_copy;
+    const int n_sum = h.n_sum, n = n_sum + h.n_copy;
     unsigned long long slot[D];
     f32x4 x[D];
     auto request = [&](int k) {
@@ -356,17 +350,17 @@ __global__ __launch_bounds__(256) void burst_kernel(const SlotArgs)
     }
     f32x4 vo = (f32x4)(0.0f), wo = vo;
     if (OPT) {
-        vo = ld_at<NTS>(reinterpret_cast<const char *>(a.v) + L.e0 * 4, L.off);
-        wo = ld_at<NTS>(reinterpret_cast<const char *>(a.w) + L.e0 * 4, L.off);
+        vo = ld_at<NTS>(reinterpret_cast<const char *>(h.v) + L.e0 * 4, L.off);
+        wo = ld_at<NTS>(reinterpret_cast<const char *>(h.w) + L.e0 * 4, L.off);
     }
-    finish_tile<FAST, NTS, OPT, STATS>(a, L, S, vo, wo, n_valid, ls);
+    finish_tile<FAST, NTS, OPT, STATS>(h, L, S, vo, wo, n_valid, ls);
     for (int k = n_sum; k < n; k += D) {
         request(k);
         arrived();
 #pragma unroll
         for (int j = 0; j < D; ++j)
             if (k + j < n) {
-                char *dst = reinterpret_cast<char *>(a.dst[k + j - n_sum]) + L.e0 * 4;
+                char *dst = reinterpret_cast<char *>(a.dst[k + j]) + L.e0 * 4;
                 if (L.in) st_at<true>(dst, L.off, slot_value<BF16>(x[j], BF16, L.odd));
             }
     }
@@ -378,56 +372,79 @@ __global__ __launch_bounds__(256) void burst_kernel(const SlotArgs)
 // more slots than CH it does so again.  One body of code whatever the number of slots (the list
 // ends in SKIPs, which are nearly free): a body for every remainder has to be fetched before it
 // runs.  NT: as for the streams of the burst kernel, or plain.  Kernel time, before and now:
-// 8193 elements, 8 processes solo 7.0 -> 4.5 us; 1 M elements, 4 processes solo 12.1 -> 10.6
+// 8193 elements, 8 processes solo 6.7 -> 4.0 us; 1 M elements, 4 processes solo 12.1 -> 10.6
 // us a round; 1 M, 8 processes, 4 late 17.2 -> 14.1.
 template <bool BF16, bool FAST, bool NT, bool NTS, bool OPT, bool STATS, int CH>
 __global__ __launch_bounds__(256) void chunk_kernel(const SlotArgs)
 {
     KSlotArgs &a = kernarg<SlotArgs>();
-    const long long nvec = slot_nvec<BF16>(a.n);
-    const long long tile = wave_index(a);
+    unsigned long long slot[CH];
+#pragma unroll
+    for (int j = 0; j < CH; ++j) slot[j] = a.slot[j];
+    const SlotHead h = read_head(a);
+#pragma unroll
+    for (int j = 0; j < CH; ++j) asm volatile("" : "+s"(slot[j]));   // requested along with the head
+    const long long nvec = slot_nvec<BF16>(h.n);
+    const long long tile = wave_index(h);
     if (tile * 64 >= nvec) {
         // the grid's last wavefront: the ragged tail
-        const long long rem = a.n - nvec * 4, t = threadIdx.x & 63u;
-        if (tile * 64 < nvec + 64 && t < rem) slot_tail_element<BF16, STATS>(a, a.e0 + nvec * 4 + t);
+        const long long rem = h.n - nvec * 4, t = threadIdx.x & 63u;
+        if (tile * 64 < nvec + 64 && t < rem) slot_tail_element<BF16, STATS>(a, h, h.e0 + nvec * 4 + t);
         return;
     }
-    const Lanes L = place_lanes(a, tile, nvec);
+    const Lanes L = place_lanes(h, tile, nvec);
     Sums S;
     S.s = S.s2 = S.term = (f32x4)(0.0f);
-    f32x4 vo = (f32x4)(0.0f), wo = vo;
-    if (OPT) {
-        vo = ld_at<NTS>(reinterpret_cast<const char *>(a.v) + L.e0 * 4, L.off);
-        wo = ld_at<NTS>(reinterpret_cast<const char *>(a.w) + L.e0 * 4, L.off);
-    }
-    const int n_sum = a.n_sum, n = n_sum + a.n_copy;
-    LaneStats ls;
-    const int n_valid = STATS ? place_stats(a, L, ls) : 0;
-    for (int k0 = 0; k0 < n; k0 += CH) {
-        f32x4 x[CH];
+    const int n_sum = h.n_sum, n = n_sum + h.n_copy;
+    f32x4 x[CH];
+    auto request = [&]() {
 #pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            x[j] = ld_slot_or_skip<BF16, NT>(a.slot[k0 + j], L);
+        for (int j = 0; j < CH; ++j) x[j] = ld_slot_or_skip<BF16, NT>(slot[j], L);
+    };
+    // slots [k0, k0 + CH): the sum, then the copies among them
+    auto consume = [&](int k0) {
+        float *dst[CH];
+        const bool copies = k0 + CH > n_sum && n > n_sum;
+        if (copies) {
+#pragma unroll
+            for (int j = 0; j < CH; ++j) dst[j] = a.dst[k0 + j];
         }
 #pragma unroll
         for (int g = 0; g < CH; g += 4)
             if (k0 + g < n_sum) {           // (what follows the sum costs no arithmetic)
 #pragma unroll
-                for (int j = g; j < g + 4; ++j) add_slot<BF16, FAST>(a.slot[k0 + j], x[j], L, S, j & 1);
+                for (int j = g; j < g + 4; ++j) add_slot<BF16, FAST>(slot[j], x[j], L, S, j & 1);
             }
         // Stores stay behind the adds: moved ahead of them, the in-order memory counter would make
         // every add wait for the acknowledgement of a store instead of for its load.
         asm volatile("" : "+v"(S.s), "+v"(S.s2), "+v"(S.term) : : "memory");
-        if (k0 + CH > n_sum) {
+        if (copies) {
 #pragma unroll
             for (int j = 0; j < CH; ++j)
-                if (a.slot[k0 + j] & kSlotCopy) {
-                    char *dst = reinterpret_cast<char *>(a.dst[k0 + j - n_sum]) + L.e0 * 4;
-                    if (L.in) st_at<NT>(dst, L.off, slot_value<BF16>(x[j], BF16, L.odd));
+                if (slot[j] & kSlotCopy) {
+                    char *to = reinterpret_cast<char *>(dst[j]) + L.e0 * 4;
+                    if (L.in) st_at<NT>(to, L.off, slot_value<BF16>(x[j], BF16, L.odd));
                 }
         }
+    };
+    f32x4 vo = (f32x4)(0.0f), wo = vo;
+    if (OPT) {
+        vo = ld_at<NTS>(reinterpret_cast<const char *>(h.v) + L.e0 * 4, L.off);
+        wo = ld_at<NTS>(reinterpret_cast<const char *>(h.w) + L.e0 * 4, L.off);
     }
-    finish_tile<FAST, NTS, OPT, STATS>(a, L, S, vo, wo, n_valid, ls);
+    request();
+    LaneStats ls;
+    const int n_valid = STATS ? place_stats(a, L, ls) : 0;
+    consume(0);
+    // (the first chunk stands apart: at the head of a loop the compiler waits for everything in
+    // flight, w and v among it, before the first slot is requested)
+    for (int k0 = CH; k0 < n; k0 += CH) {
+#pragma unroll
+        for (int j = 0; j < CH; ++j) slot[j] = a.slot[k0 + j];
+        request();
+        consume(k0);
+    }
+    finish_tile<FAST, NTS, OPT, STATS>(h, L, S, vo, wo, n_valid, ls);
     if (STATS) stats_commit(a.stats.records, a.stats.lane_records, ls, tile);
 }
 
@@ -499,25 +516,26 @@ void build_slots(const RoundArgs &a, SlotArgs &s)
     const unsigned long long none = (n > 0 ? s.slot[n - 1] & ~static_cast<unsigned long long>(kKindMask)
                                            : reinterpret_cast<unsigned long long>(any)) | kSkip;
     while (n % kBurst) s.slot[n++] = none;
-    s.n_sum = n;
-    s.n_copy = 0;
+    s.h.n_sum = n;
+    s.h.n_copy = 0;
     for (int p = 0; p < a.P; ++p)
         if ((a.store >> p) & 1ull) {
+            s.dst[n] = a.r[p];
             push(a.g[p], kSkip | kSlotCopy, bf16);
-            s.dst[s.n_copy++] = a.r[p];
+            ++s.h.n_copy;
         }
-    const unsigned long long skip = s.n_copy ? s.slot[n - 1] & ~static_cast<unsigned long long>(kSlotCopy) : none;
+    const unsigned long long skip = s.h.n_copy ? s.slot[n - 1] & ~static_cast<unsigned long long>(kSlotCopy) : none;
     for (int k = 0; k < kSlotChunk; ++k) s.slot[n + k] = skip;
-    s.w = a.w;
-    s.v = a.v;
-    s.recv = a.recv;
-    s.e0 = a.e0;
-    s.n = a.n;
-    s.inv_P = a.inv_P;
-    s.neg_lr = a.neg_lr;
-    s.mu = a.mu;
-    s.wd = a.wd;
-    s.nesterov = a.nesterov;
+    s.h.w = a.w;
+    s.h.v = a.v;
+    s.h.recv = a.recv;
+    s.h.e0 = a.e0;
+    s.h.n = a.n;
+    s.h.inv_P = a.inv_P;
+    s.h.neg_lr = a.neg_lr;
+    s.h.mu = a.mu;
+    s.h.wd = a.wd;
+    s.h.nesterov = a.nesterov;
     s.stats = a.stats;
 }
 
@@ -530,11 +548,11 @@ void build_slots(const RoundArgs &a, SlotArgs &s)
 // processes: 34.8 us, 42.7 with 14).
 int burst_waves(const SlotArgs &s, long long tiles)
 {
-    const int n = s.n_sum + s.n_copy;
+    const int n = s.h.n_sum + s.h.n_copy;
     int n_bf = 0;
     for (int k = 0; k < n; ++k)
         n_bf += (s.slot[k] & kSlotBf16) && (s.slot[k] & (kKindMask | kSlotCopy)) != kSkip;
-    const int base = s.n_copy ? 12 : 14;
+    const int base = s.h.n_copy ? 12 : 14;
     const int w0 = n > 0 ? base + base * n_bf / (2 * n) : base;
     const long long per_cu = (tiles + kCus - 1) / kCus;
     if (per_cu <= w0 + 6) return -1;
@@ -555,24 +573,24 @@ int burst_waves(const SlotArgs &s, long long tiles)
 template <bool BF16, bool FAST, bool NTS, bool OPT>
 hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStream_t st)
 {
-    const long long tiles = (slot_nvec<BF16>(s.n) + 63) / 64;
-    const long long waves = tiles + (slot_nvec<BF16>(s.n) * 4 < s.n ? 1 : 0);   // and the tail
+    const long long tiles = (slot_nvec<BF16>(s.h.n) + 63) / 64;
+    const long long waves = tiles + (slot_nvec<BF16>(s.h.n) * 4 < s.h.n ? 1 : 0);   // and the tail
     const int per = cfg.block / 64;                    // wavefronts per workgroup
     const long long g = (waves + per - 1) / per;
     // these kernels do not stride: a run beyond the thread limit of a grid (more than
     // 2^33 elements) is refused
     if (g * cfg.block > kMaxGridThreads) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(g));
-    s.waves_per_block = per;
-    s.xcd_blocks = cfg.xcd_map ? static_cast<int>(g / 8) : 0;
+    s.h.waves_per_block = per;
+    s.h.xcd_blocks = cfg.xcd_map ? static_cast<int>(g / 8) : 0;
     // A run that moves at most 96 MB is bound by latency: everything at once, no cap.  Beyond that
     // it is a stream.  (Both sides at the line: 1 M elements, 16 processes, 15 late = 210 MB: 41 us
     // at once, 34.8 in bursts; 262 k = 52 MB: 11.8 and 14.7.)  Accesses are plain where the whole model
     // moves no more than that in a round: its arrays then stay in the last-level cache from
     // round to round (1 M elements, 8 processes: 14.1 us, 16.6 with the nontemporal hint); small runs
     // of a larger model are streamed (1 M elements, 16 processes, cold: 41.9 us, 44.2 plain).
-    const long long per_element = 4ll * (s.n_sum + 2 * s.n_copy + (OPT ? 4 : 1));
-    const bool small = s.n * per_element <= kSmallRoundBytes;
+    const long long per_element = 4ll * (s.h.n_sum + 2 * s.h.n_copy + (OPT ? 4 : 1));
+    const bool small = s.h.n * per_element <= kSmallRoundBytes;
     const bool plain = model * per_element <= kSmallRoundBytes;
     int bpc = cfg.blocks_per_cu;
     if (bpc == 0) {
@@ -585,7 +603,7 @@ hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStre
                      : launch_capped(burst_kernel<BF16, FAST, NTS, OPT, false>, s, bpc, cfg, grid, st);
     // the by-products exist for the default chunk size only
     if (stats && cfg.chunk == 8) return hipErrorInvalidValue;
-    const bool few = cfg.chunk == 8 || (cfg.chunk == 0 && s.n_sum + s.n_copy <= 8);
+    const bool few = cfg.chunk == 8 || (cfg.chunk == 0 && s.h.n_sum + s.h.n_copy <= 8);
     switch ((stats ? 4 : 0) | (few ? 2 : 0) | (plain ? 1 : 0)) {
     case 0: return launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, false, 16>, s, bpc, cfg, grid, st);
     case 1: return launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, false, 16>, s, bpc, cfg, grid, st);
@@ -605,9 +623,9 @@ hipError_t launch_slots(const RoundArgs &a, const Launch &cfg, hipStream_t st)
     build_slots(a, s);
     // w, v (and recv) of a run that cannot stay in the 256 MiB last-level cache until the
     // next round are streamed; smaller ones are left to the cache
-    const long long state_bytes = s.n * 4 * ((s.w ? 2 : 0) + (s.recv ? 1 : 0));
+    const long long state_bytes = s.h.n * 4 * ((s.h.w ? 2 : 0) + (s.h.recv ? 1 : 0));
     const bool nts = cfg.nt_state < 0 ? state_bytes > kStateCacheBytes : cfg.nt_state != 0;
-    if (s.w) return nts ? launch_slots<BF16, FAST, true, true>(s, a.model, cfg, st)
+    if (s.h.w) return nts ? launch_slots<BF16, FAST, true, true>(s, a.model, cfg, st)
                         : launch_slots<BF16, FAST, false, true>(s, a.model, cfg, st);
     return nts ? launch_slots<BF16, FAST, true, false>(s, a.model, cfg, st)
                : launch_slots<BF16, FAST, false, false>(s, a.model, cfg, st);
