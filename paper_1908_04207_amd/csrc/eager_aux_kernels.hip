@@ -378,18 +378,6 @@ __global__ __launch_bounds__(256) void sgd_kernel(const SgdArgs a)
 //     g = rate_b * (u + wd*w);  v' = mu*v + g;  step = nesterov ? g + mu*v' : v';  w' = w - lr*step
 // One lane-vector per lane in both, so that record k belongs to elements [256k, 256k + 256).
 
-// bucket of the lane's 4 elements (they never straddle a bucket start: starts are multiples
-// of 4) and how many of them lie inside it; the search starts at the wavefront's bucket
-__device__ __forceinline__ int lane_bucket(const long long *tbl, int nb, int wave_bucket, long long e,
-                                           int &n_valid)
-{
-    int b = wave_bucket;
-    while (b + 1 < nb && tbl[2 * (b + 1)] <= e) ++b;
-    const long long left = tbl[2 * b + 1] - e;
-    n_valid = left >= 4 ? 4 : left > 0 ? static_cast<int>(left) : 0;
-    return b;
-}
-
 // A wavefront takes K consecutive tiles of 256 elements.  Where they all lie inside one bucket,
 // as nearly always, it requests u and w of one tile after the other, squares and sums in its
 // lanes, and combines the lanes once at the end: one record instead of K, and K times fewer
@@ -397,67 +385,71 @@ __device__ __forceinline__ int lane_bucket(const long long *tbl, int nb, int wav
 // is mixed.  It is bound by the reads of u and w (25.6 M elements after a round: 36 us = 5.7 TB/s,
 // 54.6 before; most of the difference is that lars_kernel no longer leaves 200 MB of w and v in the
 // last-level cache which this kernel's reads would push out).
-template <bool NT>
+// SINGLE: a wavefront per tile, for small runs, which groups would leave with few wavefronts.
+template <bool NT, bool SINGLE>
 __global__ __launch_bounds__(64) void norms_kernel(const SgdArgs a, const StatsArgs st)
 {
-    constexpr int K = kNormsTiles;
-    typedef const long long __attribute__((address_space(4))) KLong;
+    constexpr int K = kNormsTiles, T = SINGLE ? 1 : K;       // tiles of the wavefront
     KLong *tbl = (KLong *)reinterpret_cast<unsigned long long>(st.table);
     const long long nvec = a.n / 4;
-    const long long tile0 = static_cast<long long>(blockIdx.x) * K;
-    const long long first = a.e0 + tile0 * 256, last = first + K * 256;
+    const long long tile0 = static_cast<long long>(blockIdx.x) * T;
     const unsigned lane = threadIdx.x & 63u;
-    const f32x4 *up = reinterpret_cast<const f32x4 *>(a.u + first) + lane;
-    const f32x4 *wp = reinterpret_cast<const f32x4 *>(a.w + first) + lane;
-    const bool whole = (tile0 + K) * 64 <= nvec;
-    f32x4 u, w;
-    if (whole) {
-        u = ld_f4<NT>(reinterpret_cast<const float *>(up));
-        w = ld_f4<NT>(reinterpret_cast<const float *>(wp));
-    }
-    int bucket = st.b_lo;
-    for (int hi = st.b_hi; hi - bucket > 1;) {
-        const int mid = (bucket + hi) >> 1;
-        if (tbl[2 * mid] <= first) bucket = mid;
-        else hi = mid;
-    }
-    if (whole && tbl[2 * bucket + 1] >= last) {
-        LaneStats ls = {0.0, 0.0, 0u, bucket};
+    bool whole = false;
+    if constexpr (!SINGLE) {
+        const long long first = a.e0 + tile0 * 256, last = first + K * 256;
+        const f32x4 *up = reinterpret_cast<const f32x4 *>(a.u + first) + lane;
+        const f32x4 *wp = reinterpret_cast<const f32x4 *>(a.w + first) + lane;
+        whole = (tile0 + K) * 64 <= nvec;
+        f32x4 u, w;
+        if (whole) {
+            u = ld_f4<NT>(reinterpret_cast<const float *>(up));
+            w = ld_f4<NT>(reinterpret_cast<const float *>(wp));
+        }
+        int bucket = st.b_lo;
+        for (int hi = st.b_hi; hi - bucket > 1;) {
+            const int mid = (bucket + hi) >> 1;
+            if (tbl[2 * mid] <= first) bucket = mid;
+            else hi = mid;
+        }
+        whole = whole && tbl[2 * bucket + 1] >= last;
+        if (whole) {
+            LaneStats ls = {0.0, 0.0, 0u, bucket};
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const f32x4 x = u, y = w;
-            if (k + 1 < K) {
-                u = ld_f4<NT>(reinterpret_cast<const float *>(up + (k + 1) * 64));
-                w = ld_f4<NT>(reinterpret_cast<const float *>(wp + (k + 1) * 64));
+            for (int k = 0; k < K; ++k) {
+                const f32x4 x = u, y = w;
+                if (k + 1 < K) {
+                    u = ld_f4<NT>(reinterpret_cast<const float *>(up + (k + 1) * 64));
+                    w = ld_f4<NT>(reinterpret_cast<const float *>(wp + (k + 1) * 64));
+                }
+                stats_add(ls, x.x, y.x, true);
+                stats_add(ls, x.y, y.y, true);
+                stats_add(ls, x.z, y.z, true);
+                stats_add(ls, x.w, y.w, true);
             }
-            stats_add(ls, x.x, y.x, true);
-            stats_add(ls, x.y, y.y, true);
-            stats_add(ls, x.z, y.z, true);
-            stats_add(ls, x.w, y.w, true);
-        }
-        const double su = wave_sum(ls.ssu), sw = wave_sum(ls.ssw);
-        unsigned nf = 0u;
-        if (__builtin_amdgcn_ballot_w64(ls.nf != 0u) != 0ull) nf = wave_sum(ls.nf);
-        if (lane == 0u) {
-            const StatsRecord rec = {su, sw, bucket, nf, 0};
-            st.records[tile0] = rec;
-        }
-    } else {
-        for (int k = 0; k < K; ++k) {
-            const long long vi = (tile0 + k) * 64 + lane;
-            LaneStats ls = {0.0, 0.0, 0u, -1};
-            if (vi < nvec) {
-                u = ld_f4<NT>(a.u + a.e0 + vi * 4);
-                w = ld_f4<NT>(a.w + a.e0 + vi * 4);
-                int n_valid;
-                ls.bucket = bucket = lane_bucket(st.table, st.n_buckets, bucket, a.e0 + vi * 4, n_valid);
-                if (n_valid > 0) stats_add(ls, u.x, w.x, true);
-                if (n_valid > 1) stats_add(ls, u.y, w.y, true);
-                if (n_valid > 2) stats_add(ls, u.z, w.z, true);
-                if (n_valid > 3) stats_add(ls, u.w, w.w, true);
+            const double su = wave_sum(ls.ssu), sw = wave_sum(ls.ssw);
+            unsigned nf = 0u;
+            if (__builtin_amdgcn_ballot_w64(ls.nf != 0u) != 0ull) nf = wave_sum(ls.nf);
+            if (lane == 0u) {
+                const StatsRecord rec = {su, sw, bucket, nf, 0};
+                st.records[tile0] = rec;
             }
-            stats_commit(st.records, st.lane_records, ls, tile0 + k, k == 0 ? 1 : 0);
         }
+    }
+    for (int k = 0; k < T && !whole; ++k) {
+        const long long vi = (tile0 + k) * 64 + lane;
+        LaneStats ls = {0.0, 0.0, 0u, -1};
+        if (vi < nvec) {
+            const long long e = a.e0 + vi * 4;
+            const f32x4 u = ld_f4<NT>(a.u + e), w = ld_f4<NT>(a.w + e);
+            long long end;
+            ls.bucket = tile_bucket(st.table, st.b_lo, st.b_hi, a.e0 + (tile0 + k) * 256, e, end);
+            const int n_valid = inside(e, end);
+            if (n_valid > 0) stats_add(ls, u.x, w.x, true);
+            if (n_valid > 1) stats_add(ls, u.y, w.y, true);
+            if (n_valid > 2) stats_add(ls, u.z, w.z, true);
+            if (n_valid > 3) stats_add(ls, u.w, w.w, true);
+        }
+        stats_commit(st.records, st.lane_records, ls, tile0 + k, (tile0 + k) % K == 0 ? 1 : 0);
     }
     const long long rem = a.n - nvec * 4;
     if (blockIdx.x == 0 && static_cast<long long>(threadIdx.x) < rem) {
@@ -490,7 +482,6 @@ __device__ __forceinline__ f32x4 scaled_gradient(float rate, float wd, f32x4 u, 
 template <bool FAST, bool NT>
 __global__ __launch_bounds__(64) void lars_kernel(const SgdArgs a, const StatsArgs st)
 {
-    typedef const long long __attribute__((address_space(4))) KLong;
     KLong *tbl = (KLong *)reinterpret_cast<unsigned long long>(st.table);
     const long long nvec = a.n / 4;
     const long long vi = static_cast<long long>(blockIdx.x) * 64 + threadIdx.x;
@@ -516,8 +507,8 @@ __global__ __launch_bounds__(64) void lars_kernel(const SgdArgs a, const StatsAr
         float rate = rates[static_cast<long long>(b) * kStep];
         for (++b; b < st.b_hi; ++b) {
             const long long start = tbl[2 * b];
-            if (start >= first + 256) break;
             const float r = rates[static_cast<long long>(b) * kStep];
+            if (start >= first + 256) break;
             if (e >= start) rate = r;
         }
         f32x4 vn, wn;
@@ -559,6 +550,11 @@ int views_average_waves(int n_views)
 
 }  // namespace
 
+// Whether norms_kernel takes a tile per wavefront instead of groups: below 2 M elements, where groups
+// leave too few wavefronts (norms + finish, single and in groups: 13 k elements in 58 buckets 7.4 and
+// 16.6 us, 0.9 M 7.6 and 12.5 us).
+static bool norms_single(long long records) { return records < 8192; }
+
 hipError_t launch_stats_finish(const StatsArgs &args, hipStream_t stream)
 {
     const int n = args.b_hi - args.b_lo;
@@ -569,7 +565,7 @@ hipError_t launch_stats_finish(const StatsArgs &args, hipStream_t stream)
     // One workgroup per bucket takes two trips to memory for 12 k records (ResNet-50, 161 buckets of up
     // to 9 k records: 6.7 us in one launch, 9.9 us with a first stage); with more the first stage
     // is worth its launch (262 k records: 9.5 us, 42 us without).  Groups of norms_kernel count once.
-    if (a.want_rate) {                   // the records are norms_kernel's
+    if (a.want_rate && !norms_single(a.n_records)) {
         a.slices = a.slices <= 12 ? 1 : (a.slices + kNormsTiles - 1) / kNormsTiles;
         if (a.slices > 1) {
             hipLaunchKernelGGL(stats_slice_kernel<true>, dim3(n, a.slices), threads, 0, stream, a);
@@ -666,15 +662,19 @@ long long norms_records(long long n)
 hipError_t launch_norms(const SgdArgs &a, const StatsArgs &st, hipStream_t stream)
 {
     if (a.n <= 0) return hipSuccess;
-    const long long g = norms_records(a.n) / kNormsTiles;
+    const long long tiles = norms_records(a.n);
+    const bool single = norms_single(tiles);
+    const long long g = single ? tiles : tiles / kNormsTiles;
     if (g * 64 > kMaxGridThreads) return hipErrorInvalidValue;    // the kernel does not stride
+    const dim3 grid(static_cast<unsigned>(g)), block(64);
     // u and w are read again by the update right after: leave them in the last-level cache
     // when both fit
-    const dim3 grid(static_cast<unsigned>(g)), block(64);
-    if (a.n * 8 <= kStateCacheBytes)
-        hipLaunchKernelGGL(norms_kernel<false>, grid, block, 0, stream, a, st);
+    if (single)
+        hipLaunchKernelGGL((norms_kernel<false, true>), grid, block, 0, stream, a, st);
+    else if (a.n * 8 <= kStateCacheBytes)
+        hipLaunchKernelGGL((norms_kernel<false, false>), grid, block, 0, stream, a, st);
     else
-        hipLaunchKernelGGL(norms_kernel<true>, grid, block, 0, stream, a, st);
+        hipLaunchKernelGGL((norms_kernel<true, false>), grid, block, 0, stream, a, st);
     return hipGetLastError();
 }
 
