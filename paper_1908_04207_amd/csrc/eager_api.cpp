@@ -3,6 +3,7 @@
 // that one kernel launch each can cover.  All arithmetic of a round runs in the kernels.
 #include "../../include/eager_tuning.h"
 #include "eager_internal.h"
+#include "eager_rules.h"
 
 #include <algorithm>
 #include <cmath>
@@ -225,7 +226,7 @@ int partial_allreduce(eager_ctx *ctx, int want_mode, const eager_plan *plan, uin
         int e = b + 1;
         while (e < b1 && ctx->valid[e] == ctx->valid[b]) ++e;
         const int64_t n = ctx->offset[e - 1] + ctx->numel[e - 1] - ctx->offset[b];
-        if (n > (int64_t{1} << 33))
+        if (n > eager::kMaxRunElements)
             return fail(ctx, EAGER_EINVAL, "buckets %d..%d span %lld elements in one send-buffer state; "
                                            "one call covers at most 2^33 per such stretch: use smaller ranges",
                         b, e - 1, static_cast<long long>(n));

@@ -4,6 +4,7 @@
 #pragma once
 
 #include "eager_internal.h"
+#include "eager_rules.h"
 
 #include <mutex>
 #include <set>
@@ -258,10 +259,6 @@ __device__ __forceinline__ void stats_commit(StatsRecord *records, StatsRecord *
 constexpr int kLdsPerCu = 160 * 1024;
 constexpr int kLdsUnit = 1280;
 constexpr int kCus = 256;
-
-// A grid must hold fewer than 2^32 threads in total; a launch beyond that is not refused
-// by the runtime, its thread count wraps.  Every launcher stays at or below 2^31.
-constexpr long long kMaxGridThreads = 1ll << 31;
 
 // Parameters and momentum above this size are streamed past the caches (see finish_tile).
 constexpr long long kStateCacheBytes = 256ll << 20;

@@ -9,6 +9,15 @@ namespace eager {
 
 constexpr int kMaxP = 64;
 
+// Lane-vectors (groups of 4 elements) of a run that the vector path of a round covers.  With bf16
+// gradients two lanes share one 16-byte piece, so the vector path ends at a multiple of 8
+// elements and never reads beyond the run.
+template <bool BF16>
+__host__ __device__ inline long long slot_nvec(long long n)
+{
+    return BF16 ? (n / 8) * 2 : n / 4;
+}
+
 // Optional by-products of a round, per bucket (same layout as eager_bucket_stats of the public
 // header): squared norm of the averaged update and of the parameters before the update (finite
 // elements only), number of non-finite elements of the update.

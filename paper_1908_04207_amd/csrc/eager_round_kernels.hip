@@ -25,6 +25,7 @@
 //     one record per tile (the helpers live in eager_device.h, the kernels that finish
 //     them in eager_aux_kernels.hip).
 #include "eager_device.h"
+#include "eager_rules.h"
 
 #include <algorithm>
 
@@ -227,15 +228,6 @@ __device__ __forceinline__ void slot_tail_element(KSlotArgs &a, const SlotHead &
         h.v[i] = v;
         h.w[i] = w;
     }
-}
-
-// Lane-vectors (groups of 4 elements) of a run that the vector path covers.  With bf16
-// gradients two lanes share one 16-byte piece, so the vector path ends at a multiple of 8
-// elements and never reads beyond the run.
-template <bool BF16>
-__host__ __device__ __forceinline__ long long slot_nvec(long long n)
-{
-    return BF16 ? (n / 8) * 2 : n / 4;
 }
 
 // The head of the arguments, all of it requested at once and waited for here: read where it is
@@ -581,12 +573,9 @@ template <bool BF16, bool FAST, bool NTS, bool OPT>
 hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStream_t st)
 {
     const long long tiles = (slot_nvec<BF16>(s.h.n) + 63) / 64;
-    const long long waves = tiles + (slot_nvec<BF16>(s.h.n) * 4 < s.h.n ? 1 : 0);   // and the tail
     const int per = cfg.block / 64;                    // wavefronts per workgroup
-    const long long g = (waves + per - 1) / per;
-    // these kernels do not stride: a run beyond the thread limit of a grid (more than
-    // 2^33 elements) is refused
-    if (g * cfg.block > kMaxGridThreads) return hipErrorInvalidValue;
+    const long long g = round_workgroups(s.h.n, BF16, cfg.block);
+    if (g * cfg.block > kMaxRoundThreads) return hipErrorInvalidValue;     // (no run of a call is as long)
     const dim3 grid(static_cast<unsigned>(g));
     s.h.waves_per_block = per;
     s.h.xcd_blocks = cfg.xcd_map ? static_cast<int>(g / 8) : 0;

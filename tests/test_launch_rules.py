@@ -1,0 +1,43 @@
+"""The launch rules of csrc/eager_rules.h on the CPU, and on the GPU the largest run a call accepts."""
+import os
+import subprocess
+
+import pytest
+import torch
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_rules_on_the_host(tmp_path):
+    exe = tmp_path / "launch_rules_host"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined",
+                           "-fno-sanitize-recover=all", "-static-libasan", "-Wall", "-Wextra", "-Werror",
+                           "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include",
+                           os.path.join(ROOT, "tests", "c", "launch_rules_host.cpp"), "-o", str(exe)])
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", (r.stdout[-500:], r.stderr[-2000:])
+
+
+@pytest.mark.gpu
+def test_a_run_just_below_the_largest():
+    """2^33 - 1 elements: every tile but the last is full and three elements are left over.  One process
+    on time, so the result is its gradient."""
+    from paper_1908_04207_amd import binding as eb
+    n = (1 << 33) - 1
+    if torch.cuda.mem_get_info()[0] < 9 * n:
+        pytest.skip("needs 77 GB of free device memory")
+    dev = torch.device("cuda:0")
+    grad = torch.empty(n + 1, device=dev)
+    step = 1 << 28
+    for k in range(0, n + 1, step):
+        grad[k:k + step] = torch.arange(k % 1009, k % 1009 + step, device=dev, dtype=torch.int32).remainder(997)
+    recv = torch.full((n + 1,), -1.0, device=dev)
+    unread = torch.zeros(4, device=dev)              # an on-time process's empty send buffer
+    ctx = eb.Context(1, [0], [n])
+    ctx.eager_partial_allreduce_solo(eb.make_plan(eb.SOLO, 1, 0, 1), [grad], [unread], recv=recv)
+    torch.cuda.synchronize()
+    for k in range(0, n, step):
+        e = min(k + step, n)
+        assert torch.equal(recv[k:e], grad[k:e]), k
+    assert recv[n].item() == -1.0
+    ctx.close()
