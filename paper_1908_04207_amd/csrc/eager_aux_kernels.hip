@@ -9,13 +9,14 @@
 namespace eager {
 namespace {
 
-constexpr int kStatsThreads = 1024, kStatsWaves = kStatsThreads / 64;
-
+// The finishing kernels come with two workgroup sizes, see finish_threads.
+//
 // Adds the plain records (one per tile whose elements all lie in one bucket) with index in
 // [lo, hi) that belong to bucket b: 8 independent loads per thread in flight, wavefront sums by
-// DPP, the 16 wavefronts of the workgroup through LDS.  The totals arrive in wavefront 0.  What
-// bounds it is latency: 1024 threads take 8192 records (2 M elements) in one trip, so a first stage
-// is launched for larger buckets only (see launch_stats_finish).
+// DPP, the wavefronts of the workgroup through LDS.  The totals arrive in wavefront 0.  What
+// bounds it is latency, so that the number of trips counts: 1024 threads take 8192 records in one
+// (stats_slice_kernel), the 832 of them that add records in stats_finish_kernel 6656, 256 threads
+// 2048; of norms_kernel's groups of records half as many, each 8 tiles.
 // Records of norms_kernel come in groups of kNormsTiles: the first of a group holds the sums of
 // all, unless it is flagged - then every tile of the group has a record of its own.
 constexpr int kNormsTiles = 8;
@@ -58,9 +59,11 @@ __device__ __forceinline__ void add_records(const StatsRecord *records, long lon
 
 // (the count travels as a double: integers below 2^53 add exactly, and a 32-bit sum could
 // overflow on a bucket of billions of elements)
+template <int THREADS>
 __device__ __forceinline__ void workgroup_sum(double &su, double &sw, double &nf)
 {
-    __shared__ double part[3][kStatsWaves];
+    constexpr unsigned kWaves = THREADS / 64;
+    __shared__ double part[3][kWaves];
     su = wave_sum(su);
     sw = wave_sum(sw);
     nf = wave_sum(nf);
@@ -71,8 +74,12 @@ __device__ __forceinline__ void workgroup_sum(double &su, double &sw, double &nf
         part[2][wave] = nf;
     }
     __syncthreads();
-    if (wave == 0) {                     // the totals are needed there
-        const bool has = lane < kStatsWaves;
+    if constexpr (kWaves == 4) {
+        su = (part[0][0] + part[0][1]) + (part[0][2] + part[0][3]);
+        sw = (part[1][0] + part[1][1]) + (part[1][2] + part[1][3]);
+        nf = (part[2][0] + part[2][1]) + (part[2][2] + part[2][3]);
+    } else if (wave == 0) {              // the totals are needed there
+        const bool has = lane < kWaves;
         su = wave_sum(has ? part[0][lane] : 0.0);
         sw = wave_sum(has ? part[1][lane] : 0.0);
         nf = wave_sum(has ? part[2][lane] : 0.0);
@@ -90,8 +97,8 @@ __device__ __forceinline__ void bucket_records(const StatsArgs &a, int b, long l
 
 // First stage for buckets with many records (a flat model is ONE bucket: millions of records):
 // workgroup (bucket, slice) adds one slice of the bucket's plain records and leaves a partial.
-template <bool GROUPED>
-__global__ __launch_bounds__(kStatsThreads) void stats_slice_kernel(const StatsArgs a)
+template <bool GROUPED, int THREADS>
+__global__ __launch_bounds__(THREADS) void stats_slice_kernel(const StatsArgs a)
 {
     const int b = a.b_lo + static_cast<int>(blockIdx.x);
     const int s = static_cast<int>(blockIdx.y);
@@ -103,8 +110,8 @@ __global__ __launch_bounds__(kStatsThreads) void stats_slice_kernel(const StatsA
     const long long lo = s == 0 ? w0 : first + s * len;
     const long long hi = s + 1 == a.slices || first + (s + 1) * len > w1 ? w1 : first + (s + 1) * len;
     double su = 0.0, sw = 0.0, nf = 0.0;
-    add_records<kStatsThreads, GROUPED>(a.records, lo, hi, b, su, sw, nf);
-    workgroup_sum(su, sw, nf);
+    add_records<THREADS, GROUPED>(a.records, lo, hi, b, su, sw, nf);
+    workgroup_sum<THREADS>(su, sw, nf);
     if (threadIdx.x == 0) {
         // a slice holds at most 2^33 / 256 / slices records of 256 elements: the count fits
         const StatsRecord out = {su, sw, b, static_cast<unsigned>(nf), 0};
@@ -116,19 +123,22 @@ __global__ __launch_bounds__(kStatsThreads) void stats_slice_kernel(const StatsA
 // touch the bucket (they are consecutive) - a uniform wavefront's sums (or the partials of the
 // first stage), a mixed wavefront's lane records of this bucket - and the records of the ragged
 // tail; one thread writes the bucket's totals.
-template <bool GROUPED>
-__global__ __launch_bounds__(kStatsThreads) void stats_finish_kernel(const StatsArgs a)
+template <bool GROUPED, int THREADS>
+__global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs a)
 {
     const int b = a.b_lo + static_cast<int>(blockIdx.x);
     long long w0, w1;
     bucket_records(a, b, w0, w1);
     double su = 0.0, sw = 0.0, nf = 0.0;
     // Only the first and the last wavefront of the bucket can be mixed.  The lane records of the
-    // first, those of the last and the ragged tail have a wavefront of this workgroup each (one lane
-    // per record), so that their dependent loads run beside the others' and not after them.
-    constexpr int kPlain = kStatsThreads - 3 * 64;
-    const int which = static_cast<int>(threadIdx.x >> 6) - kPlain / 64, lane = threadIdx.x & 63;
-    if (which < 0) {
+    // first, those of the last and the ragged tail are read by a wavefront each (one lane per
+    // record); in the larger workgroup these are wavefronts of their own, so that their dependent
+    // loads run beside the others' and not after them.
+    constexpr bool kApart = THREADS > 256;
+    constexpr int kPlain = kApart ? THREADS - 3 * 64 : THREADS;
+    const int wave = static_cast<int>(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int which = kApart ? wave - kPlain / 64 : wave;
+    if (!kApart || which < 0) {
         if (a.slices == 1) {
             add_records<kPlain, GROUPED>(a.records, w0, w1, b, su, sw, nf);
         } else if (static_cast<int>(threadIdx.x) < a.slices) {
@@ -137,7 +147,8 @@ __global__ __launch_bounds__(kStatsThreads) void stats_finish_kernel(const Stats
             sw = r.ssw;
             nf = r.nf;
         }
-    } else if (which < 2) {
+    }
+    if (which == 0 || which == 1) {
         const long long t = which == 0 ? w0 : w1 - 1;
         // (in a group that is not flagged only the first record has been written)
         if (w1 > w0 && (which == 0 || t != w0) &&
@@ -146,21 +157,21 @@ __global__ __launch_bounds__(kStatsThreads) void stats_finish_kernel(const Stats
             if (r.bucket == -1) {
                 const StatsRecord lr = a.lane_records[static_cast<long long>(r.nf) * 64 + lane];
                 if (lr.bucket == b) {
-                    su = lr.ssu;
-                    sw = lr.ssw;
-                    nf = lr.nf;
+                    su += lr.ssu;
+                    sw += lr.ssw;
+                    nf += lr.nf;
                 }
             }
         }
-    } else if (lane < a.tail_count) {
+    } else if (which == 2 && lane < a.tail_count) {
         const StatsRecord tr = a.lane_records[static_cast<long long>(a.n_buckets) * 64 + lane];
         if (tr.bucket == b) {
-            su = tr.ssu;
-            sw = tr.ssw;
-            nf = tr.nf;
+            su += tr.ssu;
+            sw += tr.ssw;
+            nf += tr.nf;
         }
     }
-    workgroup_sum(su, sw, nf);
+    workgroup_sum<THREADS>(su, sw, nf);
     if (threadIdx.x == 0) {
         BucketStats out;
         out.sumsq_update = su;
@@ -555,32 +566,36 @@ int views_average_waves(int n_views)
 // 16.6 us, 0.9 M 7.6 and 12.5 us).
 static bool norms_single(long long records) { return records < 8192; }
 
+namespace {
+template <bool GROUPED, int THREADS>
+hipError_t launch_finish(const StatsArgs &a, int n, hipStream_t stream)
+{
+    const dim3 threads(THREADS);
+    if (a.slices > 1) {
+        hipLaunchKernelGGL((stats_slice_kernel<GROUPED, THREADS>), dim3(n, a.slices), threads, 0, stream, a);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((stats_finish_kernel<GROUPED, THREADS>), dim3(n), threads, 0, stream, a);
+    return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_stats_finish(const StatsArgs &args, hipStream_t stream)
 {
     const int n = args.b_hi - args.b_lo;
     if (n <= 0) return hipSuccess;
     if (args.slices > kStatsMaxSlices || args.slices < 1) return hipErrorInvalidValue;
     StatsArgs a = args;
-    const dim3 threads(kStatsThreads);
     // One workgroup per bucket takes two trips to memory for 12 k records (ResNet-50, 161 buckets of up
     // to 9 k records: 6.7 us in one launch, 9.9 us with a first stage); with more the first stage
     // is worth its launch (262 k records: 9.5 us, 42 us without).  Groups of norms_kernel count once.
-    if (a.want_rate && !norms_single(a.n_records)) {
+    const bool grouped = a.want_rate && !norms_single(a.n_records), wide = finish_threads(n) == 1024;
+    if (grouped) {
         a.slices = a.slices <= 12 ? 1 : (a.slices + kNormsTiles - 1) / kNormsTiles;
-        if (a.slices > 1) {
-            hipLaunchKernelGGL(stats_slice_kernel<true>, dim3(n, a.slices), threads, 0, stream, a);
-            if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL(stats_finish_kernel<true>, dim3(n), threads, 0, stream, a);
-        return hipGetLastError();
+        return wide ? launch_finish<true, 1024>(a, n, stream) : launch_finish<true, 256>(a, n, stream);
     }
     if (a.slices <= 3) a.slices = 1;
-    if (a.slices > 1) {
-        hipLaunchKernelGGL(stats_slice_kernel<false>, dim3(n, a.slices), threads, 0, stream, a);
-        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(stats_finish_kernel<false>, dim3(n), threads, 0, stream, a);
-    return hipGetLastError();
+    return wide ? launch_finish<false, 1024>(a, n, stream) : launch_finish<false, 256>(a, n, stream);
 }
 
 hipError_t launch_stash(const StashArgs &a, bool bf16, hipStream_t stream)

@@ -23,4 +23,13 @@ inline long long round_workgroups(long long n, bool bf16, int block)
     return (waves + per - 1) / per;
 }
 
+// Threads of the workgroup that finishes a bucket's statistics.  1024 make fewest trips to memory and
+// are best while the chip holds most of the buckets' workgroups at once; with many buckets, which
+// are then small, four times as many workgroups of 256 run at a time.  (Norms, finish and update of
+// the layer-wise rule behind a round, 1024 and 256 threads: 600 buckets in 40 M elements 403 and 407
+// us, 800 in 36 M 366 and 363, 1000 in 20 M 219 and 216, 2000 in 16 M 181 and 171; a round of two
+// processes with norms, 65536 buckets in 4 M elements, 290 and 147 us.)  It also bounds the grid: 2^32 threads are more than
+// 16 M buckets, or 262 k where one of them takes all the slices of a first stage.
+inline int finish_threads(int n_buckets) { return n_buckets > 768 ? 256 : 1024; }
+
 }  // namespace eager

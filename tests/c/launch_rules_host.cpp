@@ -32,9 +32,23 @@ static int grids()
     return 0;
 }
 
+// The finishing kernels: many buckets get small workgroups, and no more threads in all than a
+// workgroup of 256 per bucket and slice would take.
+static int finishing()
+{
+    for (int n : {1, 2, 161, 600, 768, 769, 1000, 4096, 65536, 1 << 20, (1 << 24) - 1}) {
+        const long long t = finish_threads(n);
+        CHECK(t == 256 || t == 1024);
+        CHECK(n >= 1000 ? t == 256 : n > 600 || t == 1024);
+        CHECK(n * t <= 1024 * 1024ll || t == 256);
+        CHECK(n * t < 1ll << 32);
+    }
+    return 0;
+}
+
 int main()
 {
-    if (grids()) return 1;
+    if (grids() || finishing()) return 1;
     std::printf("ok\n");
     return 0;
 }
