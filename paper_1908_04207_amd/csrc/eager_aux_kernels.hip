@@ -389,24 +389,25 @@ __global__ __launch_bounds__(256) void sgd_kernel(const SgdArgs a)
 //     g = rate_b * (u + wd*w);  v' = mu*v + g;  step = nesterov ? g + mu*v' : v';  w' = w - lr*step
 // One lane-vector per lane in both, so that record k belongs to elements [256k, 256k + 256).
 
-// A wavefront takes K consecutive tiles of 256 elements.  Where they all lie inside one bucket,
-// as nearly always, it requests u and w of one tile after the other, squares and sums in its
-// lanes, and combines the lanes once at the end: one record instead of K, and K times fewer
-// cross-lane steps in fp64.  Other wavefronts leave a record per tile, or per lane where a tile
-// is mixed.  It is bound by the reads of u and w (25.6 M elements after a round: 36 us = 5.7 TB/s,
-// 54.6 before; most of the difference is that lars_kernel no longer leaves 200 MB of w and v in the
-// last-level cache which this kernel's reads would push out).
-// SINGLE: a wavefront per tile, for small runs, which groups would leave with few wavefronts.
-template <bool NT, bool SINGLE>
+// A wavefront takes one tile of 256 elements and leaves its record, or a record per lane where several
+// buckets share it.  What bounds it are the reads of u and w, which stay in the last-level cache for
+// the update right after where they fit (25.6 M elements, 161 buckets: norms, finish and update 114
+// us, 119 in groups, 124 with four tiles per wavefront).
+// GROUPED: K consecutive tiles, for large models of large buckets (see norms_grouped).  Where they
+// all lie inside one bucket the wavefront requests u and w of one tile after the other, squares and
+// sums in its lanes, and combines the lanes once at the end: one record instead of K, and K times
+// fewer cross-lane steps in fp64.  Other groups leave a record per tile or per lane, tile after tile.
+template <bool GROUPED>
 __global__ __launch_bounds__(64) void norms_kernel(const SgdArgs a, const StatsArgs st)
 {
-    constexpr int K = kNormsTiles, T = SINGLE ? 1 : K;       // tiles of the wavefront
+    constexpr int K = kNormsTiles, T = GROUPED ? K : 1;      // tiles of the wavefront
+    constexpr bool NT = GROUPED;
     KLong *tbl = (KLong *)reinterpret_cast<unsigned long long>(st.table);
     const long long nvec = a.n / 4;
     const long long tile0 = static_cast<long long>(blockIdx.x) * T;
     const unsigned lane = threadIdx.x & 63u;
     bool whole = false;
-    if constexpr (!SINGLE) {
+    if constexpr (GROUPED) {
         const long long first = a.e0 + tile0 * 256, last = first + K * 256;
         const f32x4 *up = reinterpret_cast<const f32x4 *>(a.u + first) + lane;
         const f32x4 *wp = reinterpret_cast<const f32x4 *>(a.w + first) + lane;
@@ -561,11 +562,6 @@ int views_average_waves(int n_views)
 
 }  // namespace
 
-// Whether norms_kernel takes a tile per wavefront instead of groups: below 2 M elements, where groups
-// leave too few wavefronts (norms + finish, single and in groups: 13 k elements in 58 buckets 7.4 and
-// 16.6 us, 0.9 M 7.6 and 12.5 us).
-static bool norms_single(long long records) { return records < 8192; }
-
 namespace {
 template <bool GROUPED, int THREADS>
 hipError_t launch_finish(const StatsArgs &a, int n, hipStream_t stream)
@@ -589,7 +585,7 @@ hipError_t launch_stats_finish(const StatsArgs &args, hipStream_t stream)
     // One workgroup per bucket takes two trips to memory for 12 k records (ResNet-50, 161 buckets of up
     // to 9 k records: 6.7 us in one launch, 9.9 us with a first stage); with more the first stage
     // is worth its launch (262 k records: 9.5 us, 42 us without).  Groups of norms_kernel count once.
-    const bool grouped = a.want_rate && !norms_single(a.n_records), wide = finish_threads(n) == 1024;
+    const bool grouped = a.want_rate && norms_grouped(a.n_records, n), wide = finish_threads(n) == 1024;
     if (grouped) {
         a.slices = a.slices <= 12 ? 1 : (a.slices + kNormsTiles - 1) / kNormsTiles;
         return wide ? launch_finish<true, 1024>(a, n, stream) : launch_finish<true, 256>(a, n, stream);
@@ -678,18 +674,14 @@ hipError_t launch_norms(const SgdArgs &a, const StatsArgs &st, hipStream_t strea
 {
     if (a.n <= 0) return hipSuccess;
     const long long tiles = norms_records(a.n);
-    const bool single = norms_single(tiles);
-    const long long g = single ? tiles : tiles / kNormsTiles;
+    const bool grouped = norms_grouped(tiles, st.b_hi - st.b_lo);
+    const long long g = grouped ? tiles / kNormsTiles : tiles;
     if (g * 64 > kMaxGridThreads) return hipErrorInvalidValue;    // the kernel does not stride
     const dim3 grid(static_cast<unsigned>(g)), block(64);
-    // u and w are read again by the update right after: leave them in the last-level cache
-    // when both fit
-    if (single)
-        hipLaunchKernelGGL((norms_kernel<false, true>), grid, block, 0, stream, a, st);
-    else if (a.n * 8 <= kStateCacheBytes)
-        hipLaunchKernelGGL((norms_kernel<false, false>), grid, block, 0, stream, a, st);
-    else
-        hipLaunchKernelGGL((norms_kernel<true, false>), grid, block, 0, stream, a, st);
+    // (the grouped form is for runs whose u and w do not fit the last-level cache; elsewhere they are
+    // left there for the update right after)
+    if (grouped) hipLaunchKernelGGL((norms_kernel<true>), grid, block, 0, stream, a, st);
+    else hipLaunchKernelGGL((norms_kernel<false>), grid, block, 0, stream, a, st);
     return hipGetLastError();
 }
 

@@ -32,4 +32,15 @@ inline long long round_workgroups(long long n, bool bf16, int block)
 // 16 M buckets, or 262 k where one of them takes all the slices of a first stage.
 inline int finish_threads(int n_buckets) { return n_buckets > 768 ? 256 : 1024; }
 
+// Whether the norms pass of the layer-wise rule works in groups of 8 tiles: from 50 M elements, with
+// 32 k elements per bucket on average.  A group that buckets share goes through its tiles one by one
+// (4 M elements in buckets of 3000, the three kernels of the rule: 41 us in groups, 29.7 by tiles), and
+// below 50 M elements even whole groups leave too few wavefronts (2.3 M in 161 buckets 26.8 and 17.2;
+// 40 M in 600 190 and 179).  Above: 67 M in one bucket behind a round 632 and 644, 200 M in 2000 909 and
+// 943, 140 M in 3000 637 and 670, 64 M in 400 both 292; but 268 M in one bucket 1190 and 1184.
+inline bool norms_grouped(long long tiles, int n_buckets)
+{
+    return tiles >= 3 << 16 && tiles >= 128ll * n_buckets;
+}
+
 }  // namespace eager

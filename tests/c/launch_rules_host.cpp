@@ -46,9 +46,22 @@ static int finishing()
     return 0;
 }
 
+// The norms pass works in groups of tiles only where nearly all groups lie inside one bucket.
+static int norms()
+{
+    const long long line = 50'331'648 / 256;
+    CHECK(norms_grouped(line, 1) && !norms_grouped(line - 1, 1));
+    CHECK(norms_grouped(line, static_cast<int>(line / 128)) && !norms_grouped(line, static_cast<int>(line / 128) + 1));
+    for (long long elements : {4ll << 20, 16ll << 20, 64ll << 20, 1ll << 30, 1ll << 33})
+        for (long long bucket : {64, 512, 3000, 10'000, 30'000})
+            CHECK(!norms_grouped(elements / 256, static_cast<int>(elements / bucket)));
+    CHECK(!norms_grouped(8, 1) && norms_grouped(1ll << 25, 1 << 18));
+    return 0;
+}
+
 int main()
 {
-    if (grids() || finishing()) return 1;
+    if (grids() || finishing() || norms()) return 1;
     std::printf("ok\n");
     return 0;
 }

@@ -1,6 +1,6 @@
 """Per-bucket statistics and the layer-wise rule of models with many buckets: both sizes of the
-finishing workgroup, with and without a first stage, next to buckets of one element, against plain
-64-bit sums."""
+finishing workgroup, with and without a first stage, next to buckets of one element; and of a model
+large enough for the norms pass in groups of tiles.  Against plain 64-bit sums."""
 import numpy as np
 import pytest
 import torch
@@ -76,4 +76,50 @@ def test_sums_and_rates(eb, count, large):
     ok = np.isfinite(want)
     assert np.array_equal(np.isfinite(have), ok)
     assert np.max(np.abs(have[ok] - want[ok])) <= 1e-6 * np.max(np.abs(want[ok]))
+    ctx.close()
+
+
+@pytest.mark.parametrize("extra", [0, 3])
+def test_norms_in_groups_of_tiles(eb, extra):
+    """52 M elements: groups of 8 tiles that lie inside one bucket, that buckets share, that end with
+    the run; enough records for the first stage; a range of buckets for which groups are too few."""
+    num = [2048 * 3, 100, 2047, 2049, 5, 256, 2048, 50_400_001, 1, 1_300_003, 30_000, 2048 * 8, 77, 250_000 + extra]
+    off, n = [], 0
+    for m in num:
+        off.append(n)
+        n = (n + m + 3) // 4 * 4
+    dev = torch.device("cuda:0")
+    trust, eps, lr, mu = 0.02, 1e-9, 0.1, 0.9
+    ctx = eb.Context(1, off, num)
+    stats = torch.zeros(len(num) * 32, dtype=torch.uint8, device=dev)
+    need = ctx.eager_stats_workspace_bytes()
+    ws = torch.full((need,), 0x5A, dtype=torch.uint8, device=dev)            # stale records
+    ctx.eager_stats_attach(stats, ws, need)
+    gen = torch.Generator(device=dev).manual_seed(11)
+    u = torch.empty(n, device=dev).normal_(0.0, 1e-3, generator=gen)
+    w0 = torch.empty(n, device=dev).normal_(0.0, 0.02, generator=gen)
+    u[off[1]], u[off[7] + 4_000_000], u[off[-1] + num[-1] - 1] = float("nan"), float("inf"), float("-inf")
+    w0[off[9] + 17] = float("nan")
+    for b0, b1 in ((0, len(num)), (8, len(num)), (0, len(num))):
+        w, v = w0.clone(), torch.zeros(n, device=dev)
+        stats.zero_()
+        ctx.eager_sgd_step_lars(u, (w, v, lr, mu), trust, eps, b0=b0, b1=b1)
+        torch.cuda.synchronize()
+        norms = stats.view(torch.float64).view(-1, 4)[:, :2].cpu()
+        bad = stats.view(torch.int64).view(-1, 4)[:, 2].cpu()
+        rates = stats.view(torch.float32).view(-1, 8)[:, 6].cpu()
+        for b in range(b0, b1):
+            sl = slice(off[b], off[b] + num[b])
+            x, y = u[sl].double(), w0[sl].double()
+            fine = torch.isfinite(x)
+            su, sw = float(x[fine].square().sum()), float(y[torch.isfinite(y)].square().sum())
+            assert int(bad[b]) == int((~fine).sum()), b
+            assert abs(float(norms[b, 0]) - su) <= 1e-10 * su and abs(float(norms[b, 1]) - sw) <= 1e-10 * sw, b
+            rate = trust * sw ** 0.5 / (su ** 0.5 + eps)
+            assert abs(float(rates[b]) - rate) <= 1.2e-7 * rate, b           # one rounding to fp32
+            want = y - lr * (rate * x)
+            ok = torch.isfinite(want)
+            assert torch.equal(torch.isfinite(w[sl]), ok)
+            # a handful of fp32 roundings per element
+            assert float((w[sl].double() - want)[ok].abs().max()) <= 1e-6 * float(want[ok].abs().max())
     ctx.close()

@@ -104,8 +104,9 @@ def test_statistics_of_a_streamed_round(eb, dtype):
     [3], [255, 4096, 1], [2048 * 40 + 3, 1_400_001, 9],
     [13_000_001, 40, 2_000_000]])                         # enough records for the first stage
 def test_layerwise_norms_by_groups_of_tiles(eb, num):
-    """Norms, rates and the layer-wise step over buckets that lie anywhere in the groups of tiles
-    the norms pass works in, in a workspace that a round with statistics has used before."""
+    """Norms, rates and the layer-wise step over buckets that begin and end anywhere in groups of 8
+    tiles (the norms pass itself works in groups from 50 M elements only), in a workspace that a round
+    with statistics has used before."""
     off, cur = [], 0
     for m in num:
         off.append(cur)
