@@ -694,7 +694,7 @@ hipError_t launch_sgd_lars(const SgdArgs &a, const StatsArgs &st, bool fast, hip
     // w and v are streamed unless u, w and v stay in the last-level cache until the next step
     // (norms, rate and update on 10 M elements: 98 us streamed, 99 not; 4 M: 55.9 and 54.0; 25.6 M after
     // a round: 117 and 136)
-    const bool nt = a.n * 12 > kSmallRoundBytes;
+    const bool nt = a.n * 12 > 96ll << 20;
     const dim3 grid(static_cast<unsigned>(g)), block(64);
     if (fast) {
         if (nt) hipLaunchKernelGGL((lars_kernel<true, true>), grid, block, 0, stream, a, st);

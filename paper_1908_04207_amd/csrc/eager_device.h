@@ -263,9 +263,6 @@ constexpr int kCus = 256;
 // Parameters and momentum above this size are streamed past the caches (see finish_tile).
 constexpr long long kStateCacheBytes = 256ll << 20;
 
-// A round that moves no more than this works out of the last-level cache (see launch_slots).
-constexpr long long kSmallRoundBytes = 96ll << 20;
-
 template <typename K, typename A, typename... Extra>
 hipError_t launch_capped(K kernel, const A &a, int bpc, const Launch &cfg, dim3 grid,
                          hipStream_t st, Extra... extra)

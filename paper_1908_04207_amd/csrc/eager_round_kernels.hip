@@ -579,15 +579,8 @@ hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStre
     const dim3 grid(static_cast<unsigned>(g));
     s.h.waves_per_block = per;
     s.h.xcd_blocks = cfg.xcd_map ? static_cast<int>(g / 8) : 0;
-    // A run that moves at most 96 MB is bound by latency: everything at once, no cap.  Beyond that
-    // it is a stream.  (Both sides at the line: 1 M elements, 16 processes, 15 late = 210 MB: 41 us
-    // at once, 34.8 in bursts; 262 k = 52 MB: 11.8 and 14.7.)  Accesses are plain where the whole model
-    // moves no more than that in a round: its arrays then stay in the last-level cache from
-    // round to round (1 M elements, 8 processes: 14.1 us, 16.6 with the nontemporal hint); small runs
-    // of a larger model are streamed (1 M elements, 16 processes, cold: 41.9 us, 44.2 plain).
-    const long long per_element = 4ll * (s.h.n_sum + 2 * s.h.n_copy + (OPT ? 4 : 1));
-    const bool small = s.h.n * per_element <= kSmallRoundBytes;
-    const bool plain = model * per_element <= kSmallRoundBytes;
+    const bool small = small_round(s, OPT);
+    const bool plain = model * round_bytes(s, OPT) <= kPlainRoundBytes;
     int bpc = cfg.blocks_per_cu;
     if (bpc == 0) {
         const int w = small || cfg.chunk != 0 ? -1 : burst_waves(s, tiles, s.stats.stats != nullptr, OPT);

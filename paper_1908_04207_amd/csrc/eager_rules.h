@@ -43,4 +43,36 @@ inline bool norms_grouped(long long tiles, int n_buckets)
     return tiles >= 3 << 16 && tiles >= 128ll * n_buckets;
 }
 
+// Bytes a launch of a round moves per element: every stream read once by its type, the copies, and
+// w and v read and written or the receive buffer written.
+inline long long round_bytes(const SlotArgs &s, bool update)
+{
+    long long bytes = update ? 16 : 4;
+    for (int k = 0; k < s.h.n_sum + s.h.n_copy; ++k) {
+        const bool copy = (s.slot[k] & kSlotCopy) != 0, skip = (s.slot[k] & kKindMask) == kSkip && !copy;
+        if (!skip) bytes += ((s.slot[k] & kSlotBf16) ? 2 : 4) + (copy ? 4 : 0);
+    }
+    return bytes;
+}
+
+// A run that moves at most this is bound by latency: everything at once, no cap (chunk_kernel).  Beyond
+// it is a stream (burst_kernel): from 96 MiB where it only reads fp32 streams, from 112 MiB where bursts
+// are shorter (bf16) or copies follow them.  Both sides, chunks and bursts, one state in a loop: 8
+// processes on time, fp32, 96 MiB 18.3 and 15.0 us, 112 MiB 21.4 and 19.3, 16 processes 112 MiB 19.8 and 17.6;
+// 3 processes, 1 late, 88 MiB 13.9 and 18.1, 100 MiB 15.7 and 17.9; 8 processes, 4 late, 100 MiB 17.1 and
+// 18.6; 16 on time with bf16 gradients 100 MiB 16.2 and 19.2.
+inline bool small_round(const SlotArgs &s, bool update)
+{
+    bool reads_fp32 = s.h.n_copy == 0;
+    for (int k = 0; k < s.h.n_sum; ++k) reads_fp32 = reads_fp32 && !(s.slot[k] & kSlotBf16);
+    return s.h.n * round_bytes(s, update) <= (reads_fp32 ? 96ll : 112ll) << 20;
+}
+
+// Accesses of a small run are plain where the whole model moves no more than 56 MiB in a round: its
+// arrays then stay in the last-level cache from round to round.  Small runs of a larger model are
+// streamed.  Both sides, plain and streamed, one state in a loop: 8 processes, 4 late, 40 MiB 6.4
+// and 7.7 us; 16 processes, all on time, 64 MiB 12.0 and 10.4, 8 processes 11.4 and 9.9; with cold buffers
+// 9.9 and 10.6 at 40 MiB, 14.1 and 13.6 at 64.
+constexpr long long kPlainRoundBytes = 56ll << 20;
+
 }  // namespace eager

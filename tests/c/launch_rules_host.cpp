@@ -59,9 +59,39 @@ static int norms()
     return 0;
 }
 
+// Bytes by the type of each stream; what fills the list up moves nothing.
+static int bytes()
+{
+    SlotArgs s{};
+    auto push = [&s](unsigned long long tag) { s.slot[s.h.n_sum + s.h.n_copy] = 0x10000ull * (s.h.n_sum + s.h.n_copy + 1) | tag; };
+    for (unsigned tag : {0u + kAdd, 0u + kHold, kPair + 0u + kSlotBf16, kAdd + 0u + kSlotBf16, 0u + kSkip}) {
+        push(tag);
+        ++s.h.n_sum;
+    }
+    CHECK(round_bytes(s, true) == 2 * 4 + 2 * 2 + 16 && round_bytes(s, false) == 2 * 4 + 2 * 2 + 4);
+    for (unsigned tag : {kSkip + 0u + kSlotCopy, kSkip + 0u + kSlotCopy + kSlotBf16}) {
+        push(tag);
+        ++s.h.n_copy;
+    }
+    CHECK(round_bytes(s, true) == 12 + 8 + 6 + 16);
+    // the line between the two forms of a round, with and without what shortens its bursts
+    s.h.n = (112ll << 20) / 42;
+    CHECK(small_round(s, true));
+    ++s.h.n;
+    CHECK(!small_round(s, true));
+    SlotArgs f{};
+    f.slot[0] = f.slot[1] = 0x10000 | kAdd;
+    f.h.n_sum = 2;
+    f.h.n = (96ll << 20) / 24;
+    CHECK(small_round(f, true));
+    ++f.h.n;
+    CHECK(!small_round(f, true) && small_round(f, false));
+    return 0;
+}
+
 int main()
 {
-    if (grids() || finishing() || norms()) return 1;
+    if (grids() || finishing() || norms() || bytes()) return 1;
     std::printf("ok\n");
     return 0;
 }

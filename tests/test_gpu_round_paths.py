@@ -1,7 +1,8 @@
 """The two forms of a round - everything at once for small runs, bursts for large ones - at the
 sizes where each can go wrong: edges of tiles, ragged tails, one element, both sides of the line
 between them, slot lists of odd length and without any slot; against the oracle, bit for bit in
-fixed order.  (The line: a run that moves 96 MiB, 4 bytes per slot and copy side and 16 for w, v.)
+fixed order.  (The line: a run that moves 112 MiB, gradients counted by their type, 4 bytes for a send
+buffer read or written, 16 for w and v.)
 """
 import numpy as np
 import pytest
@@ -12,7 +13,7 @@ from workloads import grads as wg
 
 pytestmark = pytest.mark.gpu
 
-LINE = 96 << 20
+LINE = 112 << 20
 
 
 @pytest.fixture(scope="module")
@@ -53,7 +54,7 @@ def test_small_runs_at_tile_edges(eb, dtype, order):
 def test_both_sides_of_the_line_between_the_forms(eb, dtype, off):
     align = 8 if dtype == "bf16" else 4
     # mask 0b011 of 3 with nothing pending: 2 slots, 1 copy, w and v read and written
-    n = LINE // (4 * (2 + 2 + 4)) + off
+    n = LINE // (26 if dtype == "bf16" else 32) + off
     pair = Pair(eb, 3, [0], [n], (n + align - 1) // align * align, dtype, 0, seed=5)
     _rounds(eb, pair, [0b011, 0b110, 0b111], 0, n)
 
