@@ -254,12 +254,8 @@ __device__ __forceinline__ void stats_commit(StatsRecord *records, StatsRecord *
 
 // LDS is not used by the kernels; a dynamic allocation only caps how many workgroups a CU
 // holds at once.  A stream that mixes reads and writes is fastest on MI355X with about 26 KiB
-// of loads in flight per CU; beyond it HBM throughput falls again.  LDS is handed out in units of
-// 1280 bytes.
-constexpr int kLdsPerCu = 160 * 1024;
-constexpr int kLdsUnit = 1280;
-constexpr int kCus = 256;
-
+// of loads in flight per CU; beyond it HBM throughput falls again.  (LDS is handed out in units,
+// see eager_rules.h for the counts that this can realise.)
 // Parameters and momentum above this size are streamed past the caches (see finish_tile).
 constexpr long long kStateCacheBytes = 256ll << 20;
 

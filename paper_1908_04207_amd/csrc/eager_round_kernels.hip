@@ -531,44 +531,6 @@ void build_slots(const RoundArgs &a, SlotArgs &s)
     s.stats = a.stats;
 }
 
-// Resident wavefronts per CU of the burst kernel: 14, or 12 where it also copies, for fp32 streams
-// (26 KiB in flight), up to 1.75 times as many with bf16 streams, whose bursts are half as large
-// (34 of 34 streams bf16, 43 M elements: 585 us with 22-24, 619 with 21, 780 with 14, 594 with 28; 27 of
-// 34: 946 with 22-24, 960 with 19; 1 of 16, 451 M elements: 5.6 ms with 14, 5.7 with 12 or 16).  With
-// by-products a wavefront also computes for a while with nothing in flight: beside the short bursts
-// of bf16 streams (27 of 34) 1091 us with 28, 1112 with 22; with copies and the update rule (8
-// processes, 26 M elements, finish included) 298.8 us with 16, 300 with 18, 309.5 with 12.  Into
-// the receive buffer alone it is the other way round: 386 us a layer-wise step with 12, 394 with 16.  A run of few
-// generations of wavefronts takes the neighbouring count that fills them best (2 M elements, 32
-// tiles per CU: 49.3 us with 16, 52.1 with 14); one that fits the chip at once needs no cap (1 M
-// elements, 16 processes: 34.8 us, 42.7 with 14).
-int burst_waves(const SlotArgs &s, long long tiles, bool stats, bool update)
-{
-    const int n = s.h.n_sum + s.h.n_copy;
-    int n_bf = 0;
-    for (int k = 0; k < n; ++k)
-        n_bf += (s.slot[k] & kSlotBf16) && (s.slot[k] & (kKindMask | kSlotCopy)) != kSkip;
-    const int base = s.h.n_copy ? 12 : 14;
-    int w0 = base;
-    if (n > 0) w0 += (3 * base * n_bf) / (4 * n);
-    if (n > 0 && stats && !s.h.n_copy) w0 += 6 * n_bf / n;
-    if (n > 0 && stats && s.h.n_copy && update) w0 += 4 * (n - n_bf) / n;
-    const long long per_cu = (tiles + kCus - 1) / kCus;
-    if (per_cu <= w0 + 6) return -1;
-    int best = w0;
-    double least = 1e9;
-    for (int w = w0 - 2; w <= w0 + 4; ++w) {
-        const long long generations = (per_cu + w - 1) / w;
-        const double cost = static_cast<double>(generations * w) / static_cast<double>(per_cu) +
-                            0.01 * (w > w0 ? w - w0 : w0 - w);
-        if (cost < least) {
-            least = cost;
-            best = w;
-        }
-    }
-    return best;
-}
-
 template <bool BF16, bool FAST, bool NTS, bool OPT>
 hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStream_t st)
 {
@@ -583,7 +545,7 @@ hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStre
     const bool plain = model * round_bytes(s, OPT) <= kPlainRoundBytes;
     int bpc = cfg.blocks_per_cu;
     if (bpc == 0) {
-        const int w = small || cfg.chunk != 0 ? -1 : burst_waves(s, tiles, s.stats.stats != nullptr, OPT);
+        const int w = small || cfg.chunk != 0 ? -1 : burst_waves(s, tiles, s.stats.stats != nullptr, OPT, NTS);
         bpc = w < 0 ? -1 : (w + per - 1) / per;
     }
     const bool stats = s.stats.stats != nullptr;

@@ -6,6 +6,15 @@
 
 namespace eager {
 
+constexpr int kCus = 256;
+
+// Occupancy is capped with LDS, which is handed out in units of 1280 bytes: a cap of w workgroups per
+// CU realises floor(128 / floor(128 / w)) of them, so 32 (which is no cap for workgroups of one
+// wavefront), 25, 21, 18, 16, 14, 12, 11, 10, 9 ... exist and the counts between run as the next one up.
+constexpr int kLdsPerCu = 160 * 1024;
+constexpr int kLdsUnit = 1280;
+constexpr int kLdsUnits = kLdsPerCu / kLdsUnit;
+
 // A grid must hold fewer than 2^32 threads in total; a launch beyond that is not refused
 // by the runtime, its thread count wraps.  Every launcher stays at or below 2^31, and a round at
 // one workgroup more: a run of 2^33 elements is 2^31 threads, and one that ends just below it
@@ -74,5 +83,58 @@ inline bool small_round(const SlotArgs &s, bool update)
 // and 7.7 us; 16 processes, all on time, 64 MiB 12.0 and 10.4, 8 processes 11.4 and 9.9; with cold buffers
 // 9.9 and 10.6 at 40 MiB, 14.1 and 13.6 at 64.
 constexpr long long kPlainRoundBytes = 56ll << 20;
+
+// Resident wavefronts per CU of the burst kernel, -1: no cap.
+//   * 14 for fp32 streams (26 KiB in flight), 12 where copies follow.  A wavefront with few slots spends
+//     more of its life on its arguments, on w and v and on stores, so short lists with copies take
+//     more: 18 up to 5 slots, 14 up to 9 (3 processes, 1 late, 26 M elements: 139 us with 12, 130 with
+//     18; into the receive buffer 109 and 94; 4 processes, 2 late 177 and 175 with 14; 8 processes, 4
+//     late, 12 slots: 289 with 12, 295 with 16).
+//   * Up to 1.75 times as many with bf16 streams, whose bursts are half as large (34 of 34 streams bf16,
+//     43 M elements: 585 us with 25, 619 with 21, 780 with 14, 594 without a cap; 27 of 34: 946 with 25,
+//     960 with 21), and more still where the wavefront moves little else: into the receive buffer (8
+//     processes on time, 40 M elements: 118 us without a cap, 127 with 25; 16 processes 230 and 243), or
+//     beside by-products while w and v come from the last-level cache (8 processes, 16 M: 84 and 85; but
+//     80 M elements 426 and 410).
+//   * With by-products it also computes for a while with nothing in flight: 2 more beside fp32 streams (8
+//     processes, 32 M elements: 239 us with 14, 230 with 16; 16 processes 414 and 406), 4 more where copies
+//     and the update rule meet (8 processes, 26 M elements, finish included: 298.8 with 16, 309.5 with
+//     12); into the receive buffer with copies none (386 us a layer-wise step with 12, 394 with 16).
+//   * A run of few generations of wavefronts takes the neighbouring count that fills them best (2 M
+//     elements, 32 tiles per CU: 49.3 us with 16, 52.1 with 14); one that fits the chip at once needs no
+//     cap (1 M elements, 16 processes: 34.8 us, 42.7 with 14).
+inline int burst_waves(const SlotArgs &s, long long tiles, bool stats, bool update, bool state_streamed)
+{
+    const int n = s.h.n_sum + s.h.n_copy;
+    int n_bf = 0;
+    for (int k = 0; k < n; ++k)
+        n_bf += (s.slot[k] & kSlotBf16) && (s.slot[k] & (kKindMask | kSlotCopy)) != kSkip;
+    int w0 = !s.h.n_copy ? 14 : n <= 5 ? 18 : n <= 9 ? 14 : 12;
+    if (n > 0) {
+        w0 += 3 * 14 * n_bf / (4 * n);
+        if (s.h.n_copy) {
+            if (stats && update) w0 += 4 * (n - n_bf) / n;
+        } else {
+            if (!update || (stats && !state_streamed)) w0 += 6 * n_bf / n;
+            if (stats) w0 += 2 * (n - n_bf) / n;
+        }
+    }
+    const long long per_cu = (tiles + kCus - 1) / kCus;
+    if (per_cu <= w0 + 6) return -1;
+    int best = -1;
+    double least = 1e9;
+    for (int units = 4; units <= 16; ++units) {
+        const int w = kLdsUnits / units;
+        if (w < w0 - 2 || 3 * w > 4 * w0) continue;
+        const long long generations = (per_cu + w - 1) / w;
+        const double cost = static_cast<double>(generations * w) / static_cast<double>(per_cu) +
+                            0.16 / w0 * (w > w0 ? w - w0 : w0 - w);
+        if (cost < least) {
+            least = cost;
+            best = w;
+        }
+    }
+    return best == 32 ? -1 : best;
+}
 
 }  // namespace eager

@@ -89,9 +89,37 @@ static int bytes()
     return 0;
 }
 
+// The burst kernel's occupancy: a count that the LDS cap can realise, for every list and length, and
+// more for short lists with copies and for bf16 streams than for long fp32 ones.
+static int occupancy()
+{
+    auto waves = [](int sums, int copies, bool bf16, long long tiles, bool stats, bool update, bool streamed) {
+        SlotArgs s{};
+        s.h.n_sum = sums;
+        s.h.n_copy = copies;
+        for (int k = 0; k < sums + copies; ++k)
+            s.slot[k] = 0x10000ull * (k + 1) + (k < sums ? 0u + kAdd : kSkip + 0u + kSlotCopy) + (bf16 ? 0u + kSlotBf16 : 0u);
+        return burst_waves(s, tiles, stats, update, streamed);
+    };
+    for (int sums = 0; sums <= 128; sums += 2)
+        for (int copies = 0; copies <= 63 && sums + copies <= 128; copies += copies < 8 ? 1 : 5)
+            for (long long tiles : {0ll, 1ll, 4097ll, 8192ll, 19'532ll, 62'500ll, 100'000ll, 262'144ll, 6'000'000ll, 1ll << 25})
+                for (int flags = 0; flags < 16; ++flags) {
+                    const int w = waves(sums, copies, flags & 1, tiles, flags & 2, flags & 4, flags & 8);
+                    CHECK(w == -1 || (w >= 10 && w <= 25 && kLdsUnits / (kLdsUnits / w) == w));
+                    CHECK(w == -1 || w * kCus < tiles);
+                }
+    const long long many = 1ll << 22;
+    CHECK(waves(16, 0, false, many, false, true, true) == 14 && waves(12, 4, false, many, false, true, true) == 12);
+    CHECK(waves(4, 1, false, many, false, true, true) == 18 && waves(4, 3, false, many, false, true, true) == 14);
+    CHECK(waves(16, 0, true, many, false, true, true) == 25 && waves(16, 0, true, many, false, false, true) == -1);
+    CHECK(waves(16, 0, false, many, true, true, true) == 16);
+    return 0;
+}
+
 int main()
 {
-    if (grids() || finishing() || norms() || bytes()) return 1;
+    if (grids() || finishing() || norms() || bytes() || occupancy()) return 1;
     std::printf("ok\n");
     return 0;
 }
