@@ -26,8 +26,9 @@ extern "C" {
  *                update kernel followed by the copy kernel
  *   "chunk"      streams whose loads are in flight together per wavefront: 0 (default) = 2 for
  *                runs that move more than 96 MiB (112 where gradients are bf16 or late ones are
- *                copied in the same pass; gradients counted by their type), else 8 or 16 (by the
- *                length of the list); 8, 16 = that many for any run.  Per-bucket statistics need 0
+ *                copied in the same pass, 56 for one or two bf16 streams alone; gradients counted
+ *                by their type), else 8 or 16 (by the length of the list); 8, 16 = that many for
+ *                any run.  Per-bucket statistics need 0
  *                or 16
  *   "block"      threads per workgroup: 64 (default), 128 or 256
  *   "blocks_per_cu" 0 = chosen from the round (default); -1 = no cap; 1..32 = at most that many

@@ -86,6 +86,12 @@ static int bytes()
     CHECK(small_round(f, true));
     ++f.h.n;
     CHECK(!small_round(f, true) && small_round(f, false));
+    f.slot[0] |= kSlotBf16;
+    f.slot[1] |= kSlotBf16;
+    f.h.n = (56ll << 20) / 20;
+    CHECK(small_round(f, true));
+    ++f.h.n;
+    CHECK(!small_round(f, true));
     return 0;
 }
 
