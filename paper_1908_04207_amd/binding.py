@@ -8,12 +8,14 @@ current torch stream is used unless a stream is given.
 ctypes defines every call and what it accepts.  The calls of a training step hand their
 arguments to the extension module _marshal first, which knows the usual forms (lists of
 tensors, pointer tables, tuples of floats) and calls the same entry points without a ctypes
-object per argument; it returns NotImplemented for everything else.
+object per argument; it returns NotImplemented for everything else.  Without the module ctypes
+takes every call.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Sequence
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -125,17 +127,35 @@ def _load() -> ctypes.CDLL:
 
 
 lib = _load()
+
+
+class _CtypesOnly:
+    """Stands in for the extension module where it has not been built for this interpreter: knows no
+    form of any call, so that ctypes takes all of them."""
+    @staticmethod
+    def _unknown(*_):
+        return NotImplemented
+
+    plan_participation = plan_quorum = round = step = stash = views = _unknown
+
+    @staticmethod
+    def streams(*_):
+        pass
+
+
 try:
     from . import _marshal
 except ImportError as e:
-    raise ImportError(f"the argument marshalling module is missing ({e}): build it with "
-                      "`python -m paper_1908_04207_amd.build`") from e
-_marshal.bind(tuple(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in (
-    "eager_plan_participation", "eager_plan_quorum", "eager_partial_allreduce_solo",
-    "eager_partial_allreduce_majority", "eager_partial_allreduce_quorum",
-    "eager_partial_allreduce_lagging", "eager_partial_allreduce_exchange", "eager_sgd_step",
-    "eager_sgd_step_lars", "eager_stash", "eager_sgd_step_views", "eager_average_views")),
-    Plan, ctypes.Array)
+    warnings.warn(f"the argument marshalling module is not there ({e}): every call goes through ctypes.  "
+                  "Build it with `python -m paper_1908_04207_amd.build`", RuntimeWarning)
+    _marshal = _CtypesOnly
+else:
+    _marshal.bind(tuple(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in (
+        "eager_plan_participation", "eager_plan_quorum", "eager_partial_allreduce_solo",
+        "eager_partial_allreduce_majority", "eager_partial_allreduce_quorum",
+        "eager_partial_allreduce_lagging", "eager_partial_allreduce_exchange", "eager_sgd_step",
+        "eager_sgd_step_lars", "eager_stash", "eager_sgd_step_views", "eager_average_views")),
+        Plan, ctypes.Array)
 # a child process has no current stream before torch says so again
 os.register_at_fork(after_in_child=lambda: _marshal.streams(None, None))
 

@@ -12,7 +12,9 @@ import os
 import subprocess
 import sys
 import sysconfig
+import warnings
 from concurrent.futures import ThreadPoolExecutor
+from typing import Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -20,7 +22,8 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libeager.so")
 STAMP = LIB + ".srchash"
-MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+MARSHAL_STAMP = MARSHAL + ".srchash"
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ["eager_round_kernels.hip", "eager_aux_kernels.hip", "eager_static_kernels.hip",
            "eager_calib_kernels.hip", "eager_api.cpp"]
@@ -101,32 +104,48 @@ def build(verbose: bool = False, extra=(), force: bool = True) -> str:
         objs = list(pool.map(compile_one, SOURCES))
     if os.path.exists(STAMP):
         os.remove(STAMP)
-    build_marshal(verbose)
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     if verbose:
         print(" ".join(cmd), flush=True)
     _run(cmd)
     with open(STAMP, "w") as f:
         f.write(digest + "\n")
+    build_marshal(verbose)
     return LIB
 
 
-def build_marshal(verbose: bool = False) -> str:
+def build_marshal(verbose: bool = False) -> Optional[str]:
+    """The extension module for this interpreter, or None (and a warning) where it cannot be
+    compiled; its stamp records either."""
+    untagged = os.path.join(os.path.dirname(MARSHAL), "_marshal.so")    # any interpreter would load it
+    for stale in (MARSHAL, MARSHAL_STAMP, untagged):
+        if os.path.exists(stale):
+            os.remove(stale)
+    built: Optional[str] = MARSHAL
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "eager_marshal.cpp"),
            "-o", MARSHAL]
     if verbose:
         print(" ".join(cmd), flush=True)
-    _run(cmd)
-    return MARSHAL
+    try:
+        _run(cmd)
+    except (OSError, subprocess.CalledProcessError) as e:
+        warnings.warn(f"the argument marshalling module was not built ({e}): calls go through ctypes")
+        built = None
+    with open(MARSHAL_STAMP, "w") as f:
+        f.write(source_hash() + ("\n" if built else " not built\n"))
+    return built
 
 
 def is_current() -> bool:
-    """Whether the built library was compiled from the sources as they are now."""
-    if not (os.path.exists(LIB) and os.path.exists(MARSHAL) and os.path.exists(STAMP)):
+    """Whether the built library was compiled from the sources as they are now, and the extension
+    module for this interpreter too, or tried to be."""
+    if not (os.path.exists(LIB) and os.path.exists(STAMP) and os.path.exists(MARSHAL_STAMP)):
         return False
-    with open(STAMP) as f:
-        return f.read().strip() == source_hash()
+    with open(STAMP) as f, open(MARSHAL_STAMP) as m:
+        of_library, of_module = f.read().strip(), m.read().split()
+    digest = source_hash()
+    return of_library == digest and of_module[:1] == [digest] and (os.path.exists(MARSHAL) or len(of_module) > 1)
 
 
 def ensure_built() -> str:
