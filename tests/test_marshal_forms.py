@@ -1,7 +1,9 @@
 """The native argument marshalling against the ctypes path, which defines what a call accepts and
 how it refuses: every form of argument goes through both, and the outcome - status, message, type
 of exception, plan - must be the same.  All calls are refused by the library's own checks before
-anything is launched, so this runs without a GPU.
+anything is launched, so this runs without a GPU.  (Most refusals here come from the receive
+buffer, before the library looks at the other arguments: what the extension hands over is checked in
+test_marshal_arguments.py.)
 """
 import ctypes
 
