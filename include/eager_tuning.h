@@ -20,9 +20,10 @@ extern "C" {
  * ones: EINVAL.  Every combination of listed values has a kernel.
  *   "split"      0 = chosen per round (default): the send-buffer rewrite of the late
  *                processes runs as a copy kernel of its own after the reduction when the round
- *                moves 512 MiB or more and either the fused pass would read more than 16
- *                streams, or 8 or more processes are late, or 3 or more are late and the run has
- *                2^25 elements or more.  1 = always one fused kernel; 2 = always reduction +
+ *                moves 512 MiB or more (4 bytes per stream read or written whatever its type, 16
+ *                for w and v) and either the fused pass would read more than 16 streams, or 8 or
+ *                more processes are late, or 3 or more are late and the run has 2^25 elements or
+ *                more.  1 = always one fused kernel; 2 = always reduction +
  *                update kernel followed by the copy kernel
  *   "chunk"      streams whose loads are in flight together per wavefront: 0 (default) = 2 for
  *                runs that move more than 96 MiB (112 where gradients are bf16 or late ones are
@@ -31,8 +32,9 @@ extern "C" {
  *                any run.  Per-bucket statistics need 0
  *                or 16
  *   "block"      threads per workgroup: 64 (default), 128 or 256
- *   "blocks_per_cu" 0 = chosen from the round (default); -1 = no cap; 1..32 = at most that many
- *                workgroups resident per CU
+ *   "blocks_per_cu" 0 = chosen from the round (default; no cap where "chunk" is 8 or 16); -1 = no
+ *                cap; 1..32 = that many workgroups resident per CU, or the next count above it that
+ *                LDS in units of 1280 bytes can enforce (..., 12, 14, 16, 18, 21, 25, 32)
  *   "nt_state"   nontemporal hint on w, v and recv too: -1 (default) = when they exceed 256 MiB
  *                in the call (they cannot stay in the last-level cache until the next round),
  *                0 = never, 1 = always
@@ -42,7 +44,7 @@ extern "C" {
  *   "carry_block", "carry_vec", "carry_blocks_per_cu"  shape of the copy kernel of a split
  *                round: threads per workgroup (64 default, 128, 256), groups of 4 elements per
  *                thread (1 default, 2, 4), resident workgroups per CU (-1 = no cap, default;
- *                1..32)
+ *                1..32 as above)
  *   "round_stats" 1 (default) = with statistics attached every round writes the by-products;
  *                0 = rounds leave them alone (for callers that attach the statistics only as
  *                the workspace of eager_sgd_step_lars, which forms its own norms)
@@ -55,11 +57,12 @@ int eager_set_launch(eager_ctx *ctx, const char *key, int value);
  * alignment, sizes or counts outside the stated ranges), EDEVICE.
  *   copy  dst <- src, nbytes a multiple of 16
  *   read  sums src (nbytes, a multiple of 16) in registers; *sink is written practically never
- *   mix   what a plain kernel with a round's mix of streams reaches: lane-vector i (16 bytes) of
- *         each of the n_read (1..80) streams is loaded, the values are added up, and the sum is
- *         stored to lane-vector i of each of the n_write (0..80) streams; same access shape as a
- *         round (one tile of 256 elements per wavefront, up to 16 loads in flight per lane,
- *         nontemporal).  n_vec lane-vectors per stream.  Bit j of read_half_mask marks read stream (one of the first 64)
+ *   mix   a plain kernel with a round's mix of streams: lane-vector i (16 bytes) of each of the
+ *         n_read (1..80) streams is loaded, the values are added up, and the sum is stored to
+ *         lane-vector i of each of the n_write (0..80) streams; one tile of 256 elements per
+ *         wavefront, up to 16 loads in flight per lane, nontemporal.  (A streamed round keeps 2 in
+ *         flight in each of more wavefronts, which is the better shape: a rate to compare with, not a
+ *         ceiling.)  n_vec lane-vectors per stream.  Bit j of read_half_mask marks read stream (one of the first 64)
  *         j as half-width: it holds 8 bytes per lane-vector (n_vec * 8 bytes, n_vec even), read the
  *         way a round reads bf16 gradients.  waves_per_cu: 0 = no cap, 1..32 = at most that many
  *         64-lane workgroups resident per CU.  sink: 4 writable bytes, needed when n_write is 0.

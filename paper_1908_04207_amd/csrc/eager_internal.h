@@ -92,7 +92,8 @@ struct RoundArgs {
     unsigned long long valid;    // bit p: R_p holds an undelivered gradient
     unsigned long long gload;    // bit p: this launch reads G_p (every process that has a gradient
                                  // when fused; only on-time processes when the carry runs as
-                                 // its own kernel)
+                                 // its own kernel); follows from active and store, for recorders of
+                                 // launches
     unsigned long long store;    // bit p: this launch stores G_p into R_p (late processes when
                                  // fused; none otherwise)
     float *w;                    // parameters (NULL: no update rule)
@@ -212,6 +213,7 @@ hipError_t launch_round(const RoundArgs &a, bool bf16, bool fast, const Launch &
 hipError_t launch_carry(const CarryArgs &a, bool bf16, const Launch &cfg, hipStream_t stream);
 hipError_t launch_stats_finish(const StatsArgs &a, hipStream_t stream);
 long long slot_records(long long n, bool bf16, int block);   // tiles of a round, one record each
+                                                             // (whatever the workgroups)
 int slot_tail(long long n, bool bf16);                       // elements of its ragged tail
 hipError_t launch_stash(const StashArgs &a, bool bf16, hipStream_t stream);
 hipError_t launch_views_sgd(const ViewsArgs &a, bool fast, const Launch &cfg, hipStream_t stream);

@@ -364,8 +364,8 @@ __global__ __launch_bounds__(256) void burst_kernel(const SlotArgs)
 // more slots than CH it does so again.  One body of code whatever the number of slots (the list
 // ends in SKIPs, which are nearly free): a body for every remainder has to be fetched before it
 // runs.  NT: as for the streams of the burst kernel, or plain.  Kernel time, before and now:
-// 8193 elements, 8 processes solo 6.7 -> 4.0 us; 1 M elements, 4 processes solo 12.1 -> 10.6
-// us a round; 1 M, 8 processes, 4 late 17.2 -> 14.1.
+// 8193 elements, 8 processes solo 6.7 -> 4.0 us; 1 M elements, 4 processes solo 11.6 -> 10.7
+// us a round; 1 M, 8 processes, 4 late 15.8 -> 13.9.
 template <bool BF16, bool FAST, bool NT, bool NTS, bool OPT, bool STATS, int CH>
 __global__ __launch_bounds__(256) void chunk_kernel(const SlotArgs)
 {
@@ -559,7 +559,8 @@ hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStre
     if (cfg.chunk == 0 && !small && !late_in_recv)
         return stats ? launch_capped(burst_kernel<BF16, FAST, NTS, OPT, true>, s, bpc, cfg, grid, st)
                      : launch_capped(burst_kernel<BF16, FAST, NTS, OPT, false>, s, bpc, cfg, grid, st);
-    // the by-products exist for the default chunk size only
+    // (8-slot chunks with by-products serve the rule's own choice of short lists; as a launch option
+    // that pair has always been refused, by the caller with a message of its own)
     if (stats && cfg.chunk == 8) return hipErrorInvalidValue;
     const bool few = cfg.chunk == 8 || (cfg.chunk == 0 && s.h.n_sum + s.h.n_copy <= 8);
     switch ((stats ? 4 : 0) | (few ? 2 : 0) | (plain ? 1 : 0)) {
@@ -649,9 +650,8 @@ hipError_t launch_carry(const CarryArgs &a, bool bf16, const Launch &cfg, hipStr
     return bf16 ? launch_carry_t<true>(a, cfg, stream) : launch_carry_t<false>(a, cfg, stream);
 }
 
-long long slot_records(long long n, bool bf16, int block)
+long long slot_records(long long n, bool bf16, int)
 {
-    (void)block;
     const long long nvec = bf16 ? slot_nvec<true>(n) : slot_nvec<false>(n);
     return (nvec + 63) / 64;
 }
