@@ -541,8 +541,8 @@ hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStre
     const dim3 grid(static_cast<unsigned>(g));
     s.h.waves_per_block = per;
     s.h.xcd_blocks = cfg.xcd_map ? static_cast<int>(g / 8) : 0;
-    const bool small = small_round(s, OPT);
-    const bool plain = model * round_bytes(s, OPT) <= kPlainRoundBytes;
+    const long long per_element = round_bytes(s, OPT);
+    const bool small = small_round(s, per_element), plain = model * per_element <= kPlainRoundBytes;
     int bpc = cfg.blocks_per_cu;
     if (bpc == 0) {
         const int w = small || cfg.chunk != 0 ? -1 : burst_waves(s, tiles, s.stats.stats != nullptr, OPT, NTS);
@@ -553,7 +553,7 @@ hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStre
     // before the result is stored over it, which is the order of the chunk kernel.  (Copies before
     // the update in the burst kernel too: 0.4 % slower over all rounds with copies, up to 1.5 %.)
     bool late_in_recv = false;
-    for (int k = s.h.n_sum; k < s.h.n_sum + s.h.n_copy; ++k)
+    for (int k = s.h.n_sum; !small && k < s.h.n_sum + s.h.n_copy; ++k)
         late_in_recv |= (s.slot[k] & ~static_cast<unsigned long long>(kSlotTag)) ==
                         reinterpret_cast<unsigned long long>(s.h.recv);
     if (cfg.chunk == 0 && !small && !late_in_recv)

@@ -64,20 +64,23 @@ inline long long round_bytes(const SlotArgs &s, bool update)
     return bytes;
 }
 
-// A run that moves at most this is bound by latency: everything at once, no cap (chunk_kernel).  Beyond
-// it is a stream (burst_kernel): from 96 MiB where it only reads fp32 streams, from 112 MiB where bursts
-// are shorter (bf16) or copies follow them, and from 56 MiB where one or two bf16 streams are all there
-// is, which a wavefront takes in one burst anyway (the chunk is filled up with loads of no use).  Both sides, chunks and bursts, one state in a loop: 8
-// processes on time, fp32, 96 MiB 18.3 and 15.0 us, 112 MiB 21.4 and 19.3, 16 processes 112 MiB 19.8 and 17.6;
-// 3 processes, 1 late, 88 MiB 13.9 and 18.1, 100 MiB 15.7 and 17.9; 8 processes, 4 late, 100 MiB 17.1 and
-// 18.6; 16 on time with bf16 gradients 100 MiB 16.2 and 19.2, but one process 80 MiB 17.1 and 16.6, two
-// 14.4 and 13.3.
-inline bool small_round(const SlotArgs &s, bool update)
+// Whether a run is bound by latency - everything at once, no cap (chunk_kernel) - and not a stream
+// (burst_kernel).  A stream begins at 96 MiB moved where the run only reads fp32 streams, at 112 MiB where
+// bursts are shorter (bf16) or copies follow them, and at 56 MiB where one or two bf16 streams are all
+// there is, which a wavefront takes in one burst anyway (a chunk is filled up with loads of no
+// use).  Both sides, chunks and bursts, one state in a loop: 8 processes on time, fp32, 96 MiB 18.3
+// and 15.0 us, 112 MiB 21.4 and 19.3, 16 processes 112 MiB 19.8 and 17.6; 3 processes, 1 late, 88 MiB 13.9
+// and 18.1, 100 MiB 15.7 and 17.9; 8 processes, 4 late, 100 MiB 17.1 and 18.6; 16 on time with bf16
+// gradients 100 MiB 16.2 and 19.2, but one process 80 MiB 17.1 and 16.6, two 14.4 and 13.3.
+inline bool small_round(const SlotArgs &s, long long bytes_per_element)
 {
+    const long long moved = s.h.n * bytes_per_element;
+    if (moved <= 56ll << 20) return true;
+    if (moved > 112ll << 20) return false;
+    if (s.h.n_copy) return true;
     bool bf16 = false;
     for (int k = 0; k < s.h.n_sum; ++k) bf16 = bf16 || (s.slot[k] & kSlotBf16);
-    const long long mib = s.h.n_copy ? 112 : !bf16 ? 96 : s.h.n_sum <= 2 ? 56 : 112;
-    return s.h.n * round_bytes(s, update) <= mib << 20;
+    return bf16 ? s.h.n_sum > 2 : moved <= 96ll << 20;
 }
 
 // Accesses of a small run are plain where the whole model moves no more than 56 MiB in a round: its

@@ -76,22 +76,22 @@ static int bytes()
     CHECK(round_bytes(s, true) == 12 + 8 + 6 + 16);
     // the line between the two forms of a round, with and without what shortens its bursts
     s.h.n = (112ll << 20) / 42;
-    CHECK(small_round(s, true));
+    CHECK(small_round(s, 42));
     ++s.h.n;
-    CHECK(!small_round(s, true));
+    CHECK(!small_round(s, 42));
     SlotArgs f{};
     f.slot[0] = f.slot[1] = 0x10000 | kAdd;
     f.h.n_sum = 2;
     f.h.n = (96ll << 20) / 24;
-    CHECK(small_round(f, true));
+    CHECK(small_round(f, 24));
     ++f.h.n;
-    CHECK(!small_round(f, true) && small_round(f, false));
+    CHECK(!small_round(f, 24) && small_round(f, 12));
     f.slot[0] |= kSlotBf16;
     f.slot[1] |= kSlotBf16;
     f.h.n = (56ll << 20) / 20;
-    CHECK(small_round(f, true));
+    CHECK(small_round(f, 20));
     ++f.h.n;
-    CHECK(!small_round(f, true));
+    CHECK(!small_round(f, 20));
     return 0;
 }
 
