@@ -37,8 +37,8 @@ inline long long round_workgroups(long long n, bool bf16, int block)
 // are then small, four times as many workgroups of 256 run at a time.  (Norms, finish and update of
 // the layer-wise rule behind a round, 1024 and 256 threads: 600 buckets in 40 M elements 403 and 407
 // us, 800 in 36 M 366 and 363, 1000 in 20 M 219 and 216, 2000 in 16 M 181 and 171; a round of two
-// processes with norms, 65536 buckets in 4 M elements, 290 and 147 us.)  It also bounds the grid: 2^32 threads are more than
-// 16 M buckets, or 262 k where one of them takes all the slices of a first stage.
+// processes with norms, 65536 buckets in 4 M elements, 290 and 147 us.)  It also bounds the grid: 2^32
+// threads are 16 M buckets, or 262 k where one of them takes all the slices of a first stage.
 inline int finish_threads(int n_buckets) { return n_buckets > 768 ? 256 : 1024; }
 
 // Whether the norms pass of the layer-wise rule works in groups of 8 tiles: from 50 M elements, with
