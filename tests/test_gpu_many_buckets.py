@@ -79,11 +79,14 @@ def test_sums_and_rates(eb, count, large):
     ctx.close()
 
 
-@pytest.mark.parametrize("extra", [0, 3])
-def test_norms_in_groups_of_tiles(eb, extra):
-    """52 M elements: groups of 8 tiles that lie inside one bucket, that buckets share, that end with
-    the run; enough records for the first stage; a range of buckets for which groups are too few."""
-    num = [2048 * 3, 100, 2047, 2049, 5, 256, 2048, 50_400_001, 1, 1_300_003, 30_000, 2048 * 8, 77, 250_000 + extra]
+@pytest.mark.parametrize("num", [
+    [2048 * 3, 100, 2047, 2049, 5, 256, 2048, 50_400_001, 1, 1_300_003, 30_000, 2048 * 8, 77, 250_000],
+    [2048 * 3, 100, 2047, 2049, 5, 256, 2048, 50_400_001, 1, 1_300_003, 30_000, 2048 * 8, 77, 250_003],
+    [52_001, 60_000, 2048 * 20, 7, 90_002] * 240])
+def test_norms_in_groups_of_tiles(eb, num):
+    """More than 50 M elements: groups of 8 tiles that lie inside one bucket, that buckets share, that
+    end with the run; enough records for the first stage; a range of buckets for which groups are too
+    few; more buckets than the large finishing workgroups are for."""
     off, n = [], 0
     for m in num:
         off.append(n)
