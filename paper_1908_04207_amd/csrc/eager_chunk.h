@@ -1,0 +1,385 @@
+// gfx950 kernel of the round for small runs, whose time is the one from launch to the last store:
+// a launch, one trip to the arguments, one trip to the streams.  Included by the files that
+// instantiate it, one per gradient type with and without by-products (compiled side by side).
+#pragma once
+
+#include "eager_device.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace eager {
+namespace {
+
+// What a lane owns: W consecutive elements, 4 or 1, lane-vector number `at` of the launch.
+template <int W> struct Width;
+template <> struct Width<4> { typedef f32x4 type; };
+template <> struct Width<1> { typedef float type; };
+
+template <bool NT>
+__device__ __forceinline__ float ld_one(const char *base, unsigned off)
+{
+    asm("" : "+v"(off));
+    typedef const float __attribute__((address_space(1))) GF;
+    GF *p = (GF *)(base + off);
+    if (NT) return __builtin_nontemporal_load(p);
+    return *p;
+}
+template <bool NT>
+__device__ __forceinline__ float ld_half(const char *base, unsigned off)      // 16 bits, in the lower half
+{
+    asm("" : "+v"(off));
+    typedef const unsigned short __attribute__((address_space(1))) GH;
+    GH *p = (GH *)(base + off);
+    const unsigned short x = NT ? __builtin_nontemporal_load(p) : *p;
+    return __uint_as_float(static_cast<unsigned>(x));
+}
+template <bool NT>
+__device__ __forceinline__ void st_one(char *base, unsigned off, float x)
+{
+    asm("" : "+v"(off));
+    typedef float __attribute__((address_space(1))) GFw;
+    GFw *p = (GFw *)(base + off);
+    if (NT) __builtin_nontemporal_store(x, p);
+    else *p = x;
+}
+template <int W, bool NT>
+__device__ __forceinline__ typename Width<W>::type ld_vec(const void *base, unsigned off)
+{
+    const char *p = static_cast<const char *>(base);
+    if constexpr (W == 4) return ld_at<NT>(p, off);
+    else return ld_one<NT>(p, off);
+}
+template <int W, bool NT>
+__device__ __forceinline__ void st_vec(void *base, unsigned off, typename Width<W>::type x)
+{
+    char *p = static_cast<char *>(base);
+    if constexpr (W == 4) st_at<NT>(p, off, x);
+    else st_one<NT>(p, off, x);
+}
+
+// A bf16 stream's values as loaded -> fp32.  W = 4: of the 16-byte piece that two lanes share the
+// upper half belongs to the odd one.
+__device__ __forceinline__ f32x4 widen(f32x4 raw, bool odd)
+{
+    const u32x4 r = __builtin_bit_cast(u32x4, raw);
+    const unsigned a = odd ? r.z : r.x, b = odd ? r.w : r.y;
+    f32x4 x;
+    x.x = __uint_as_float(a << 16);
+    x.y = __uint_as_float(a & 0xffff0000u);
+    x.z = __uint_as_float(b << 16);
+    x.w = __uint_as_float(b & 0xffff0000u);
+    return x;
+}
+__device__ __forceinline__ float widen(float raw, bool) { return __uint_as_float(__float_as_uint(raw) << 16); }
+
+template <bool>
+__device__ __forceinline__ void update_rule(const UpdateRule &r, float u, float vo, float wo, float &vn, float &wn)
+{
+    vn = vo;
+    wn = wo;
+    update_rule_scalar(r, u, vn, wn);
+}
+
+// Copies out of the argument segment.
+__device__ __forceinline__ ChunkHead read(const ChunkHead __attribute__((address_space(4))) &from)
+{
+    ChunkHead h;
+    __builtin_memcpy(&h, (const void __attribute__((address_space(4))) *)&from, sizeof h);
+    return h;
+}
+__device__ __forceinline__ ChunkBits read(const ChunkBits __attribute__((address_space(4))) &from)
+{
+    ChunkBits b;
+    __builtin_memcpy(&b, (const void __attribute__((address_space(4))) *)&from, sizeof b);
+    return b;
+}
+
+// A word that the compiler must not connect with an earlier look at it: it would bring a load down to
+// where its value is used, next to the other branch that asks for the same slot.
+// (W, as a remark in the assembly, keeps the two widths' statements apart.)
+template <int W, typename T>
+__device__ __forceinline__ T opaque(T x)
+{
+    asm volatile("; %1" : "+s"(x) : "n"(W));
+    return x;
+}
+
+// f(0), f(1), ... f(n - 1), at most CH of them, by number: one branch per step, one way out.
+template <int CH, int J = 0, typename F>
+__device__ __forceinline__ void first_of(int n, const F &f)
+{
+    if constexpr (J < CH) {
+        if (__builtin_expect(n > J, 1)) {
+            f(std::integral_constant<int, J>());
+            first_of<CH, J + 1>(n, f);
+        }
+    }
+}
+
+// What one wavefront does: lane-vectors [at0, at0 + 64) of W elements, up to `end`, with CH slots in
+// flight.  What bounds it is how many instructions a wavefront issues between its trips to memory - a
+// wavefront on its own issues one in 4 cycles or more, 600 of them are a microsecond - so nothing is done
+// for a slot that is not there, and what is done with one is a branch on a bit: a load is one
+// instruction, an ADD one per element.  (All loads are waited for together, before the first branch
+// that depends on a slot's kind: the registers of a slot that was not read are never looked at.)
+template <int W, int CH, bool BF16, bool NT, bool NTS, bool OPT, bool STATS, int READ, typename K>
+__device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsigned long long (&slot)[READ], unsigned at0,
+                                           unsigned end, long long record)
+{
+    typedef typename Width<W>::type V;
+    const unsigned lane = threadIdx.x & 63u, mine = at0 + lane;
+    const bool in = mine < end;
+    const unsigned at = in ? mine : end - 1u;
+    const unsigned off = at * (4u * W);
+    const unsigned off_bf = W == 4 ? (at >> 1) * 16u : at * 2u;
+    const bool odd = (at & 1u) != 0u;
+
+    V s = (V)(0.0f), held = s, x[CH];
+    auto request = [&](int k0, const ChunkBits &b, auto address) {
+        first_of<CH>(h.n_slots - k0, [&](auto J) {
+            constexpr int j = decltype(J)::value;
+            const char *base = reinterpret_cast<const char *>(address(J));
+            if constexpr (!BF16) x[j] = ld_vec<W, NT>(base, off);
+            else if constexpr (W == 4) x[j] = ld_vec<W, NT>(base, b.bf >> j & 1u ? off_bf : off);
+            else if (b.bf >> j & 1u) x[j] = ld_half<NT>(base, off_bf);
+            else x[j] = ld_vec<W, NT>(base, off);
+        });
+    };
+    // the sum, then the copies, of the slots in flight
+    auto consume = [&](int k0, ChunkBits b) {
+#pragma unroll
+        for (int j = 0; j < CH; ++j) asm volatile("; %1" : "+v"(x[j]) : "n"(W) : "memory");
+        const int sums = opaque<W>(h.n_sum) - k0;
+        if (BF16) {
+            b.bf = opaque<W>(b.bf);
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                if (b.bf >> j & 1u) x[j] = widen(x[j], odd);
+        }
+        {
+            b.pair = opaque<W>(b.pair);
+#pragma unroll
+            for (int g = 0; g < CH; g += 8)
+                if (b.pair >> g & 255u) {
+#pragma unroll
+                    for (int j = g; j < g + 8; ++j)
+                        if (b.pair >> j & 1u) {
+                            V &before = j ? x[j ? j - 1 : 0] : held;
+                            x[j] = before + x[j];
+                            before = (V)(0.0f);           // (nothing more to add: s is never -0.0f)
+                            asm volatile("; %2" : "+v"(x[j]), "+v"(before) : "n"(W));     // (a branch, not 8 selects)
+                        }
+                }
+            if (sums > CH && (b.hold >> (CH - 1) & 1u)) {
+                held = x[CH - 1];
+                x[CH - 1] = (V)(0.0f);
+            }
+        }
+        first_of<CH>(sums, [&](auto J) {
+            constexpr int j = decltype(J)::value;
+            s = s + x[j];
+            asm volatile("; %1" : "+v"(s) : "n"(W));
+        });
+        // Stores stay behind the adds: moved ahead of them, the in-order memory counter would make
+        // every add wait for the acknowledgement of a store instead of for its load.
+        asm volatile("; %1" : "+v"(s) : "n"(W) : "memory");
+        b.copy = opaque<W>(b.copy);
+        if (b.copy && in) {
+#pragma unroll
+            for (int g = 0; g < CH; g += 8)
+                if (b.copy >> g & 255u) {
+                    auto *dst = &a.dst[k0 + g - h.dst_first];
+                    float *to[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) to[j] = dst[j];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if (b.copy >> (g + j) & 1u) st_vec<W, NT>(to[j], off, x[g + j]);
+                }
+        }
+    };
+
+    V vo = (V)(0.0f), wo = vo;
+    if (OPT) {
+        vo = ld_vec<W, NTS>(h.v, off);
+        wo = ld_vec<W, NTS>(h.w, off);
+    }
+    // w and v go first (16 processes on time, bf16, 72 MiB moved: 10.8 us, 15.7 with them last)
+    request(0, h.first, [&](auto J) {
+        constexpr int j = decltype(J)::value;
+        if constexpr (j < READ) return slot[j];
+        else return a.slot[j];
+    });
+    LaneStats ls = {0.0, 0.0, 0u, -1};
+    int n_valid = 0;
+    if constexpr (STATS) {
+        const long long e = a.first + static_cast<long long>(at) * W;
+        if constexpr (W == 4) {
+            long long stop;
+            const int b = tile_bucket(a.stats.table, a.stats.b_lo, a.stats.b_hi, a.first + at0 * 4ll, e, stop);
+            if (in) {
+                ls.bucket = b;
+                n_valid = inside(e, stop);
+            }
+        } else {
+            ls.bucket = find_bucket(a.stats.table, a.stats.n_buckets, e);
+            if (e < a.stats.table[2 * ls.bucket + 1]) n_valid = 1;
+            else ls.bucket = -2;                                   // padding
+        }
+    }
+    consume(0, h.first);
+    // (the first chunk stands apart: at the head of a loop the compiler waits for everything in
+    // flight, w and v among it, before the first slot is requested)
+    for (int k0 = CH; k0 < h.n_slots; k0 += CH) {
+        ChunkBits b = read(a.bits[k0 / kChunkWord]);
+        const int shift = k0 % kChunkWord;
+        b.pair >>= shift;
+        b.hold >>= shift;
+        b.copy >>= shift;
+        b.bf >>= shift;
+        request(k0, b, [&](auto J) { return a.slot[k0 + decltype(J)::value]; });
+        consume(k0, b);
+    }
+
+    const V avg = s * h.inv_P;
+    if constexpr (STATS) {
+        if constexpr (W == 4) {
+            const f32x4 w_old = OPT ? wo : (f32x4)(0.0f);
+            if (n_valid > 0) stats_add(ls, avg.x, w_old.x, OPT);
+            if (n_valid > 1) stats_add(ls, avg.y, w_old.y, OPT);
+            if (n_valid > 2) stats_add(ls, avg.z, w_old.z, OPT);
+            if (n_valid > 3) stats_add(ls, avg.w, w_old.w, OPT);
+        } else if (n_valid) {
+            stats_add(ls, avg, OPT ? wo : 0.0f, OPT);
+        }
+    }
+    V vn, wn;
+    if (OPT) {
+        const UpdateRule rule = {h.neg_lr, h.mu, h.wd, h.nesterov};
+        update_rule<false>(rule, avg, vo, wo, vn, wn);
+    }
+    if (in) {
+        if (h.recv) st_vec<W, NTS>(h.recv, off, avg);
+        if (OPT) {
+            st_vec<W, NTS>(h.v, off, vn);
+            st_vec<W, NTS>(h.w, off, wn);
+        }
+        if constexpr (STATS && W == 1) {
+            // the ragged tail: one record per element, in the block after the last bucket's
+            const StatsRecord rec = {ls.ssu, ls.ssw, ls.bucket, ls.nf, 0};
+            a.stats.lane_records[static_cast<long long>(a.stats.n_buckets) * 64 + lane] = rec;
+        }
+    }
+    if constexpr (STATS && W == 4) stats_commit(a.stats.records, a.stats.lane_records, ls, record);
+}
+
+// One tile of 64 lane-vectors per wavefront, 4 elements to a lane, and the ragged tail (at most 3
+// elements, 7 with bf16 gradients) by a wavefront of its own, one element to a lane.  A very small run
+// is taken one element to a lane altogether: a quarter of the arithmetic in each of four times as many
+// wavefronts, for which there is room.
+template <bool BF16, bool NT, bool NTS, bool OPT, bool STATS, int CH, typename ARGS>
+__global__ __launch_bounds__(256) void chunk_kernel(const ARGS)
+{
+    const ARGS __attribute__((address_space(4))) &a = kernarg<ARGS>();
+    // The head, the first slots and a word of every further line of the arguments are requested at
+    // once: read where they are used, each is a trip of its own (32 processes, 16 late, 64 elements: 5.37
+    // us with the lines of a short list only, 4.80 with these).
+    ChunkHead h = read(a.h);
+    unsigned long long slot[CH];
+#pragma unroll
+    for (int j = 0; j < CH; ++j) slot[j] = a.slot[j];
+    typedef const unsigned __attribute__((address_space(4))) Word;
+    constexpr int far = ARGS::kSlots > kChunkWord ? kChunkWord : 0, step = far / 4;
+    const unsigned line[] = {*(Word *)&a.slot[16], *(Word *)&a.slot[24], *(Word *)&a.dst[0], *(Word *)&a.dst[8],
+                             *(Word *)&a.dst[16], *(Word *)&a.slot[far], *(Word *)&a.slot[far + step],
+                             *(Word *)&a.slot[far + 2 * step], *(Word *)&a.slot[far + 3 * step],
+                             *(Word *)&a.dst[3 * step], *(Word *)&a.bits[far / kChunkWord]};
+    if constexpr (far > 0)
+        asm volatile("" : "+s"(h.w), "+s"(slot[0]), "+s"(slot[CH - 1]) : "s"(line[0]), "s"(line[1]), "s"(line[2]),
+                     "s"(line[3]), "s"(line[4]), "s"(line[5]), "s"(line[6]), "s"(line[7]), "s"(line[8]),
+                     "s"(line[9]), "s"(line[10]));
+    else
+        asm volatile("" : "+s"(h.w), "+s"(slot[0]), "+s"(slot[CH - 1]) : "s"(line[0]), "s"(line[1]), "s"(line[2]),
+                     "s"(line[3]), "s"(line[4]));
+    asm volatile("" : "+s"(h.v), "+s"(h.recv), "+s"(h.n), "+s"(h.n_sum), "+s"(h.n_slots));
+    asm volatile("" : "+s"(h.dst_first), "+s"(h.narrow), "+s"(h.waves_per_block), "+s"(h.xcd_blocks),
+                 "+s"(h.inv_P), "+s"(h.neg_lr), "+s"(h.mu), "+s"(h.wd), "+s"(h.nesterov));
+    asm volatile("" : "+s"(h.first.pair), "+s"(h.first.hold), "+s"(h.first.copy), "+s"(h.first.bf));
+#pragma unroll
+    for (int j = 1; j < CH - 1; ++j) asm volatile("" : "+s"(slot[j]));
+    // Workgroups are dealt to the 8 XCDs round robin; xcd_blocks gives every XCD one contiguous
+    // eighth of the launch instead (a launch option, for A/B).
+    unsigned bid = blockIdx.x;
+    const unsigned per = static_cast<unsigned>(h.xcd_blocks);
+    if (per && bid < per * 8u) bid = (bid % 8u) * per + bid / 8u;
+    const unsigned wave = bid * static_cast<unsigned>(h.waves_per_block) +
+                          static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
+    unsigned first = wave * 64u;
+    if (!h.narrow) {
+        const unsigned nvec = BF16 ? h.n / 8u * 2u : h.n / 4u, tiles = (nvec + 63u) / 64u;
+        if (wave < tiles) {
+            chunk_body<4, CH, BF16, NT, NTS, OPT, STATS>(a, h, slot, first, nvec, wave);
+            return;
+        }
+        first = wave == tiles ? nvec * 4u : h.n;
+    }
+    if (first < h.n) chunk_body<1, STATS ? 16 : 32, BF16, NT, NTS, OPT, STATS>(a, h, slot, first, h.n, 0);
+}
+
+template <bool BF16, bool NT, bool NTS, bool OPT, bool STATS, int CH, typename A>
+hipError_t launch_segments(const SlotArgs &s, bool fast, A &a, int bpc, const Launch &cfg, hipStream_t st)
+{
+    const int per = cfg.block / 64;                    // wavefronts per workgroup
+    for (long long first = 0; first < s.h.n; first += kChunkElements) {
+        const long long n = std::min(s.h.n - first, kChunkElements);
+        fill_chunk(s, fast, first, n, a);
+        a.h.narrow = chunk_narrow(s.h.n, a.h.n_slots, STATS);
+        const long long g = a.h.narrow ? (n + cfg.block - 1) / cfg.block : round_workgroups(n, BF16, cfg.block);
+        a.h.waves_per_block = per;
+        a.h.xcd_blocks = cfg.xcd_map ? static_cast<int>(g / 8) : 0;
+        if constexpr (STATS) {
+            a.first = s.h.e0 + first;
+            a.stats = s.stats;
+            a.stats.records += first / 256;
+        }
+        const hipError_t e = launch_capped(chunk_kernel<BF16, NT, NTS, OPT, STATS, CH, A>, a, bpc, cfg,
+                                           dim3(static_cast<unsigned>(g)), st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+template <bool BF16, bool NT, bool NTS, bool OPT, bool STATS, int CH>
+hipError_t launch_sized(const SlotArgs &s, bool fast, int bpc, const Launch &cfg, hipStream_t st)
+{
+    // (w, v and recv are streamed in runs too long for the shorter block to matter)
+    if constexpr (!NTS)
+        if (chunk_fits(s, kChunkFewSlots, kChunkFewCopies)) {
+            ChunkArgs<kChunkFewSlots, kChunkFewCopies, STATS> a;
+            return launch_segments<BF16, NT, false, OPT, STATS, CH>(s, fast, a, bpc, cfg, st);
+        }
+    ChunkArgs<kMaxSlots, kMaxP, STATS> a;
+    return launch_segments<BF16, NT, NTS, OPT, STATS, CH>(s, fast, a, bpc, cfg, st);
+}
+
+template <bool BF16, bool OPT, bool STATS, int CH>
+hipError_t launch_hints(const SlotArgs &s, bool fast, bool nt, bool nts, int bpc, const Launch &cfg, hipStream_t st)
+{
+    if (nts) return launch_sized<BF16, true, true, OPT, STATS, CH>(s, fast, bpc, cfg, st);
+    return nt ? launch_sized<BF16, true, false, OPT, STATS, CH>(s, fast, bpc, cfg, st)
+              : launch_sized<BF16, false, false, OPT, STATS, CH>(s, fast, bpc, cfg, st);
+}
+
+template <bool BF16, bool STATS>
+hipError_t launch_kind(const SlotArgs &s, bool fast, bool nt, bool nts, bool eight, int bpc, const Launch &cfg,
+                       hipStream_t st)
+{
+    if (s.h.w) return eight ? launch_hints<BF16, true, STATS, 8>(s, fast, nt, nts, bpc, cfg, st)
+                            : launch_hints<BF16, true, STATS, 16>(s, fast, nt, nts, bpc, cfg, st);
+    return eight ? launch_hints<BF16, false, STATS, 8>(s, fast, nt, nts, bpc, cfg, st)
+                 : launch_hints<BF16, false, STATS, 16>(s, fast, nt, nts, bpc, cfg, st);
+}
+
+}  // namespace
+}  // namespace eager

@@ -1,0 +1,12 @@
+// chunk_kernel with bf16 gradients and by-products.
+#include "eager_chunk.h"
+
+namespace eager {
+
+hipError_t launch_chunk_bf16_stats(const SlotArgs &s, bool fast, bool nt, bool nts, bool eight, int bpc, const Launch &cfg,
+                        hipStream_t st)
+{
+    return launch_kind<true, true>(s, fast, nt, nts, eight, bpc, cfg, st);
+}
+
+}  // namespace eager

@@ -46,6 +46,30 @@ __device__ __forceinline__ u32x4 ld_u4(const void *p)
     return *reinterpret_cast<const u32x4 *>(p);
 }
 
+// An access as a uniform base and a 32-bit byte offset of the lane.
+typedef const f32x4 __attribute__((address_space(1))) GF4;
+typedef f32x4 __attribute__((address_space(1))) GF4w;
+
+// (the empty statement keeps the widening of the offset next to the access, where it folds into
+// the instruction's scalar-base form; hoisted out of it, every stream would hold a 64-bit address
+// per lane)
+template <bool NT>
+__device__ __forceinline__ f32x4 ld_at(const char *base, unsigned off)
+{
+    asm("" : "+v"(off));
+    GF4 *p = (GF4 *)(base + off);
+    if (NT) return __builtin_nontemporal_load(p);
+    return *p;
+}
+template <bool NT>
+__device__ __forceinline__ void st_at(char *base, unsigned off, f32x4 x)
+{
+    asm("" : "+v"(off));
+    GF4w *p = (GF4w *)(base + off);
+    if (NT) __builtin_nontemporal_store(x, p);
+    else *p = x;
+}
+
 // The update rule U of Algorithm 2, lines 7-8, for one element or one vector of 4:
 //   g = u + wd*w  (only if wd != 0);  v' = mu*v + g;  step = nesterov ? g + mu*v' : v';
 //   w' = w - lr*step

@@ -151,6 +151,47 @@ struct SlotArgs {
     StatsArgs stats;
 };
 
+// A round as the kernel for small runs takes it: what a wavefront would have to work out from the
+// slots is worked out by the host.  The bases are those of the first element of the launch, so that
+// an access is the base and a 32-bit offset; what is done with slot k is bit k of a word each.  The
+// list holds the sum, then the copies, and nothing to fill it up; the destination of slot k stands at
+// dst[k - dst_first], dst_first being a multiple of 8 at or below the first copy.
+//   pair   the slot completes the one before it (a HOLD)     hold   it waits for the next one
+//   copy   it is stored to its destination                   bf     the stream is bf16
+struct ChunkBits {
+    unsigned pair, hold, copy, bf;
+};
+constexpr int kChunkWord = 32;            // slots that a ChunkBits covers
+constexpr long long kChunkElements = 1ll << 29;   // of one launch, for the 32-bit offsets
+struct ChunkHead {
+    float *w, *v, *recv;
+    unsigned n;                           // elements
+    int n_sum, n_slots, dst_first;
+    int narrow;                           // 1: a lane owns one element and not four
+    int waves_per_block, xcd_blocks;
+    float inv_P, neg_lr, mu, wd;
+    int nesterov;
+    ChunkBits first;                      // of slots 0..31
+};
+// The arguments travel to the device with every launch and the host pays by the byte, so lists of up to
+// 32 slots and 16 copies (8 processes always, 16 in most rounds) have a block of their own size.
+template <int SLOTS, int COPIES, bool STATS>
+struct ChunkArgs;
+template <int SLOTS, int COPIES>
+struct ChunkArgs<SLOTS, COPIES, false> {
+    static constexpr int kSlots = SLOTS, kCopies = COPIES;
+    ChunkHead h;
+    unsigned long long slot[SLOTS];
+    float *dst[COPIES + 8];
+    ChunkBits bits[SLOTS / kChunkWord];
+};
+template <int SLOTS, int COPIES>
+struct ChunkArgs<SLOTS, COPIES, true> : ChunkArgs<SLOTS, COPIES, false> {
+    long long first;                      // arena index of the launch's first element
+    StatsArgs stats;                      // records: those of the launch
+};
+constexpr int kChunkFewSlots = 32, kChunkFewCopies = 16;
+
 // The carry as a kernel of its own: R_p <- G_p for every late process, one (source,
 // destination) pair after the other.
 struct CarryArgs {
@@ -210,6 +251,10 @@ struct Launch {
 
 hipError_t launch_round(const RoundArgs &a, bool bf16, bool fast, const Launch &cfg,
                         hipStream_t stream);
+// the round in chunks of 16 slots (eight: of 8); nt: streams nontemporal, nts: w, v and recv too
+typedef hipError_t ChunkLauncher(const SlotArgs &s, bool fast, bool nt, bool nts, bool eight, int bpc,
+                                 const Launch &cfg, hipStream_t st);
+ChunkLauncher launch_chunk_f32, launch_chunk_f32_stats, launch_chunk_bf16, launch_chunk_bf16_stats;
 hipError_t launch_carry(const CarryArgs &a, bool bf16, const Launch &cfg, hipStream_t stream);
 hipError_t launch_stats_finish(const StatsArgs &a, hipStream_t stream);
 long long slot_records(long long n, bool bf16, int block);   // tiles of a round, one record each

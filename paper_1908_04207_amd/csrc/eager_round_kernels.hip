@@ -11,11 +11,12 @@
 //     contiguous KiB per fp32 stream and instruction;
 //   * burst_kernel, for runs that stream from HBM: many wavefronts per CU, two loads in flight
 //     in each; occupancy is capped so that the bytes in flight match what the memory side holds;
-//   * chunk_kernel, for runs that latency bounds: up to 16 loads in flight per lane, no cap;
-//   * which streams exist and what is done with each is decided on the host and applied in
-//     the kernel with scalar bit masks: no branch around a load, empty send buffers cost
-//     no bytes, the send buffer of an on-time process is "cleared" by a flag on the host,
-//     not by writing zeros;
+//   * chunk_kernel (eager_chunk.h), for runs that latency bounds: up to 16 or 32 loads in flight per
+//     lane, no cap;
+//   * which streams exist and what is done with each is decided on the host: empty send buffers
+//     cost no bytes, the send buffer of an on-time process is "cleared" by a flag on the host,
+//     not by writing zeros; burst_kernel applies the actions with scalar bit masks, chunk_kernel
+//     with a branch per slot;
 //   * the accumulator stays in fp32 registers; in fixed-order mode contributions are added
 //     in ascending rank order from +0.0f with contraction off, so the result is defined
 //     bit for bit; fast mode keeps two partial sums and lets the compiler fuse;
@@ -49,29 +50,6 @@ struct Lanes {
     bool odd;              // the lane-vector is the upper half of that piece
     bool in;               // the lane-vector belongs to the run
 };
-
-typedef const f32x4 __attribute__((address_space(1))) GF4;
-typedef f32x4 __attribute__((address_space(1))) GF4w;
-
-// (the empty statement keeps the widening of the offset next to the access, where it folds into
-// the instruction's scalar-base form; hoisted out of it, every stream would hold a 64-bit address
-// per lane)
-template <bool NT>
-__device__ __forceinline__ f32x4 ld_at(const char *base, unsigned off)
-{
-    asm("" : "+v"(off));
-    GF4 *p = (GF4 *)(base + off);
-    if (NT) return __builtin_nontemporal_load(p);
-    return *p;
-}
-template <bool NT>
-__device__ __forceinline__ void st_at(char *base, unsigned off, f32x4 x)
-{
-    asm("" : "+v"(off));
-    GF4w *p = (GF4w *)(base + off);
-    if (NT) __builtin_nontemporal_store(x, p);
-    else *p = x;
-}
 
 // 16 bytes of a slot's stream (raw: a bf16 stream is widened by slot_value).  For a SKIP every
 // lane loads one and the same piece: hardly any traffic.
@@ -359,87 +337,6 @@ __global__ __launch_bounds__(256) void burst_kernel(const SlotArgs)
     if (STATS) stats_commit(a.stats.records, a.stats.lane_records, ls, tile);
 }
 
-// The round for small runs: what counts there is the time from launch to the last store, so a
-// wavefront (one tile) requests w and v and CH slots at once and waits for all of it together; with
-// more slots than CH it does so again.  One body of code whatever the number of slots (the list
-// ends in SKIPs, which are nearly free): a body for every remainder has to be fetched before it
-// runs.  NT: as for the streams of the burst kernel, or plain.  Kernel time, before and now:
-// 8193 elements, 8 processes solo 6.7 -> 4.0 us; 1 M elements, 4 processes solo 11.6 -> 10.7
-// us a round; 1 M, 8 processes, 4 late 15.8 -> 13.9.
-template <bool BF16, bool FAST, bool NT, bool NTS, bool OPT, bool STATS, int CH>
-__global__ __launch_bounds__(256) void chunk_kernel(const SlotArgs)
-{
-    KSlotArgs &a = kernarg<SlotArgs>();
-    unsigned long long slot[CH];
-#pragma unroll
-    for (int j = 0; j < CH; ++j) slot[j] = a.slot[j];
-    const SlotHead h = read_head(a);
-#pragma unroll
-    for (int j = 0; j < CH; ++j) asm volatile("" : "+s"(slot[j]));   // requested along with the head
-    const long long nvec = slot_nvec<BF16>(h.n);
-    const long long tile = wave_index(h);
-    if (tile * 64 >= nvec) {
-        // the grid's last wavefront: the ragged tail
-        const long long rem = h.n - nvec * 4, t = threadIdx.x & 63u;
-        if (tile * 64 < nvec + 64 && t < rem) slot_tail_element<BF16, STATS>(a, h, h.e0 + nvec * 4 + t);
-        return;
-    }
-    const Lanes L = place_lanes(h, tile, nvec);
-    Sums S;
-    S.s = S.s2 = S.term = (f32x4)(0.0f);
-    const int n_sum = h.n_sum, n = n_sum + h.n_copy;
-    f32x4 x[CH];
-    auto request = [&]() {
-#pragma unroll
-        for (int j = 0; j < CH; ++j) x[j] = ld_slot_or_skip<BF16, NT>(slot[j], L);
-    };
-    // slots [k0, k0 + CH): the sum, then the copies among them
-    auto consume = [&](int k0) {
-        float *dst[CH];
-        const bool copies = k0 + CH > n_sum && n > n_sum;
-        if (copies) {
-#pragma unroll
-            for (int j = 0; j < CH; ++j) dst[j] = a.dst[k0 + j];
-        }
-#pragma unroll
-        for (int g = 0; g < CH; g += 4)
-            if (k0 + g < n_sum) {           // (what follows the sum costs no arithmetic)
-#pragma unroll
-                for (int j = g; j < g + 4; ++j) add_slot<BF16, FAST>(slot[j], x[j], L, S, j & 1);
-            }
-        // Stores stay behind the adds: moved ahead of them, the in-order memory counter would make
-        // every add wait for the acknowledgement of a store instead of for its load.
-        asm volatile("" : "+v"(S.s), "+v"(S.s2), "+v"(S.term) : : "memory");
-        if (copies) {
-#pragma unroll
-            for (int j = 0; j < CH; ++j)
-                if (slot[j] & kSlotCopy) {
-                    char *to = reinterpret_cast<char *>(dst[j]) + L.e0 * 4;
-                    if (L.in) st_at<NT>(to, L.off, slot_value<BF16>(x[j], BF16, L.odd));
-                }
-        }
-    };
-    f32x4 vo = (f32x4)(0.0f), wo = vo;
-    if (OPT) {
-        vo = ld_at<NTS>(reinterpret_cast<const char *>(h.v) + L.e0 * 4, L.off);
-        wo = ld_at<NTS>(reinterpret_cast<const char *>(h.w) + L.e0 * 4, L.off);
-    }
-    request();
-    LaneStats ls;
-    const int n_valid = STATS ? place_stats(a, L, ls) : 0;
-    consume(0);
-    // (the first chunk stands apart: at the head of a loop the compiler waits for everything in
-    // flight, w and v among it, before the first slot is requested)
-    for (int k0 = CH; k0 < n; k0 += CH) {
-#pragma unroll
-        for (int j = 0; j < CH; ++j) slot[j] = a.slot[k0 + j];
-        request();
-        consume(k0);
-    }
-    finish_tile<FAST, NTS, OPT, STATS>(h, L, S, vo, wo, n_valid, ls);
-    if (STATS) stats_commit(a.stats.records, a.stats.lane_records, ls, tile);
-}
-
 // R_p <- G_p for the late processes, as a plain copy: pair after pair (blockIdx.y is the
 // pair, and workgroups are dealt out x first), so that at any time the device streams one
 // source and one destination.  A copy of few streams runs near the read-only rate on MI355X,
@@ -563,16 +460,9 @@ hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStre
     // that pair has always been refused, by the caller with a message of its own)
     if (stats && cfg.chunk == 8) return hipErrorInvalidValue;
     const bool few = cfg.chunk == 8 || (cfg.chunk == 0 && s.h.n_sum + s.h.n_copy <= 8);
-    switch ((stats ? 4 : 0) | (few ? 2 : 0) | (plain ? 1 : 0)) {
-    case 0: return launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, false, 16>, s, bpc, cfg, grid, st);
-    case 1: return launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, false, 16>, s, bpc, cfg, grid, st);
-    case 2: return launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, false, 8>, s, bpc, cfg, grid, st);
-    case 3: return launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, false, 8>, s, bpc, cfg, grid, st);
-    case 4: return launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, true, 16>, s, bpc, cfg, grid, st);
-    case 5: return launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, true, 16>, s, bpc, cfg, grid, st);
-    case 6: return launch_capped(chunk_kernel<BF16, FAST, true, NTS, OPT, true, 8>, s, bpc, cfg, grid, st);
-    default: return launch_capped(chunk_kernel<BF16, FAST, false, NTS, OPT, true, 8>, s, bpc, cfg, grid, st);
-    }
+    ChunkLauncher *const launch = BF16 ? (stats ? launch_chunk_bf16_stats : launch_chunk_bf16)
+                                       : (stats ? launch_chunk_f32_stats : launch_chunk_f32);
+    return launch(s, FAST, !plain, NTS, few, bpc, cfg, st);
 }
 
 template <bool BF16, bool FAST>

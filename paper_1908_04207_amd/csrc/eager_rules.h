@@ -90,6 +90,61 @@ inline bool small_round(const SlotArgs &s, long long bytes_per_element)
 // 9.9 and 10.6 at 40 MiB, 14.1 and 13.6 at 64.
 constexpr long long kPlainRoundBytes = 56ll << 20;
 
+// The same round for the kernel of small runs: elements [first, first + n) of the run.  `A` has room for
+// the list (slots that fill it up are left out).
+inline bool chunk_fits(const SlotArgs &s, int slots, int copies)
+{
+    return s.h.n_sum + s.h.n_copy <= slots && s.h.n_copy <= copies;
+}
+template <typename A>
+void fill_chunk(const SlotArgs &s, bool fast, long long first, long long n, A &a)
+{
+    const long long e = s.h.e0 + first;
+    auto at = [e](float *p) { return p ? p + e : nullptr; };
+    a.h.w = at(s.h.w);
+    a.h.v = at(s.h.v);
+    a.h.recv = at(s.h.recv);
+    a.h.n = static_cast<unsigned>(n);
+    a.h.inv_P = s.h.inv_P;
+    a.h.neg_lr = s.h.neg_lr;
+    a.h.mu = s.h.mu;
+    a.h.wd = s.h.wd;
+    a.h.nesterov = s.h.nesterov;
+    for (ChunkBits &b : a.bits) b = ChunkBits{0u, 0u, 0u, 0u};
+    int k = 0;
+    auto push = [&](unsigned long long slot, unsigned ChunkBits::*what) {
+        const bool bf = (slot & kSlotBf16) != 0;
+        const unsigned bit = 1u << (k % kChunkWord);
+        ChunkBits &b = a.bits[k / kChunkWord];
+        if (what) b.*what |= bit;
+        if (bf) b.bf |= bit;
+        a.slot[k++] = (slot & ~static_cast<unsigned long long>(kSlotTag)) +
+                      static_cast<unsigned long long>(e) * (bf ? 2 : 4);
+    };
+    for (int j = 0; j < s.h.n_sum; ++j) {
+        const unsigned kind = static_cast<unsigned>(s.slot[j]) & kKindMask;
+        if (kind == kSkip) continue;
+        // (in any order a pair is two terms)
+        push(s.slot[j], fast || kind == kAdd ? nullptr : kind == kPair ? &ChunkBits::pair : &ChunkBits::hold);
+    }
+    a.h.n_sum = k;
+    a.h.dst_first = k & ~7;
+    for (int j = 0; j < s.h.n_copy; ++j) {
+        a.dst[k - a.h.dst_first] = s.dst[s.h.n_sum + j] + e;
+        push(s.slot[s.h.n_sum + j], &ChunkBits::copy);
+    }
+    a.h.n_slots = k;
+    a.h.first = a.bits[0];
+}
+
+// Whether a lane of such a launch owns one element and not four: four times the wavefronts with a
+// quarter of the arithmetic each, and up to 32 slots in one trip to memory instead of 16.  From 9 slots
+// on, up to 128 k elements (one launch after another, 4 elements to a lane and 1): 8 processes, 4 late, 4096
+// elements 2.96 and 2.86 us, 65536 3.47 and 3.52, 131072 4.54 and 4.35, 262144 5.69 and 6.00; 16 processes, 8
+// late, 4096 4.24 and 3.28, 131072 5.93 and 5.16, 262144 8.4 and 9.1; but with 3 slots 2.60 and 2.66, 2.87 and
+// 3.12.  (By-products are kept per 256 elements, so a launch with them is never narrow.)
+inline bool chunk_narrow(long long n, int slots, bool stats) { return !stats && slots > 8 && n <= 1ll << 17; }
+
 // Resident wavefronts per CU of the burst kernel, -1: no cap.
 //   * 14 for fp32 streams (26 KiB in flight), 12 where copies follow.  A wavefront with few slots spends
 //     more of its life on its arguments, on w and v and on stores, so short lists with copies take

@@ -68,6 +68,40 @@ def test_many_slots_and_copies(eb, P, n):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("P,n", [(9, 1), (9, 63), (17, 65), (17, 4099), (40, 257), (9, 131_072), (12, 131_073)])
+def test_one_element_to_a_lane(eb, dtype, P, n):
+    """Very small runs of many slots, up to 131072 elements one to a lane; pairs across the 8, 16 and 32 slots
+    that are in flight together (process 0 is on time with nothing pending, then everybody is late but it)."""
+    pair = Pair(eb, P, [0], [n], (n + 7) // 8 * 8, dtype, 0, seed=P + n)
+    everyone = (1 << P) - 1
+    _rounds(eb, pair, [1, everyone, 0b101, everyone & ~1, everyone], 0, n)
+
+
+def test_a_run_longer_than_one_launch_of_chunks(eb):
+    """Beyond 2^29 elements chunk_kernel goes over a run in several launches: element by element against torch,
+    and the statistics of both."""
+    n = (1 << 29) + 1027
+    if torch.cuda.mem_get_info()[0] < 30 * n:
+        pytest.skip("needs 16 GB of free device memory")
+    dev = torch.device("cuda:0")
+    ctx = eb.Context(2, [0], [n])
+    ctx.eager_set_launch("chunk", 16)
+    G = [torch.empty(n, device=dev).normal_() for _ in range(2)]
+    unread = torch.zeros(4, device=dev)
+    recv = torch.full((n + 1,), -1.0, device=dev)
+    stats = torch.zeros(32, dtype=torch.uint8, device=dev)
+    need = ctx.eager_stats_workspace_bytes()
+    ctx.eager_stats_attach(stats, torch.empty(need, dtype=torch.uint8, device=dev), need)
+    ctx.eager_partial_allreduce(eb.make_plan(eb.MAJORITY, 2, 0, 0b11), G, [unread, unread], recv=recv)
+    torch.cuda.synchronize()
+    want = G[0].add_(G[1]).mul_(0.5)
+    assert torch.equal(recv[:n], want) and recv[n].item() == -1.0
+    total = sum(float((x.double() ** 2).sum()) for x in want.split(1 << 27))
+    assert abs(float(stats.view(torch.float64)[0]) - total) <= 1e-10 * total
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_statistics_of_a_streamed_round(eb, dtype):
     """By-products in the burst form, buckets that begin and end anywhere in a tile."""
     num = [1, 255, 7, 1_000_003, 64, 4096, 2_000_001, 129, 300_000]

@@ -18,6 +18,17 @@ def test_rules_on_the_host(tmp_path):
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.stdout[-500:], r.stderr[-2000:])
 
 
+def test_chunk_lists_on_the_host(tmp_path):
+    """The list that chunk_kernel takes, worked through as the kernel does, against the slots it was made of."""
+    exe = tmp_path / "chunk_list_host"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined",
+                           "-fno-sanitize-recover=all", "-static-libasan", "-ffp-contract=off", "-Wall", "-Wextra",
+                           "-Werror", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include",
+                           os.path.join(ROOT, "tests", "c", "chunk_list_host.cpp"), "-o", str(exe)])
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", (r.stdout[-500:], r.stderr[-2000:])
+
+
 @pytest.mark.gpu
 def test_a_run_just_below_the_largest():
     """2^33 - 1 elements: every tile but the last is full and three elements are left over.  One process
