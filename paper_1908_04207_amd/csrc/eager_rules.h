@@ -121,11 +121,13 @@ void fill_chunk(const SlotArgs &s, bool fast, long long first, long long n, A &a
         a.slot[k++] = (slot & ~static_cast<unsigned long long>(kSlotTag)) +
                       static_cast<unsigned long long>(e) * (bf ? 2 : 4);
     };
-    for (int j = 0; j < s.h.n_sum; ++j) {
+    int terms = s.h.n_sum;
+    while (terms > 0 && (s.slot[terms - 1] & kKindMask) == kSkip) --terms;
+    for (int j = 0; j < terms; ++j) {
         const unsigned kind = static_cast<unsigned>(s.slot[j]) & kKindMask;
-        if (kind == kSkip) continue;
-        // (in any order a pair is two terms)
-        push(s.slot[j], fast || kind == kAdd ? nullptr : kind == kPair ? &ChunkBits::pair : &ChunkBits::hold);
+        // in any order every two terms are a pair: half as many roundings at the size of the whole sum
+        const unsigned does = !fast ? kind : k & 1 ? kPair : j + 1 < terms ? kHold : kAdd;
+        push(s.slot[j], does == kAdd ? nullptr : does == kPair ? &ChunkBits::pair : &ChunkBits::hold);
     }
     a.h.n_sum = k;
     a.h.dst_first = k & ~7;
