@@ -64,9 +64,8 @@ __device__ __forceinline__ void workgroup_sum(double &su, double &sw, double &nf
 {
     constexpr unsigned kWaves = THREADS / 64;
     __shared__ double part[3][kWaves];
-    su = wave_sum(su);
-    sw = wave_sum(sw);
-    nf = wave_sum(nf);
+    wave_sums(su, sw);
+    if (__builtin_amdgcn_ballot_w64(nf != 0.0) != 0ull) nf = wave_sum(nf);
     const unsigned wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
     if (lane == 0u) {
         part[0][wave] = su;
@@ -433,12 +432,10 @@ __global__ __launch_bounds__(64) void norms_kernel(const SgdArgs a, const StatsA
                     u = ld_f4<NT>(reinterpret_cast<const float *>(up + (k + 1) * 64));
                     w = ld_f4<NT>(reinterpret_cast<const float *>(wp + (k + 1) * 64));
                 }
-                stats_add(ls, x.x, y.x, true);
-                stats_add(ls, x.y, y.y, true);
-                stats_add(ls, x.z, y.z, true);
-                stats_add(ls, x.w, y.w, true);
+                stats_vector<true>(ls, x, y, 4);
             }
-            const double su = wave_sum(ls.ssu), sw = wave_sum(ls.ssw);
+            double su = ls.ssu, sw = ls.ssw;
+            wave_sums(su, sw);
             unsigned nf = 0u;
             if (__builtin_amdgcn_ballot_w64(ls.nf != 0u) != 0ull) nf = wave_sum(ls.nf);
             if (lane == 0u) {
@@ -455,11 +452,7 @@ __global__ __launch_bounds__(64) void norms_kernel(const SgdArgs a, const StatsA
             const f32x4 u = ld_f4<NT>(a.u + e), w = ld_f4<NT>(a.w + e);
             long long end;
             ls.bucket = tile_bucket(st.table, st.b_lo, st.b_hi, a.e0 + (tile0 + k) * 256, e, end);
-            const int n_valid = inside(e, end);
-            if (n_valid > 0) stats_add(ls, u.x, w.x, true);
-            if (n_valid > 1) stats_add(ls, u.y, w.y, true);
-            if (n_valid > 2) stats_add(ls, u.z, w.z, true);
-            if (n_valid > 3) stats_add(ls, u.w, w.w, true);
+            stats_vector<true>(ls, u, w, inside(e, end));
         }
         stats_commit(st.records, st.lane_records, ls, tile0 + k, (tile0 + k) % K == 0 ? 1 : 0);
     }

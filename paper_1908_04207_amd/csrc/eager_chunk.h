@@ -136,26 +136,35 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
     const bool odd = (at & 1u) != 0u;
 
     V s = (V)(0.0f), held = s, x[CH];
+    // (W = 1: loads of 2 and of 4 bytes into registers of their own, or the one on the other branch
+    // waits for the one before it)
+    V half[W == 1 && BF16 ? CH : 1];
     auto request = [&](int k0, const ChunkBits &b, auto address) {
         first_of<CH>(h.n_slots - k0, [&](auto J) {
             constexpr int j = decltype(J)::value;
             const char *base = reinterpret_cast<const char *>(address(J));
             if constexpr (!BF16) x[j] = ld_vec<W, NT>(base, off);
             else if constexpr (W == 4) x[j] = ld_vec<W, NT>(base, b.bf >> j & 1u ? off_bf : off);
-            else if (b.bf >> j & 1u) x[j] = ld_half<NT>(base, off_bf);
+            else if (b.bf >> j & 1u) half[j] = ld_half<NT>(base, off_bf);
             else x[j] = ld_vec<W, NT>(base, off);
         });
     };
     // the sum, then the copies, of the slots in flight
     auto consume = [&](int k0, ChunkBits b) {
 #pragma unroll
-        for (int j = 0; j < CH; ++j) asm volatile("; %1" : "+v"(x[j]) : "n"(W) : "memory");
+        for (int j = 0; j < CH; ++j) {
+            if constexpr (W == 1 && BF16) asm volatile("; %2" : "+v"(x[j]), "+v"(half[j]) : "n"(W) : "memory");
+            else asm volatile("; %1" : "+v"(x[j]) : "n"(W) : "memory");
+        }
         const int sums = opaque<W>(h.n_sum) - k0;
         if (BF16) {
             b.bf = opaque<W>(b.bf);
 #pragma unroll
             for (int j = 0; j < CH; ++j)
-                if (b.bf >> j & 1u) x[j] = widen(x[j], odd);
+                if (b.bf >> j & 1u) {
+                    if constexpr (W == 1) x[j] = widen(half[j], odd);
+                    else x[j] = widen(x[j], odd);
+                }
         }
         {
             b.pair = opaque<W>(b.pair);
@@ -245,11 +254,7 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
     const V avg = s * h.inv_P;
     if constexpr (STATS) {
         if constexpr (W == 4) {
-            const f32x4 w_old = OPT ? wo : (f32x4)(0.0f);
-            if (n_valid > 0) stats_add(ls, avg.x, w_old.x, OPT);
-            if (n_valid > 1) stats_add(ls, avg.y, w_old.y, OPT);
-            if (n_valid > 2) stats_add(ls, avg.z, w_old.z, OPT);
-            if (n_valid > 3) stats_add(ls, avg.w, w_old.w, OPT);
+            stats_vector<OPT>(ls, avg, wo, n_valid);
         } else if (n_valid) {
             stats_add(ls, avg, OPT ? wo : 0.0f, OPT);
         }

@@ -126,13 +126,7 @@ __device__ __forceinline__ void finish_tile(const SlotHead &h, const Lanes &L, c
     if (FAST) sum = sum + S.s2;
     const f32x4 avg = sum * h.inv_P;
     if (STATS) {
-        // n_valid: how many of the lane's 4 elements lie inside their bucket (the rest
-        // is padding between buckets)
-        const f32x4 w_old = OPT ? wo : (f32x4)(0.0f);
-        if (n_valid > 0) stats_add(ls, avg.x, w_old.x, OPT);
-        if (n_valid > 1) stats_add(ls, avg.y, w_old.y, OPT);
-        if (n_valid > 2) stats_add(ls, avg.z, w_old.z, OPT);
-        if (n_valid > 3) stats_add(ls, avg.w, w_old.w, OPT);
+        stats_vector<OPT>(ls, avg, wo, n_valid);
     }
     f32x4 vn, wn;
     if (OPT) {

@@ -190,3 +190,33 @@ def test_layerwise_norms_by_groups_of_tiles(eb, num):
                     scale = float(want[fine].abs().max())
                     assert float((got.double() - want)[fine].abs().max()) <= 1e-6 * scale
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [4, 255, 256, 1027, 16389])
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_statistics_where_elements_are_not_finite(eb, n, bad):
+    """A tile whose sums are taken without a look at its elements beside tiles that hold one that is not
+    finite, in the update and in the parameters: counted and left out."""
+    dev = torch.device("cuda:0")
+    arena = (n + 3) // 4 * 4
+    ctx = eb.Context(2, [0], [n])
+    stats = torch.zeros(32, dtype=torch.uint8, device=dev)
+    need = ctx.eager_stats_workspace_bytes()
+    workspace = torch.empty(need, dtype=torch.uint8, device=dev)     # (the caller's as long as it is attached)
+    ctx.eager_stats_attach(stats, workspace, need)
+    G = [wg.fill(torch.empty(arena), 4, 0, p, 1.0).to(dev) for p in range(2)]
+    w = wg.fill(torch.empty(arena), 4, 0, wg.PARAM_RANK, 1.0).to(dev)
+    G[1][n // 2] = bad
+    G[0][n - 1] = bad
+    w[n // 3] = bad
+    u, w0 = ((G[0].double() + G[1].double()) / 2)[:n], w[:n].double()
+    R = [torch.zeros(arena, device=dev) for _ in range(2)]
+    ctx.eager_partial_allreduce(eb.make_plan(eb.MAJORITY, 2, 0, 0b11), G, R, opt=(w, torch.zeros_like(w), 0.1, 0.9))
+    torch.cuda.synchronize()
+    got = stats.view(torch.float64)[:2].tolist()
+    assert int(stats.view(torch.int64)[2]) == int((~torch.isfinite(u)).sum())
+    for value, x in zip(got, (u, w0)):
+        want = float((x[torch.isfinite(x)] ** 2).sum())
+        # the sum of two fp32 values rounds once (2^-24 relative, its square 2^-23)
+        assert abs(value - want) <= 1.3e-7 * want
+    ctx.close()
