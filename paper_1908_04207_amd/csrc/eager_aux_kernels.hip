@@ -21,6 +21,23 @@ namespace {
 // all, unless it is flagged - then every tile of the group has a record of its own.
 constexpr int kNormsTiles = 8;
 
+// All of a record has been asked for before any of it is looked at: left alone the compiler moves the
+// loads of the sums behind the branch on the bucket, a trip to memory after the other.
+__device__ __forceinline__ void whole(StatsRecord &r)
+{
+    asm volatile("" : "+v"(r.ssu), "+v"(r.ssw), "+v"(r.bucket), "+v"(r.nf));
+}
+
+// The numbers among the arguments of the finishing kernels, asked for at once with the first pointers.
+// (A pointer that went through a statement would be a flat one.)
+__device__ __forceinline__ StatsArgs at_once(const StatsArgs &from)
+{
+    StatsArgs a = from;
+    asm volatile("" : "+s"(a.e0), "+s"(a.n_records), "+s"(a.b_lo), "+s"(a.n_buckets), "+s"(a.tail_count),
+                 "+s"(a.slices), "+s"(a.want_rate), "+s"(a.trust), "+s"(a.eps), "+s"(a.wd));
+    return a;
+}
+
 template <int THREADS, bool GROUPED>
 __device__ __forceinline__ void add_records(const StatsRecord *records, long long lo, long long hi,
                                             int b, double &su, double &sw, double &nf)
@@ -88,7 +105,8 @@ __device__ __forceinline__ void workgroup_sum(double &su, double &sw, double &nf
 // records of bucket b: [w0, w1)
 __device__ __forceinline__ void bucket_records(const StatsArgs &a, int b, long long &w0, long long &w1)
 {
-    const long long start = a.table[2 * b], end = a.table[2 * b + 1];
+    KLong *tbl = (KLong *)reinterpret_cast<unsigned long long>(a.table);
+    const long long start = tbl[2 * b], end = tbl[2 * b + 1];
     w0 = (start - a.e0) / 256;
     w1 = (end - a.e0 + 255) / 256;
     if (w1 > a.n_records) w1 = a.n_records;
@@ -97,8 +115,9 @@ __device__ __forceinline__ void bucket_records(const StatsArgs &a, int b, long l
 // First stage for buckets with many records (a flat model is ONE bucket: millions of records):
 // workgroup (bucket, slice) adds one slice of the bucket's plain records and leaves a partial.
 template <bool GROUPED, int THREADS>
-__global__ __launch_bounds__(THREADS) void stats_slice_kernel(const StatsArgs a)
+__global__ __launch_bounds__(THREADS) void stats_slice_kernel(const StatsArgs args)
 {
+    const StatsArgs a = at_once(args);
     const int b = a.b_lo + static_cast<int>(blockIdx.x);
     const int s = static_cast<int>(blockIdx.y);
     long long w0, w1;
@@ -123,8 +142,9 @@ __global__ __launch_bounds__(THREADS) void stats_slice_kernel(const StatsArgs a)
 // first stage), a mixed wavefront's lane records of this bucket - and the records of the ragged
 // tail; one thread writes the bucket's totals.
 template <bool GROUPED, int THREADS>
-__global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs a)
+__global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs args)
 {
+    const StatsArgs a = at_once(args);
     const int b = a.b_lo + static_cast<int>(blockIdx.x);
     long long w0, w1;
     bucket_records(a, b, w0, w1);
@@ -150,11 +170,19 @@ __global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs a
     if (which == 0 || which == 1) {
         const long long t = which == 0 ? w0 : w1 - 1;
         // (in a group that is not flagged only the first record has been written)
-        if (w1 > w0 && (which == 0 || t != w0) &&
-            (!GROUPED || a.records[t / kNormsTiles * kNormsTiles].flag)) {
-            const StatsRecord r = a.records[t];
-            if (r.bucket == -1) {
-                const StatsRecord lr = a.lane_records[static_cast<long long>(r.nf) * 64 + lane];
+        if (w1 > w0 && (which == 0 || t != w0)) {
+            // A mixed wavefront's lane records stand in the block of its first lane's bucket: this one, or
+            // nearly always the one before where the tile begins in front of this bucket.  They are asked
+            // for beside the record that says so, not after it (with all of either: layer-wise steps of 0.6 to
+            // 45 M elements, two finishing launches each, 0.5 to 1 us less).
+            const bool before = a.e0 + t * 256 < ((KLong *)reinterpret_cast<unsigned long long>(a.table))[2 * b];
+            const int guess = before && b > 0 ? b - 1 : b;
+            const long long flag = GROUPED ? a.records[t / kNormsTiles * kNormsTiles].flag : 1;
+            StatsRecord r = a.records[t], lr = a.lane_records[static_cast<long long>(guess) * 64 + lane];
+            whole(r);
+            whole(lr);
+            if (flag && r.bucket == -1) {
+                if (static_cast<int>(r.nf) != guess) lr = a.lane_records[static_cast<long long>(r.nf) * 64 + lane];
                 if (lr.bucket == b) {
                     su += lr.ssu;
                     sw += lr.ssw;
@@ -163,7 +191,8 @@ __global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs a
             }
         }
     } else if (which == 2 && lane < a.tail_count) {
-        const StatsRecord tr = a.lane_records[static_cast<long long>(a.n_buckets) * 64 + lane];
+        StatsRecord tr = a.lane_records[static_cast<long long>(a.n_buckets) * 64 + lane];
+        whole(tr);
         if (tr.bucket == b) {
             su += tr.ssu;
             sw += tr.ssw;
