@@ -376,9 +376,16 @@ class Context:
         self._check(lib.eager_flush(self._h, b0, b1, r, _ptr(recv), o, _stream(stream)),
                     "eager_flush")
 
-    def eager_partial_allreduce(self, plan: Plan, *a, **kw):
-        """Dispatch on plan.mode to the entry point of that name."""
-        getattr(self, _ALLREDUCE[plan.mode])(plan, *a, **kw)
+    def eager_partial_allreduce(self, plan: Plan, grads, resid, recv=None, opt=None, b0: int = 0,
+                                b1: Optional[int] = None, stream=None):
+        """The entry point of plan.mode, which is also its number in _marshal."""
+        mode = plan.mode
+        st = _marshal.round(mode, self._addr, self.P, self.n_buckets, plan, 0, b0, b1, grads, resid, recv, opt,
+                            stream) if mode in _ALLREDUCE else NotImplemented
+        if st is NotImplemented:
+            getattr(self, _ALLREDUCE[mode])(plan, grads, resid, recv, opt, b0, b1, stream)
+        elif st != OK:
+            self._check(st, _ALLREDUCE[mode])
 
     def eager_sgd_step(self, update, opt, b0: int = 0, b1: Optional[int] = None, stream=None):
         st = _marshal.step(self._addr, self.n_buckets, b0, b1, update, opt, None, None, stream)
