@@ -91,7 +91,8 @@ def test_a_run_longer_than_one_launch_of_chunks(eb):
     recv = torch.full((n + 1,), -1.0, device=dev)
     stats = torch.zeros(32, dtype=torch.uint8, device=dev)
     need = ctx.eager_stats_workspace_bytes()
-    ctx.eager_stats_attach(stats, torch.empty(need, dtype=torch.uint8, device=dev), need)
+    workspace = torch.empty(need, dtype=torch.uint8, device=dev)     # (the caller's as long as it is attached)
+    ctx.eager_stats_attach(stats, workspace, need)
     ctx.eager_partial_allreduce(eb.make_plan(eb.MAJORITY, 2, 0, 0b11), G, [unread, unread], recv=recv)
     torch.cuda.synchronize()
     want = G[0].add_(G[1]).mul_(0.5)

@@ -369,3 +369,20 @@ def test_missing_library_is_an_error_not_a_fallback(monkeypatch, tmp_path):
     for mod in (eb, async_sgd, hyperplane):
         src = inspect.getsource(mod)
         assert "import oracle" not in src and "from oracle" not in src, mod.__name__
+
+
+def test_statistics_buffers_in_the_tests_outlive_the_call():
+    """Context.eager_stats_attach takes addresses; the buffers stay the caller's as long as they are
+    attached.  A tensor made inside the call would be freed when it returns, so no caller here does that."""
+    import ast
+    files = [os.path.join(ROOT, "bench.py"), os.path.join(ROOT, "perf", "cases.py")]
+    files += [os.path.join(ROOT, "tests", f) for f in os.listdir(os.path.join(ROOT, "tests")) if f.endswith(".py")]
+    calls = 0
+    for path in files:
+        for node in ast.walk(ast.parse(open(path).read())):
+            if isinstance(node, ast.Call) and getattr(node.func, "attr", "") == "eager_stats_attach":
+                calls += 1
+                for buffer in node.args[:2]:
+                    held = (ast.Name, ast.Attribute, ast.Constant, ast.Subscript)
+                    assert isinstance(buffer, held), f"{path}:{node.lineno}: {ast.unparse(buffer)}"
+    assert calls > 10
