@@ -289,10 +289,12 @@ class Context:
     def _allreduce(self, kind, fn, what, plan, grads, resid, recv, opt, b0, b1, stream, absent=0):
         st = _marshal.round(kind, self._addr, self.P, self.n_buckets, plan, absent, b0, b1, grads,
                             resid, recv, opt, stream)
-        if st is not NotImplemented:
-            if st != OK:
-                self._check(st, what)
-            return
+        if st is NotImplemented:
+            self._allreduce_ctypes(fn, what, plan, grads, resid, recv, opt, b0, b1, stream)
+        elif st != OK:
+            self._check(st, what)
+
+    def _allreduce_ctypes(self, fn, what, plan, grads, resid, recv, opt, b0, b1, stream):
         b1 = self.n_buckets if b1 is None else b1
         P = len(grads)
         g = grads if isinstance(grads, ctypes.Array) else self.pointers(grads)
@@ -380,12 +382,13 @@ class Context:
                                 b1: Optional[int] = None, stream=None):
         """The entry point of plan.mode, which is also its number in _marshal."""
         mode = plan.mode
+        what = _ALLREDUCE[mode]
         st = _marshal.round(mode, self._addr, self.P, self.n_buckets, plan, 0, b0, b1, grads, resid, recv, opt,
-                            stream) if mode in _ALLREDUCE else NotImplemented
-        if st is NotImplemented:
-            getattr(self, _ALLREDUCE[mode])(plan, grads, resid, recv, opt, b0, b1, stream)
+                            stream)
+        if st is NotImplemented:            # (asked once: a form that it does not know costs as much as one it does)
+            self._allreduce_ctypes(getattr(lib, what), what, plan, grads, resid, recv, opt, b0, b1, stream)
         elif st != OK:
-            self._check(st, _ALLREDUCE[mode])
+            self._check(st, what)
 
     def eager_sgd_step(self, update, opt, b0: int = 0, b1: Optional[int] = None, stream=None):
         st = _marshal.step(self._addr, self.n_buckets, b0, b1, update, opt, None, None, stream)

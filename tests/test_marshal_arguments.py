@@ -287,3 +287,26 @@ def test_current_stream(stubs):
         eb._marshal.streams(None, None)
     assert [args[-1] for _, args in stubs.calls] == [A * 50] * 3 and asked == [3] * 3
     ctx.close()
+
+
+@pytest.mark.parametrize("name", ["", "_solo", "_majority", "_quorum", "_lagging"])
+def test_a_form_that_is_not_known_is_marshalled_once(stubs, monkeypatch, name):
+    """A rate that is not exactly a float goes through ctypes; the module is asked about the call once."""
+    asked = []
+
+    class Asked:
+        def __getattr__(self, fn):
+            return lambda *a: asked.append(fn) or getattr(module, fn)(*a)
+
+    module = eb._marshal
+    monkeypatch.setattr(eb, "_marshal", Asked())
+    ctx = eb.Context(P, [64 * k for k in range(BUCKETS)], [64] * BUCKETS)
+    bufs = [A * (k + 1) for k in range(2 * P)]
+    absent = [0] if name == "_lagging" else []
+    for mode in (eb.SOLO, eb.MAJORITY, eb.QUORUM) if not name else (eb.SOLO,):
+        asked.clear(), stubs.calls.clear()
+        getattr(ctx, "eager_partial_allreduce" + name)(eb.make_plan(mode, P, 0, 1), *absent, bufs[:P], bufs[P:],
+                                                       opt=(A * 20, A * 21, np.float64(0.1), 0.9), stream=0)
+        assert asked == ["round"] and len(stubs.calls) == 1
+        assert stubs.calls[0][0] == (["eager_partial_allreduce" + name] if name else NAMES[2:5])[0 if name else mode]
+    ctx.close()
