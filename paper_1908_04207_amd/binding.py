@@ -380,9 +380,16 @@ class Context:
 
     def eager_partial_allreduce(self, plan: Plan, grads, resid, recv=None, opt=None, b0: int = 0,
                                 b1: Optional[int] = None, stream=None):
-        """The entry point of plan.mode, which is also its number in _marshal."""
+        """The method of plan.mode.  Where that is this class's own - not one of a subclass, nor set on the object or
+        the class - it is not called but done here: plan.mode is the call's number in _marshal."""
         mode = plan.mode
         what = _ALLREDUCE[mode]
+        method = getattr(self, what)
+        if getattr(method, "__func__", None) is not _OWN_ALLREDUCE[mode]:
+            # (what was left out stays left out: an override need not take what it has no use for)
+            given = dict(recv=recv, opt=opt, b1=b1, stream=stream, b0=b0 or None)
+            method(plan, grads, resid, **{k: x for k, x in given.items() if x is not None})
+            return
         st = _marshal.round(mode, self._addr, self.P, self.n_buckets, plan, 0, b0, b1, grads, resid, recv, opt,
                             stream)
         if st is NotImplemented:            # (asked once: a form that it does not know costs as much as one it does)
@@ -471,6 +478,9 @@ class Context:
 
     def eager_set_launch(self, key: str, value: int) -> None:
         self._check(lib.eager_set_launch(self._h, key.encode(), value), "eager_set_launch")
+
+
+_OWN_ALLREDUCE = {mode: getattr(Context, name) for mode, name in _ALLREDUCE.items()}
 
 
 def eager_calib_copy(dst, src, nbytes: int, stream=None) -> None:

@@ -310,3 +310,43 @@ def test_a_form_that_is_not_known_is_marshalled_once(stubs, monkeypatch, name):
         assert asked == ["round"] and len(stubs.calls) == 1
         assert stubs.calls[0][0] == (["eager_partial_allreduce" + name] if name else NAMES[2:5])[0 if name else mode]
     ctx.close()
+
+
+def test_a_replaced_method_of_a_mode_is_called(stubs, monkeypatch):
+    """eager_partial_allreduce goes through the method of the plan's mode where a subclass, the object or the class
+    has another than the binding's, with the arguments that the caller gave."""
+    seen = []
+
+    class Logged(eb.Context):
+        def eager_partial_allreduce_solo(self, plan, grads, resid, **kw):
+            seen.append(("solo", plan.step, grads, resid, kw))
+            super().eager_partial_allreduce_solo(plan, grads, resid, **kw)
+
+        def eager_partial_allreduce_quorum(self, plan, grads, resid, opt=None):     # takes fewer
+            seen.append(("quorum", plan.step, grads, resid, {"opt": opt}))
+
+    def make(cls):
+        return cls(P, [64 * k for k in range(BUCKETS)], [64] * BUCKETS)
+
+    G, R = [A * (k + 1) for k in range(P)], [A * (k + 9) for k in range(P)]
+    opt = (A * 20, A * 21, 0.1, 0.9)
+    ctx = make(Logged)
+    ctx.eager_partial_allreduce(eb.make_plan(eb.SOLO, P, 1, 1), G, R, A * 30, opt, 0, 2, 0)
+    assert seen == [("solo", 1, G, R, dict(recv=A * 30, opt=opt, b1=2, stream=0))]
+    assert [c[0] for c in stubs.calls] == [NAMES[2]] and stubs.calls[0][1][2:4] == [0, 2]
+    ctx.eager_partial_allreduce(eb.make_plan(eb.QUORUM, P, 2, 1), G, R, opt=opt)
+    assert seen[1:] == [("quorum", 2, G, R, {"opt": opt})] and len(stubs.calls) == 1
+    ctx.eager_partial_allreduce(eb.make_plan(eb.MAJORITY, P, 3, 1), G, R, opt=opt, b0=1, stream=0)   # not replaced
+    assert len(seen) == 2 and stubs.calls[1][0] == NAMES[3] and stubs.calls[1][1][2:4] == [1, BUCKETS]
+    ctx.eager_partial_allreduce_majority = lambda plan, *a, **kw: seen.append((plan.step, a, kw))
+    ctx.eager_partial_allreduce(eb.make_plan(eb.MAJORITY, P, 4, 1), G, R, b0=1, b1=1)
+    assert seen[2] == (4, (G, R), dict(b0=1, b1=1)) and len(stubs.calls) == 2
+    ctx.close()
+    plain = make(eb.Context)
+    with monkeypatch.context() as m:
+        m.setattr(eb.Context, "eager_partial_allreduce_solo", lambda self, plan, *a, **kw: seen.append((plan.step, a, kw)))
+        plain.eager_partial_allreduce(eb.make_plan(eb.SOLO, P, 5, 1), G, R)
+    assert seen[3] == (5, (G, R), {}) and len(stubs.calls) == 2
+    plain.eager_partial_allreduce(eb.make_plan(eb.SOLO, P, 6, 1), G, R, opt=opt, stream=0)
+    assert len(seen) == 4 and len(stubs.calls) == 3
+    plain.close()
