@@ -221,3 +221,48 @@ def test_statistics_where_elements_are_not_finite(eb, n, bad):
         # the sum of two fp32 values rounds once (2^-24 relative, its square 2^-23)
         assert abs(value - want) <= 1.3e-7 * want
     ctx.close()
+
+
+@pytest.mark.parametrize("size", [1, 30, 63, 255, 258, 513])
+def test_statistics_beside_padding(eb, size):
+    """Buckets whose last lane is part padding, which holds infinities and NaN: what lies in it is neither added
+    nor counted, by a round (plain and into the receive buffer) and by the layer-wise rule."""
+    nb, dev = 7, torch.device("cuda:0")
+    stride = (size + 3) // 4 * 4 + (0 if size % 4 else 4)
+    off, n = [b * stride for b in range(nb)], nb * stride
+    inside = torch.zeros(n, dtype=torch.bool, device=dev)
+    for o in off:
+        inside[o:o + size] = True
+    ctx = eb.Context(2, off, [size] * nb)
+    stats = torch.zeros(nb * 32, dtype=torch.uint8, device=dev)
+    need = ctx.eager_stats_workspace_bytes()
+    workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+    ctx.eager_stats_attach(stats, workspace, need)
+    bad = torch.tensor([float("nan"), float("inf"), float("-inf")], device=dev).repeat(n)[:n]
+
+    def values(rank):
+        x = wg.fill(torch.empty(n), 4, 0, rank, 1.0).to(dev)
+        return torch.where(inside, x, bad)
+
+    def check(u, w, what):
+        torch.cuda.synchronize()
+        got = stats.view(torch.float64).view(nb, 4)[:, :2]
+        assert int(stats.view(torch.int64).view(nb, 4)[:, 2].abs().max()) == 0, what
+        for k, x in enumerate((u, w)):
+            for b, o in enumerate(off):
+                want = float((x[o:o + size].double() ** 2).sum()) if x is not None else 0.0
+                # sums in 64 bits of the exact squares of what is stored
+                assert abs(float(got[b, k]) - want) <= 1e-12 * want, (what, b, k)
+
+    G = [values(0), values(1)]
+    R = [torch.zeros(n, device=dev) for _ in range(2)]
+    w, v, recv = values(wg.PARAM_RANK), torch.zeros(n, device=dev), torch.zeros(n, device=dev)
+    w0 = w.clone()
+    ctx.eager_partial_allreduce(eb.make_plan(eb.MAJORITY, 2, 0, 0b11), G, R, recv=recv, opt=(w, v, 0.1, 0.9))
+    check(recv, w0, "fused")
+    ctx.eager_partial_allreduce(eb.make_plan(eb.MAJORITY, 2, 1, 0b11), G, R, recv=recv)
+    check(recv, None, "into the receive buffer")
+    u, w0 = values(5), w.clone()
+    ctx.eager_sgd_step_lars(u, (w, v, 0.1, 0.9), 0.02, 1e-9)
+    check(u, w0, "layer-wise")
+    ctx.close()
