@@ -169,13 +169,18 @@ __global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs a
     }
     if (which == 0 || which == 1) {
         const long long t = which == 0 ? w0 : w1 - 1;
+        // Tile t has lane records where this bucket or the next begins inside it, or where the run ends there.
+        // (Asked for without a look at that, those of buckets that have their tiles to themselves were 2 KiB a bucket
+        // that nobody needs: 16 M elements in buckets of 255, round with norms 164 and 148 us, layer-wise step 169 and 156.)
+        KLong *tbl = (KLong *)reinterpret_cast<unsigned long long>(a.table);
+        const long long tile = a.e0 + t * 256, beyond = tbl[2 * b + (b + 1 < a.b_hi ? 2 : 1)];
+        const bool before = tile < tbl[2 * b], behind = beyond < tile + 256;
         // (in a group that is not flagged only the first record has been written)
-        if (w1 > w0 && (which == 0 || t != w0)) {
+        if (w1 > w0 && (which == 0 || t != w0) && (before || behind)) {
             // A mixed wavefront's lane records stand in the block of its first lane's bucket: this one, or
             // nearly always the one before where the tile begins in front of this bucket.  They are asked
             // for beside the record that says so, not after it (with all of either: layer-wise steps of 0.6 to
             // 45 M elements, two finishing launches each, 0.5 to 1 us less).
-            const bool before = a.e0 + t * 256 < ((KLong *)reinterpret_cast<unsigned long long>(a.table))[2 * b];
             const int guess = before && b > 0 ? b - 1 : b;
             const long long flag = GROUPED ? a.records[t / kNormsTiles * kNormsTiles].flag : 1;
             StatsRecord r = a.records[t], lr = a.lane_records[static_cast<long long>(guess) * 64 + lane];
