@@ -1,6 +1,6 @@
 // gfx950 kernel of the round for small runs, whose time is the one from launch to the last store:
 // a launch, one trip to the arguments, one trip to the streams.  Included by the files that
-// instantiate it, one per gradient type with and without by-products (compiled side by side).
+// instantiate it, one per gradient type and order, with and without by-products (compiled side by side).
 #pragma once
 
 #include "eager_device.h"
@@ -123,7 +123,7 @@ __device__ __forceinline__ void first_of(int n, const F &f)
 // for a slot that is not there, and what is done with one is a branch on a bit: a load is one
 // instruction, an ADD one per element.  (All loads are waited for together, before the first branch
 // that depends on a slot's kind: the registers of a slot that was not read are never looked at.)
-template <int W, int CH, bool BF16, bool NT, bool NTS, bool OPT, bool STATS, int READ, typename K>
+template <int W, int CH, bool BF16, bool FAST, bool NT, bool NTS, bool OPT, bool STATS, int READ, typename K>
 __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsigned long long (&slot)[READ], unsigned at0,
                                            unsigned end, long long record)
 {
@@ -135,7 +135,8 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
     const unsigned off_bf = W == 4 ? (at >> 1) * 16u : at * 2u;
     const bool odd = (at & 1u) != 0u;
 
-    V s = (V)(0.0f), held = s, x[CH];
+    // (FAST: two sums that take the slots in turn, s and s2, as in the kernel of large runs; no pairs)
+    V s = (V)(0.0f), s2 = s, held = s, x[CH];
     // (W = 1: loads of 2 and of 4 bytes into registers of their own, or the one on the other branch
     // waits for the one before it)
     V half[W == 1 && BF16 ? CH : 1];
@@ -166,7 +167,7 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
                     else x[j] = widen(x[j], odd);
                 }
         }
-        {
+        if constexpr (!FAST) {
             b.pair = opaque<W>(b.pair);
 #pragma unroll
             for (int g = 0; g < CH; g += 8)
@@ -187,12 +188,14 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
         }
         first_of<CH>(sums, [&](auto J) {
             constexpr int j = decltype(J)::value;
-            s = s + x[j];
-            asm volatile("; %1" : "+v"(s) : "n"(W));
+            V &part = FAST && j & 1 ? s2 : s;
+            part = part + x[j];
+            asm volatile("; %1" : "+v"(part) : "n"(W));
         });
         // Stores stay behind the adds: moved ahead of them, the in-order memory counter would make
         // every add wait for the acknowledgement of a store instead of for its load.
         asm volatile("; %1" : "+v"(s) : "n"(W) : "memory");
+        if constexpr (FAST) asm volatile("; %1" : "+v"(s2) : "n"(W) : "memory");
         b.copy = opaque<W>(b.copy);
         if (b.copy && in) {
 #pragma unroll
@@ -251,6 +254,7 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
         consume(k0, b);
     }
 
+    if constexpr (FAST) s = s + s2;
     const V avg = s * h.inv_P;
     if constexpr (STATS) {
         if constexpr (W == 4) {
@@ -283,7 +287,7 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
 // elements, 7 with bf16 gradients) by a wavefront of its own, one element to a lane.  A very small run
 // is taken one element to a lane altogether: a quarter of the arithmetic in each of four times as many
 // wavefronts, for which there is room.
-template <bool BF16, bool NT, bool NTS, bool OPT, bool STATS, int CH, typename ARGS>
+template <bool BF16, bool FAST, bool NT, bool NTS, bool OPT, bool STATS, int CH, typename ARGS>
 __global__ __launch_bounds__(256) void chunk_kernel(const ARGS)
 {
     const ARGS __attribute__((address_space(4))) &a = kernarg<ARGS>();
@@ -324,21 +328,21 @@ __global__ __launch_bounds__(256) void chunk_kernel(const ARGS)
     if (!h.narrow) {
         const unsigned nvec = BF16 ? h.n / 8u * 2u : h.n / 4u, tiles = (nvec + 63u) / 64u;
         if (wave < tiles) {
-            chunk_body<4, CH, BF16, NT, NTS, OPT, STATS>(a, h, slot, first, nvec, wave);
+            chunk_body<4, CH, BF16, FAST, NT, NTS, OPT, STATS>(a, h, slot, first, nvec, wave);
             return;
         }
         first = wave == tiles ? nvec * 4u : h.n;
     }
-    if (first < h.n) chunk_body<1, STATS ? 16 : 32, BF16, NT, NTS, OPT, STATS>(a, h, slot, first, h.n, 0);
+    if (first < h.n) chunk_body<1, STATS ? 16 : 32, BF16, FAST, NT, NTS, OPT, STATS>(a, h, slot, first, h.n, 0);
 }
 
-template <bool BF16, bool NT, bool NTS, bool OPT, bool STATS, int CH, typename A>
-hipError_t launch_segments(const SlotArgs &s, bool fast, A &a, int bpc, const Launch &cfg, hipStream_t st)
+template <bool BF16, bool FAST, bool NT, bool NTS, bool OPT, bool STATS, int CH, typename A>
+hipError_t launch_segments(const SlotArgs &s, A &a, int bpc, const Launch &cfg, hipStream_t st)
 {
     const int per = cfg.block / 64;                    // wavefronts per workgroup
     for (long long first = 0; first < s.h.n; first += kChunkElements) {
         const long long n = std::min(s.h.n - first, kChunkElements);
-        fill_chunk(s, fast, first, n, a);
+        fill_chunk(s, first, n, a);
         a.h.narrow = chunk_narrow(s.h.n, a.h.n_slots, STATS);
         const long long g = a.h.narrow ? (n + cfg.block - 1) / cfg.block : round_workgroups(n, BF16, cfg.block);
         a.h.waves_per_block = per;
@@ -348,42 +352,42 @@ hipError_t launch_segments(const SlotArgs &s, bool fast, A &a, int bpc, const La
             a.stats = s.stats;
             a.stats.records += first / 256;
         }
-        const hipError_t e = launch_capped(chunk_kernel<BF16, NT, NTS, OPT, STATS, CH, A>, a, bpc, cfg,
+        const hipError_t e = launch_capped(chunk_kernel<BF16, FAST, NT, NTS, OPT, STATS, CH, A>, a, bpc, cfg,
                                            dim3(static_cast<unsigned>(g)), st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-template <bool BF16, bool NT, bool NTS, bool OPT, bool STATS, int CH>
-hipError_t launch_sized(const SlotArgs &s, bool fast, int bpc, const Launch &cfg, hipStream_t st)
+template <bool BF16, bool FAST, bool NT, bool NTS, bool OPT, bool STATS, int CH>
+hipError_t launch_sized(const SlotArgs &s, int bpc, const Launch &cfg, hipStream_t st)
 {
     // (w, v and recv are streamed in runs too long for the shorter block to matter)
     if constexpr (!NTS)
         if (chunk_fits(s, kChunkFewSlots, kChunkFewCopies)) {
             ChunkArgs<kChunkFewSlots, kChunkFewCopies, STATS> a;
-            return launch_segments<BF16, NT, false, OPT, STATS, CH>(s, fast, a, bpc, cfg, st);
+            return launch_segments<BF16, FAST, NT, false, OPT, STATS, CH>(s, a, bpc, cfg, st);
         }
     ChunkArgs<kMaxSlots, kMaxP, STATS> a;
-    return launch_segments<BF16, NT, NTS, OPT, STATS, CH>(s, fast, a, bpc, cfg, st);
+    return launch_segments<BF16, FAST, NT, NTS, OPT, STATS, CH>(s, a, bpc, cfg, st);
 }
 
-template <bool BF16, bool OPT, bool STATS, int CH>
-hipError_t launch_hints(const SlotArgs &s, bool fast, bool nt, bool nts, int bpc, const Launch &cfg, hipStream_t st)
+template <bool BF16, bool FAST, bool OPT, bool STATS, int CH>
+hipError_t launch_hints(const SlotArgs &s, bool nt, bool nts, int bpc, const Launch &cfg, hipStream_t st)
 {
-    if (nts) return launch_sized<BF16, true, true, OPT, STATS, CH>(s, fast, bpc, cfg, st);
-    return nt ? launch_sized<BF16, true, false, OPT, STATS, CH>(s, fast, bpc, cfg, st)
-              : launch_sized<BF16, false, false, OPT, STATS, CH>(s, fast, bpc, cfg, st);
+    if (nts) return launch_sized<BF16, FAST, true, true, OPT, STATS, CH>(s, bpc, cfg, st);
+    return nt ? launch_sized<BF16, FAST, true, false, OPT, STATS, CH>(s, bpc, cfg, st)
+              : launch_sized<BF16, FAST, false, false, OPT, STATS, CH>(s, bpc, cfg, st);
 }
 
-template <bool BF16, bool STATS>
-hipError_t launch_kind(const SlotArgs &s, bool fast, bool nt, bool nts, bool eight, int bpc, const Launch &cfg,
+template <bool BF16, bool FAST, bool STATS>
+hipError_t launch_kind(const SlotArgs &s, bool nt, bool nts, bool eight, int bpc, const Launch &cfg,
                        hipStream_t st)
 {
-    if (s.h.w) return eight ? launch_hints<BF16, true, STATS, 8>(s, fast, nt, nts, bpc, cfg, st)
-                            : launch_hints<BF16, true, STATS, 16>(s, fast, nt, nts, bpc, cfg, st);
-    return eight ? launch_hints<BF16, false, STATS, 8>(s, fast, nt, nts, bpc, cfg, st)
-                 : launch_hints<BF16, false, STATS, 16>(s, fast, nt, nts, bpc, cfg, st);
+    if (s.h.w) return eight ? launch_hints<BF16, FAST, true, STATS, 8>(s, nt, nts, bpc, cfg, st)
+                            : launch_hints<BF16, FAST, true, STATS, 16>(s, nt, nts, bpc, cfg, st);
+    return eight ? launch_hints<BF16, FAST, false, STATS, 8>(s, nt, nts, bpc, cfg, st)
+                 : launch_hints<BF16, FAST, false, STATS, 16>(s, nt, nts, bpc, cfg, st);
 }
 
 }  // namespace

@@ -3,10 +3,9 @@
 
 namespace eager {
 
-hipError_t launch_chunk_bf16_stats(const SlotArgs &s, bool fast, bool nt, bool nts, bool eight, int bpc, const Launch &cfg,
-                        hipStream_t st)
+hipError_t launch_chunk_bf16_stats(const SlotArgs &s, bool nt, bool nts, bool eight, int bpc, const Launch &cfg, hipStream_t st)
 {
-    return launch_kind<true, true>(s, fast, nt, nts, eight, bpc, cfg, st);
+    return launch_kind<true, false, true>(s, nt, nts, eight, bpc, cfg, st);
 }
 
 }  // namespace eager

@@ -3,10 +3,9 @@
 
 namespace eager {
 
-hipError_t launch_chunk_f32(const SlotArgs &s, bool fast, bool nt, bool nts, bool eight, int bpc, const Launch &cfg,
-                        hipStream_t st)
+hipError_t launch_chunk_f32(const SlotArgs &s, bool nt, bool nts, bool eight, int bpc, const Launch &cfg, hipStream_t st)
 {
-    return launch_kind<false, false>(s, fast, nt, nts, eight, bpc, cfg, st);
+    return launch_kind<false, false, false>(s, nt, nts, eight, bpc, cfg, st);
 }
 
 }  // namespace eager

@@ -157,6 +157,7 @@ struct SlotArgs {
 // list holds the sum, then the copies, and nothing to fill it up; the destination of slot k stands at
 // dst[k - dst_first], dst_first being a multiple of 8 at or below the first copy.
 //   pair   the slot completes the one before it (a HOLD)     hold   it waits for the next one
+//          (neither is looked at where the order is free)
 //   copy   it is stored to its destination                   bf     the stream is bf16
 struct ChunkBits {
     unsigned pair, hold, copy, bf;
@@ -252,9 +253,10 @@ struct Launch {
 hipError_t launch_round(const RoundArgs &a, bool bf16, bool fast, const Launch &cfg,
                         hipStream_t stream);
 // the round in chunks of 16 slots (eight: of 8); nt: streams nontemporal, nts: w, v and recv too
-typedef hipError_t ChunkLauncher(const SlotArgs &s, bool fast, bool nt, bool nts, bool eight, int bpc,
-                                 const Launch &cfg, hipStream_t st);
+typedef hipError_t ChunkLauncher(const SlotArgs &s, bool nt, bool nts, bool eight, int bpc, const Launch &cfg,
+                                 hipStream_t st);
 ChunkLauncher launch_chunk_f32, launch_chunk_f32_stats, launch_chunk_bf16, launch_chunk_bf16_stats;
+ChunkLauncher launch_chunk_f32_fast, launch_chunk_f32_fast_stats, launch_chunk_bf16_fast, launch_chunk_bf16_fast_stats;
 hipError_t launch_carry(const CarryArgs &a, bool bf16, const Launch &cfg, hipStream_t stream);
 hipError_t launch_stats_finish(const StatsArgs &a, hipStream_t stream);
 long long slot_records(long long n, bool bf16, int block);   // tiles of a round, one record each

@@ -454,9 +454,11 @@ hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStre
     // that pair has always been refused, by the caller with a message of its own)
     if (stats && cfg.chunk == 8) return hipErrorInvalidValue;
     const bool few = cfg.chunk == 8 || (cfg.chunk == 0 && s.h.n_sum + s.h.n_copy <= 8);
-    ChunkLauncher *const launch = BF16 ? (stats ? launch_chunk_bf16_stats : launch_chunk_bf16)
-                                       : (stats ? launch_chunk_f32_stats : launch_chunk_f32);
-    return launch(s, FAST, !plain, NTS, few, bpc, cfg, st);
+    ChunkLauncher *const fixed = BF16 ? (stats ? launch_chunk_bf16_stats : launch_chunk_bf16)
+                                      : (stats ? launch_chunk_f32_stats : launch_chunk_f32);
+    ChunkLauncher *const any = BF16 ? (stats ? launch_chunk_bf16_fast_stats : launch_chunk_bf16_fast)
+                                    : (stats ? launch_chunk_f32_fast_stats : launch_chunk_f32_fast);
+    return (FAST ? any : fixed)(s, !plain, NTS, few, bpc, cfg, st);
 }
 
 template <bool BF16, bool FAST>

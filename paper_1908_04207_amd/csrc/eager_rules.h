@@ -97,7 +97,7 @@ inline bool chunk_fits(const SlotArgs &s, int slots, int copies)
     return s.h.n_sum + s.h.n_copy <= slots && s.h.n_copy <= copies;
 }
 template <typename A>
-void fill_chunk(const SlotArgs &s, bool fast, long long first, long long n, A &a)
+void fill_chunk(const SlotArgs &s, long long first, long long n, A &a)
 {
     const long long e = s.h.e0 + first;
     auto at = [e](float *p) { return p ? p + e : nullptr; };
@@ -125,9 +125,7 @@ void fill_chunk(const SlotArgs &s, bool fast, long long first, long long n, A &a
     while (terms > 0 && (s.slot[terms - 1] & kKindMask) == kSkip) --terms;
     for (int j = 0; j < terms; ++j) {
         const unsigned kind = static_cast<unsigned>(s.slot[j]) & kKindMask;
-        // in any order every two terms are a pair: half as many roundings at the size of the whole sum
-        const unsigned does = !fast ? kind : k & 1 ? kPair : j + 1 < terms ? kHold : kAdd;
-        push(s.slot[j], does == kAdd ? nullptr : does == kPair ? &ChunkBits::pair : &ChunkBits::hold);
+        push(s.slot[j], kind == kAdd ? nullptr : kind == kPair ? &ChunkBits::pair : &ChunkBits::hold);
     }
     a.h.n_sum = k;
     a.h.dst_first = k & ~7;

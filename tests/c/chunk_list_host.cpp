@@ -15,27 +15,31 @@ static float at(unsigned long long address, bool bf)      // some number that be
     return static_cast<float>(static_cast<int>(address * 2654435761u >> 7 & 0xffffff) - 0x800000) * (bf ? 1e-3f : 1e-6f);
 }
 
-// in chunks of CH, pairs across them by the held value; the copies as (destination, source)
+// in chunks of CH, pairs across them by the held value, or in any order two sums in turn; the copies as
+// (destination, source)
 template <typename A>
-static float by_chunks(const A &a, int CH, std::vector<std::pair<float *, float>> &copies)
+static float by_chunks(const A &a, int CH, bool fast, std::vector<std::pair<float *, float>> &copies)
 {
-    float s = 0.0f, held = 0.0f;
+    float s = 0.0f, s2 = 0.0f, held = 0.0f;
     for (int k0 = 0; k0 < a.h.n_slots; k0 += CH) {
         std::vector<float> x(CH, 1e30f);
         auto bit = [&](unsigned ChunkBits::*m, int j) { return a.bits[(k0 + j) / kChunkWord].*m >> (k0 + j) % kChunkWord & 1u; };
         for (int j = 0; j < CH && k0 + j < a.h.n_slots; ++j) x[j] = at(a.slot[k0 + j], bit(&ChunkBits::bf, j));
         const int sums = a.h.n_sum - k0;
-        for (int j = 0; j < CH && k0 + j < A::kSlots; ++j)
+        for (int j = 0; !fast && j < CH && k0 + j < A::kSlots; ++j)
             if (bit(&ChunkBits::pair, j)) {
                 float &before = j ? x[j - 1] : held;
                 x[j] = before + x[j];
                 before = 0.0f;
             }
-        if (sums > CH && bit(&ChunkBits::hold, CH - 1)) {
+        if (!fast && sums > CH && bit(&ChunkBits::hold, CH - 1)) {
             held = x[CH - 1];
             x[CH - 1] = 0.0f;
         }
-        for (int j = 0; j < CH && j < sums; ++j) s = s + x[j];
+        for (int j = 0; j < CH && j < sums; ++j) {
+            float &part = fast && j & 1 ? s2 : s;
+            part = part + x[j];
+        }
         for (int j = 0; j < CH && k0 + j < A::kSlots; ++j)
             if (bit(&ChunkBits::copy, j)) {
                 const int d = k0 + j - a.h.dst_first;
@@ -43,20 +47,19 @@ static float by_chunks(const A &a, int CH, std::vector<std::pair<float *, float>
                 copies.push_back({a.dst[d], x[j]});
             }
     }
-    return s;
+    return s + s2;
 }
 
 template <int SLOTS, int COPIES>
-static bool same(const SlotArgs &s, bool fast, float sum, float by_twos, const std::vector<std::pair<float *, float>> &copies)
+static bool same(const SlotArgs &s, bool fast, float sum, float in_turn, const std::vector<std::pair<float *, float>> &copies)
 {
     ChunkArgs<SLOTS, COPIES, false> a;
     std::memset(static_cast<void *>(&a), 0xff, sizeof a);
-    fill_chunk(s, fast, 512, 99, a);
+    fill_chunk(s, 512, 99, a);
     for (int CH : {8, 16, 32}) {
         std::vector<std::pair<float *, float>> got;
-        const float t = by_chunks(a, CH, got);
-        // (in any order: the terms two by two, which rounds at the size of the whole sum half as often)
-        if (std::memcmp(&t, fast ? &by_twos : &sum, 4) || got != copies) return false;
+        const float t = by_chunks(a, CH, fast, got);
+        if (std::memcmp(&t, fast ? &in_turn : &sum, 4) || got != copies) return false;
     }
     const bool w = a.h.w == (s.h.w ? s.h.w + s.h.e0 + 512 : nullptr);
     return w && a.h.n == 99 && !std::memcmp(&a.h.first, &a.bits[0], sizeof a.h.first);
@@ -88,14 +91,12 @@ int main()
             else if (r || on) term = value(p, r);
             if (r || on) sum = sum + term;
         }
-        float by_twos = 0.0f;
-        for (int k = 0; k < n; k += 2) {
-            auto x = [&](int j) {
-                const bool bf = (s.slot[j] & kSlotBf16) != 0;
-                return at((s.slot[j] & ~static_cast<unsigned long long>(kSlotTag)) + (s.h.e0 + 512) * (bf ? 2 : 4), bf);
-            };
-            by_twos = by_twos + (k + 1 < n ? x(k) + x(k + 1) : x(k));
+        float part[2] = {0.0f, 0.0f};         // in any order: two sums that take the slots in turn
+        for (int k = 0; k < n; ++k) {
+            const bool bf = (s.slot[k] & kSlotBf16) != 0;
+            part[k & 1] += at((s.slot[k] & ~static_cast<unsigned long long>(kSlotTag)) + (s.h.e0 + 512) * (bf ? 2 : 4), bf);
         }
+        const float in_turn = part[0] + part[1];
         while (n % kBurst) s.slot[n++] = 0x10000000ull | kSkip;
         s.h.n_sum = n;
         std::vector<std::pair<float *, float>> copies;
@@ -108,8 +109,8 @@ int main()
             }
         const bool few = chunk_fits(s, kChunkFewSlots, kChunkFewCopies);
         if (!chunk_fits(s, kMaxSlots, kMaxP) && s.h.n_sum + s.h.n_copy > kMaxSlots + 1) return 1;
-        if ((few && !same<kChunkFewSlots, kChunkFewCopies>(s, fast, sum, by_twos, copies)) ||
-            !same<kMaxSlots, kMaxP>(s, fast, sum, by_twos, copies)) {
+        if ((few && !same<kChunkFewSlots, kChunkFewCopies>(s, fast, sum, in_turn, copies)) ||
+            !same<kMaxSlots, kMaxP>(s, fast, sum, in_turn, copies)) {
             std::printf("trial %d: P %d\n", trial, P);
             return 1;
         }

@@ -103,6 +103,30 @@ def test_a_run_longer_than_one_launch_of_chunks(eb):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("P,n", [(3, 40_003), (8, 300_007), (32, 50_001), (64, 140_001)])
+def test_any_order_is_as_close_as_two_sums(eb, dtype, P, n):
+    """A small round in fast order, every second process with a pending buffer: as far from the sum in 64 bits as
+    two sums in 32 bits that take the streams in turn, send buffer before gradient (a rounding more or less where the
+    halves meet: 1 %; adding the streams in pairs is 16 % off at 32 processes with bf16 gradients, 23 % at 64)."""
+    dev, tdt = torch.device("cuda:0"), torch.bfloat16 if dtype == "bf16" else torch.float32
+    G = [wg.fill(torch.empty(n, dtype=tdt), 9, 0, p, 1e-3).to(dev) for p in range(P)]
+    R = [wg.fill(torch.empty(n), 9, 1, p, 1e-3).to(dev) for p in range(P)]
+    ctx = eb.Context(P, [0], [n], eb.BF16 if dtype == "bf16" else eb.F32, eb.ORDER_FAST)
+    pending = [p for p in range(P) if p % 2 == 0]
+    ctx.eager_set_valid(0, sum(1 << p for p in pending))
+    recv = torch.empty(n, device=dev)
+    ctx.eager_partial_allreduce(eb.make_plan(eb.MAJORITY, P, 0, (1 << P) - 1), G, R, recv=recv)
+    streams = [x for p in range(P) for x in ([R[p]] if p in pending else []) + [G[p]]]
+    part = [torch.zeros(n, device=dev) for _ in range(2)]
+    for k, x in enumerate(streams):
+        part[k % 2] += x.float()
+    exact = sum(x.double() for x in streams) / P
+    error = lambda x: float((x.double() - exact).square().mean().sqrt())          # noqa: E731
+    assert error(recv) <= 1.01 * error((part[0] + part[1]) * torch.tensor(1.0 / P, device=dev))
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_statistics_of_a_streamed_round(eb, dtype):
     """By-products in the burst form, buckets that begin and end anywhere in a tile."""
     num = [1, 255, 7, 1_000_003, 64, 4096, 2_000_001, 129, 300_000]
