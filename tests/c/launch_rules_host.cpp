@@ -123,9 +123,19 @@ static int occupancy()
     return 0;
 }
 
+// One element to a lane: short runs of long lists without by-products, and only where the number of loads in
+// flight is the library's to choose.
+static int narrow()
+{
+    CHECK(chunk_narrow(1, 9, false, 0) && chunk_narrow(1 << 17, 128, false, 0));
+    CHECK(!chunk_narrow((1 << 17) + 1, 128, false, 0) && !chunk_narrow(64, 8, false, 0) && !chunk_narrow(64, 9, true, 0));
+    for (int chunk : {8, 16}) CHECK(!chunk_narrow(1, 9, false, chunk) && !chunk_narrow(1 << 17, 128, false, chunk));
+    return 0;
+}
+
 int main()
 {
-    if (grids() || finishing() || norms() || bytes() || occupancy()) return 1;
+    if (narrow() || grids() || finishing() || norms() || bytes() || occupancy()) return 1;
     std::printf("ok\n");
     return 0;
 }
