@@ -375,7 +375,8 @@ hipError_t launch_sized(const SlotArgs &s, int bpc, const Launch &cfg, hipStream
 template <bool BF16, bool FAST, bool OPT, bool STATS, int CH>
 hipError_t launch_hints(const SlotArgs &s, bool nt, bool nts, int bpc, const Launch &cfg, hipStream_t st)
 {
-    if (nts) return launch_sized<BF16, FAST, true, true, OPT, STATS, CH>(s, bpc, cfg, st);
+    if (nts) return nt ? launch_sized<BF16, FAST, true, true, OPT, STATS, CH>(s, bpc, cfg, st)
+                       : launch_sized<BF16, FAST, false, true, OPT, STATS, CH>(s, bpc, cfg, st);
     return nt ? launch_sized<BF16, FAST, true, false, OPT, STATS, CH>(s, bpc, cfg, st)
               : launch_sized<BF16, FAST, false, false, OPT, STATS, CH>(s, bpc, cfg, st);
 }

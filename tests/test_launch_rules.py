@@ -29,6 +29,19 @@ def test_chunk_lists_on_the_host(tmp_path):
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.stdout[-500:], r.stderr[-2000:])
 
 
+def test_hints_of_streams_and_of_the_state_are_independent():
+    """"nt_state" concerns w, v and the receive buffer: chunk_kernel exists with every combination of their hint
+    (fourth parameter) and the streams' (third), for every type, order, kind and length of list."""
+    import itertools
+    import re
+    from paper_1908_04207_amd import build
+    names = subprocess.check_output(["nm", "-C", build.LIB], text=True)
+    kernels = {tuple(m.split(", ")) for m in re.findall(r"chunk_kernel<((?:\w+, ){7})", names)}
+    kernels = {k[:6] + (k[6].strip(" ,"),) for k in kernels}
+    flags = ("false", "true")
+    assert kernels == set(itertools.product(flags, flags, flags, flags, flags, flags, ("8", "16")))
+
+
 @pytest.mark.gpu
 def test_a_run_just_below_the_largest():
     """2^33 - 1 elements: every tile but the last is full and three elements are left over.  One process
