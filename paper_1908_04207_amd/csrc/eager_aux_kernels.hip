@@ -640,8 +640,7 @@ hipError_t launch_stash(const StashArgs &a, bool bf16, hipStream_t stream)
 }
 
 namespace {
-template <typename K>
-hipError_t launch_views(K kernel, const ViewsArgs &a, const Launch &cfg, int auto_waves,
+hipError_t launch_views(void (*kernel)(ViewsArgs), const ViewsArgs &a, const Launch &cfg, int auto_waves,
                         hipStream_t stream)
 {
     if (a.n <= 0 || a.n_views <= 0) return hipSuccess;

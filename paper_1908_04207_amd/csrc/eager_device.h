@@ -327,6 +327,19 @@ __device__ __forceinline__ void stats_commit(StatsRecord *records, StatsRecord *
     if ((threadIdx.x & 63u) == 0u) records[wave_index] = rec;
 }
 
+// A kernel with arguments of the types that it declares: what is handed over is an array of addresses, from which
+// the runtime copies as many bytes as the kernel takes.  (The runtime's own call: the configuration stack and the
+// look at the last error behind a <<<>>> launch are 0.15 of 2.35 us, and a small round is bound by what it costs
+// the host.)
+template <typename... A>
+hipError_t launch(void (*kernel)(A...), dim3 grid, dim3 block, unsigned lds, hipStream_t st, const A &...a)
+{
+    void *args[] = {const_cast<A *>(&a)...};
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, args, lds, st);
+    if (e != hipSuccess) (void)hipGetLastError();        // reported here, and nowhere again
+    return e;
+}
+
 // LDS is not used by the kernels; a dynamic allocation only caps how many workgroups a CU
 // holds at once.  A stream that mixes reads and writes is fastest on MI355X with about 26 KiB
 // of loads in flight per CU; beyond it HBM throughput falls again.  (LDS is handed out in units,
@@ -334,8 +347,8 @@ __device__ __forceinline__ void stats_commit(StatsRecord *records, StatsRecord *
 // Parameters and momentum above this size are streamed past the caches (see finish_tile).
 constexpr long long kStateCacheBytes = 256ll << 20;
 
-template <typename K, typename A>
-hipError_t launch_capped(K kernel, const A &a, int bpc, const Launch &cfg, dim3 grid,
+template <typename A>
+hipError_t launch_capped(void (*kernel)(A), const A &a, int bpc, const Launch &cfg, dim3 grid,
                          hipStream_t st)
 {
     unsigned lds = 0;
@@ -355,12 +368,7 @@ hipError_t launch_capped(K kernel, const A &a, int bpc, const Launch &cfg, dim3 
             raised.insert(fn);
         }
     }
-    // (the runtime's own call: its configuration stack and the look at the last error behind a <<<>>>
-    // launch are 0.15 of 2.35 us, and a small round is bound by what it costs the host)
-    void *args[] = {const_cast<A *>(&a)};
-    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, dim3(cfg.block), args, lds, st);
-    if (e != hipSuccess) (void)hipGetLastError();        // reported here, and nowhere again
-    return e;
+    return launch(kernel, grid, dim3(cfg.block), lds, st, a);
 }
 
 inline unsigned grid_for(long long nvec, long long per_block, int max_blocks)

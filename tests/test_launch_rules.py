@@ -29,6 +29,18 @@ def test_chunk_lists_on_the_host(tmp_path):
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.stdout[-500:], r.stderr[-2000:])
 
 
+@pytest.mark.parametrize("wrong", [0, 1, 2, 3])
+def test_launches_take_a_kernel_with_arguments_of_its_own_types(wrong):
+    from paper_1908_04207_amd import build
+    r = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *build.FLAGS, "--offload-host-only",
+                        "-fsyntax-only", f"-DWRONG={wrong}", "-x", "hip",
+                        os.path.join(ROOT, "tests", "c", "launch_types.hip")], capture_output=True, text=True)
+    if wrong:
+        assert r.returncode != 0 and "no matching function for call to 'launch" in r.stderr, r.stderr[-2000:]
+    else:
+        assert r.returncode == 0, r.stderr[-2000:]
+
+
 def test_hints_of_streams_and_of_the_state_are_independent():
     """"nt_state" concerns w, v and the receive buffer: chunk_kernel exists with every combination of their hint
     (fourth parameter) and the streams' (third), for every type, order, kind and length of list."""
