@@ -595,11 +595,10 @@ hipError_t launch_finish(const StatsArgs &a, int n, hipStream_t stream)
 {
     const dim3 threads(THREADS);
     if (a.slices > 1) {
-        hipLaunchKernelGGL((stats_slice_kernel<GROUPED, THREADS>), dim3(n, a.slices), threads, 0, stream, a);
-        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+        const hipError_t e = launch(stats_slice_kernel<GROUPED, THREADS>, dim3(n, a.slices), threads, 0, stream, a);
+        if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((stats_finish_kernel<GROUPED, THREADS>), dim3(n), threads, 0, stream, a);
-    return hipGetLastError();
+    return launch(stats_finish_kernel<GROUPED, THREADS>, dim3(n), threads, 0, stream, a);
 }
 }  // namespace
 
@@ -629,14 +628,11 @@ hipError_t launch_stash(const StashArgs &a, bool bf16, hipStream_t stream)
     const bool stride = g > kMaxGridThreads / 64;
     if (stride) g = kMaxGridThreads / 64;
     const dim3 grid(static_cast<unsigned>(g)), block(64);
-    if (bf16) {
-        if (stride) hipLaunchKernelGGL((stash_kernel<true, true>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((stash_kernel<true, false>), grid, block, 0, stream, a);
-    } else {
-        if (stride) hipLaunchKernelGGL((stash_kernel<false, true>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((stash_kernel<false, false>), grid, block, 0, stream, a);
-    }
-    return hipGetLastError();
+    if (bf16)
+        return stride ? launch(stash_kernel<true, true>, grid, block, 0, stream, a)
+                      : launch(stash_kernel<true, false>, grid, block, 0, stream, a);
+    return stride ? launch(stash_kernel<false, true>, grid, block, 0, stream, a)
+                  : launch(stash_kernel<false, false>, grid, block, 0, stream, a);
 }
 
 namespace {
@@ -677,16 +673,15 @@ hipError_t launch_sgd(const SgdArgs &a, bool fast, const Launch &cfg, hipStream_
     const bool stride = static_cast<long long>(grid.x) * 64 < nvec;
     const bool nt = a.n * 8 > kStateCacheBytes;
     switch ((fast ? 4 : 0) | (nt ? 2 : 0) | (stride ? 1 : 0)) {
-    case 0: hipLaunchKernelGGL((sgd_kernel<false, false, false>), grid, block, 0, stream, a); break;
-    case 1: hipLaunchKernelGGL((sgd_kernel<false, false, true>), grid, block, 0, stream, a); break;
-    case 2: hipLaunchKernelGGL((sgd_kernel<false, true, false>), grid, block, 0, stream, a); break;
-    case 3: hipLaunchKernelGGL((sgd_kernel<false, true, true>), grid, block, 0, stream, a); break;
-    case 4: hipLaunchKernelGGL((sgd_kernel<true, false, false>), grid, block, 0, stream, a); break;
-    case 5: hipLaunchKernelGGL((sgd_kernel<true, false, true>), grid, block, 0, stream, a); break;
-    case 6: hipLaunchKernelGGL((sgd_kernel<true, true, false>), grid, block, 0, stream, a); break;
-    default: hipLaunchKernelGGL((sgd_kernel<true, true, true>), grid, block, 0, stream, a); break;
+    case 0: return launch(sgd_kernel<false, false, false>, grid, block, 0, stream, a);
+    case 1: return launch(sgd_kernel<false, false, true>, grid, block, 0, stream, a);
+    case 2: return launch(sgd_kernel<false, true, false>, grid, block, 0, stream, a);
+    case 3: return launch(sgd_kernel<false, true, true>, grid, block, 0, stream, a);
+    case 4: return launch(sgd_kernel<true, false, false>, grid, block, 0, stream, a);
+    case 5: return launch(sgd_kernel<true, false, true>, grid, block, 0, stream, a);
+    case 6: return launch(sgd_kernel<true, true, false>, grid, block, 0, stream, a);
+    default: return launch(sgd_kernel<true, true, true>, grid, block, 0, stream, a);
     }
-    return hipGetLastError();
 }
 
 // tiles of 256 elements that the norms kernel leaves a record for
@@ -706,9 +701,8 @@ hipError_t launch_norms(const SgdArgs &a, const StatsArgs &st, hipStream_t strea
     const dim3 grid(static_cast<unsigned>(g)), block(64);
     // (the grouped form is for runs whose u and w do not fit the last-level cache; elsewhere they are
     // left there for the update right after)
-    if (grouped) hipLaunchKernelGGL((norms_kernel<true>), grid, block, 0, stream, a, st);
-    else hipLaunchKernelGGL((norms_kernel<false>), grid, block, 0, stream, a, st);
-    return hipGetLastError();
+    return grouped ? launch(norms_kernel<true>, grid, block, 0, stream, a, st)
+                   : launch(norms_kernel<false>, grid, block, 0, stream, a, st);
 }
 
 hipError_t launch_sgd_lars(const SgdArgs &a, const StatsArgs &st, bool fast, hipStream_t stream)
@@ -722,14 +716,11 @@ hipError_t launch_sgd_lars(const SgdArgs &a, const StatsArgs &st, bool fast, hip
     // a round: 117 and 136)
     const bool nt = a.n * 12 > 96ll << 20;
     const dim3 grid(static_cast<unsigned>(g)), block(64);
-    if (fast) {
-        if (nt) hipLaunchKernelGGL((lars_kernel<true, true>), grid, block, 0, stream, a, st);
-        else hipLaunchKernelGGL((lars_kernel<true, false>), grid, block, 0, stream, a, st);
-    } else {
-        if (nt) hipLaunchKernelGGL((lars_kernel<false, true>), grid, block, 0, stream, a, st);
-        else hipLaunchKernelGGL((lars_kernel<false, false>), grid, block, 0, stream, a, st);
-    }
-    return hipGetLastError();
+    if (fast)
+        return nt ? launch(lars_kernel<true, true>, grid, block, 0, stream, a, st)
+                  : launch(lars_kernel<true, false>, grid, block, 0, stream, a, st);
+    return nt ? launch(lars_kernel<false, true>, grid, block, 0, stream, a, st)
+              : launch(lars_kernel<false, false>, grid, block, 0, stream, a, st);
 }
 
 }  // namespace eager

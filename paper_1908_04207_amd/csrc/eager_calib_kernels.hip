@@ -97,18 +97,16 @@ hipError_t launch_copy(void *dst, const void *src, long long nbytes, hipStream_t
     // the fastest plain copy found on MI355X: 64-thread workgroups, one vector per lane
     long long g = (nvec + 63) / 64;
     if (g > kMaxGridThreads / 64) g = kMaxGridThreads / 64;   // the kernel strides
-    hipLaunchKernelGGL(copy_kernel, dim3(static_cast<unsigned>(g)), dim3(64), 0, stream,
-                       static_cast<f32x4 *>(dst), static_cast<const f32x4 *>(src), nvec);
-    return hipGetLastError();
+    return launch(copy_kernel, dim3(static_cast<unsigned>(g)), dim3(64), 0, stream, static_cast<f32x4 *>(dst),
+                  static_cast<const f32x4 *>(src), nvec);
 }
 
 hipError_t launch_read(const void *src, long long nbytes, float *sink, hipStream_t stream)
 {
     const long long nvec = nbytes / 16;
     if (nvec <= 0) return hipSuccess;
-    hipLaunchKernelGGL(read_kernel, dim3(grid_for(nvec, 256, 256 * 32)), dim3(256), 0, stream,
-                       static_cast<const f32x4 *>(src), nvec, sink);
-    return hipGetLastError();
+    return launch(read_kernel, dim3(grid_for(nvec, 256, 256 * 32)), dim3(256), 0, stream,
+                  static_cast<const f32x4 *>(src), nvec, sink);
 }
 
 hipError_t launch_mix(const MixArgs &a, int waves_per_cu, hipStream_t stream)

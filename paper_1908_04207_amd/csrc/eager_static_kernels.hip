@@ -5,7 +5,7 @@
 // until the process ends.  In host code the array's name is only a stand-in for the symbol:
 // its device address is looked up once per device with hipGetSymbolAddress, and that pointer -
 // never the name - is what kernels and the host side get.
-#include "eager_internal.h"
+#include "eager_device.h"
 
 #include <mutex>
 
@@ -54,8 +54,7 @@ hipError_t launch_table_fill(long long *table, const long long *start_end, int n
         a.count = n_buckets - first < kTableChunk ? n_buckets - first : kTableChunk;
         for (int i = 0; i < 2 * a.count; ++i) a.start_end[i] = start_end[2 * first + i];
         for (int i = 2 * a.count; i < 2 * kTableChunk; ++i) a.start_end[i] = 0;
-        hipLaunchKernelGGL(table_fill_kernel, dim3(1), dim3(256), 0, stream, a);
-        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+        if (hipError_t e = launch(table_fill_kernel, dim3(1), dim3(256), 0, stream, a); e != hipSuccess) return e;
     }
     return hipSuccess;
 }

@@ -77,3 +77,47 @@ def test_a_run_just_below_the_largest():
         assert torch.equal(recv[k:e], grad[k:e]), k
     assert recv[n].item() == -1.0
     ctx.close()
+
+
+@pytest.mark.gpu
+def test_an_error_of_another_call_is_not_a_launch_s():
+    """The runtime keeps the last error of a thread until somebody asks.  One that an unrelated call has left there
+    (a device that does not exist) is not reported by any launch of the library as its own, nor taken away."""
+    import ctypes
+    from paper_1908_04207_amd import binding as eb
+    dev, n, P = torch.device("cuda:0"), 1000, 2
+    torch.cuda.synchronize()
+    hip = ctypes.CDLL(eb.LIB_PATH)                  # the runtime that the library is linked with
+    t = lambda: torch.zeros(n, device=dev)          # noqa: E731
+    G, R, w, v, u = [t(), t()], [t(), t()], t(), t(), t()
+    ctx, plain = eb.Context(P, [0], [n]), eb.Context(P, [0], [n])
+    stats = torch.zeros(32, dtype=torch.uint8, device=dev)
+    need = ctx.eager_stats_workspace_bytes()
+    workspace, sink = torch.empty(need, dtype=torch.uint8, device=dev), t()
+    ctx.eager_stats_attach(stats, workspace, need)
+    opt, s = (w, v, 0.1, 0.9), torch.cuda.current_stream().cuda_stream
+    step = iter(range(100))
+    plan = lambda mask: eb.make_plan(eb.MAJORITY, P, next(step), mask)      # noqa: E731
+    calls = {
+        "round": lambda: plain.eager_partial_allreduce(plan(0b01), G, R, opt=opt, stream=s),
+        "round with norms": lambda: ctx.eager_partial_allreduce(plan(0b11), G, R, recv=u, stream=s),
+        "step": lambda: plain.eager_sgd_step(u, opt, stream=s),
+        "layer-wise step": lambda: ctx.eager_sgd_step_lars(u, opt, 0.02, 1e-9, stream=s),
+        "layer-wise step, own scratch": lambda: plain.eager_sgd_step_lars_static(u, opt, 0.02, stats, 1e-9, stream=s),
+        "stash": lambda: plain.eager_stash(1, G[1], R[1], stream=s),
+        "flush": lambda: plain.eager_flush(R, opt=opt, stream=s),
+        "views": lambda: plain.eager_sgd_step_views(u, [w], [v], 0.1, 0.9, stream=s),
+        "average": lambda: plain.eager_average_views([w, v], stream=s),
+        "copy": lambda: eb.eager_calib_copy(R[0], G[0], 4 * n, stream=s),
+        "read": lambda: eb.eager_calib_read(G[0], 4 * n, sink, stream=s),
+        "mix": lambda: eb.eager_calib_mix(G, R, n // 4, sink=sink, stream=s)}
+    for name, call in calls.items():
+        left = hip.hipSetDevice(1 << 20)
+        assert left != 0
+        try:
+            call()
+        finally:
+            assert hip.hipGetLastError() == left, name
+            assert hip.hipGetLastError() == 0
+    torch.cuda.synchronize()
+    ctx.close(), plain.close()
