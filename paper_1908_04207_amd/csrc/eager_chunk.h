@@ -71,10 +71,13 @@ __device__ __forceinline__ f32x4 widen(f32x4 raw, bool odd)
     x.w = __uint_as_float(b & 0xffff0000u);
     return x;
 }
-__device__ __forceinline__ float widen(float raw, bool) { return __uint_as_float(__float_as_uint(raw) << 16); }
+__device__ __forceinline__ float widen(float raw) { return __uint_as_float(__float_as_uint(raw) << 16); }
 
-template <bool>
-__device__ __forceinline__ void update_rule(const UpdateRule &r, float u, float vo, float wo, float &vn, float &wn)
+__device__ __forceinline__ void apply_rule(const UpdateRule &r, f32x4 u, f32x4 vo, f32x4 wo, f32x4 &vn, f32x4 &wn)
+{
+    update_rule<false>(r, u, vo, wo, vn, wn);
+}
+__device__ __forceinline__ void apply_rule(const UpdateRule &r, float u, float vo, float wo, float &vn, float &wn)
 {
     vn = vo;
     wn = wo;
@@ -163,7 +166,7 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
 #pragma unroll
             for (int j = 0; j < CH; ++j)
                 if (b.bf >> j & 1u) {
-                    if constexpr (W == 1) x[j] = widen(half[j], odd);
+                    if constexpr (W == 1) x[j] = widen(half[j]);
                     else x[j] = widen(x[j], odd);
                 }
         }
@@ -266,7 +269,7 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
     V vn, wn;
     if (OPT) {
         const UpdateRule rule = {h.neg_lr, h.mu, h.wd, h.nesterov};
-        update_rule<false>(rule, avg, vo, wo, vn, wn);
+        apply_rule(rule, avg, vo, wo, vn, wn);
     }
     if (in) {
         if (h.recv) st_vec<W, NTS>(h.recv, off, avg);

@@ -127,8 +127,8 @@ struct RoundArgs {
 // ends in SKIPs.  A slot is ONE scalar load for the kernel: the arena base, whose low four bits are
 // zero, with the action and the type in those bits.  What every wavefront reads first stands first.
 constexpr int kMaxSlots = 2 * kMaxP;
-constexpr int kSlotChunk = 16;
 constexpr int kBurst = 2;              // slots in flight per wavefront of the burst kernel
+constexpr int kSlotFill = 8;           // SKIPs behind the list: its ragged tail takes slots 8 at a time
 enum SlotKind : unsigned {
     kAdd = 0, kHold = 1, kPair = 2, kSkip = 3, kKindMask = 3,
     kSlotBf16 = 4,                     // the stream is bf16
@@ -146,8 +146,8 @@ struct SlotHead {
 };
 struct SlotArgs {
     SlotHead h;
-    unsigned long long slot[kMaxSlots + kSlotChunk + kBurst];   // a process has at most two slots
-    float *dst[kMaxSlots + kSlotChunk + kBurst];                // of slot k where it is a copy
+    unsigned long long slot[kMaxSlots + kSlotFill + kBurst];   // a process has at most two slots
+    float *dst[kMaxSlots + kSlotFill + kBurst];                // of slot k where it is a copy
     StatsArgs stats;
 };
 

@@ -53,7 +53,7 @@ struct Lanes {
 
 // 16 bytes of a slot's stream (raw: a bf16 stream is widened by slot_value).  For a SKIP every
 // lane loads one and the same piece: hardly any traffic.
-template <bool BF16, bool NT = true>
+template <bool BF16>
 __device__ __forceinline__ f32x4 ld_slot_or_skip(unsigned long long slot, const Lanes &L)
 {
     const bool skip = (slot & (kKindMask | kSlotCopy)) == kSkip;
@@ -61,7 +61,7 @@ __device__ __forceinline__ f32x4 ld_slot_or_skip(unsigned long long slot, const 
     const char *base = reinterpret_cast<const char *>(slot & ~static_cast<unsigned long long>(kSlotTag)) +
                        L.e0 * (is_bf ? 2 : 4);
     const unsigned off = L.off, off_bf = L.off_bf;
-    return ld_at<NT>(base, (is_bf ? off_bf : off) & (skip ? 0u : ~0u));
+    return ld_at<true>(base, (is_bf ? off_bf : off) & (skip ? 0u : ~0u));
 }
 
 template <bool BF16>
@@ -161,7 +161,7 @@ template <bool BF16, bool STATS>
 __device__ __forceinline__ void slot_tail_element(KSlotArgs &a, const SlotHead &h, long long i)
 {
     float s = 0.0f, term = 0.0f;
-    constexpr int C = 8;                  // the list ends in at least 16 SKIPs
+    constexpr int C = kSlotFill;          // what is read beyond the list are SKIPs
     for (int k0 = 0; k0 < h.n_sum; k0 += C) {
         float x[C];
 #pragma unroll
@@ -408,7 +408,7 @@ void build_slots(const RoundArgs &a, SlotArgs &s)
             ++s.h.n_copy;
         }
     const unsigned long long skip = s.h.n_copy ? s.slot[n - 1] & ~static_cast<unsigned long long>(kSlotCopy) : none;
-    for (int k = 0; k < kSlotChunk; ++k) s.slot[n + k] = skip;
+    for (int k = 0; k < kSlotFill; ++k) s.slot[n + k] = skip;
     s.h.w = a.w;
     s.h.v = a.v;
     s.h.recv = a.recv;
