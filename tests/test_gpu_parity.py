@@ -752,11 +752,12 @@ def test_nonfinite_and_denormal_values(eb):
 
 @pytest.mark.parametrize("dtype,launch", [("f32", {"split": 1}), ("f32", {"split": 2}), ("bf16", {})])
 def test_signed_zeros_bit_for_bit(eb, dtype, launch):
-    """Gradients, send buffers, parameters and momentum that are -0.0: the kernel applies a
-    slot's action with masks (a masked-out term is +0.0), the oracle with branches; the results
-    must still agree in every bit, the sign of a zero included - stored late gradients keep their
-    sign, a sum that starts from +0.0 never becomes -0.0.  Late, late again with a pending
-    buffer, on time with a pending buffer, and everybody on time."""
+    """Gradients, send buffers, parameters and momentum that are -0.0, in a small round (chunk_kernel;
+    every form of a round, the masks of burst_kernel among them:
+    test_signed_zeros_and_infinities_in_every_form): the results must agree with the oracle's in every
+    bit, the sign of a zero included - stored late gradients keep their sign, a sum that starts from
+    +0.0 never becomes -0.0.  Late, late again with a pending buffer, on time with a pending buffer, and
+    everybody on time."""
     P, n = 4, 520
     pair = Pair(eb, P, [0, 264], [260, 256], n, dtype, seed=6)
     for key, val in launch.items():

@@ -77,6 +77,45 @@ def test_one_element_to_a_lane(eb, dtype, P, n):
     _rounds(eb, pair, [1, everyone, 0b101, everyone & ~1, everyone], 0, n)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("form", ["narrow", "chunks of 8", "chunks of 16", "bursts"])
+def test_signed_zeros_and_infinities_in_every_form(eb, dtype, form):
+    """Late, late again with a pending buffer, on time with one (a pair), everybody on time: gradients, pending
+    buffers, parameters and momentum of -0.0, and infinities and NaN that meet in a sum, a pair or not at all, bit
+    for bit in fixed order - with branches (chunk_kernel, one element to a lane and four) and with the masks of
+    burst_kernel, where what is masked out is +0.0.  In the ragged tail too."""
+    P = 4 if form == "bursts" else 9
+    # every mask moves at least all gradients, w and v, the latter two read and written
+    per = P * (2 if dtype == "bf16" else 4) + 16
+    n = LINE // per + 303 if form == "bursts" else 523
+    assert (n * per > LINE) == (form == "bursts")
+    pair = Pair(eb, P, [0], [n], (n + 7) // 8 * 8, dtype, 0, seed=6)
+    if form.startswith("chunks"):
+        pair.ctx.eager_set_launch("chunk", int(form.split()[-1]))
+    neg = torch.full((pair.arena,), -0.0, dtype=pair.dtype)
+    mixed = neg.clone()
+    mixed[::3] = 0.0
+    mixed[1::7] = -1e-3
+    mixed[5::11] = 1e-3
+    for t, start in ((pair.w, 0), (pair.v, 32)):
+        t[start:start + 64] = -0.0
+        t[n - 40:] = -0.0
+    pair.oracle.w[:] = pair.w.cpu().numpy()
+    pair.oracle.v[:] = pair.v.cpu().numpy()
+    inf, everyone = float("inf"), (1 << P) - 1
+    at = [200, 257, n - 2]                               # first tile, second tile, ragged tail
+    for t, mask in enumerate([everyone & ~2, everyone & ~6, 0b1010, everyone, 1, everyone & ~1, everyone]):
+        g = [(neg if (t + p) % 2 == 0 else mixed).clone() for p in range(P)]
+        for k in at:
+            g[t % P][k] = inf                            # alone; it may be pending for a while
+            g[1][k + 1], g[2][k + 1] = inf, -inf         # two that meet, in one round or in two
+        g[0][210 + t] = float("nan")
+        pair.round(eb.make_plan(eb.SOLO, P, t, mask), pair.set_grads(g), want_recv=True)
+        pair.compare(exact=True, check_recv=True, what=f"{form}, round {t}, mask {mask:#b}")
+    assert np.signbit(pair.oracle_recv[pair.oracle_recv == 0.0]).sum() == 0
+    assert np.isnan(pair.oracle.w[[210, at[1] + 1]]).all() and np.isfinite(pair.oracle.w[:200]).all()
+
+
 def test_a_run_longer_than_one_launch_of_chunks(eb):
     """Beyond 2^29 elements chunk_kernel goes over a run in several launches: element by element against torch,
     and the statistics of both."""
