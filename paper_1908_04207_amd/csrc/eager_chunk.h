@@ -294,9 +294,10 @@ template <bool BF16, bool FAST, bool NT, bool NTS, bool OPT, bool STATS, int CH,
 __global__ __launch_bounds__(256) void chunk_kernel(const ARGS)
 {
     const ARGS __attribute__((address_space(4))) &a = kernarg<ARGS>();
-    // The head, the first slots and a word of every further line of the arguments are requested at
-    // once: read where they are used, each is a trip of its own (32 processes, 16 late, 64 elements: 5.37
-    // us with the lines of a short list only, 4.80 with these).
+    // The head, the first slots and a word of the lines that follow are requested at once - all lines of the
+    // short block; of the long one slots up to 63 and destinations up to 24 -: read where they are used, each is
+    // a trip of its own (32 processes, 16 late, 64 elements: 5.37 us with the lines of a short list only, 4.80 with
+    // these).
     ChunkHead h = read(a.h);
     unsigned long long slot[CH];
 #pragma unroll

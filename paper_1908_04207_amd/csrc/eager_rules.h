@@ -67,11 +67,12 @@ inline long long round_bytes(const SlotArgs &s, bool update)
 // Whether a run is bound by latency - everything at once, no cap (chunk_kernel) - and not a stream
 // (burst_kernel).  A stream begins at 96 MiB moved where the run only reads fp32 streams, at 112 MiB where
 // bursts are shorter (bf16) or copies follow them, and at 56 MiB where one or two bf16 streams are all
-// there is, which a wavefront takes in one burst anyway (a chunk is filled up with loads of no
-// use).  Both sides, chunks and bursts, one state in a loop: 8 processes on time, fp32, 96 MiB 18.3
-// and 15.0 us, 112 MiB 21.4 and 19.3, 16 processes 112 MiB 19.8 and 17.6; 3 processes, 1 late, 88 MiB 13.9
-// and 18.1, 100 MiB 15.7 and 17.9; 8 processes, 4 late, 100 MiB 17.1 and 18.6; 16 on time with bf16
-// gradients 100 MiB 16.2 and 19.2, but one process 80 MiB 17.1 and 16.6, two 14.4 and 13.3.
+// there is, which a wavefront takes in one burst anyway.  Both sides, chunks and bursts, one state in a
+// loop: 8 processes on time, fp32, 96 MiB 15.2 and 16.7 us, 112 MiB 17.7 and 17.8, into the receive buffer 96
+// MiB 17.4 and 16.4; 16 processes 96 MiB 16.7 and 16.1, 112 MiB 20.0 and 17.8; 3 processes, 1 late, 100 MiB 15.2 and
+// 17.4, 128 MiB 22.0 and 21.8; 8 processes, 4 late, 100 MiB 15.8 and 18.1, 112 MiB 18.6 and 19.6; 16 on time with
+// bf16 gradients 100 MiB 16.9 and 19.4, 128 MiB 21.5 and 23.2.  One bf16 stream 80 MiB 15.1 and 16.5, two 13.4 and 13.4:
+// the line at 56 MiB was drawn when chunks were filled up with loads (17.1 and 16.6, 14.4 and 13.3).
 inline bool small_round(const SlotArgs &s, long long bytes_per_element)
 {
     const long long moved = s.h.n * bytes_per_element;
