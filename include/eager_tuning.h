@@ -28,9 +28,10 @@ extern "C" {
  *   "chunk"      streams whose loads are in flight together per wavefront: 0 (default) = 2 for
  *                runs that move more than 96 MiB (112 where gradients are bf16 or late ones are
  *                copied in the same pass, 56 for one or two bf16 streams alone; gradients counted
- *                by their type), else 8 or 16 (by the length of the list), or 32 with one element to a
- *                lane (up to 2^17 elements and more than 8 streams, no statistics); 8, 16 = that
- *                many, four elements to a lane, for any run.  Per-bucket statistics need 0 or 16
+ *                by their type), else 8 or 16 (by the length of the list), or 32 with one element
+ *                to a lane (more than 8 streams, no statistics, up to 2^17 elements, 2^15 with more
+ *                than 40 copies of bf16 gradients); 8, 16 = that many, four elements to a lane, for
+ *                any run.  Per-bucket statistics need 0 or 16
  *   "block"      threads per workgroup: 64 (default), 128 or 256
  *   "blocks_per_cu" 0 = chosen from the round (default; no cap where "chunk" is 8 or 16); -1 = no
  *                cap; 1..32 = that many workgroups resident per CU, or the next count above it that

@@ -347,7 +347,7 @@ hipError_t launch_segments(const SlotArgs &s, A &a, int bpc, const Launch &cfg, 
     for (long long first = 0; first < s.h.n; first += kChunkElements) {
         const long long n = std::min(s.h.n - first, kChunkElements);
         fill_chunk(s, first, n, a);
-        a.h.narrow = chunk_narrow(s.h.n, a.h.n_slots, STATS, cfg.chunk);
+        a.h.narrow = chunk_narrow(s.h.n, a.h.n_slots, s.h.n_copy, BF16, STATS, cfg.chunk);
         const long long g = a.h.narrow ? (n + cfg.block - 1) / cfg.block : round_workgroups(n, BF16, cfg.block);
         a.h.waves_per_block = per;
         a.h.xcd_blocks = cfg.xcd_map ? static_cast<int>(g / 8) : 0;

@@ -143,11 +143,14 @@ void fill_chunk(const SlotArgs &s, long long first, long long n, A &a)
 // on, up to 128 k elements (one launch after another, 4 elements to a lane and 1): 8 processes, 4 late, 4096
 // elements 2.96 and 2.86 us, 65536 3.47 and 3.52, 131072 4.54 and 4.35, 262144 5.69 and 6.00; 16 processes, 8
 // late, 4096 4.24 and 3.28, 131072 5.93 and 5.16, 262144 8.4 and 9.1; but with 3 slots 2.60 and 2.66, 2.87 and
-// 3.12.  (By-products are kept per 256 elements, so a launch with them is never narrow; nor is one whose
-// loads in flight the caller has set: chunk, 0 where it has not.)
-inline bool chunk_narrow(long long n, int slots, bool stats, int chunk)
+// 3.12.  Up to 32 k where more than 40 bf16 gradients are copied (64 processes, 63 late, bf16: 32 k elements 15.7
+// and 15.8 us, 64 k 16.5 and 20.3, 128 k 20.8 and 27.9; 48 processes, 47 late, 128 k 15.7 and 18.4; but 64 processes,
+// 32 late, 128 k 13.4 and 13.2, and with fp32 gradients, 63 late, 20.2 and 18.4).  (By-products are kept per 256 elements,
+// so a launch with them is never narrow; nor is one whose loads in flight the caller has set: chunk, 0 where it
+// has not.)
+inline bool chunk_narrow(long long n, int slots, int copies, bool bf16, bool stats, int chunk)
 {
-    return chunk == 0 && !stats && slots > 8 && n <= 1ll << 17;
+    return chunk == 0 && !stats && slots > 8 && n <= (bf16 && copies > 40 ? 1ll << 15 : 1ll << 17);
 }
 
 // Resident wavefronts per CU of the burst kernel, -1: no cap.

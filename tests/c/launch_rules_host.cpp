@@ -127,9 +127,15 @@ static int occupancy()
 // flight is the library's to choose.
 static int narrow()
 {
-    CHECK(chunk_narrow(1, 9, false, 0) && chunk_narrow(1 << 17, 128, false, 0));
-    CHECK(!chunk_narrow((1 << 17) + 1, 128, false, 0) && !chunk_narrow(64, 8, false, 0) && !chunk_narrow(64, 9, true, 0));
-    for (int chunk : {8, 16}) CHECK(!chunk_narrow(1, 9, false, chunk) && !chunk_narrow(1 << 17, 128, false, chunk));
+    for (int bf16 = 0; bf16 < 2; ++bf16) {
+        auto is = [bf16](long long n, int slots, int copies, bool stats, int chunk) {
+            return chunk_narrow(n, slots, copies, bf16 != 0, stats, chunk);
+        };
+        CHECK(is(1, 9, 0, false, 0) && is(1 << 17, 128, 40, false, 0) && is(1 << 15, 128, 63, false, 0));
+        CHECK(is(1 << 16, 128, 63, false, 0) != bf16 && is(1 << 17, 95, 47, false, 0) != bf16);
+        CHECK(!is((1 << 17) + 1, 128, 0, false, 0) && !is(64, 8, 0, false, 0) && !is(64, 9, 0, true, 0));
+        for (int chunk : {8, 16}) CHECK(!is(1, 9, 0, false, chunk) && !is(1 << 17, 128, 0, false, chunk));
+    }
     return 0;
 }
 
