@@ -120,6 +120,9 @@ __device__ __forceinline__ void first_of(int n, const F &f)
     }
 }
 
+// s_waitcnt vmcnt(0) and nothing else
+constexpr int kStoresArrived = 0x0f70;
+
 // What one wavefront does: lane-vectors [at0, at0 + 64) of W elements, up to `end`, with CH slots in
 // flight.  What bounds it is how many instructions a wavefront issues between its trips to memory - a
 // wavefront on its own issues one in 4 cycles or more, 600 of them are a microsecond - so nothing is done
@@ -210,7 +213,10 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
                     for (int j = 0; j < 8; ++j) to[j] = dst[j];
 #pragma unroll
                     for (int j = 0; j < 8; ++j)
-                        if (b.copy >> (g + j) & 1u) st_vec<W, NT>(to[j], off, x[g + j]);
+                        if (b.copy >> (g + j) & 1u) {
+                            st_vec<W, NT>(to[j], off, x[g + j]);
+                            if (NT && W == 4 && CH == 16 && h.form == kPaced) __builtin_amdgcn_s_waitcnt(kStoresArrived);
+                        }
                 }
         }
     };
@@ -316,7 +322,7 @@ __global__ __launch_bounds__(256) void chunk_kernel(const ARGS)
         asm volatile("" : "+s"(h.w), "+s"(slot[0]), "+s"(slot[CH - 1]) : "s"(line[0]), "s"(line[1]), "s"(line[2]),
                      "s"(line[3]), "s"(line[4]));
     asm volatile("" : "+s"(h.v), "+s"(h.recv), "+s"(h.n), "+s"(h.n_sum), "+s"(h.n_slots));
-    asm volatile("" : "+s"(h.dst_first), "+s"(h.narrow), "+s"(h.waves_per_block), "+s"(h.xcd_blocks),
+    asm volatile("" : "+s"(h.dst_first), "+s"(h.form), "+s"(h.waves_per_block), "+s"(h.xcd_blocks),
                  "+s"(h.inv_P), "+s"(h.neg_lr), "+s"(h.mu), "+s"(h.wd), "+s"(h.nesterov));
     asm volatile("" : "+s"(h.first.pair), "+s"(h.first.hold), "+s"(h.first.copy), "+s"(h.first.bf));
 #pragma unroll
@@ -329,7 +335,7 @@ __global__ __launch_bounds__(256) void chunk_kernel(const ARGS)
     const unsigned wave = bid * static_cast<unsigned>(h.waves_per_block) +
                           static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
     unsigned first = wave * 64u;
-    if (!h.narrow) {
+    if (h.form != kNarrow) {
         const unsigned nvec = BF16 ? h.n / 8u * 2u : h.n / 4u, tiles = (nvec + 63u) / 64u;
         if (wave < tiles) {
             chunk_body<4, CH, BF16, FAST, NT, NTS, OPT, STATS>(a, h, slot, first, nvec, wave);
@@ -347,8 +353,9 @@ hipError_t launch_segments(const SlotArgs &s, A &a, int bpc, const Launch &cfg, 
     for (long long first = 0; first < s.h.n; first += kChunkElements) {
         const long long n = std::min(s.h.n - first, kChunkElements);
         fill_chunk(s, first, n, a);
-        a.h.narrow = chunk_narrow(s.h.n, a.h.n_slots, s.h.n_copy, BF16, STATS, cfg.chunk);
-        const long long g = a.h.narrow ? (n + cfg.block - 1) / cfg.block : round_workgroups(n, BF16, cfg.block);
+        const bool narrow = chunk_narrow(s.h.n, a.h.n_slots, s.h.n_copy, BF16, STATS, cfg.chunk);
+        a.h.form = narrow ? kNarrow : NT && CH == 16 && chunk_paced(s, a.h.n_slots, BF16, OPT) ? kPaced : kWide;
+        const long long g = narrow ? (n + cfg.block - 1) / cfg.block : round_workgroups(n, BF16, cfg.block);
         a.h.waves_per_block = per;
         a.h.xcd_blocks = cfg.xcd_map ? static_cast<int>(g / 8) : 0;
         if constexpr (STATS) {

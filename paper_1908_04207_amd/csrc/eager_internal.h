@@ -164,11 +164,16 @@ struct ChunkBits {
 };
 constexpr int kChunkWord = 32;            // slots that a ChunkBits covers
 constexpr long long kChunkElements = 1ll << 29;   // of one launch, for the 32-bit offsets
+enum ChunkForm : int {
+    kWide,                                // a lane owns four elements
+    kNarrow,                              // one
+    kPaced                                // four, and a copy's store waits for the one before it
+};
 struct ChunkHead {
     float *w, *v, *recv;
     unsigned n;                           // elements
     int n_sum, n_slots, dst_first;
-    int narrow;                           // 1: a lane owns one element and not four
+    int form;                             // ChunkForm
     int waves_per_block, xcd_blocks;
     float inv_P, neg_lr, mu, wd;
     int nesterov;

@@ -139,9 +139,29 @@ static int narrow()
     return 0;
 }
 
+// A copy's store waits for the one before it: one chunk of many copies, a run that streams and is resident at once.
+static int paced()
+{
+    auto is = [](int sums, int copies, bool bf16, bool update, long long n) {
+        SlotArgs s{};
+        s.h.n = n;
+        s.h.n_sum = sums;
+        s.h.n_copy = copies;
+        for (int k = 0; k < sums + copies; ++k)
+            s.slot[k] = 0x10000ull * (k + 1) + (k < sums ? 0u + kAdd : kSkip + 0u + kSlotCopy) + (bf16 && k >= sums ? 0u + kSlotBf16 : 0u);
+        return chunk_paced(s, sums + copies, bf16, update);
+    };
+    const long long streams = (56ll << 20) / (32 + 7 * 6 + 16) + 1, resident = 20 * 256 * 256;
+    CHECK(is(8, 7, true, true, streams) && !is(8, 7, true, true, streams - 1));
+    CHECK(is(8, 7, true, true, resident) && !is(8, 7, true, true, resident + 1) && is(8, 7, false, false, resident));
+    CHECK(is(6, 5, true, true, 1 << 20) && !is(6, 5, false, true, 1 << 20) && !is(6, 4, true, true, 1 << 20));
+    CHECK(is(9, 7, true, true, 1 << 20) && !is(10, 7, true, true, 1 << 20));
+    return 0;
+}
+
 int main()
 {
-    if (narrow() || grids() || finishing() || norms() || bytes() || occupancy()) return 1;
+    if (paced() || narrow() || grids() || finishing() || norms() || bytes() || occupancy()) return 1;
     std::printf("ok\n");
     return 0;
 }
