@@ -346,6 +346,15 @@ __global__ __launch_bounds__(256) void chunk_kernel(const ARGS)
     if (first < h.n) chunk_body<1, STATS ? 16 : 32, BF16, FAST, NT, NTS, OPT, STATS>(a, h, slot, first, h.n, 0);
 }
 
+template <typename A>
+int kernel_waves(void (*kernel)(A))
+{
+    hipFuncAttributes of;
+    if (hipFuncGetAttributes(&of, reinterpret_cast<const void *>(kernel)) == hipSuccess) return resident_waves(of.numRegs);
+    (void)hipGetLastError();
+    return 0;
+}
+
 template <bool BF16, bool FAST, bool NT, bool NTS, bool OPT, bool STATS, int CH, typename A>
 hipError_t launch_segments(const SlotArgs &s, A &a, int bpc, const Launch &cfg, hipStream_t st)
 {
@@ -354,7 +363,13 @@ hipError_t launch_segments(const SlotArgs &s, A &a, int bpc, const Launch &cfg, 
         const long long n = std::min(s.h.n - first, kChunkElements);
         fill_chunk(s, first, n, a);
         const bool narrow = chunk_narrow(s.h.n, a.h.n_slots, s.h.n_copy, BF16, STATS, cfg.chunk);
-        a.h.form = narrow ? kNarrow : NT && CH == 16 && chunk_paced(s, a.h.n_slots, BF16, OPT) ? kPaced : kWide;
+        a.h.form = narrow ? kNarrow : kWide;
+        if constexpr (NT && CH == 16)
+            if (!narrow && chunk_paced(s, a.h.n_slots, BF16, OPT, 32)) {
+                // (the kernel is asked for its registers once, and only where all else speaks for it)
+                static const int resident = kernel_waves(chunk_kernel<BF16, FAST, NT, NTS, OPT, STATS, CH, A>);
+                if (chunk_paced(s, a.h.n_slots, BF16, OPT, resident)) a.h.form = kPaced;
+            }
         const long long g = narrow ? (n + cfg.block - 1) / cfg.block : round_workgroups(n, BF16, cfg.block);
         a.h.waves_per_block = per;
         a.h.xcd_blocks = cfg.xcd_map ? static_cast<int>(g / 8) : 0;

@@ -153,17 +153,25 @@ inline bool chunk_narrow(long long n, int slots, int copies, bool bf16, bool sta
     return chunk == 0 && !stats && slots > 8 && n <= (bf16 && copies > 40 ? 1ll << 15 : 1ll << 17);
 }
 
+// Wavefronts that a CU holds of a kernel with so many vector registers: 512 on each of its 4 SIMDs, handed out in
+// eights.
+inline int resident_waves(int registers)
+{
+    const int each = (registers + 7) / 8 * 8;
+    return registers < 1 ? 0 : each <= 64 ? 32 : 4 * (512 / each);
+}
+
 // Whether the copies' stores of such a launch go out one at a time.  Where all its wavefronts are resident at once
-// (20 per CU) that keeps the stores of the first behind the loads of the last, and the memory side reads for a
+// (`resident` per CU, 20 or 16 in chunks of 16) that keeps the stores of the first behind the loads of the last, and the memory side reads for a
 // while and then writes.  It takes 6 copies to pay, 5 with bf16 gradients, a list in flight as a whole (further
 // loads would wait behind the stores) and a run that streams.  Stores at once and one at a time, one state in a
 // loop, 58, 72, 88 and 104 MiB moved: 8 processes, 7 late, bf16 10.3 11.8 14.7 17.6 and 9.0 11.4 12.9 16.0 us, fp32 9.2
 // 11.7 14.5 17.8 and 8.8 11.5 14.2 17.2; 8 processes, 5 late, bf16 9.9 11.7 14.7 and 9.0 11.1 13.9, but at 104 MiB (23 tiles
 // per CU) 16.8 and 18.1; 10 processes, 4 late, bf16 14.3 and 14.8 at 88; 12 processes, 11 late, 23 slots 11.6 and 13.4
 // at 72.
-inline bool chunk_paced(const SlotArgs &s, int slots, bool bf16, bool update)
+inline bool chunk_paced(const SlotArgs &s, int slots, bool bf16, bool update, int resident)
 {
-    return slots <= 16 && s.h.n_copy >= (bf16 ? 5 : 6) && s.h.n <= 20ll * kCus * 256 &&
+    return slots <= 16 && s.h.n_copy >= (bf16 ? 5 : 6) && s.h.n <= static_cast<long long>(resident) * kCus * 256 &&
            s.h.n * round_bytes(s, update) > kPlainRoundBytes;
 }
 

@@ -142,20 +142,23 @@ static int narrow()
 // A copy's store waits for the one before it: one chunk of many copies, a run that streams and is resident at once.
 static int paced()
 {
-    auto is = [](int sums, int copies, bool bf16, bool update, long long n) {
+    CHECK(resident_waves(99) == 16 && resident_waves(96) == 20 && resident_waves(92) == 20 && resident_waves(50) == 32);
+    CHECK(resident_waves(0) == 0 && resident_waves(80) == 24 && resident_waves(72) == 28);
+    auto is = [](int sums, int copies, bool bf16, bool update, long long n, int resident = 20) {
         SlotArgs s{};
         s.h.n = n;
         s.h.n_sum = sums;
         s.h.n_copy = copies;
         for (int k = 0; k < sums + copies; ++k)
             s.slot[k] = 0x10000ull * (k + 1) + (k < sums ? 0u + kAdd : kSkip + 0u + kSlotCopy) + (bf16 && k >= sums ? 0u + kSlotBf16 : 0u);
-        return chunk_paced(s, sums + copies, bf16, update);
+        return chunk_paced(s, sums + copies, bf16, update, resident);
     };
     const long long streams = (56ll << 20) / (32 + 7 * 6 + 16) + 1, resident = 20 * 256 * 256;
     CHECK(is(8, 7, true, true, streams) && !is(8, 7, true, true, streams - 1));
     CHECK(is(8, 7, true, true, resident) && !is(8, 7, true, true, resident + 1) && is(8, 7, false, false, resident));
     CHECK(is(6, 5, true, true, 1 << 20) && !is(6, 5, false, true, 1 << 20) && !is(6, 4, true, true, 1 << 20));
     CHECK(is(9, 7, true, true, 1 << 20) && !is(10, 7, true, true, 1 << 20));
+    CHECK(is(8, 7, true, true, 1 << 20, 16) && !is(8, 7, true, true, (1 << 20) + 1, 16) && !is(8, 7, true, true, 1 << 20, 0));
     return 0;
 }
 

@@ -116,6 +116,15 @@ def test_signed_zeros_and_infinities_in_every_form(eb, dtype, form):
     assert np.isnan(pair.oracle.w[[210, at[1] + 1]]).all() and np.isfinite(pair.oracle.w[:200]).all()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [700_003, 1_048_576, 16 * 65536 + 5, 20 * 65536, 20 * 65536 + 1])
+def test_stores_of_copies_one_at_a_time(eb, dtype, n):
+    """Runs of 56 to 112 MiB with many copies, on both sides of the number of elements up to which all wavefronts are
+    resident (16 or 20 tiles per CU): 7, 6 and 5 of 8 late, fused and into the receive buffer."""
+    pair = Pair(eb, 8, [0], [n], (n + 7) // 8 * 8, dtype, 0, seed=n % 97)
+    _rounds(eb, pair, [0b00000001, 0b00010000, 0b01000001, 0b10000000, 0b00110001, 0b00000010], 0, n)
+
+
 def test_a_run_longer_than_one_launch_of_chunks(eb):
     """Beyond 2^29 elements chunk_kernel goes over a run in several launches: element by element against torch,
     and the statistics of both."""
