@@ -157,7 +157,7 @@ struct SlotArgs {
 // list holds the sum, then the copies, and nothing to fill it up; the destination of slot k stands at
 // dst[k - dst_first], dst_first being a multiple of 8 at or below the first copy.
 //   pair   the slot completes the one before it (a HOLD)     hold   it waits for the next one
-//          (neither is looked at where the order is free)
+//          (neither is looked at where the order is free; there all fp32 streams stand before the bf16 ones)
 //   copy   it is stored to its destination                   bf     the stream is bf16
 struct ChunkBits {
     unsigned pair, hold, copy, bf;

@@ -98,7 +98,7 @@ inline bool chunk_fits(const SlotArgs &s, int slots, int copies)
     return s.h.n_sum + s.h.n_copy <= slots && s.h.n_copy <= copies;
 }
 template <typename A>
-void fill_chunk(const SlotArgs &s, long long first, long long n, A &a)
+void fill_chunk(const SlotArgs &s, bool any_order, long long first, long long n, A &a)
 {
     const long long e = s.h.e0 + first;
     auto at = [e](float *p) { return p ? p + e : nullptr; };
@@ -124,9 +124,16 @@ void fill_chunk(const SlotArgs &s, long long first, long long n, A &a)
     };
     int terms = s.h.n_sum;
     while (terms > 0 && (s.slot[terms - 1] & kKindMask) == kSkip) --terms;
-    for (int j = 0; j < terms; ++j) {
+    auto term = [&](int j) {
         const unsigned kind = static_cast<unsigned>(s.slot[j]) & kKindMask;
         push(s.slot[j], kind == kAdd ? nullptr : kind == kPair ? &ChunkBits::pair : &ChunkBits::hold);
+    };
+    if (any_order) {
+        for (unsigned long long type : {0ull, static_cast<unsigned long long>(kSlotBf16)})
+            for (int j = 0; j < terms; ++j)
+                if ((s.slot[j] & kSlotBf16) == type) term(j);
+    } else {
+        for (int j = 0; j < terms; ++j) term(j);
     }
     a.h.n_sum = k;
     a.h.dst_first = k & ~7;

@@ -15,12 +15,12 @@ static float at(unsigned long long address, bool bf)      // some number that be
     return static_cast<float>(static_cast<int>(address * 2654435761u >> 7 & 0xffffff) - 0x800000) * (bf ? 1e-3f : 1e-6f);
 }
 
-// in chunks of CH, pairs across them by the held value, or in any order two sums in turn; the copies as
-// (destination, source)
+// in chunks of CH, pairs across them by the held value, or in any order two sums of fp32 streams in
+// turn and two of bf16 streams; the copies as (destination, source)
 template <typename A>
 static float by_chunks(const A &a, int CH, bool fast, std::vector<std::pair<float *, float>> &copies)
 {
-    float s = 0.0f, s2 = 0.0f, held = 0.0f;
+    float s = 0.0f, s2 = 0.0f, s3 = 0.0f, s4 = 0.0f, held = 0.0f;
     for (int k0 = 0; k0 < a.h.n_slots; k0 += CH) {
         std::vector<float> x(CH, 1e30f);
         auto bit = [&](unsigned ChunkBits::*m, int j) { return a.bits[(k0 + j) / kChunkWord].*m >> (k0 + j) % kChunkWord & 1u; };
@@ -37,7 +37,7 @@ static float by_chunks(const A &a, int CH, bool fast, std::vector<std::pair<floa
             x[CH - 1] = 0.0f;
         }
         for (int j = 0; j < CH && j < sums; ++j) {
-            float &part = fast && j & 1 ? s2 : s;
+            float &part = !fast ? s : bit(&ChunkBits::bf, j) ? (j & 1 ? s4 : s3) : j & 1 ? s2 : s;
             part = part + x[j];
         }
         for (int j = 0; j < CH && k0 + j < A::kSlots; ++j)
@@ -47,7 +47,7 @@ static float by_chunks(const A &a, int CH, bool fast, std::vector<std::pair<floa
                 copies.push_back({a.dst[d], x[j]});
             }
     }
-    return s + s2;
+    return fast ? (s + s2) + (s3 + s4) : s;
 }
 
 template <int SLOTS, int COPIES>
@@ -55,7 +55,7 @@ static bool same(const SlotArgs &s, bool fast, float sum, float in_turn, const s
 {
     ChunkArgs<SLOTS, COPIES, false> a;
     std::memset(static_cast<void *>(&a), 0xff, sizeof a);
-    fill_chunk(s, 512, 99, a);
+    fill_chunk(s, fast, 512, 99, a);
     for (int CH : {8, 16, 32}) {
         std::vector<std::pair<float *, float>> got;
         const float t = by_chunks(a, CH, fast, got);
@@ -91,12 +91,13 @@ int main()
             else if (r || on) term = value(p, r);
             if (r || on) sum = sum + term;
         }
-        float part[2] = {0.0f, 0.0f};         // in any order: two sums that take the slots in turn
-        for (int k = 0; k < n; ++k) {
+        float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};     // in any order: the fp32 streams in turn, then the bf16 streams
+        int m = 0;
+        for (int type = 0; type < 2; ++type) for (int k = 0; k < n; ++k) {
             const bool bf = (s.slot[k] & kSlotBf16) != 0;
-            part[k & 1] += at((s.slot[k] & ~static_cast<unsigned long long>(kSlotTag)) + (s.h.e0 + 512) * (bf ? 2 : 4), bf);
+            if (bf == (type != 0)) part[2 * type + (m++ & 1)] += at((s.slot[k] & ~static_cast<unsigned long long>(kSlotTag)) + (s.h.e0 + 512) * (bf ? 2 : 4), bf);
         }
-        const float in_turn = part[0] + part[1];
+        const float in_turn = (part[0] + part[1]) + (part[2] + part[3]);
         while (n % kBurst) s.slot[n++] = 0x10000000ull | kSkip;
         s.h.n_sum = n;
         std::vector<std::pair<float *, float>> copies;

@@ -151,26 +151,30 @@ def test_a_run_longer_than_one_launch_of_chunks(eb):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("P,n", [(3, 40_003), (8, 300_007), (32, 50_001), (64, 140_001)])
-def test_any_order_is_as_close_as_two_sums(eb, dtype, P, n):
-    """A small round in fast order, every second process with a pending buffer: as far from the sum in 64 bits as
-    two sums in 32 bits that take the streams in turn, send buffer before gradient (a rounding more or less where the
-    halves meet: 1 %; adding the streams in pairs is 16 % off at 32 processes with bf16 gradients, 23 % at 64)."""
+@pytest.mark.parametrize("P,n", [(3, 90_003), (4, 300_003), (6, 60_001), (8, 300_007), (32, 50_001), (64, 140_001)])
+@pytest.mark.parametrize("pending", ["every second", "all but one", "first half"])
+def test_any_order_is_no_further_from_the_sum(eb, dtype, P, n, pending):
+    """A small round in fast order with pending buffers: no further from the sum in 64 bits than two sums in 32 bits
+    that take the streams in turn, send buffer before gradient, nor than one sum of pairs of neighbours.  (With fp32
+    gradients the three differ by up to 0.7 % either way, and that of n elements by less than 1 %: 2 %.)"""
     dev, tdt = torch.device("cuda:0"), torch.bfloat16 if dtype == "bf16" else torch.float32
     G = [wg.fill(torch.empty(n, dtype=tdt), 9, 0, p, 1e-3).to(dev) for p in range(P)]
     R = [wg.fill(torch.empty(n), 9, 1, p, 1e-3).to(dev) for p in range(P)]
     ctx = eb.Context(P, [0], [n], eb.BF16 if dtype == "bf16" else eb.F32, eb.ORDER_FAST)
-    pending = [p for p in range(P) if p % 2 == 0]
-    ctx.eager_set_valid(0, sum(1 << p for p in pending))
+    late = [p for p in range(P) if {"every second": p % 2 == 0, "all but one": p != 1, "first half": p < P // 2}[pending]]
+    ctx.eager_set_valid(0, sum(1 << p for p in late))
     recv = torch.empty(n, device=dev)
     ctx.eager_partial_allreduce(eb.make_plan(eb.MAJORITY, P, 0, (1 << P) - 1), G, R, recv=recv)
-    streams = [x for p in range(P) for x in ([R[p]] if p in pending else []) + [G[p]]]
-    part = [torch.zeros(n, device=dev) for _ in range(2)]
+    streams = [x for p in range(P) for x in ([R[p]] if p in late else []) + [G[p]]]
+    part = [torch.zeros(n, device=dev) for _ in range(3)]
     for k, x in enumerate(streams):
         part[k % 2] += x.float()
+    for k in range(0, len(streams), 2):
+        part[2] += streams[k].float() + streams[k + 1].float() if k + 1 < len(streams) else streams[k].float()
     exact = sum(x.double() for x in streams) / P
     error = lambda x: float((x.double() - exact).square().mean().sqrt())          # noqa: E731
-    assert error(recv) <= 1.01 * error((part[0] + part[1]) * torch.tensor(1.0 / P, device=dev))
+    inv = torch.tensor(1.0 / P, device=dev)
+    assert error(recv) <= 1.02 * min(error((part[0] + part[1]) * inv), error(part[2] * inv))
     ctx.close()
 
 
