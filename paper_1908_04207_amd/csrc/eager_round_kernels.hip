@@ -19,7 +19,8 @@
 //     with a branch per slot;
 //   * the accumulator stays in fp32 registers; in fixed-order mode contributions are added
 //     in ascending rank order from +0.0f with contraction off, so the result is defined
-//     bit for bit; fast mode keeps two partial sums that take the streams in turn;
+//     bit for bit; fast mode keeps two partial sums that take the streams in turn (chunk_kernel: two of
+//     fp32 streams and two of bf16 streams);
 //   * carry_kernel: the send-buffer rewrite of late processes as a plain pair-by-pair
 //     copy, when a round is split;
 //   * optional per-bucket norms as by-products of the same pass: DPP sums inside wavefronts,
