@@ -252,11 +252,12 @@ int partial_allreduce(eager_ctx *ctx, int want_mode, const eager_plan *plan, uin
         a.gload = split ? plan->mask : (plan->mask | late);
         a.store = split ? 0 : late;
         if (round_stats) {
-            a.stats.e0 = a.e0;
+            const int64_t back = eager::run_back(a.e0, a.n);     // records: one per tile of the launch
+            a.stats.e0 = a.e0 - back;
             a.stats.b_lo = b;
             a.stats.b_hi = e;
-            a.stats.n_records = eager::slot_records(a.n, ctx->bf16, ctx->launch.block);
-            a.stats.tail_count = eager::slot_tail(a.n, ctx->bf16);
+            a.stats.n_records = eager::slot_records(a.n + back, ctx->bf16, ctx->launch.block);
+            a.stats.tail_count = eager::slot_tail(a.n + back, ctx->bf16);
             a.stats.slices = stats_slices(ctx, b, e);
         }
         hipError_t he = eager::launch_round(a, ctx->bf16, ctx->fast, ctx->launch,

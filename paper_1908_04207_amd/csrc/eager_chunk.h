@@ -98,6 +98,8 @@ __device__ __forceinline__ ChunkBits read(const ChunkBits __attribute__((address
     return b;
 }
 
+__device__ __forceinline__ int form_of(const ChunkHead &h) { return h.form & ((1 << kFormBits) - 1); }
+
 // A word that the compiler must not connect with an earlier look at it: it would bring a load down to
 // where its value is used, next to the other branch that asks for the same slot.
 // (W, as a remark in the assembly, keeps the two widths' statements apart.)
@@ -135,8 +137,9 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
 {
     typedef typename Width<W>::type V;
     const unsigned lane = threadIdx.x & 63u, mine = at0 + lane;
-    const bool in = mine < end;
-    const unsigned at = in ? mine : end - 1u;
+    const unsigned begin = (static_cast<unsigned>(h.form) >> kFormBits) / W;       // (inside the first tile)
+    const unsigned up = mine > begin ? mine : begin, at = up < end ? up : end - 1u;
+    const bool in = at == mine;
     const unsigned off = at * (4u * W);
     const unsigned off_bf = W == 4 ? (at >> 1) * 16u : at * 2u;
     const bool odd = (at & 1u) != 0u;
@@ -226,7 +229,7 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
                     for (int j = 0; j < 8; ++j)
                         if (b.copy >> (g + j) & 1u) {
                             st_vec<W, NT>(to[j], off, x[g + j]);
-                            if (NT && W == 4 && CH == 16 && h.form == kPaced) __builtin_amdgcn_s_waitcnt(kStoresArrived);
+                            if (NT && W == 4 && CH == 16 && form_of(h) == kPaced) __builtin_amdgcn_s_waitcnt(kStoresArrived);
                         }
                 }
         }
@@ -250,10 +253,8 @@ __device__ __forceinline__ void chunk_body(K &a, const ChunkHead &h, const unsig
         if constexpr (W == 4) {
             long long stop;
             const int b = tile_bucket(a.stats.table, a.stats.b_lo, a.stats.b_hi, a.first + at0 * 4ll, e, stop);
-            if (in) {
-                ls.bucket = b;
-                n_valid = inside(e, stop);
-            }
+            if (mine < end) ls.bucket = b;             // (in front of the run: the bucket of its first element)
+            if (in) n_valid = inside(e, stop);
         } else {
             ls.bucket = find_bucket(a.stats.table, a.stats.n_buckets, e);
             if (e < a.stats.table[2 * ls.bucket + 1]) n_valid = 1;
@@ -347,7 +348,7 @@ __global__ __launch_bounds__(256) void chunk_kernel(const ARGS)
     const unsigned wave = bid * static_cast<unsigned>(h.waves_per_block) +
                           static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
     unsigned first = wave * 64u;
-    if (h.form != kNarrow) {
+    if (form_of(h) != kNarrow) {
         const unsigned nvec = BF16 ? h.n / 8u * 2u : h.n / 4u, tiles = (nvec + 63u) / 64u;
         if (wave < tiles) {
             chunk_body<4, CH, BF16, FAST, NT, NTS, OPT, STATS>(a, h, slot, first, nvec, wave);
@@ -375,12 +376,12 @@ hipError_t launch_segments(const SlotArgs &s, A &a, int bpc, const Launch &cfg, 
         const long long n = std::min(s.h.n - first, kChunkElements);
         fill_chunk(s, FAST, first, n, a);
         const bool narrow = chunk_narrow(s.h.n, a.h.n_slots, s.h.n_copy, BF16, STATS, cfg.chunk);
-        a.h.form = narrow ? kNarrow : kWide;
+        a.h.form |= narrow ? kNarrow : kWide;
         if constexpr (NT && CH == 16)
             if (!narrow && chunk_paced(s, a.h.n_slots, BF16, OPT, 32)) {
                 // (the kernel is asked for its registers once, and only where all else speaks for it)
                 static const int resident = kernel_waves(chunk_kernel<BF16, FAST, NT, NTS, OPT, STATS, CH, A>);
-                if (chunk_paced(s, a.h.n_slots, BF16, OPT, resident)) a.h.form = kPaced;
+                if (chunk_paced(s, a.h.n_slots, BF16, OPT, resident)) a.h.form |= kPaced;
             }
         const long long g = narrow ? (n + cfg.block - 1) / cfg.block : round_workgroups(n, BF16, cfg.block);
         a.h.waves_per_block = per;

@@ -143,6 +143,7 @@ struct SlotHead {
     float *w, *v, *recv;
     float inv_P, neg_lr, mu, wd;
     int nesterov;
+    int skip;                          // lane-vectors of the first tile that stand before the run (run_back)
 };
 struct SlotArgs {
     SlotHead h;
@@ -167,13 +168,16 @@ constexpr long long kChunkElements = 1ll << 29;   // of one launch, for the 32-b
 enum ChunkForm : int {
     kWide,                                // a lane owns four elements
     kNarrow,                              // one
-    kPaced                                // four, and a copy's store waits for the one before it
+    kPaced,                               // four, and a copy's store waits for the one before it
+    kFormBits = 2
 };
 struct ChunkHead {
     float *w, *v, *recv;
     unsigned n;                           // elements
     int n_sum, n_slots, dst_first;
-    int form;                             // ChunkForm
+    int form;                             // ChunkForm; above its bits, the elements of the first tile that stand
+                                          // before the run (a word of their own moved all that follows by 8
+                                          // bytes: 0.2 us more for each launch of 12 slots or more)
     int waves_per_block, xcd_blocks;
     float inv_P, neg_lr, mu, wd;
     int nesterov;
@@ -206,6 +210,7 @@ struct CarryArgs {
     int count;                   // number of pairs
     long long e0;                // first element of the run
     long long n;                 // elements in the run
+    int skip;                    // (launcher) lane-vectors at e0 that stand before it, see run_back
 };
 
 // A gradient finished after its round: R <- G (empty send buffer) or R <- R + G.

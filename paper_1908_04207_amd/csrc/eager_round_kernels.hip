@@ -42,14 +42,15 @@ namespace {
 // never a branch around a load.
 //
 // Addresses are a uniform base (stream + first element of the tile) plus a 32-bit offset of the
-// lane.  Lanes beyond the last lane-vector repeat it: their loads stay inside the run and their
-// results are never stored.
+// lane.  Lanes beyond the last lane-vector or before the first repeat it: their loads stay inside the run
+// and their results are never stored.
 struct Lanes {
     long long e0;          // first element of the tile (arena index), uniform
     unsigned off;          // byte offset of the lane-vector in an fp32 stream
     unsigned off_bf;       // byte offset of the 16-byte piece of a bf16 stream that holds it
     bool odd;              // the lane-vector is the upper half of that piece
     bool in;               // the lane-vector belongs to the run
+    bool held;             // it does, or stands in front of it
 };
 
 // 16 bytes of a slot's stream (raw: a bf16 stream is widened by slot_value).  For a SKIP every
@@ -212,7 +213,7 @@ __device__ __forceinline__ SlotHead read_head(KSlotArgs &a)
     __builtin_memcpy(&h, (const void __attribute__((address_space(4))) *)&a.h, sizeof h);
     asm volatile("" : "+s"(h.e0), "+s"(h.n), "+s"(h.n_sum), "+s"(h.n_copy), "+s"(h.waves_per_block),
                  "+s"(h.xcd_blocks), "+s"(h.w), "+s"(h.v), "+s"(h.recv), "+s"(h.inv_P), "+s"(h.neg_lr),
-                 "+s"(h.mu), "+s"(h.wd), "+s"(h.nesterov));
+                 "+s"(h.mu), "+s"(h.wd), "+s"(h.nesterov), "+s"(h.skip));
     return h;
 }
 
@@ -234,10 +235,12 @@ __device__ __forceinline__ Lanes place_lanes(const SlotHead &h, long long tile, 
     const unsigned lane = threadIdx.x & 63u;
     const long long left = nvec - tile * 64;                   // uniform, > 0
     const unsigned last = left > 64 ? 63u : static_cast<unsigned>(left) - 1u;
-    const unsigned lv = lane < last ? lane : last;
+    const unsigned first = tile == 0 ? static_cast<unsigned>(h.skip) : 0u;
+    const unsigned up = lane > first ? lane : first, lv = up < last ? up : last;
     Lanes L;
     L.e0 = h.e0 + tile * 256;
-    L.in = lane <= last;
+    L.held = lane <= last;
+    L.in = lv == lane;
     L.off = lv * 16u;
     L.off_bf = (lv >> 1) * 16u;
     L.odd = (lv & 1u) != 0;
@@ -250,7 +253,7 @@ __device__ __forceinline__ int place_stats(KSlotArgs &a, const Lanes &L, LaneSta
     const long long e = L.e0 + (L.off >> 2);
     long long end;
     const int b = tile_bucket(a.stats.table, a.stats.b_lo, a.stats.b_hi, L.e0, e, end);
-    ls = {0.0, 0.0, 0u, L.in ? b : -1};
+    ls = {0.0, 0.0, 0u, L.held ? b : -1};       // (in front of the run: the bucket of its first element)
     return L.in ? inside(e, end) : 0;
 }
 
@@ -354,7 +357,7 @@ __global__ __launch_bounds__(256) void carry_kernel(const CarryArgs a)
 #pragma unroll
     for (int k = 0; k < V; ++k) {
         const long long vi = base + static_cast<long long>(k) * blockDim.x;
-        if (vi < nvec) {
+        if (vi >= a.skip && vi < nvec) {
             const long long e = a.e0 + vi * 4;
             if (BF16) {
                 const u32x2 g = __builtin_nontemporal_load(
@@ -371,7 +374,7 @@ __global__ __launch_bounds__(256) void carry_kernel(const CarryArgs a)
 #pragma unroll
     for (int k = 0; k < V; ++k) {
         const long long vi = base + static_cast<long long>(k) * blockDim.x;
-        if (vi < nvec) st_f4<true>(dst + a.e0 + vi * 4, x[k]);
+        if (vi >= a.skip && vi < nvec) st_f4<true>(dst + a.e0 + vi * 4, x[k]);
     }
     const long long rem = a.n - nvec * 4;
     if (blockIdx.x == 0 && static_cast<long long>(threadIdx.x) < rem) {
@@ -413,8 +416,10 @@ void build_slots(const RoundArgs &a, SlotArgs &s)
     s.h.w = a.w;
     s.h.v = a.v;
     s.h.recv = a.recv;
-    s.h.e0 = a.e0;
-    s.h.n = a.n;
+    const long long back = run_back(a.e0, a.n);
+    s.h.e0 = a.e0 - back;
+    s.h.n = a.n + back;
+    s.h.skip = static_cast<int>(back / 4);
     s.h.inv_P = a.inv_P;
     s.h.neg_lr = a.neg_lr;
     s.h.mu = a.mu;
@@ -531,9 +536,14 @@ hipError_t launch_carry_t(const CarryArgs &a, const Launch &cfg, hipStream_t str
     }
 }
 
-hipError_t launch_carry(const CarryArgs &a, bool bf16, const Launch &cfg, hipStream_t stream)
+hipError_t launch_carry(const CarryArgs &args, bool bf16, const Launch &cfg, hipStream_t stream)
 {
-    if (a.n <= 0 || a.count <= 0) return hipSuccess;
+    if (args.n <= 0 || args.count <= 0) return hipSuccess;
+    CarryArgs a = args;
+    const long long back = run_back(a.e0, a.n);
+    a.e0 -= back;
+    a.n += back;
+    a.skip = static_cast<int>(back / 4);
     return bf16 ? launch_carry_t<true>(a, cfg, stream) : launch_carry_t<false>(a, cfg, stream);
 }
 

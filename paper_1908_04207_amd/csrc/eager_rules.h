@@ -23,6 +23,19 @@ constexpr long long kMaxGridThreads = 1ll << 31;
 constexpr long long kMaxRoundThreads = kMaxGridThreads + 256;
 constexpr long long kMaxRunElements = 1ll << 33;
 
+// Elements by which a launch steps back from the first element of its run: its tiles then begin at multiples
+// of 64 elements of the arena - whole cache lines of 128 bytes, of bf16 streams too, where the arena begins at
+// one - and the first tile leaves out what stands before the run.  Buckets begin at any 16 bytes.  A tile that does not
+// begin at a line shares lines with the next one, which another XCD reads and writes: both fetch it, and
+// both write a part of it.  (Ranges that begin 32 bytes behind a line, time over that of the bytes and a launch, before
+// and now: 8 processes, 4 late, 0.5, 1, 4 and 8 M elements 1.24 1.17 1.13 1.05 and 1.16 1.09 1.05 0.98; 12, 11 late, 1.26 1.17
+// 1.12 1.11 and 1.14 1.07 1.04 1.02; bf16, 16, 8 late, 1.38 1.25 1.20 1.14 and 1.26 1.16 1.11 1.05.)
+constexpr long long kTileAlign = 64, kAlignFrom = 1024;
+inline long long run_back(long long e0, long long n)
+{
+    return n < kAlignFrom || n > kMaxRunElements - kTileAlign ? 0 : e0 % kTileAlign;
+}
+
 // Workgroups of a round over n elements: a wavefront per tile, one more for the ragged tail.
 inline long long round_workgroups(long long n, bool bf16, int block)
 {
@@ -111,6 +124,7 @@ void fill_chunk(const SlotArgs &s, bool any_order, long long first, long long n,
     a.h.mu = s.h.mu;
     a.h.wd = s.h.wd;
     a.h.nesterov = s.h.nesterov;
+    a.h.form = first == 0 ? s.h.skip * 4 << kFormBits : 0;
     for (ChunkBits &b : a.bits) b = ChunkBits{0u, 0u, 0u, 0u};
     int k = 0;
     auto push = [&](unsigned long long slot, unsigned ChunkBits::*what) {
