@@ -27,7 +27,8 @@ MARSHAL_STAMP = MARSHAL + ".srchash"
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ["eager_round_kernels.hip", "eager_chunk_f32.hip", "eager_chunk_f32_stats.hip", "eager_chunk_bf16.hip",
            "eager_chunk_bf16_stats.hip", "eager_chunk_f32_fast.hip", "eager_chunk_f32_fast_stats.hip",
-           "eager_chunk_bf16_fast.hip", "eager_chunk_bf16_fast_stats.hip", "eager_aux_kernels.hip", "eager_static_kernels.hip",
+           "eager_chunk_bf16_fast.hip", "eager_chunk_bf16_fast_stats.hip", "eager_short_f32.hip", "eager_short_f32_fast.hip",
+           "eager_short_bf16.hip", "eager_short_bf16_fast.hip", "eager_aux_kernels.hip", "eager_static_kernels.hip",
            "eager_calib_kernels.hip", "eager_api.cpp"]
 
 # -ffp-contract=off: the fixed-order mode defines every rounding; fused multiply-adds are

@@ -202,6 +202,28 @@ struct ChunkArgs<SLOTS, COPIES, true> : ChunkArgs<SLOTS, COPIES, false> {
 };
 constexpr int kChunkFewSlots = 32, kChunkFewCopies = 16;
 
+// A small round whose list is short, as its own kernel takes it (eager_short.h): all that a wavefront needs is 192 or
+// 256 bytes, whole lines of the scalar cache that a few loads bring into registers, and the host copies no more than
+// that to the device.  Bases are those of the launch's first element and the sum stands before the copies as in
+// ChunkArgs.  Of 8 slots, slot k is copied to dst[k]; of 16, the copies stand in the second half - right behind the sum, or
+// from slot 8 on where it is shorter - and slot k is copied to dst[k - 8]: every index is one that the compiler knows.
+//   shape   slots of the sum, from bit 8 all slots (of 8) or those of the second half (of 16), Nesterov bit 16, ChunkForm from
+//           bit 17, from bit 24 on the elements of the first tile that stand before the run
+//   bits    of slot k: bit k as `pair`, bit 16 + k as `bf` of ChunkBits
+//   copies  bit k: slot k is copied
+constexpr int kShortForm = 17, kShortSkip = 24, kShortCopies = 8;
+template <int SLOTS>
+struct alignas(64) ShortArgs {
+    static constexpr int kHalf = SLOTS - 8;    // slot k is copied to dst[k - kHalf]
+    float *w, *v, *recv;
+    unsigned n, shape, bits, copies;
+    float inv_P, neg_lr, mu, wd;
+    unsigned unused[2];
+    unsigned long long slot[SLOTS];
+    float *dst[kShortCopies];
+};
+static_assert(sizeof(ShortArgs<8>) == 192 && sizeof(ShortArgs<16>) == 256, "whole lines");
+
 // The carry as a kernel of its own: R_p <- G_p for every late process, one (source,
 // destination) pair after the other.
 struct CarryArgs {
@@ -267,6 +289,9 @@ typedef hipError_t ChunkLauncher(const SlotArgs &s, bool nt, bool nts, bool eigh
                                  hipStream_t st);
 ChunkLauncher launch_chunk_f32, launch_chunk_f32_stats, launch_chunk_bf16, launch_chunk_bf16_stats;
 ChunkLauncher launch_chunk_f32_fast, launch_chunk_f32_fast_stats, launch_chunk_bf16_fast, launch_chunk_bf16_fast_stats;
+// the round with a short list (see short_round), bursts of 8 slots or 16; nt: streams nontemporal
+typedef hipError_t ShortLauncher(const SlotArgs &s, bool nt, hipStream_t st);
+ShortLauncher launch_short_f32, launch_short_f32_fast, launch_short_bf16, launch_short_bf16_fast;
 hipError_t launch_carry(const CarryArgs &a, bool bf16, const Launch &cfg, hipStream_t stream);
 hipError_t launch_stats_finish(const StatsArgs &a, hipStream_t stream);
 long long slot_records(long long n, bool bf16, int block);   // tiles of a round, one record each

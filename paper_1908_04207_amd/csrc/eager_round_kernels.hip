@@ -456,6 +456,12 @@ hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStre
     if (cfg.chunk == 0 && !small && !late_in_recv)
         return stats ? launch_capped(burst_kernel<BF16, FAST, NTS, OPT, true>, s, bpc, cfg, grid, st)
                      : launch_capped(burst_kernel<BF16, FAST, NTS, OPT, false>, s, bpc, cfg, grid, st);
+    // (launch options are for the general kernel)
+    if (cfg.chunk == 0 && small && cfg.block == 64 && !cfg.xcd_map && bpc < 0 && !NTS && short_round(s)) {
+        ShortLauncher *const f = BF16 ? (FAST ? launch_short_bf16_fast : launch_short_bf16)
+                                      : (FAST ? launch_short_f32_fast : launch_short_f32);
+        return f(s, !plain, st);
+    }
     // (8-slot chunks with by-products serve the rule's own choice of short lists; as a launch option
     // that pair has always been refused, by the caller with a message of its own)
     if (stats && cfg.chunk == 8) return hipErrorInvalidValue;

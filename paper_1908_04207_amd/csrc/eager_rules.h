@@ -4,6 +4,8 @@
 
 #include "eager_internal.h"
 
+#include <algorithm>
+
 namespace eager {
 
 constexpr int kCus = 256;
@@ -104,6 +106,14 @@ inline bool small_round(const SlotArgs &s, long long bytes_per_element)
 // 9.9 and 10.6 at 40 MiB, 14.1 and 13.6 at 64.
 constexpr long long kPlainRoundBytes = 56ll << 20;
 
+// Slots of the sum without what fills them up.
+inline int sum_terms(const SlotArgs &s)
+{
+    int n = s.h.n_sum;
+    while (n > 0 && (s.slot[n - 1] & kKindMask) == kSkip) --n;
+    return n;
+}
+
 // The same round for the kernel of small runs: elements [first, first + n) of the run.  `A` has room for
 // the list (slots that fill it up are left out).
 inline bool chunk_fits(const SlotArgs &s, int slots, int copies)
@@ -136,8 +146,7 @@ void fill_chunk(const SlotArgs &s, bool any_order, long long first, long long n,
         a.slot[k++] = (slot & ~static_cast<unsigned long long>(kSlotTag)) +
                       static_cast<unsigned long long>(e) * (bf ? 2 : 4);
     };
-    int terms = s.h.n_sum;
-    while (terms > 0 && (s.slot[terms - 1] & kKindMask) == kSkip) --terms;
+    const int terms = sum_terms(s);
     auto term = [&](int j) {
         const unsigned kind = static_cast<unsigned>(s.slot[j]) & kKindMask;
         push(s.slot[j], kind == kAdd ? nullptr : kind == kPair ? &ChunkBits::pair : &ChunkBits::hold);
@@ -157,6 +166,58 @@ void fill_chunk(const SlotArgs &s, bool any_order, long long first, long long n,
     }
     a.h.n_slots = k;
     a.h.first = a.bits[0];
+}
+
+// Whether a small run goes to the kernel of short lists: it was ahead of chunk_kernel wherever both can take the list
+// (eager_short.h has the times).  (Statistics have arguments of their own; a launch is within 32-bit offsets.)
+inline bool short_round(const SlotArgs &s)
+{
+    return !s.stats.stats && sum_terms(s) + s.h.n_copy <= 16 && s.h.n_copy <= kShortCopies && s.h.n <= kChunkElements;
+}
+template <int SLOTS>
+void fill_short(const SlotArgs &s, bool any_order, int form, ShortArgs<SLOTS> &a)
+{
+    const long long e = s.h.e0;
+    auto at = [e](float *p) { return p ? p + e : nullptr; };
+    a.w = at(s.h.w);
+    a.v = at(s.h.v);
+    a.recv = at(s.h.recv);
+    a.n = static_cast<unsigned>(s.h.n);
+    a.inv_P = s.h.inv_P;
+    a.neg_lr = s.h.neg_lr;
+    a.mu = s.h.mu;
+    a.wd = s.h.wd;
+    auto base = [e](unsigned long long slot) {
+        return (slot & ~static_cast<unsigned long long>(kSlotTag)) + static_cast<unsigned long long>(e) * (slot & kSlotBf16 ? 2 : 4);
+    };
+    const int terms = sum_terms(s);
+    unsigned bits = 0u;
+    int k = 0;
+    auto term = [&](int j) {
+        const unsigned long long slot = s.slot[j];
+        bits |= ((slot & kKindMask) == kPair ? 1u << k : 0u) | (slot & kSlotBf16 ? 0x10000u << k : 0u);
+        a.slot[k++] = base(slot);
+    };
+    if (any_order) {                 // all fp32 streams before the bf16 ones
+        for (int j = 0; j < terms; ++j)
+            if (!(s.slot[j] & kSlotBf16)) term(j);
+        for (int j = 0; j < terms; ++j)
+            if (s.slot[j] & kSlotBf16) term(j);
+    } else {
+        for (int j = 0; j < terms; ++j) term(j);
+    }
+    const int first = std::max(terms, a.kHalf);           // of the copies
+    k = first;
+    for (int j = 0; j < s.h.n_copy; ++j) {
+        const unsigned long long slot = s.slot[s.h.n_sum + j];
+        a.dst[k - a.kHalf] = s.dst[s.h.n_sum + j] + e;
+        bits |= slot & kSlotBf16 ? 0x10000u << k : 0u;
+        a.slot[k++] = base(slot);
+    }
+    a.bits = bits;
+    a.copies = (1u << k) - (1u << first);
+    a.shape = static_cast<unsigned>(terms | (k - a.kHalf) << 8 | (s.h.nesterov ? 1 << 16 : 0) | form << kShortForm) |
+              static_cast<unsigned>(s.h.skip * 4) << kShortSkip;
 }
 
 // Whether a lane of such a launch owns one element and not four: four times the wavefronts with a

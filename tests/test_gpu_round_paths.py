@@ -78,6 +78,16 @@ def test_one_element_to_a_lane(eb, dtype, P, n):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("n", [3, 64, 257, 4099, 131_072, 131_081, 262_147])
+def test_short_lists_of_every_length(eb, dtype, order, n):
+    """1 to 16 streams, one element to a lane and four: 16 as 8 pairs, 15 with 7 copies, copies behind a sum of one slot
+    and behind one of nine, exactly 8."""
+    pair = Pair(eb, 8, [0], [n], (n + 7) // 8 * 8, dtype, order, seed=n % 89)
+    _rounds(eb, pair, [1, 255, 1, 2, 255, 0b1111, 255 & ~0b11, 0b10101010, 255, 0b11111110], order, n)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("form", ["narrow", "chunks of 8", "chunks of 16", "bursts"])
 def test_signed_zeros_and_infinities_in_every_form(eb, dtype, form):
     """Late, late again with a pending buffer, on time with one (a pair), everybody on time: gradients, pending

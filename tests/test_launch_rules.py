@@ -29,6 +29,17 @@ def test_chunk_lists_on_the_host(tmp_path):
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.stdout[-500:], r.stderr[-2000:])
 
 
+def test_short_lists_on_the_host(tmp_path):
+    """The list that short_kernel takes, in the same way."""
+    exe = tmp_path / "short_list_host"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined",
+                           "-fno-sanitize-recover=all", "-static-libasan", "-ffp-contract=off", "-Wall", "-Wextra",
+                           "-Werror", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include",
+                           os.path.join(ROOT, "tests", "c", "short_list_host.cpp"), "-o", str(exe)])
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", (r.stdout[-500:], r.stderr[-2000:])
+
+
 @pytest.mark.parametrize("wrong", [0, 1, 2, 3])
 def test_launches_take_a_kernel_with_arguments_of_its_own_types(wrong):
     from paper_1908_04207_amd import build
