@@ -67,8 +67,7 @@ uint64_t initiator_hash(uint64_t seed, uint64_t step)
 // wavefronts a round kernel may be launched with over the whole arena, whatever the block size
 int64_t max_records(const eager_ctx *ctx)
 {
-    const int64_t span = ctx->offset.back() + ctx->numel.back() - ctx->offset.front();
-    return span / 256 + 8;
+    return eager::stats_tiles(ctx->offset.front(), ctx->offset.back() + ctx->numel.back());
 }
 
 // Fills the parts of the statistics arguments that do not depend on the run: where the bucket

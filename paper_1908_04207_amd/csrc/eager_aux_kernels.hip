@@ -14,13 +14,10 @@ namespace {
 // Adds the plain records (one per tile whose elements all lie in one bucket) with index in
 // [lo, hi) that belong to bucket b: 8 independent loads per thread in flight, wavefront sums by
 // DPP, the wavefronts of the workgroup through LDS.  The totals arrive in wavefront 0.  What
-// bounds it is latency, so that the number of trips counts: 1024 threads take 8192 records in one
-// (stats_slice_kernel), the 832 of them that add records in stats_finish_kernel 6656, 256 threads
-// 2048; of norms_kernel's groups of records half as many, each 8 tiles.
+// bounds it is latency, so that the number of trips counts: the 832 threads that add records of 1024 take
+// 6656 records in one, 256 threads 2048; of norms_kernel's groups of records half as many, each 8 tiles.
 // Records of norms_kernel come in groups of kNormsTiles: the first of a group holds the sums of
 // all, unless it is flagged - then every tile of the group has a record of its own.
-constexpr int kNormsTiles = 8;
-
 // All of a record has been asked for before any of it is looked at: left alone the compiler moves the
 // loads of the sums behind the branch on the bucket, a trip to memory after the other.
 __device__ __forceinline__ void whole(StatsRecord &r)
@@ -34,7 +31,7 @@ __device__ __forceinline__ StatsArgs at_once(const StatsArgs &from)
 {
     StatsArgs a = from;
     asm volatile("" : "+s"(a.e0), "+s"(a.n_records), "+s"(a.b_lo), "+s"(a.n_buckets), "+s"(a.tail_count),
-                 "+s"(a.slices), "+s"(a.want_rate), "+s"(a.trust), "+s"(a.eps), "+s"(a.wd));
+                 "+s"(a.slices), "+s"(a.per_slice), "+s"(a.want_rate), "+s"(a.trust), "+s"(a.eps), "+s"(a.wd));
     return a;
 }
 
@@ -102,6 +99,10 @@ __device__ __forceinline__ void workgroup_sum(double &su, double &sw, double &nf
     }
 }
 
+// A value that another workgroup reads or has written in the same launch.
+__device__ __forceinline__ void put(double *p, double x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ double get(const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 // records of bucket b: [w0, w1)
 __device__ __forceinline__ void bucket_records(const StatsArgs &a, int b, long long &w0, long long &w1)
 {
@@ -112,42 +113,29 @@ __device__ __forceinline__ void bucket_records(const StatsArgs &a, int b, long l
     if (w1 > a.n_records) w1 = a.n_records;
 }
 
-// First stage for buckets with many records (a flat model is ONE bucket: millions of records):
-// workgroup (bucket, slice) adds one slice of the bucket's plain records and leaves a partial.
-template <bool GROUPED, int THREADS>
-__global__ __launch_bounds__(THREADS) void stats_slice_kernel(const StatsArgs args)
-{
-    const StatsArgs a = at_once(args);
-    const int b = a.b_lo + static_cast<int>(blockIdx.x);
-    const int s = static_cast<int>(blockIdx.y);
-    long long w0, w1;
-    bucket_records(a, b, w0, w1);
-    // slices begin at whole groups of records
-    const long long len = ((w1 - w0 + a.slices - 1) / a.slices + kNormsTiles - 1) / kNormsTiles * kNormsTiles;
-    const long long first = w0 / kNormsTiles * kNormsTiles;
-    const long long lo = s == 0 ? w0 : first + s * len;
-    const long long hi = s + 1 == a.slices || first + (s + 1) * len > w1 ? w1 : first + (s + 1) * len;
-    double su = 0.0, sw = 0.0, nf = 0.0;
-    add_records<THREADS, GROUPED>(a.records, lo, hi, b, su, sw, nf);
-    workgroup_sum<THREADS>(su, sw, nf);
-    if (threadIdx.x == 0) {
-        // a slice holds at most 2^33 / 256 / slices records of 256 elements: the count fits
-        const StatsRecord out = {su, sw, b, static_cast<unsigned>(nf), 0};
-        a.partials[static_cast<long long>(b) * kStatsMaxSlices + s] = out;
-    }
-}
-
-// One workgroup per bucket of the run: adds the records of the wavefronts whose 256 elements
-// touch the bucket (they are consecutive) - a uniform wavefront's sums (or the partials of the
-// first stage), a mixed wavefront's lane records of this bucket - and the records of the ragged
-// tail; one thread writes the bucket's totals.
+// The sums of a bucket: the records of the wavefronts whose 256 elements touch the bucket (they are
+// consecutive) - a uniform wavefront's sums, a mixed wavefront's lane records of this bucket - and the records of the
+// ragged tail; one thread writes the bucket's totals.  One workgroup per bucket (blockIdx.x) and slice of its records
+// (blockIdx.y, see launch_stats_finish).  Where there are several, each leaves a partial, and the last to arrive adds
+// them, in the order of the slices: the totals do not depend on who that is.  Partials and count are written
+// and read past the caches of an XCD (agent scope); a partial has arrived in memory before its workgroup counts itself.
 template <bool GROUPED, int THREADS>
 __global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs args)
 {
     const StatsArgs a = at_once(args);
-    const int b = a.b_lo + static_cast<int>(blockIdx.x);
+    const int b = a.b_lo + static_cast<int>(blockIdx.x), slice = static_cast<int>(blockIdx.y);
     long long w0, w1;
     bucket_records(a, b, w0, w1);
+    // slices begin at whole groups of records
+    const long long head = w0 / kNormsTiles * kNormsTiles;
+    int slices = 1;
+    if (a.slices > 1) {                   // (a division, and a run has at most 2^25 records)
+        const unsigned per = static_cast<unsigned>(a.per_slice), count = (static_cast<unsigned>(w1 - head) + per - 1u) / per;
+        slices = static_cast<int>(count < 1u ? 1u : count < static_cast<unsigned>(a.slices) ? count : a.slices);
+        if (slice >= slices) return;
+    }
+    const long long lo = slice == 0 ? w0 : head + static_cast<long long>(slice) * a.per_slice;
+    const long long hi = slice + 1 == slices ? w1 : head + (slice + 1ll) * a.per_slice;
     double su = 0.0, sw = 0.0, nf = 0.0;
     // Only the first and the last wavefront of the bucket can be mixed.  The lane records of the
     // first, those of the last and the ragged tail are read by a wavefront each (one lane per
@@ -157,17 +145,8 @@ __global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs a
     constexpr int kPlain = kApart ? THREADS - 3 * 64 : THREADS;
     const int wave = static_cast<int>(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int which = kApart ? wave - kPlain / 64 : wave;
-    if (!kApart || which < 0) {
-        if (a.slices == 1) {
-            add_records<kPlain, GROUPED>(a.records, w0, w1, b, su, sw, nf);
-        } else if (static_cast<int>(threadIdx.x) < a.slices) {
-            const StatsRecord r = a.partials[static_cast<long long>(b) * kStatsMaxSlices + threadIdx.x];
-            su = r.ssu;
-            sw = r.ssw;
-            nf = r.nf;
-        }
-    }
-    if (which == 0 || which == 1) {
+    if (!kApart || which < 0) add_records<kPlain, GROUPED>(a.records, lo, hi, b, su, sw, nf);
+    if (slice == 0 && (which == 0 || which == 1)) {
         const long long t = which == 0 ? w0 : w1 - 1;
         // Tile t has lane records where this bucket or the next begins inside it, or where the run ends there.
         // (Asked for without a look at that, those of buckets that have their tiles to themselves were 2 KiB a bucket
@@ -195,7 +174,7 @@ __global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs a
                 }
             }
         }
-    } else if (which == 2 && lane < a.tail_count) {
+    } else if (slice == 0 && which == 2 && lane < a.tail_count) {
         StatsRecord tr = a.lane_records[static_cast<long long>(a.n_buckets) * 64 + lane];
         whole(tr);
         if (tr.bucket == b) {
@@ -205,7 +184,29 @@ __global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs a
         }
     }
     workgroup_sum<THREADS>(su, sw, nf);
-    if (threadIdx.x == 0) {
+    if (wave != 0) return;
+    if (slices > 1) {
+        StatsRecord *part = a.partials + static_cast<long long>(b) * kStatsMaxSlices;
+        unsigned before = 0u;
+        if (lane == 0) {
+            put(&part[slice].ssu, su);
+            put(&part[slice].ssw, sw);
+            put(reinterpret_cast<double *>(&part[slice].bucket), nf);     // (the count of a partial, in 64 bits)
+            asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+            // (it begins again at zero by itself)
+            before = __builtin_amdgcn_atomic_inc32(reinterpret_cast<unsigned *>(&part->flag), static_cast<unsigned>(slices) - 1u,
+                                                   __ATOMIC_RELAXED, "agent");
+        }
+        if (__builtin_amdgcn_readfirstlane(static_cast<int>(before)) != slices - 1) return;
+        asm volatile("" : : : "memory");
+        const bool has = lane < slices;
+        su = has ? get(&part[lane].ssu) : 0.0;
+        sw = has ? get(&part[lane].ssw) : 0.0;
+        nf = has ? get(reinterpret_cast<const double *>(&part[lane].bucket)) : 0.0;
+        wave_sums(su, sw);
+        if (__builtin_amdgcn_ballot_w64(nf != 0.0) != 0ull) nf = wave_sum(nf);
+    }
+    if (lane == 0) {
         BucketStats out;
         out.sumsq_update = su;
         out.sumsq_params = sw;
@@ -589,35 +590,20 @@ int views_average_waves(int n_views)
 
 }  // namespace
 
-namespace {
-template <bool GROUPED, int THREADS>
-hipError_t launch_finish(const StatsArgs &a, int n, hipStream_t stream)
-{
-    const dim3 threads(THREADS);
-    if (a.slices > 1) {
-        const hipError_t e = launch(stats_slice_kernel<GROUPED, THREADS>, dim3(n, a.slices), threads, 0, stream, a);
-        if (e != hipSuccess) return e;
-    }
-    return launch(stats_finish_kernel<GROUPED, THREADS>, dim3(n), threads, 0, stream, a);
-}
-}  // namespace
-
 hipError_t launch_stats_finish(const StatsArgs &args, hipStream_t stream)
 {
     const int n = args.b_hi - args.b_lo;
     if (n <= 0) return hipSuccess;
     if (args.slices > kStatsMaxSlices || args.slices < 1) return hipErrorInvalidValue;
     StatsArgs a = args;
-    // One workgroup per bucket takes two trips to memory for 12 k records (ResNet-50, 161 buckets of up
-    // to 9 k records: 6.7 us in one launch, 9.9 us with a first stage); with more the first stage
-    // is worth its launch (262 k records: 9.5 us, 42 us without).  Groups of norms_kernel count once.
     const bool grouped = a.want_rate && norms_grouped(a.n_records, n), wide = finish_threads(n) == 1024;
-    if (grouped) {
-        a.slices = a.slices <= 12 ? 1 : (a.slices + kNormsTiles - 1) / kNormsTiles;
-        return wide ? launch_finish<true, 1024>(a, n, stream) : launch_finish<true, 256>(a, n, stream);
-    }
-    if (a.slices <= 3) a.slices = 1;
-    return wide ? launch_finish<false, 1024>(a, n, stream) : launch_finish<false, 256>(a, n, stream);
+    finish_slices(a, n);
+    const dim3 grid(static_cast<unsigned>(n), static_cast<unsigned>(a.slices)), threads(wide ? 1024 : 256);
+    if (grouped)
+        return wide ? launch(stats_finish_kernel<true, 1024>, grid, threads, 0, stream, a)
+                    : launch(stats_finish_kernel<true, 256>, grid, threads, 0, stream, a);
+    return wide ? launch(stats_finish_kernel<false, 1024>, grid, threads, 0, stream, a)
+                : launch(stats_finish_kernel<false, 256>, grid, threads, 0, stream, a);
 }
 
 hipError_t launch_stash(const StashArgs &a, bool bf16, hipStream_t stream)

@@ -141,9 +141,9 @@ __device__ __forceinline__ float load_grad_scalar(const void *g, long long i)
 // place on this path where cross-lane work belongs: a lane sums its 4 elements, the 64 lanes
 // of a wavefront are combined with DPP moves inside rows of 16 lanes and lane reads across
 // the 4 rows, and one lane writes one record per wavefront.  A wavefront whose elements lie in
-// several buckets leaves one record per lane instead.  No atomics anywhere and fixed trees:
-// the result is reproducible bit for bit.  A finishing kernel adds the records of a bucket,
-// combining the wavefronts of its workgroup through LDS.
+// several buckets leaves one record per lane instead.  A finishing kernel adds the records of a bucket,
+// combining the wavefronts of its workgroup through LDS and several workgroups through memory.  Fixed trees, whoever
+// arrives last: the result is reproducible bit for bit.
 struct LaneStats {
     double ssu, ssw;   // squares of the update / of the old parameters
     unsigned nf;       // non-finite elements of the update

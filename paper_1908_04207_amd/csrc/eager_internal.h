@@ -55,17 +55,21 @@ struct StatsArgs {
     // trust * |w| / (|u| + wd * |w| + eps), or 1 where a norm is zero
     int want_rate;
     float trust, wd, eps;
-    // A bucket with many records is added up by `slices` workgroups first, one partial each
-    // (partials[bucket * kStatsMaxSlices + slice]); 1: the finishing kernel reads the records.
+    // A bucket with many records is added up by several workgroups, at most `slices`, of `per_slice` records each: one
+    // partial each (partials[bucket * kStatsMaxSlices + slice]), and the last of them to arrive adds these.  The bucket's
+    // first partial counts the arrivals in its `flag`, zero between launches.
     StatsRecord *partials;
-    int slices;
+    int slices, per_slice;
 };
 constexpr int kStatsMaxSlices = 64;
+// The workspace: bucket table (16 bytes each), a record for each of `stats_tiles` tiles, (n_buckets + 1) blocks of 64 lane
+// records, kStatsMaxSlices partials per bucket.
+inline long long stats_tiles(long long first, long long end) { return (end - first) / 256 + 8; }
 constexpr long long kStatsRecordsPerSlice = 4096;
 
 // Capacity of the entry point that allocates nothing: its statistics workspace is a fixed
 // device array inside the library (bucket table, one record per 256 elements, lane records,
-// partials - the layout of the caller-provided workspace), so the context may hold at most this
+// partials - the layout of the caller-provided workspace, see stats_tiles), so the context may hold at most this
 // many buckets and span at most this many elements.
 constexpr int kStaticMaxBuckets = 512;
 constexpr long long kStaticMaxElements = 1ll << 27;
@@ -79,6 +83,7 @@ constexpr int kTableChunk = 120;
 struct TableArgs {
     long long *table;            // device: start, end of every bucket
     int first, count;            // buckets [first, first + count) are written
+    StatsRecord *partials;       // their counts of arrivals are cleared
     long long start_end[2 * kTableChunk];
 };
 

@@ -53,7 +53,7 @@ inline long long round_workgroups(long long n, bool bf16, int block)
 // the layer-wise rule behind a round, 1024 and 256 threads: 600 buckets in 40 M elements 403 and 407
 // us, 800 in 36 M 366 and 363, 1000 in 20 M 219 and 216, 2000 in 16 M 181 and 171; a round of two
 // processes with norms, 65536 buckets in 4 M elements, 290 and 147 us.)  It also bounds the grid: 2^32
-// threads are 16 M buckets, or 262 k where one of them takes all the slices of a first stage.
+// threads are 16 M buckets, or 262 k where one of them takes all the slices.
 inline int finish_threads(int n_buckets) { return n_buckets > 768 ? 256 : 1024; }
 
 // Whether the norms pass of the layer-wise rule works in groups of 8 tiles: from 50 M elements, with
@@ -65,6 +65,22 @@ inline int finish_threads(int n_buckets) { return n_buckets > 768 ? 256 : 1024; 
 inline bool norms_grouped(long long tiles, int n_buckets)
 {
     return tiles >= 3 << 16 && tiles >= 128ll * n_buckets;
+}
+
+// The slices of the finishing kernel, from the number that the caller counted: of 4096 records each, for the
+// largest of the launch's `buckets`.  4096 are one trip to memory for a workgroup; where they are not enough, half or a quarter as many are faster while
+// that makes no more workgroups than CUs, most of which have nothing to do where the other buckets are small (1 bucket of 12 k
+// records 5.4 us with 4096, 5.0 with 1024; but up to 4 k in slices, 1.5 M elements in 22 buckets, norms and layer-wise step
+// 27.6 us, 26.0 with one workgroup to a bucket; 5 of up to 50 k 6.3 and 5.7; but 48 of up to 20 k 6.4 and 11.0).  A first launch for
+// the slices and a second for the totals, which this was, took 8.9, 9.6 and 9.7; and 7.8 for 161 of up to 9 k, 6.7 now.
+constexpr int kNormsTiles = 8;         // records of norms_kernel come in groups of so many
+inline void finish_slices(StatsArgs &a, int buckets)
+{
+    const bool most = a.slices == kStatsMaxSlices;
+    long long per = kStatsRecordsPerSlice;
+    for (; a.slices > 1 && per > 1024 && a.slices * 2 <= kStatsMaxSlices && 2ll * a.slices * buckets <= kCus; per /= 2) a.slices *= 2;
+    if (most) per = (a.n_records + kStatsMaxSlices - 1) / kStatsMaxSlices;
+    a.per_slice = static_cast<int>((per + kNormsTiles - 1) / kNormsTiles * kNormsTiles);
 }
 
 // Bytes a launch of a round moves per element: every stream read once by its type, the copies, and

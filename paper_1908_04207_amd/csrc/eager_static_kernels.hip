@@ -21,6 +21,7 @@ __global__ __launch_bounds__(256) void table_fill_kernel(const TableArgs a)
 {
     const int t = static_cast<int>(threadIdx.x);
     if (t < 2 * a.count) a.table[2 * static_cast<long long>(a.first) + t] = a.start_end[t];
+    if (t < a.count) a.partials[(static_cast<long long>(a.first) + t) * kStatsMaxSlices].flag = 0;
 }
 
 }  // namespace
@@ -50,6 +51,8 @@ hipError_t launch_table_fill(long long *table, const long long *start_end, int n
     for (int first = 0; first < n_buckets; first += kTableChunk) {
         TableArgs a;
         a.table = table;
+        a.partials = reinterpret_cast<StatsRecord *>(table + 2ll * n_buckets) +
+                     stats_tiles(start_end[0], start_end[2 * n_buckets - 1]) + (n_buckets + 1ll) * 64;
         a.first = first;
         a.count = n_buckets - first < kTableChunk ? n_buckets - first : kTableChunk;
         for (int i = 0; i < 2 * a.count; ++i) a.start_end[i] = start_end[2 * first + i];
