@@ -303,7 +303,7 @@ int eager_set_update_rule(eager_ctx *ctx, float weight_decay, int nesterov);
  *                 result of the round (Algorithm 2 line 6); squares and sums in fp64
  *   sumsq_params  the same over the parameters w_i BEFORE the update (0 without opt)
  *   nonfinite     number of elements whose u_i is NaN or infinite
- * The sums are formed in a fixed order (no atomics): reproducible bit for bit from run to run
+ * The sums are formed in a fixed order: reproducible bit for bit from run to run
  * for a given launch shape; against another implementation compare with a tolerance.
  */
 typedef struct {

@@ -113,6 +113,16 @@ __device__ __forceinline__ void bucket_records(const StatsArgs &a, int b, long l
     if (w1 > a.n_records) w1 = a.n_records;
 }
 
+// fp64 square roots and division, one rounding to fp32 at the end
+__device__ __forceinline__ float layer_rate(const StatsArgs &a, double su, double sw)
+{
+    const double nu = __builtin_sqrt(su), nw = __builtin_sqrt(sw);
+    return nu > 0.0 && nw > 0.0
+               ? static_cast<float>(static_cast<double>(a.trust) * nw /
+                                    (nu + static_cast<double>(a.wd) * nw + static_cast<double>(a.eps)))
+               : 1.0f;
+}
+
 // The sums of a bucket: the records of the wavefronts whose 256 elements touch the bucket (they are
 // consecutive) - a uniform wavefront's sums, a mixed wavefront's lane records of this bucket - and the records of the
 // ragged tail; one thread writes the bucket's totals.  One workgroup per bucket (blockIdx.x) and slice of its records
@@ -211,16 +221,7 @@ __global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs a
         out.sumsq_update = su;
         out.sumsq_params = sw;
         out.nonfinite = static_cast<unsigned long long>(nf);
-        out.rate = 0.0f;
-        if (a.want_rate) {
-            // fp64 square roots and division, one rounding to fp32 at the end
-            const double nu = __builtin_sqrt(out.sumsq_update), nw = __builtin_sqrt(out.sumsq_params);
-            out.rate = (nu > 0.0 && nw > 0.0)
-                           ? static_cast<float>(static_cast<double>(a.trust) * nw /
-                                                (nu + static_cast<double>(a.wd) * nw +
-                                                 static_cast<double>(a.eps)))
-                           : 1.0f;
-        }
+        out.rate = a.want_rate ? layer_rate(a, su, sw) : 0.0f;
         out.reserved = 0u;
         a.stats[b] = out;
     }
@@ -569,6 +570,75 @@ __global__ __launch_bounds__(64) void lars_kernel(const SgdArgs a, const StatsAr
     }
 }
 
+// The layer-wise rule where every bucket is small: a workgroup per bucket, V lane-vectors to a lane, which wait in
+// registers while the workgroup adds their squares and forms the rate.  What bounds it is latency: a launch, the table,
+// one trip to u, w and v, the sums, the rate's divisions.
+template <bool FAST, bool NT, int THREADS, int V>
+__global__ __launch_bounds__(THREADS) void lars_bucket_kernel(const SgdArgs a, const StatsArgs st)
+{
+    KLong *tbl = (KLong *)reinterpret_cast<unsigned long long>(st.table);
+    const int b = st.b_lo + static_cast<int>(blockIdx.x);
+    const long long start = tbl[2 * b], end = tbl[2 * b + 1];
+    const int n = static_cast<int>(end - start), nvec = n / 4, lane = static_cast<int>(threadIdx.x);
+    const float *up = a.u + start;
+    float *wp = a.w + start, *vp = a.v + start;
+    f32x4 u[V], w[V], v[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        u[k] = w[k] = v[k] = (f32x4)(0.0f);
+        const int vi = k * THREADS + lane;
+        if (vi < nvec) {
+            u[k] = ld_f4<NT>(up + vi * 4);
+            w[k] = ld_f4<NT>(wp + vi * 4);
+            v[k] = ld_f4<NT>(vp + vi * 4);
+        }
+    }
+    // up to 3 elements behind the last lane-vector, one to a lane
+    const int last = nvec * 4 + lane;
+    float ue = 0.0f, we = 0.0f, ve = 0.0f;
+    if (last < n) {
+        ue = up[last];
+        we = wp[last];
+        ve = vp[last];
+    }
+    LaneStats ls = {0.0, 0.0, 0u, b};
+#pragma unroll
+    for (int k = 0; k < V; ++k) stats_vector<true>(ls, u[k], w[k], 4);
+    stats_add(ls, ue, we, true);
+    double su = ls.ssu, sw = ls.ssw, nf = ls.nf;
+    __shared__ float shared_rate;
+    workgroup_sum<THREADS>(su, sw, nf);
+    if (threadIdx.x < 64u) {
+        const float rate = layer_rate(st, su, sw);
+        if (threadIdx.x == 0u) {
+            const BucketStats out = {su, sw, static_cast<unsigned long long>(nf), rate, 0u};
+            st.stats[b] = out;
+            shared_rate = rate;
+        }
+    }
+    __syncthreads();
+    const float rate = shared_rate;
+    // the decay is part of the scaled gradient, so the plain rule follows with wd = 0
+    const UpdateRule rule = {a.neg_lr, a.mu, 0.0f, a.nesterov};
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        const int vi = k * THREADS + lane;
+        if (vi < nvec) {
+            f32x4 vn, wn;
+            update_rule<FAST>(rule, scaled_gradient<FAST>(rate, a.wd, u[k], w[k]), v[k], w[k], vn, wn);
+            st_f4<NT>(vp + vi * 4, vn);
+            st_f4<NT>(wp + vi * 4, wn);
+        }
+    }
+    if (last < n) {
+        float g = ue;
+        if (a.wd != 0.0f) g = fma1(a.wd, we, g);
+        update_rule_scalar(rule, rate * g, ve, we);
+        vp[last] = ve;
+        wp[last] = we;
+    }
+}
+
 // Resident wavefronts per CU of the weight-view kernels when the caller leaves it open: what
 // counts is the KiB of loads in flight per CU, about 38 for the update (1 + 2 per view loads
 // per lane, views in chunks of 8) and 32 for the average (one load per view, chunks of 16).
@@ -593,7 +663,7 @@ int views_average_waves(int n_views)
 hipError_t launch_stats_finish(const StatsArgs &args, hipStream_t stream)
 {
     const int n = args.b_hi - args.b_lo;
-    if (n <= 0) return hipSuccess;
+    if (n <= 0 || args.want_rate == kRateByBucket) return hipSuccess;
     if (args.slices > kStatsMaxSlices || args.slices < 1) return hipErrorInvalidValue;
     StatsArgs a = args;
     const bool grouped = a.want_rate && norms_grouped(a.n_records, n), wide = finish_threads(n) == 1024;
@@ -679,7 +749,7 @@ long long norms_records(long long n)
 
 hipError_t launch_norms(const SgdArgs &a, const StatsArgs &st, hipStream_t stream)
 {
-    if (a.n <= 0) return hipSuccess;
+    if (a.n <= 0 || st.want_rate == kRateByBucket) return hipSuccess;
     const long long tiles = norms_records(a.n);
     const bool grouped = norms_grouped(tiles, st.b_hi - st.b_lo);
     const long long g = grouped ? tiles / kNormsTiles : tiles;
@@ -691,8 +761,27 @@ hipError_t launch_norms(const SgdArgs &a, const StatsArgs &st, hipStream_t strea
                    : launch(norms_kernel<false>, grid, block, 0, stream, a, st);
 }
 
+namespace {
+template <int THREADS, int V>
+hipError_t launch_by_bucket(const SgdArgs &a, const StatsArgs &st, bool fast, bool nt, hipStream_t stream)
+{
+    const dim3 grid(static_cast<unsigned>(st.b_hi - st.b_lo)), block(THREADS);
+    if (fast)
+        return nt ? launch(lars_bucket_kernel<true, true, THREADS, V>, grid, block, 0, stream, a, st)
+                  : launch(lars_bucket_kernel<true, false, THREADS, V>, grid, block, 0, stream, a, st);
+    return nt ? launch(lars_bucket_kernel<false, true, THREADS, V>, grid, block, 0, stream, a, st)
+              : launch(lars_bucket_kernel<false, false, THREADS, V>, grid, block, 0, stream, a, st);
+}
+}  // namespace
+
 hipError_t launch_sgd_lars(const SgdArgs &a, const StatsArgs &st, bool fast, hipStream_t stream)
 {
+    if (st.want_rate == kRateByBucket) {
+        const bool nt = a.n * 20 > kPlainRoundBytes;
+        if (st.largest <= 1024) return launch_by_bucket<256, 1>(a, st, fast, nt, stream);
+        if (st.largest <= 4096) return launch_by_bucket<256, 4>(a, st, fast, nt, stream);
+        return launch_by_bucket<1024, 4>(a, st, fast, nt, stream);
+    }
     if (a.n <= 0) return hipSuccess;
     long long g = (a.n / 4 + 63) / 64;                            // one lane-vector per lane
     if (g < 1) g = 1;

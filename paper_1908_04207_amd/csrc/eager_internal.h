@@ -53,14 +53,16 @@ struct StatsArgs {
     int n_buckets;
     // layer-wise rate, written next to the totals when want_rate is set:
     // trust * |w| / (|u| + wd * |w| + eps), or 1 where a norm is zero
-    int want_rate;
+    int want_rate;               // kRateByBucket: by the update kernel itself, which takes a bucket per workgroup
     float trust, wd, eps;
     // A bucket with many records is added up by several workgroups, at most `slices`, of `per_slice` records each: one
     // partial each (partials[bucket * kStatsMaxSlices + slice]), and the last of them to arrive adds these.  The bucket's
     // first partial counts the arrivals in its `flag`, zero between launches.
     StatsRecord *partials;
     int slices, per_slice;
+    int largest;                 // elements of the largest bucket of the run (update with a rate per bucket)
 };
+constexpr int kRate = 1, kRateByBucket = 2;
 constexpr int kStatsMaxSlices = 64;
 // The workspace: bucket table (16 bytes each), a record for each of `stats_tiles` tiles, (n_buckets + 1) blocks of 64 lane
 // records, kStatsMaxSlices partials per bucket.

@@ -83,6 +83,18 @@ inline void finish_slices(StatsArgs &a, int buckets)
     a.per_slice = static_cast<int>((per + kNormsTiles - 1) / kNormsTiles * kNormsTiles);
 }
 
+// Whether the update with a rate per bucket takes a workgroup per bucket, whose u, w and v wait in its registers between
+// the norms and the update: one launch instead of three, 20 bytes per element instead of 28.  Up to 16384 elements in the
+// largest bucket; a workgroup of 1024 threads has a CU to itself, so that beyond 4096 many buckets must not be tiny.  Three
+// launches and this: one bucket of 256, 4096, 16384 elements 6.0 6.7 6.7 and 2.4 3.6 5.3 us; 64 of up to 1024 10.3 and 3.1;
+// 16384 of 1024 111 and 57, of up to 4096 121 and 73, of up to 16384 402 and 319; 512 of 16384 51 and 33; but one of
+// 16384 among 1024 of 256 10.2 and 12.5, among 4096 of 256 16.5 and 39.
+inline bool rate_by_bucket(long long largest, long long elements, int buckets)
+{
+    return largest <= 4096 ? buckets <= 1 << 21
+                           : largest <= 16384 && buckets <= 1 << 21 && (buckets <= 512 || elements >= 1024ll * buckets);
+}
+
 // Bytes a launch of a round moves per element: every stream read once by its type, the copies, and
 // w and v read and written or the receive buffer written.
 inline long long round_bytes(const SlotArgs &s, bool update)
