@@ -633,7 +633,7 @@ int sgd_step_lars(eager_ctx *ctx, int b0, int b1, const float *update, const eag
     int64_t largest = 0;
     for (int b = b0; b < b1; ++b) largest = std::max(largest, ctx->numel[b]);
     st.want_rate = eager::rate_by_bucket(largest, a.n, b1 - b0) ? eager::kRateByBucket : eager::kRate;
-    st.largest = static_cast<int>(std::min<int64_t>(largest, INT32_MAX));
+    if (st.want_rate == eager::kRateByBucket) st.n_records = largest;
     st.trust = trust;
     st.wd = ctx->weight_decay;
     st.eps = eps;

@@ -31,7 +31,7 @@ __device__ __forceinline__ StatsArgs at_once(const StatsArgs &from)
 {
     StatsArgs a = from;
     asm volatile("" : "+s"(a.e0), "+s"(a.n_records), "+s"(a.b_lo), "+s"(a.n_buckets), "+s"(a.tail_count),
-                 "+s"(a.slices), "+s"(a.per_slice), "+s"(a.want_rate), "+s"(a.trust), "+s"(a.eps), "+s"(a.wd));
+                 "+s"(a.want_rate), "+s"(a.trust), "+s"(a.eps), "+s"(a.wd));
     return a;
 }
 
@@ -129,23 +129,25 @@ __device__ __forceinline__ float layer_rate(const StatsArgs &a, double su, doubl
 // (blockIdx.y, see launch_stats_finish).  Where there are several, each leaves a partial, and the last to arrive adds
 // them, in the order of the slices: the totals do not depend on who that is.  Partials and count are written
 // and read past the caches of an XCD (agent scope); a partial has arrived in memory before its workgroup counts itself.
-template <bool GROUPED, int THREADS>
+template <bool GROUPED, int THREADS, bool SLICED>
 __global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs args)
 {
     const StatsArgs a = at_once(args);
-    const int b = a.b_lo + static_cast<int>(blockIdx.x), slice = static_cast<int>(blockIdx.y);
-    long long w0, w1;
+    const int b = a.b_lo + static_cast<int>(blockIdx.x), slice = SLICED ? static_cast<int>(blockIdx.y) : 0;
+    long long lo, hi, w0, w1;
     bucket_records(a, b, w0, w1);
-    // slices begin at whole groups of records
-    const long long head = w0 / kNormsTiles * kNormsTiles;
+    lo = w0;
+    hi = w1;
     int slices = 1;
-    if (a.slices > 1) {                   // (a division, and a run has at most 2^25 records)
+    if constexpr (SLICED) {               // (a run has at most 2^25 records)
+        // slices begin at whole groups of records
+        const long long head = w0 / kNormsTiles * kNormsTiles;
         const unsigned per = static_cast<unsigned>(a.per_slice), count = (static_cast<unsigned>(w1 - head) + per - 1u) / per;
         slices = static_cast<int>(count < 1u ? 1u : count < static_cast<unsigned>(a.slices) ? count : a.slices);
         if (slice >= slices) return;
+        if (slice > 0) lo = head + static_cast<long long>(slice) * a.per_slice;
+        if (slice + 1 < slices) hi = head + (slice + 1ll) * a.per_slice;
     }
-    const long long lo = slice == 0 ? w0 : head + static_cast<long long>(slice) * a.per_slice;
-    const long long hi = slice + 1 == slices ? w1 : head + (slice + 1ll) * a.per_slice;
     double su = 0.0, sw = 0.0, nf = 0.0;
     // Only the first and the last wavefront of the bucket can be mixed.  The lane records of the
     // first, those of the last and the ragged tail are read by a wavefront each (one lane per
@@ -194,8 +196,8 @@ __global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs a
         }
     }
     workgroup_sum<THREADS>(su, sw, nf);
-    if (wave != 0) return;
-    if (slices > 1) {
+    if (SLICED && wave != 0) return;
+    if (SLICED && slices > 1) {
         StatsRecord *part = a.partials + static_cast<long long>(b) * kStatsMaxSlices;
         unsigned before = 0u;
         if (lane == 0) {
@@ -216,7 +218,7 @@ __global__ __launch_bounds__(THREADS) void stats_finish_kernel(const StatsArgs a
         wave_sums(su, sw);
         if (__builtin_amdgcn_ballot_w64(nf != 0.0) != 0ull) nf = wave_sum(nf);
     }
-    if (lane == 0) {
+    if (threadIdx.x == 0) {
         BucketStats out;
         out.sumsq_update = su;
         out.sumsq_params = sw;
@@ -669,11 +671,16 @@ hipError_t launch_stats_finish(const StatsArgs &args, hipStream_t stream)
     const bool grouped = a.want_rate && norms_grouped(a.n_records, n), wide = finish_threads(n) == 1024;
     finish_slices(a, n);
     const dim3 grid(static_cast<unsigned>(n), static_cast<unsigned>(a.slices)), threads(wide ? 1024 : 256);
-    if (grouped)
-        return wide ? launch(stats_finish_kernel<true, 1024>, grid, threads, 0, stream, a)
-                    : launch(stats_finish_kernel<true, 256>, grid, threads, 0, stream, a);
-    return wide ? launch(stats_finish_kernel<false, 1024>, grid, threads, 0, stream, a)
-                : launch(stats_finish_kernel<false, 256>, grid, threads, 0, stream, a);
+    switch ((a.slices > 1 ? 4 : 0) | (grouped ? 2 : 0) | (wide ? 1 : 0)) {
+    case 0: return launch(stats_finish_kernel<false, 256, false>, grid, threads, 0, stream, a);
+    case 1: return launch(stats_finish_kernel<false, 1024, false>, grid, threads, 0, stream, a);
+    case 2: return launch(stats_finish_kernel<true, 256, false>, grid, threads, 0, stream, a);
+    case 3: return launch(stats_finish_kernel<true, 1024, false>, grid, threads, 0, stream, a);
+    case 4: return launch(stats_finish_kernel<false, 256, true>, grid, threads, 0, stream, a);
+    case 5: return launch(stats_finish_kernel<false, 1024, true>, grid, threads, 0, stream, a);
+    case 6: return launch(stats_finish_kernel<true, 256, true>, grid, threads, 0, stream, a);
+    default: return launch(stats_finish_kernel<true, 1024, true>, grid, threads, 0, stream, a);
+    }
 }
 
 hipError_t launch_stash(const StashArgs &a, bool bf16, hipStream_t stream)
@@ -778,8 +785,8 @@ hipError_t launch_sgd_lars(const SgdArgs &a, const StatsArgs &st, bool fast, hip
 {
     if (st.want_rate == kRateByBucket) {
         const bool nt = a.n * 20 > kPlainRoundBytes;
-        if (st.largest <= 1024) return launch_by_bucket<256, 1>(a, st, fast, nt, stream);
-        if (st.largest <= 4096) return launch_by_bucket<256, 4>(a, st, fast, nt, stream);
+        if (st.n_records <= 1024) return launch_by_bucket<256, 1>(a, st, fast, nt, stream);
+        if (st.n_records <= 4096) return launch_by_bucket<256, 4>(a, st, fast, nt, stream);
         return launch_by_bucket<1024, 4>(a, st, fast, nt, stream);
     }
     if (a.n <= 0) return hipSuccess;
