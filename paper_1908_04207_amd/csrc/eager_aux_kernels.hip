@@ -384,6 +384,125 @@ __global__ __launch_bounds__(64) void views_average_kernel(const ViewsArgs)
     }
 }
 
+// The two for up to 16 views, whose pointers every wavefront has in registers before it asks for the first of them: read where
+// they are used, line after line of an argument block for 64, they are trips of their own, and the host copies the block with
+// every launch.  Average and update, pointers as they come and this: 20 k elements, 8 views 3.0 3.5 and 2.6 3.3 us, 200 k 3.8 6.3
+// and 3.7 5.3, 10 views 4.0 8.1 and 4.2 6.2; 25.6 M, 6 views 214 417 and 186 411, 8 views 260 557 and 255 550.
+// An access is a view's base with the tile's first element, uniform, and the lane's offset.  NT: the views are streamed.
+template <bool NT>
+__device__ __forceinline__ f32x4 ld_view(const float *view, long long first, unsigned off)
+{
+    return ld_at<NT>(reinterpret_cast<const char *>(view + first), off);
+}
+template <bool NT>
+__device__ __forceinline__ void st_view(float *view, long long first, unsigned off, f32x4 x)
+{
+    st_at<NT>(reinterpret_cast<char *>(view + first), off, x);
+}
+template <int N, bool MOMENTUM>
+__device__ __forceinline__ FewViewsArgs<N, MOMENTUM> read_views()
+{
+    FewViewsArgs<N, MOMENTUM> a;
+    __builtin_memcpy(&a, (const void __attribute__((address_space(4))) *)&kernarg<FewViewsArgs<N, MOMENTUM>>(), sizeof a);
+    asm volatile("" : "+s"(a.e0), "+s"(a.n), "+s"(a.n_views));
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" : "+s"(a.w[j]));
+#pragma unroll
+    for (int j = 0; MOMENTUM && j < N; ++j) asm volatile("" : "+s"(a.v[j]));
+    return a;
+}
+template <bool FAST, bool NT, int N, int P0, int R>
+__device__ __forceinline__ void few_sgd(const FewViewsArgs<N, true> &a, int rem, long long first, unsigned off, f32x4 u)
+{
+    if constexpr (R >= 1) {
+        if (rem != R) {
+            few_sgd<FAST, NT, N, P0, R - 1>(a, rem, first, off, u);
+            return;
+        }
+        f32x4 wo[R], vo[R], vn[R], wn[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            vo[j] = ld_view<NT>(a.v[P0 + j], first, off);
+            wo[j] = ld_view<NT>(a.w[P0 + j], first, off);
+        }
+        const UpdateRule rule = {a.neg_lr, a.mu, a.wd, a.nesterov};
+#pragma unroll
+        for (int j = 0; j < R; ++j) update_rule<FAST>(rule, u, vo[j], wo[j], vn[j], wn[j]);
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            st_view<NT>(a.v[P0 + j], first, off, vn[j]);
+            st_view<NT>(a.w[P0 + j], first, off, wn[j]);
+        }
+    }
+}
+template <bool FAST, bool NT, int N>
+__global__ __launch_bounds__(64) void few_views_sgd_kernel(const FewViewsArgs<N, true>)
+{
+    const FewViewsArgs<N, true> a = read_views<N, true>();
+    const long long nvec = a.n / 4;
+    const long long vi = static_cast<long long>(blockIdx.x) * 64 + threadIdx.x;
+    if (vi < nvec) {
+        const long long first = a.e0 + static_cast<long long>(blockIdx.x) * 256;
+        const unsigned off = threadIdx.x * 16u;
+        const f32x4 u = ld_view<NT>(a.u, first, off);
+        if constexpr (N == 16) {
+            few_sgd<FAST, NT, N, 0, 8>(a, 8, first, off, u);
+            few_sgd<FAST, NT, N, 8, 8>(a, a.n_views - 8, first, off, u);
+        } else {
+            few_sgd<FAST, NT, N, 0, N>(a, a.n_views, first, off, u);
+        }
+    }
+    const long long rem = a.n - nvec * 4;
+    if (blockIdx.x == 0 && static_cast<long long>(threadIdx.x) < rem) {
+        const long long i = a.e0 + nvec * 4 + threadIdx.x;
+        const UpdateRule rule = {a.neg_lr, a.mu, a.wd, a.nesterov};
+        const float u = a.u[i];
+        const FewViewsArgs<N, true> __attribute__((address_space(4))) &k = kernarg<FewViewsArgs<N, true>>();
+        for (int p = 0; p < a.n_views; ++p) {
+            float v = k.v[p][i], w = k.w[p][i];
+            update_rule_scalar(rule, u, v, w);
+            k.v[p][i] = v;
+            k.w[p][i] = w;
+        }
+    }
+}
+template <bool NT, int N, int R>
+__device__ __forceinline__ void few_average(const FewViewsArgs<N, false> &a, int views, float inv, long long first, unsigned off)
+{
+    if constexpr (R >= 1) {
+        if (views != R) {
+            few_average<NT, N, R - 1>(a, views, inv, first, off);
+            return;
+        }
+        f32x4 x[R], s = (f32x4)(0.0f);
+#pragma unroll
+        for (int j = 0; j < R; ++j) x[j] = ld_view<NT>(a.w[j], first, off);
+#pragma unroll
+        for (int j = 0; j < R; ++j) s = s + x[j];
+        const f32x4 mean = s * inv;
+#pragma unroll
+        for (int j = 0; j < R; ++j) st_view<NT>(a.w[j], first, off, mean);
+    }
+}
+template <bool NT, int N>
+__global__ __launch_bounds__(64) void few_views_average_kernel(const FewViewsArgs<N, false>)
+{
+    const FewViewsArgs<N, false> a = read_views<N, false>();
+    const long long nvec = a.n / 4;
+    const long long vi = static_cast<long long>(blockIdx.x) * 64 + threadIdx.x;
+    if (vi < nvec)
+        few_average<NT, N, N>(a, a.n_views, a.inv_views, a.e0 + static_cast<long long>(blockIdx.x) * 256, threadIdx.x * 16u);
+    const long long rem = a.n - nvec * 4;
+    if (blockIdx.x == 0 && static_cast<long long>(threadIdx.x) < rem) {
+        const long long i = a.e0 + nvec * 4 + threadIdx.x;
+        const FewViewsArgs<N, false> __attribute__((address_space(4))) &k = kernarg<FewViewsArgs<N, false>>();
+        float s = 0.0f;
+        for (int p = 0; p < k.n_views; ++p) s = s + k.w[p][i];
+        const float mean = s * k.inv_views;
+        for (int p = 0; p < k.n_views; ++p) k.w[p][i] = mean;
+    }
+}
+
 // NT: w and v are too large to stay in the last-level cache until they are touched again
 // STRIDE: as in stash_kernel
 template <bool FAST, bool NT, bool STRIDE>
@@ -643,21 +762,21 @@ __global__ __launch_bounds__(THREADS) void lars_bucket_kernel(const SgdArgs a, c
 
 // Resident wavefronts per CU of the weight-view kernels when the caller leaves it open: what
 // counts is the KiB of loads in flight per CU, about 38 for the update (1 + 2 per view loads
-// per lane, views in chunks of 8) and 32 for the average (one load per view, chunks of 16).
-// Measured optima, update: 12, 8, 4, 3, 2 wavefronts for 1, 2, 4, 8, 16 views (6.8, 6.6, 6.5,
-// 6.4, 6.2 TB/s; uncapped 6.7, 6.2, 5.8, 5.7, 5.5); average: uncapped, 16, 8, 4, 4 (6.8, 6.8,
-// 6.7, 6.5, 6.3 TB/s; uncapped 6.8, 6.5, 6.0, 5.8, 5.7).
+// per lane, views in chunks of 8) and 26 for the average (one load per view).  25.6 M elements, update: 8 views 553 us
+// with 2, 538 with 3, 559 with 4, uncapped 612; 10 views 725, 710, 704, 759; 16 views 1093, 1144, 1185, 1261; average: 4 views
+// 127.4 with 8, 124.7 with 6, 130.4 with 5, uncapped 139; 6 views 191.0 with 5, 187.9 with 4, 211 with 3; 8 views 255.6 with 4,
+// 257.6 with 3; 12 views 393 and 388; 2 views 62 with 16, 65 with 12.
 int views_sgd_waves(int n_views)
 {
     const int loads = 1 + 2 * (n_views < 8 ? n_views : 8);
-    const int w = (38 + loads / 2) / loads;
-    return w < 2 ? 2 : w;
+    const int w = (38 + loads / 2) / loads, least = n_views > 12 ? 2 : 3;
+    return w < least ? least : w;
 }
 int views_average_waves(int n_views)
 {
-    const int loads = n_views < 16 ? n_views : 16;
-    const int w = 32 / loads;
-    return w > 16 ? -1 : w < 4 ? 4 : w;
+    if (n_views < 4) return n_views == 1 ? -1 : 32 / n_views;
+    const int w = 26 / n_views, least = n_views < 12 ? 4 : 3;
+    return w < least ? least : w;
 }
 
 }  // namespace
@@ -699,31 +818,75 @@ hipError_t launch_stash(const StashArgs &a, bool bf16, hipStream_t stream)
 }
 
 namespace {
-hipError_t launch_views(void (*kernel)(ViewsArgs), const ViewsArgs &a, const Launch &cfg, int auto_waves,
-                        hipStream_t stream)
+template <typename A>
+hipError_t launch_views(void (*kernel)(A), const A &a, const Launch &cfg, int auto_waves, hipStream_t stream)
 {
-    if (a.n <= 0 || a.n_views <= 0) return hipSuccess;
     long long g = (a.n / 4 + 63) / 64;
     if (g < 1) g = 1;
     if (g * 64 > kMaxGridThreads) return hipErrorInvalidValue;    // these kernels do not stride
     Launch l = cfg;
     l.block = 64;
-    // half of the traffic is stores: few wavefronts per CU, as for the rounds
-    const int bpc = cfg.blocks_per_cu == 0 ? auto_waves : cfg.blocks_per_cu;
+    // half of the traffic is stores: few wavefronts per CU, as for the rounds (but 8 views of 200 k elements, 3 tiles per
+    // CU, 5.7 us with 3 at a time and 5.3 without a cap)
+    const int bpc = cfg.blocks_per_cu != 0 ? cfg.blocks_per_cu : g <= 6 * kCus ? -1 : auto_waves;
     return launch_capped(kernel, a, bpc, l, static_cast<unsigned>(g), stream);
+}
+template <int N, bool MOMENTUM>
+FewViewsArgs<N, MOMENTUM> few_views(const ViewsArgs &a)
+{
+    FewViewsArgs<N, MOMENTUM> few;
+    few.u = a.u;
+    few.e0 = a.e0;
+    few.n = a.n;
+    few.neg_lr = a.neg_lr;
+    few.mu = a.mu;
+    few.wd = a.wd;
+    few.inv_views = a.inv_views;
+    few.nesterov = a.nesterov;
+    few.n_views = a.n_views;
+    for (int p = 0; p < a.n_views; ++p) few.w[p] = a.w[p];
+    for (int p = 0; MOMENTUM && p < a.n_views; ++p) few.v[p] = a.v[p];
+    return few;
+}
+template <bool FAST, int N>
+hipError_t launch_few_sgd(const ViewsArgs &a, bool nt, const Launch &cfg, int waves, hipStream_t stream)
+{
+    return nt ? launch_views(few_views_sgd_kernel<FAST, true, N>, few_views<N, true>(a), cfg, waves, stream)
+              : launch_views(few_views_sgd_kernel<FAST, false, N>, few_views<N, true>(a), cfg, waves, stream);
+}
+template <int N>
+hipError_t launch_few_average(const ViewsArgs &a, bool nt, const Launch &cfg, int waves, hipStream_t stream)
+{
+    return nt ? launch_views(few_views_average_kernel<true, N>, few_views<N, false>(a), cfg, waves, stream)
+              : launch_views(few_views_average_kernel<false, N>, few_views<N, false>(a), cfg, waves, stream);
 }
 }  // namespace
 
 hipError_t launch_views_sgd(const ViewsArgs &a, bool fast, const Launch &cfg, hipStream_t stream)
 {
+    if (a.n <= 0 || a.n_views <= 0) return hipSuccess;
     const int waves = views_sgd_waves(a.n_views);
+    const bool nt = a.n * (4 + 16ll * a.n_views) > kPlainRoundBytes;
+    if (a.n_views <= 4)
+        return fast ? launch_few_sgd<true, 4>(a, nt, cfg, waves, stream) : launch_few_sgd<false, 4>(a, nt, cfg, waves, stream);
+    if (a.n_views <= 8)
+        return fast ? launch_few_sgd<true, 8>(a, nt, cfg, waves, stream) : launch_few_sgd<false, 8>(a, nt, cfg, waves, stream);
+    // (streamed, 16 views are 2 % faster with the pointers read as they come: 25.6 M elements 1104 and 1123 us)
+    if (a.n_views <= (nt ? 12 : 16))
+        return fast ? launch_few_sgd<true, 16>(a, nt, cfg, waves, stream) : launch_few_sgd<false, 16>(a, nt, cfg, waves, stream);
     return fast ? launch_views(views_sgd_kernel<true>, a, cfg, waves, stream)
                 : launch_views(views_sgd_kernel<false>, a, cfg, waves, stream);
 }
 
 hipError_t launch_views_average(const ViewsArgs &a, const Launch &cfg, hipStream_t stream)
 {
-    return launch_views(views_average_kernel, a, cfg, views_average_waves(a.n_views), stream);
+    if (a.n <= 0 || a.n_views <= 0) return hipSuccess;
+    const int waves = views_average_waves(a.n_views);
+    const bool nt = a.n * 8ll * a.n_views > kPlainRoundBytes;
+    if (a.n_views <= 4) return launch_few_average<4>(a, nt, cfg, waves, stream);
+    if (a.n_views <= 8) return launch_few_average<8>(a, nt, cfg, waves, stream);
+    if (a.n_views <= 16) return launch_few_average<16>(a, nt, cfg, waves, stream);
+    return launch_views(views_average_kernel, a, cfg, waves, stream);
 }
 
 hipError_t launch_sgd(const SgdArgs &a, bool fast, const Launch &cfg, hipStream_t stream)

@@ -264,6 +264,18 @@ struct ViewsArgs {
     int nesterov;
 };
 
+// The same for up to N views, N = 4, 8 or 16, without momentum where it is not needed: whole lines of the scalar cache that
+// a few loads bring into registers.
+template <int N, bool MOMENTUM>
+struct alignas(64) FewViewsArgs {
+    const float *u;
+    long long e0, n;
+    float neg_lr, mu, wd, inv_views;
+    int nesterov, n_views;
+    float *w[N];
+    float *v[MOMENTUM ? N : 1];
+};
+
 struct SgdArgs {
     const float *u;
     float *w;
