@@ -11,15 +11,16 @@
 //     contiguous KiB per fp32 stream and instruction;
 //   * burst_kernel, for runs that stream from HBM: many wavefronts per CU, two loads in flight
 //     in each; occupancy is capped so that the bytes in flight match what the memory side holds;
-//   * chunk_kernel (eager_chunk.h), for runs that latency bounds: up to 16 or 32 loads in flight per
-//     lane, no cap;
+//   * short_kernel (eager_short.h), for runs that latency bounds and lists of up to 16 streams: the whole list and its
+//     arguments in flight at once, no cap; chunk_kernel (eager_chunk.h) for longer lists there, beside by-products and
+//     for launch options: up to 16 or 32 loads in flight per lane;
 //   * which streams exist and what is done with each is decided on the host: empty send buffers
 //     cost no bytes, the send buffer of an on-time process is "cleared" by a flag on the host,
-//     not by writing zeros; burst_kernel applies the actions with scalar bit masks, chunk_kernel
+//     not by writing zeros; burst_kernel applies the actions with scalar bit masks, the other two
 //     with a branch per slot;
 //   * the accumulator stays in fp32 registers; in fixed-order mode contributions are added
 //     in ascending rank order from +0.0f with contraction off, so the result is defined
-//     bit for bit; fast mode keeps two partial sums that take the streams in turn (chunk_kernel: two of
+//     bit for bit; fast mode keeps two partial sums that take the streams in turn (in small runs two of
 //     fp32 streams and two of bf16 streams);
 //   * carry_kernel: the send-buffer rewrite of late processes as a plain pair-by-pair
 //     copy, when a round is split;
