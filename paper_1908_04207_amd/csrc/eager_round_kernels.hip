@@ -345,7 +345,8 @@ __global__ __launch_bounds__(256) void burst_kernel(const SlotArgs)
 // division: a wavefront lives for one load and one store, so whatever stands before its load
 // counts (bf16 source, 1.1e9 elements per pair: 6.73 TB/s in this form, 6.62 with the pair
 // taken from blockIdx.x by a division, 6.46 with a striding loop around the body).
-template <bool BF16, int V>
+// BACK: the first tile begins in front of the run (a.skip).
+template <bool BF16, int V, bool BACK>
 __global__ __launch_bounds__(256) void carry_kernel(const CarryArgs a)
 {
     const unsigned pair = blockIdx.y;
@@ -358,7 +359,7 @@ __global__ __launch_bounds__(256) void carry_kernel(const CarryArgs a)
 #pragma unroll
     for (int k = 0; k < V; ++k) {
         const long long vi = base + static_cast<long long>(k) * blockDim.x;
-        if (vi >= a.skip && vi < nvec) {
+        if ((!BACK || vi >= a.skip) && vi < nvec) {
             const long long e = a.e0 + vi * 4;
             if (BF16) {
                 const u32x2 g = __builtin_nontemporal_load(
@@ -375,7 +376,7 @@ __global__ __launch_bounds__(256) void carry_kernel(const CarryArgs a)
 #pragma unroll
     for (int k = 0; k < V; ++k) {
         const long long vi = base + static_cast<long long>(k) * blockDim.x;
-        if (vi >= a.skip && vi < nvec) st_f4<true>(dst + a.e0 + vi * 4, x[k]);
+        if ((!BACK || vi >= a.skip) && vi < nvec) st_f4<true>(dst + a.e0 + vi * 4, x[k]);
     }
     const long long rem = a.n - nvec * 4;
     if (blockIdx.x == 0 && static_cast<long long>(threadIdx.x) < rem) {
@@ -523,10 +524,9 @@ hipError_t launch_carry_v(const CarryArgs &a, const Launch &cfg, hipStream_t str
             part.src[k] = a.src[first + k];
             part.dst[k] = a.dst[first + k];
         }
-        const hipError_t e = launch_capped(carry_kernel<BF16, V>, part, cfg.carry_blocks_per_cu, l,
-                                           dim3(static_cast<unsigned>(bpp),
-                                                static_cast<unsigned>(part.count)),
-                                           stream);
+        const dim3 grid(static_cast<unsigned>(bpp), static_cast<unsigned>(part.count));
+        const hipError_t e = part.skip ? launch_capped(carry_kernel<BF16, V, true>, part, cfg.carry_blocks_per_cu, l, grid, stream)
+                                       : launch_capped(carry_kernel<BF16, V, false>, part, cfg.carry_blocks_per_cu, l, grid, stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
