@@ -42,11 +42,11 @@ namespace {
 // instruction whatever the type of its stream - the type, like the action, is a scalar select and
 // never a branch around a load.
 //
-// Addresses are a uniform base (stream + first element of the tile) plus a 32-bit offset of the
-// lane.  Lanes beyond the last lane-vector or before the first repeat it: their loads stay inside the run
-// and their results are never stored.
+// Addresses are a uniform base (stream + first element of the tile that belongs to the run) plus a 32-bit
+// offset of the lane.  Lanes beyond the last lane-vector or before the first repeat it: their loads stay inside the run
+// and their results are never stored (see place_lane).
 struct Lanes {
-    long long e0;          // first element of the tile (arena index), uniform
+    long long e0;          // first element of the run in the tile (arena index), uniform
     unsigned off;          // byte offset of the lane-vector in an fp32 stream
     unsigned off_bf;       // byte offset of the 16-byte piece of a bf16 stream that holds it
     bool odd;              // the lane-vector is the upper half of that piece
@@ -233,18 +233,14 @@ __device__ __forceinline__ long long wave_index(const SlotHead &h)
 
 __device__ __forceinline__ Lanes place_lanes(const SlotHead &h, long long tile, long long nvec)
 {
-    const unsigned lane = threadIdx.x & 63u;
-    const long long left = nvec - tile * 64;                   // uniform, > 0
-    const unsigned last = left > 64 ? 63u : static_cast<unsigned>(left) - 1u;
-    const unsigned first = tile == 0 ? static_cast<unsigned>(h.skip) : 0u;
-    const unsigned up = lane > first ? lane : first, lv = up < last ? up : last;
+    const LanePlace p = place_lane(threadIdx.x & 63u, tile, nvec - tile * 64, h.skip);
     Lanes L;
-    L.e0 = h.e0 + tile * 256;
-    L.held = lane <= last;
-    L.in = lv == lane;
-    L.off = lv * 16u;
-    L.off_bf = (lv >> 1) * 16u;
-    L.odd = (lv & 1u) != 0;
+    L.e0 = h.e0 + p.first * 4;
+    L.held = p.held;
+    L.in = p.in;
+    L.off = p.at * 16u;
+    L.off_bf = (p.at >> 1) * 16u;
+    L.odd = (p.at & 1u) != 0;
     return L;
 }
 

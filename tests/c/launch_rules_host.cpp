@@ -32,6 +32,38 @@ static int grids()
     return 0;
 }
 
+// Every lane of every tile reads inside the run, a SKIP's too: 4 elements of an fp32 stream, an aligned piece of 8 of a
+// bf16 stream; the lanes that are in have the run's lane-vectors, each one.
+static int lanes()
+{
+    for (int skip = 0; skip < 16; ++skip)
+        for (long long nvec : {1024ll / 4, 1024ll / 4 + 15, 300ll, 512ll})
+            for (long long tile = 0; tile * 64 < nvec; ++tile) {
+                long long next = tile == 0 ? skip : tile * 64;
+                for (unsigned lane = 0; lane < 64; ++lane) {
+                    const LanePlace p = place_lane(lane, tile, nvec - tile * 64, skip);
+                    CHECK(p.first >= skip && p.first + p.at < nvec);
+                    if (skip % 2 == 0 && nvec % 2 == 0)
+                        CHECK((p.first + p.at) / 2 == p.first / 2 + p.at / 2 && p.first % 2 == 0);
+                    CHECK(p.in == (tile * 64 + lane >= skip && tile * 64 + lane < nvec));
+                    CHECK(p.held == (tile * 64 + lane < nvec) && p.first == place_lane(0, tile, nvec - tile * 64, skip).first);
+                    if (p.in) CHECK(p.first + p.at == next++);
+                }
+                CHECK(next == (nvec < tile * 64 + 64 ? nvec : tile * 64 + 64));
+            }
+    return 0;
+}
+
+// How far a launch steps back: to a multiple of 64 elements, runs of 1024 elements or more, and never beyond the largest run.
+static int back()
+{
+    for (long long e0 : {0ll, 4ll, 60ll, 64ll, 68ll, (1ll << 40) + 32}) {
+        CHECK(run_back(e0, 1023) == 0 && run_back(e0, 1024) == e0 % 64);
+        CHECK(run_back(e0, kMaxRunElements - 64) == e0 % 64 && run_back(e0, kMaxRunElements - 63) == 0 && run_back(e0, kMaxRunElements) == 0);
+    }
+    return 0;
+}
+
 // The finishing kernels: many buckets get small workgroups, and no more threads in all than a
 // workgroup of 256 per bucket and slice would take.
 static int finishing()
@@ -164,7 +196,7 @@ static int paced()
 
 int main()
 {
-    if (paced() || narrow() || grids() || finishing() || norms() || bytes() || occupancy()) return 1;
+    if (lanes() || back() || paced() || narrow() || grids() || finishing() || norms() || bytes() || occupancy()) return 1;
     std::printf("ok\n");
     return 0;
 }
