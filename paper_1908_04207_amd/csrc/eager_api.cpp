@@ -630,9 +630,12 @@ int sgd_step_lars(eager_ctx *ctx, int b0, int b1, const float *update, const eag
     st.b_hi = b1;
     st.n_records = eager::norms_records(a.n);
     st.tail_count = static_cast<int>(a.n % 4);
-    int64_t largest = 0;
-    for (int b = b0; b < b1; ++b) largest = std::max(largest, ctx->numel[b]);
-    st.want_rate = eager::rate_by_bucket(largest, a.n, b1 - b0) ? eager::kRateByBucket : eager::kRate;
+    int64_t largest = ctx->numel[b1 - 1], ends = 0;       // ends: behind the last whole lane-vector, with the padding
+    for (int b = b0; b + 1 < b1; ++b) {
+        largest = std::max(largest, ctx->numel[b]);
+        ends = std::max(ends, ctx->offset[b + 1] - ctx->offset[b] - ctx->numel[b] / 4 * 4);
+    }
+    st.want_rate = eager::rate_by_bucket(largest, ends, a.n, b1 - b0) ? eager::kRateByBucket : eager::kRate;
     if (st.want_rate == eager::kRateByBucket) st.n_records = largest;
     st.trust = trust;
     st.wd = ctx->weight_decay;

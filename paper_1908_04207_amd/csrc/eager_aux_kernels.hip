@@ -699,7 +699,7 @@ __global__ __launch_bounds__(THREADS) void lars_bucket_kernel(const SgdArgs a, c
 {
     KLong *tbl = (KLong *)reinterpret_cast<unsigned long long>(st.table);
     const int b = st.b_lo + static_cast<int>(blockIdx.x);
-    const long long start = tbl[2 * b], end = tbl[2 * b + 1];
+    const long long start = tbl[2 * b], end = tbl[2 * b + 1], stop = tbl[2 * b + (b + 1 < st.b_hi ? 2 : 1)];
     const int n = static_cast<int>(end - start), nvec = n / 4, lane = static_cast<int>(threadIdx.x);
     const float *up = a.u + start;
     float *wp = a.w + start, *vp = a.v + start;
@@ -714,10 +714,11 @@ __global__ __launch_bounds__(THREADS) void lars_bucket_kernel(const SgdArgs a, c
             v[k] = ld_f4<NT>(vp + vi * 4);
         }
     }
-    // up to 3 elements behind the last lane-vector, one to a lane
-    const int last = nvec * 4 + lane;
+    // up to 3 elements behind the last lane-vector, one to a lane, and the padding up to the run's next bucket
+    // (kBucketEnd elements at most)
+    const int last = nvec * 4 + lane, behind = static_cast<int>(stop - start);
     float ue = 0.0f, we = 0.0f, ve = 0.0f;
-    if (last < n) {
+    if (last < behind) {
         ue = up[last];
         we = wp[last];
         ve = vp[last];
@@ -725,7 +726,7 @@ __global__ __launch_bounds__(THREADS) void lars_bucket_kernel(const SgdArgs a, c
     LaneStats ls = {0.0, 0.0, 0u, b};
 #pragma unroll
     for (int k = 0; k < V; ++k) stats_vector<true>(ls, u[k], w[k], 4);
-    stats_add(ls, ue, we, true);
+    if (last < n) stats_add(ls, ue, we, true);
     double su = ls.ssu, sw = ls.ssw, nf = ls.nf;
     __shared__ float shared_rate;
     workgroup_sum<THREADS>(su, sw, nf);
@@ -751,7 +752,7 @@ __global__ __launch_bounds__(THREADS) void lars_bucket_kernel(const SgdArgs a, c
             st_f4<NT>(wp + vi * 4, wn);
         }
     }
-    if (last < n) {
+    if (last < behind) {
         float g = ue;
         if (a.wd != 0.0f) g = fma1(a.wd, we, g);
         update_rule_scalar(rule, rate * g, ve, we);

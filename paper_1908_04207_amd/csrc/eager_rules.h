@@ -106,10 +106,14 @@ inline void finish_slices(StatsArgs &a, int buckets)
 // launches and this: one bucket of 256, 4096, 16384 elements 6.0 6.7 6.7 and 2.4 3.6 5.3 us; 64 of up to 1024 10.3 and 3.1;
 // 16384 of 1024 111 and 57, of up to 4096 121 and 73, of up to 16384 402 and 319; 512 of 16384 51 and 33; but one of
 // 16384 among 1024 of 256 10.2 and 12.5, among 4096 of 256 16.5 and 39.
-inline bool rate_by_bucket(long long largest, long long elements, int buckets)
+// `ends`: the most elements from a bucket's last whole lane-vector to the next bucket of the run, padding included, one to a
+// lane of its workgroup.  (Padding in the registers beside the bucket's own makes one of 4096 with 8 behind it a case of
+// workgroups of 1024 threads: 4096 of up to 4096 53 us, 42 with three launches, 22 in this way.)
+constexpr int kBucketEnd = 256;
+inline bool rate_by_bucket(long long largest, long long ends, long long elements, int buckets)
 {
-    return largest <= 4096 ? buckets <= 1 << 21
-                           : largest <= 16384 && buckets <= 1 << 21 && (buckets <= 512 || elements >= 1024ll * buckets);
+    if (ends > kBucketEnd || buckets > 1 << 21) return false;
+    return largest <= 4096 || (largest <= 16384 && (buckets <= 512 || elements >= 1024ll * buckets));
 }
 
 // Bytes a launch of a round moves per element: every stream read once by its type, the copies, and

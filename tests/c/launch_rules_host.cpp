@@ -91,6 +91,19 @@ static int norms()
     return 0;
 }
 
+// A workgroup per bucket: up to 16384 elements, beyond 4096 not where most buckets are tiny, and no more behind a bucket's
+// last lane-vector than its workgroup of at least 256 threads has lanes.
+static int by_bucket()
+{
+    for (int n : {1, 512, 513, 1 << 21}) {
+        CHECK(rate_by_bucket(0, 0, 0, n) && rate_by_bucket(4096, 256, 4096, n) && !rate_by_bucket(4096, 257, 1ll << 32, n));
+        CHECK(rate_by_bucket(4097, 256, 1024ll * n, n) && rate_by_bucket(16384, 0, 1024ll * n, n));
+        CHECK(rate_by_bucket(4097, 0, 1024ll * n - 1, n) == (n <= 512) && !rate_by_bucket(16385, 0, 1ll << 32, n));
+    }
+    CHECK(!rate_by_bucket(4, 0, 1ll << 32, (1 << 21) + 1));
+    return 0;
+}
+
 // Bytes by the type of each stream; what fills the list up moves nothing.
 static int bytes()
 {
@@ -196,7 +209,7 @@ static int paced()
 
 int main()
 {
-    if (lanes() || back() || paced() || narrow() || grids() || finishing() || norms() || bytes() || occupancy()) return 1;
+    if (lanes() || back() || paced() || narrow() || grids() || finishing() || norms() || by_bucket() || bytes() || occupancy()) return 1;
     std::printf("ok\n");
     return 0;
 }
