@@ -222,20 +222,20 @@ __device__ __forceinline__ SlotHead read_head(KSlotArgs &a)
 // gives every XCD one contiguous eighth of the run instead of every eighth tile (a launch
 // option, for A/B).  (The grid's shape comes with the arguments: the built-in blockDim is a load
 // from memory that every wavefront would have to wait for.)
-__device__ __forceinline__ long long wave_index(const SlotHead &h)
+__device__ __forceinline__ unsigned wave_index(const SlotHead &h)
 {
     unsigned bid = blockIdx.x;
     const unsigned per = static_cast<unsigned>(h.xcd_blocks);
     if (per && bid < per * 8u) bid = (bid % 8u) * per + bid / 8u;
     const unsigned wave = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
-    return static_cast<long long>(bid) * h.waves_per_block + wave;
+    return bid * static_cast<unsigned>(h.waves_per_block) + wave;
 }
 
-__device__ __forceinline__ Lanes place_lanes(const SlotHead &h, long long tile, long long nvec)
+__device__ __forceinline__ Lanes place_lanes(const SlotHead &h, unsigned tile, unsigned nvec)
 {
-    const LanePlace p = place_lane(threadIdx.x & 63u, tile, nvec - tile * 64, h.skip);
+    const LanePlace p = place_lane(threadIdx.x & 63u, tile, nvec - tile * 64u, static_cast<unsigned>(h.skip));
     Lanes L;
-    L.e0 = h.e0 + p.first * 4;
+    L.e0 = h.e0 + p.first * 4ll;
     L.held = p.held;
     L.in = p.in;
     L.off = p.at * 16u;
@@ -271,12 +271,14 @@ __global__ __launch_bounds__(256) void burst_kernel(const SlotArgs)
     constexpr int D = kBurst;
     KSlotArgs &a = kernarg<SlotArgs>();
     const SlotHead h = read_head(a);
-    const long long nvec = slot_nvec<BF16>(h.n);
-    const long long tile = wave_index(h);
-    if (tile * 64 >= nvec) {
+    constexpr unsigned kRagged = BF16 ? 7u : 3u;          // (slot_nvec in 32 bits, see place_lane)
+    const unsigned nvec = static_cast<unsigned>((static_cast<unsigned long long>(h.n) & ~static_cast<unsigned long long>(kRagged)) >> 2);
+    const unsigned tile = wave_index(h);
+    if (tile * 64u >= nvec) {
         // the grid's last wavefront: the ragged tail
-        const long long rem = h.n - nvec * 4, t = threadIdx.x & 63u;
-        if (tile * 64 < nvec + 64 && t < rem) slot_tail_element<BF16, STATS>(a, h, h.e0 + nvec * 4 + t);
+        const unsigned t = threadIdx.x & 63u;
+        if (tile * 64u < nvec + 64u && t < (static_cast<unsigned>(h.n) & kRagged))
+            slot_tail_element<BF16, STATS>(a, h, h.e0 + nvec * 4ll + t);
         return;
     }
     const Lanes L = place_lanes(h, tile, nvec);

@@ -36,20 +36,22 @@ static int grids()
 // bf16 stream; the lanes that are in have the run's lane-vectors, each one.
 static int lanes()
 {
-    for (int skip = 0; skip < 16; ++skip)
-        for (long long nvec : {1024ll / 4, 1024ll / 4 + 15, 300ll, 512ll})
-            for (long long tile = 0; tile * 64 < nvec; ++tile) {
-                long long next = tile == 0 ? skip : tile * 64;
+    const unsigned most = static_cast<unsigned>(kMaxRunElements / 4);
+    for (unsigned skip = 0; skip < 16; ++skip)
+        for (unsigned nvec : {256u, 256u + 15, 300u, 512u, most - 1, most})
+            for (unsigned tile = 0; tile * 64 < nvec; tile += tile < 8 ? 1 : tile + 4 < nvec / 64 ? nvec / 64 - tile - 3 : 1) {
+                const unsigned tile0 = tile * 64;
+                unsigned next = tile == 0 ? skip : tile0;
                 for (unsigned lane = 0; lane < 64; ++lane) {
-                    const LanePlace p = place_lane(lane, tile, nvec - tile * 64, skip);
+                    const LanePlace p = place_lane(lane, tile, nvec - tile0, skip);
                     CHECK(p.first >= skip && p.first + p.at < nvec);
                     if (skip % 2 == 0 && nvec % 2 == 0)
                         CHECK((p.first + p.at) / 2 == p.first / 2 + p.at / 2 && p.first % 2 == 0);
-                    CHECK(p.in == (tile * 64 + lane >= skip && tile * 64 + lane < nvec));
-                    CHECK(p.held == (tile * 64 + lane < nvec) && p.first == place_lane(0, tile, nvec - tile * 64, skip).first);
+                    CHECK(p.in == (tile0 + lane >= skip && tile0 + lane < nvec));
+                    CHECK(p.held == (tile0 + lane < nvec) && p.first == place_lane(0, tile, nvec - tile0, skip).first);
                     if (p.in) CHECK(p.first + p.at == next++);
                 }
-                CHECK(next == (nvec < tile * 64 + 64 ? nvec : tile * 64 + 64));
+                CHECK(next == (nvec < tile0 + 64 ? nvec : tile0 + 64));
             }
     return 0;
 }
