@@ -84,14 +84,12 @@ void stats_layout(const eager_ctx *ctx, char *workspace, eager::BucketStats *sta
     st.n_buckets = ctx->n_buckets;
 }
 
-// Workgroups that add up the records of one bucket before the finishing kernel: from the
-// largest bucket of the run (one record per 256 elements)
-int stats_slices(const eager_ctx *ctx, int b0, int b1)
+// Records of the largest of buckets [b0, b1): one per 256 elements, of at most 2^33 in a run
+int largest_records(const eager_ctx *ctx, int b0, int b1)
 {
     int64_t most = 0;
     for (int b = b0; b < b1; ++b) most = std::max(most, ctx->numel[b] / 256);
-    const int64_t s = (most + eager::kStatsRecordsPerSlice - 1) / eager::kStatsRecordsPerSlice;
-    return static_cast<int>(std::min<int64_t>(std::max<int64_t>(s, 1), eager::kStatsMaxSlices));
+    return static_cast<int>(std::min<int64_t>(most, eager::kMaxRunElements / 256));
 }
 
 // Whether the send-buffer rewrite of the late processes runs as its own copy kernel after
@@ -257,7 +255,7 @@ int partial_allreduce(eager_ctx *ctx, int want_mode, const eager_plan *plan, uin
             a.stats.b_hi = e;
             a.stats.n_records = eager::slot_records(a.n + back, ctx->bf16, ctx->launch.block);
             a.stats.tail_count = eager::slot_tail(a.n + back, ctx->bf16);
-            a.stats.slices = stats_slices(ctx, b, e);
+            a.stats.largest = largest_records(ctx, b, e);
         }
         hipError_t he = eager::launch_round(a, ctx->bf16, ctx->fast, ctx->launch,
                                             static_cast<hipStream_t>(stream));
@@ -624,7 +622,7 @@ int sgd_step_lars(eager_ctx *ctx, int b0, int b1, const float *update, const eag
     eager::StatsArgs st;
     std::memset(&st, 0, sizeof st);
     stats_layout(ctx, workspace, stats, st);
-    st.slices = stats_slices(ctx, b0, b1);
+    st.largest = largest_records(ctx, b0, b1);
     st.e0 = a.e0;
     st.b_lo = b0;
     st.b_hi = b1;

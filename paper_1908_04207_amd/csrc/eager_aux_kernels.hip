@@ -786,10 +786,9 @@ hipError_t launch_stats_finish(const StatsArgs &args, hipStream_t stream)
 {
     const int n = args.b_hi - args.b_lo;
     if (n <= 0 || args.want_rate == kRateByBucket) return hipSuccess;
-    if (args.slices > kStatsMaxSlices || args.slices < 1) return hipErrorInvalidValue;
     StatsArgs a = args;
     const bool grouped = a.want_rate && norms_grouped(a.n_records, n), wide = finish_threads(n) == 1024;
-    finish_slices(a, n);
+    finish_slices(a, n, grouped);
     const dim3 grid(static_cast<unsigned>(n), static_cast<unsigned>(a.slices)), threads(wide ? 1024 : 256);
     switch ((a.slices > 1 ? 4 : 0) | (grouped ? 2 : 0) | (wide ? 1 : 0)) {
     case 0: return launch(stats_finish_kernel<false, 256, false>, grid, threads, 0, stream, a);

@@ -86,20 +86,30 @@ inline bool norms_grouped(long long tiles, int n_buckets)
     return tiles >= 3 << 16 && tiles >= 128ll * n_buckets;
 }
 
-// The slices of the finishing kernel, from the number that the caller counted: of 4096 records each, for the
-// largest of the launch's `buckets`.  4096 are one trip to memory for a workgroup; where they are not enough, half or a quarter as many are faster while
-// that makes no more workgroups than CUs, most of which have nothing to do where the other buckets are small (1 bucket of 12 k
+// The slices of the finishing kernel, for the largest of the launch's `buckets`: 4096 records to a workgroup - one in 8 where
+// they come in groups - which is one trip to memory for 1024 threads and two for 256, or as many more as 64 slices come to.
+// Half or a quarter as many are faster while that makes no more workgroups than CUs, most of which have nothing to do where
+// the other buckets are small (1 bucket of 12 k
 // records 5.4 us with 4096, 5.0 with 1024; but up to 4 k in slices, 1.5 M elements in 22 buckets, norms and layer-wise step
 // 27.6 us, 26.0 with one workgroup to a bucket; 5 of up to 50 k 6.3 and 5.7; but 48 of up to 20 k 6.4 and 11.0).  A first launch for
 // the slices and a second for the totals, which this was, took 8.9, 9.6 and 9.7; and 7.8 for 161 of up to 9 k, 6.7 now.
+// Groups: 800 buckets of 10 k elements and one of 70 M 26.6 us in 64 slices, 14.5 in 9.  Slices of the largest bucket's
+// records, not of the run's: 8 buckets of 273 k each 19.8 us in 8 slices, 13.6 in 64 (two launches 16.9).
 constexpr int kNormsTiles = 8;         // records of norms_kernel come in groups of so many
-inline void finish_slices(StatsArgs &a, int buckets)
+inline void finish_slices(StatsArgs &a, int buckets, bool grouped)
 {
-    const bool most = a.slices == kStatsMaxSlices;
-    long long per = kStatsRecordsPerSlice;
-    for (; a.slices > 1 && per > 1024 && a.slices * 2 <= kStatsMaxSlices && 2ll * a.slices * buckets <= kCus; per /= 2) a.slices *= 2;
-    if (most) per = (a.n_records + kStatsMaxSlices - 1) / kStatsMaxSlices;
-    a.per_slice = static_cast<int>((per + kNormsTiles - 1) / kNormsTiles * kNormsTiles);
+    const long long unit = grouped ? kNormsTiles : 1, most = (a.largest + unit - 1) / unit, room = kStatsMaxSlices;
+    long long per = kStatsRecordsPerSlice, n = std::max((most + per - 1) / per, 1ll);
+    if (n >= room) {
+        n = room;
+        per = (most + n - 1) / n;
+    }
+    while (n > 1 && n < room && per > 1024 && 2 * n * buckets <= kCus) {
+        n = std::min(2 * n, room);
+        per = n < room ? per / 2 : (most + n - 1) / n;
+    }
+    a.slices = static_cast<int>(n);
+    a.per_slice = static_cast<int>((per * unit + kNormsTiles - 1) / kNormsTiles * kNormsTiles);
 }
 
 // Whether the update with a rate per bucket takes a workgroup per bucket, whose u, w and v wait in its registers between

@@ -80,6 +80,39 @@ static int finishing()
     return 0;
 }
 
+static StatsArgs sliced(long long largest, int buckets, long long records, bool grouped = false)
+{
+    StatsArgs a{};
+    a.largest = static_cast<int>(largest);
+    a.n_records = records;
+    finish_slices(a, buckets, grouped);
+    return a;
+}
+
+// A bucket's records in slices: whole groups of records, enough of them for the largest bucket, and no more to a slice than
+// 4096 or, with all 64 in use, its share of that bucket, whatever stands beside it.
+static int slices()
+{
+    for (long long most : {0ll, 1ll, 4096ll, 4097ll, 12'288ll, 12'289ll, 100'000ll, 258'048ll, 258'049ll, 262'144ll, 273'438ll, 1ll << 25})
+        for (int buckets : {1, 2, 3, 8, 64, 161, 768, 769, 5000})
+            for (long long others : {0ll, 1ll, 7ll}) {
+                const StatsArgs a = sliced(most, buckets, std::min((others + 1) * most + 8, 1ll << 25));
+                CHECK(a.slices >= 1 && a.slices <= kStatsMaxSlices && a.per_slice > 0 && a.per_slice % kNormsTiles == 0);
+                if (a.slices > 1) CHECK(a.slices * static_cast<long long>(a.per_slice) >= most);
+                if (a.slices == kStatsMaxSlices) CHECK(a.per_slice < most / kStatsMaxSlices + 1 + kNormsTiles || a.per_slice <= 4096);
+                const StatsArgs alone = sliced(most, buckets, most + 8);
+                CHECK(a.slices == alone.slices && a.per_slice == alone.per_slice);
+                const StatsArgs group = sliced(most, buckets, most + 8, true), eighth = sliced((most + 7) / 8, buckets, most + 8);
+                CHECK(group.slices == eighth.slices && group.per_slice >= 8 * eighth.per_slice - 56);
+                CHECK(group.per_slice <= 8 * eighth.per_slice && group.per_slice % kNormsTiles == 0);
+                CHECK(group.slices == 1 || group.slices * static_cast<long long>(group.per_slice) >= most);
+            }
+    CHECK(sliced(4096, 161, 100'000).slices == 1 && sliced(9216, 161, 100'000).slices == 3 && sliced(12'289, 48, 100'000).slices == 4);
+    CHECK(sliced(12'288, 1, 12'290).slices == 12 && sliced(12'288, 1, 12'290).per_slice == 1024);
+    CHECK(sliced(273'438, 8, 2'187'504).slices == 64 && sliced(273'438, 8, 2'187'504).per_slice == 4280);
+    return 0;
+}
+
 // The norms pass works in groups of tiles only where nearly all groups lie inside one bucket.
 static int norms()
 {
@@ -211,7 +244,7 @@ static int paced()
 
 int main()
 {
-    if (lanes() || back() || paced() || narrow() || grids() || finishing() || norms() || by_bucket() || bytes() || occupancy()) return 1;
+    if (lanes() || back() || paced() || narrow() || grids() || finishing() || slices() || norms() || by_bucket() || bytes() || occupancy()) return 1;
     std::printf("ok\n");
     return 0;
 }

@@ -1,0 +1,59 @@
+"""Totals of buckets whose records several workgroups add: slices shortened for few buckets, 4 and 64 slices, beside empty
+and small buckets, with plain records (a round) and records in groups (the layer-wise step from 50 M elements on).  Against
+64-bit sums, and the same bits in every later call: each leaves the count of arrivals at zero."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("num", [
+    [3_200_000], [0, 5, 3_200_001, 0, 0, 257, 2_900_003, 0], [300] * 300 + [4_300_001] + [0] * 300,
+    [3] * 900 + [3_200_000, 1_700_000], [67_000_003, 0, 1000, 3_300_000], [66_500_000, 66_100_003, 4],
+    [60_000_000] + [250_000] * 200, [67_000_000] + [2000] * 900])
+def test_totals(num):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1908_04207_amd import binding as eb
+    dev, off, n = torch.device("cuda:0"), [], 0
+    for m in num:
+        off.append(n)
+        n = (n + m + 3) // 4 * 4
+    trust, eps = 0.02, 1e-9
+    gen = torch.Generator(device=dev).manual_seed(len(num))
+    G, w0, v = (torch.empty(max(n, 4), device=dev).normal_(0.0, s, generator=gen) for s in (1e-3, 0.02, 1e-3))
+    last = max(b for b, m in enumerate(num) if m)
+    G[off[last] + num[last] - 1] = float("nan")
+    u, unread = torch.empty_like(G), torch.zeros(4, device=dev)
+
+    def sums(x):
+        return torch.stack([torch.nan_to_num(x[o:o + m].double(), nan=0.0).square().sum() for o, m in zip(off, num)])
+
+    su, sw = sums(G), sums(w0)
+    ctx = eb.Context(1, off, num)
+    raw = torch.empty(len(num) * 32, dtype=torch.uint8, device=dev)
+    need = ctx.eager_stats_workspace_bytes()
+    ws = torch.full((need,), 0x5A, dtype=torch.uint8, device=dev)
+    ctx.eager_stats_attach(raw, ws, need)
+    calls = {
+        "round": lambda k: ctx.eager_partial_allreduce(eb.make_plan(eb.MAJORITY, 1, k, 1), [G], [unread], recv=u),
+        "step": lambda k: ctx.eager_sgd_step_lars(u, (w0.clone(), v.clone(), 0.1, 0.9), trust, eps)}
+    for name, call in calls.items():
+        first = None
+        for k in range(3):
+            raw.fill_(0x5A)
+            call(k)
+            torch.cuda.synchronize()
+            if first is None:
+                first = raw.clone()
+            assert torch.equal(raw, first), (name, k)
+        got = first.view(torch.float64).view(-1, 4)
+        # (64-bit sums in another order: 1e-10 is what the statistics promise)
+        assert ((got[:, 0] - su).abs() <= 1e-10 * su).all(), name
+        assert first.view(torch.int64).view(-1, 4)[:, 2].tolist() == [int(b == last) for b in range(len(num))], name
+        if name == "step":
+            assert ((got[:, 1] - sw).abs() <= 1e-10 * sw).all()
+            rate = trust * sw.sqrt() / (su.sqrt() + eps)
+            rate = torch.where((su > 0) & (sw > 0), rate, torch.ones_like(rate))
+            assert ((first.view(torch.float32).view(-1, 8)[:, 6].double() - rate).abs() <= 1.2e-7 * rate).all()
+    ctx.close()
