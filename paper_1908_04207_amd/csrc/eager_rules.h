@@ -72,7 +72,7 @@ inline long long round_workgroups(long long n, bool bf16, int block)
 // the layer-wise rule behind a round, 1024 and 256 threads: 600 buckets in 40 M elements 403 and 407
 // us, 800 in 36 M 366 and 363, 1000 in 20 M 219 and 216, 2000 in 16 M 181 and 171; a round of two
 // processes with norms, 65536 buckets in 4 M elements, 290 and 147 us.)  It also bounds the grid: 2^32
-// threads are 16 M buckets, or 262 k where one of them takes all the slices.
+// threads are 16 M buckets; finish_slices keeps below.
 inline int finish_threads(int n_buckets) { return n_buckets > 768 ? 256 : 1024; }
 
 // Whether the norms pass of the layer-wise rule works in groups of 8 tiles: from 50 M elements, with
@@ -98,7 +98,10 @@ inline bool norms_grouped(long long tiles, int n_buckets)
 constexpr int kNormsTiles = 8;         // records of norms_kernel come in groups of so many
 inline void finish_slices(StatsArgs &a, int buckets, bool grouped)
 {
-    const long long unit = grouped ? kNormsTiles : 1, most = (a.largest + unit - 1) / unit, room = kStatsMaxSlices;
+    const long long unit = grouped ? kNormsTiles : 1, most = (a.largest + unit - 1) / unit;
+    // (a grid of more threads than a launch takes would wrap: 131072 buckets times 64 slices are just as many)
+    const long long fits = kMaxGridThreads / (static_cast<long long>(finish_threads(buckets)) * buckets);
+    const long long room = std::min<long long>(std::max(fits, 1ll), kStatsMaxSlices);
     long long per = kStatsRecordsPerSlice, n = std::max((most + per - 1) / per, 1ll);
     if (n >= room) {
         n = room;

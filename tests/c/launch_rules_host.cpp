@@ -107,6 +107,14 @@ static int slices()
                 CHECK(group.per_slice <= 8 * eighth.per_slice && group.per_slice % kNormsTiles == 0);
                 CHECK(group.slices == 1 || group.slices * static_cast<long long>(group.per_slice) >= most);
             }
+    // every grid within what a launch takes
+    for (int buckets : {1000, 65'536, 131'072, 200'000, 262'144, 1 << 20, 1 << 23})
+        for (long long most : {12'289ll, 258'049ll, 1ll << 25})
+            for (bool grouped : {false, true}) {
+                const StatsArgs a = sliced(most, buckets, 1ll << 25, grouped);
+                CHECK(a.slices >= 1 && static_cast<long long>(a.slices) * buckets * finish_threads(buckets) <= kMaxGridThreads);
+                CHECK(a.slices == 1 || a.slices * static_cast<long long>(a.per_slice) >= most);
+            }
     CHECK(sliced(4096, 161, 100'000).slices == 1 && sliced(9216, 161, 100'000).slices == 3 && sliced(12'289, 48, 100'000).slices == 4);
     CHECK(sliced(12'288, 1, 12'290).slices == 12 && sliced(12'288, 1, 12'290).per_slice == 1024);
     CHECK(sliced(273'438, 8, 2'187'504).slices == 64 && sliced(273'438, 8, 2'187'504).per_slice == 4280);
