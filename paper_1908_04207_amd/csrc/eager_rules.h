@@ -93,9 +93,21 @@ inline bool norms_grouped(long long tiles, int n_buckets)
 // records 5.4 us with 4096, 5.0 with 1024; but up to 4 k in slices, 1.5 M elements in 22 buckets, norms and layer-wise step
 // 27.6 us, 26.0 with one workgroup to a bucket; 5 of up to 50 k 6.3 and 5.7; but 48 of up to 20 k 6.4 and 11.0).  A first launch for
 // the slices and a second for the totals, which this was, took 8.9, 9.6 and 9.7; and 7.8 for 161 of up to 9 k, 6.7 now.
+// Two or three slices are a trip less and a count of arrivals more: see few_slices.
 // Groups: 800 buckets of 10 k elements and one of 70 M 26.6 us in 64 slices, 14.5 in 9.  Slices of the largest bucket's
 // records, not of the run's: 8 buckets of 273 k each 19.8 us in 8 slices, 13.6 in 64 (two launches 16.9).
 constexpr int kNormsTiles = 8;         // records of norms_kernel come in groups of so many
+// Whether 2 or 3 slices are worth it.  Not where one workgroup has the records in about a trip, nor where those of the other
+// buckets that have nothing to do (n slices are n workgroups to every bucket) do not all fit the chip beside them; of
+// 256 threads, which take more trips, up to 1536 buckets.  Two processes with norms, one bucket of 1.1, 2 and 3.1 M elements among
+// small ones, one workgroup to a bucket and slices: 64 buckets 9.5 13.4 16.5 and 9.6 11.2 14.6 us, 161 10.0 13.7 17.8 and 10.9
+// 12.7 15.7, 600 10.8 14.4 18.5 and 12.4 15.6 19.5, 1000 12.3 15.7 20.5 and 12.4 14.9 17.7, 3000 15.4 18.5 23.3 and 16.6 19.8 24.0;
+// every 8th of 200 and of 400 of 2.5 M, the finishing kernel alone 9.9 15.7 and 11.2 17.8.
+inline bool few_slices(long long records, long long slices, int buckets)
+{
+    if (finish_threads(buckets) < 1024) return records > 5632 && buckets <= 1536;
+    return records > (buckets <= 64 ? 5632 : 7168) && slices * buckets < 2 * kCus;
+}
 inline void finish_slices(StatsArgs &a, int buckets, bool grouped)
 {
     const long long unit = grouped ? kNormsTiles : 1, most = (a.largest + unit - 1) / unit;
@@ -103,6 +115,7 @@ inline void finish_slices(StatsArgs &a, int buckets, bool grouped)
     const long long fits = kMaxGridThreads / (static_cast<long long>(finish_threads(buckets)) * buckets);
     const long long room = std::min<long long>(std::max(fits, 1ll), kStatsMaxSlices);
     long long per = kStatsRecordsPerSlice, n = std::max((most + per - 1) / per, 1ll);
+    if (n <= 3 && !few_slices(most, n, buckets)) n = 1;
     if (n >= room) {
         n = room;
         per = (most + n - 1) / n;

@@ -115,7 +115,12 @@ static int slices()
                 CHECK(a.slices >= 1 && static_cast<long long>(a.slices) * buckets * finish_threads(buckets) <= kMaxGridThreads);
                 CHECK(a.slices == 1 || a.slices * static_cast<long long>(a.per_slice) >= most);
             }
-    CHECK(sliced(4096, 161, 100'000).slices == 1 && sliced(9216, 161, 100'000).slices == 3 && sliced(12'289, 48, 100'000).slices == 4);
+    CHECK(sliced(4096, 161, 100'000).slices == 1 && sliced(9216, 161, 100'000).slices == 3 && sliced(9216, 171, 100'000).slices == 1);
+    // two or three only where they pay: not for little more than 4096 records, nor beside too many others
+    CHECK(sliced(5632, 1, 5640).slices == 1 && sliced(5633, 1, 5640).slices > 1 && sliced(7168, 65, 9000).slices == 1);
+    CHECK(sliced(7169, 65, 9000).slices == 2 && sliced(7169, 255, 9000).slices == 2 && sliced(7169, 256, 9000).slices == 1);
+    CHECK(sliced(5633, 769, 9000).slices == 2 && sliced(12'288, 1536, 20'000).slices == 3 && sliced(12'288, 1537, 20'000).slices == 1);
+    CHECK(sliced(12'289, 48, 100'000).slices == 4);
     CHECK(sliced(12'288, 1, 12'290).slices == 12 && sliced(12'288, 1, 12'290).per_slice == 1024);
     CHECK(sliced(273'438, 8, 2'187'504).slices == 64 && sliced(273'438, 8, 2'187'504).per_slice == 4280);
     return 0;
