@@ -84,12 +84,14 @@ void stats_layout(const eager_ctx *ctx, char *workspace, eager::BucketStats *sta
     st.n_buckets = ctx->n_buckets;
 }
 
-// Records of the largest of buckets [b0, b1): one per 256 elements, of at most 2^33 in a run
-int largest_records(const eager_ctx *ctx, int b0, int b1)
+// The slices of the finishing kernel, from the largest bucket of the run (one record per 256 elements, of at most 2^33)
+void stats_slices(const eager_ctx *ctx, eager::StatsArgs &st)
 {
     int64_t most = 0;
-    for (int b = b0; b < b1; ++b) most = std::max(most, ctx->numel[b] / 256);
-    return static_cast<int>(std::min<int64_t>(most, eager::kMaxRunElements / 256));
+    for (int b = st.b_lo; b < st.b_hi; ++b) most = std::max(most, ctx->numel[b] / 256);
+    st.largest = static_cast<int>(std::min<int64_t>(most, eager::kMaxRunElements / 256));
+    const int buckets = st.b_hi - st.b_lo;
+    eager::finish_slices(st, buckets, st.want_rate && eager::norms_grouped(st.n_records, buckets));
 }
 
 // Whether the send-buffer rewrite of the late processes runs as its own copy kernel after
@@ -255,7 +257,7 @@ int partial_allreduce(eager_ctx *ctx, int want_mode, const eager_plan *plan, uin
             a.stats.b_hi = e;
             a.stats.n_records = eager::slot_records(a.n + back, ctx->bf16, ctx->launch.block);
             a.stats.tail_count = eager::slot_tail(a.n + back, ctx->bf16);
-            a.stats.largest = largest_records(ctx, b, e);
+            stats_slices(ctx, a.stats);
         }
         hipError_t he = eager::launch_round(a, ctx->bf16, ctx->fast, ctx->launch,
                                             static_cast<hipStream_t>(stream));
@@ -622,7 +624,6 @@ int sgd_step_lars(eager_ctx *ctx, int b0, int b1, const float *update, const eag
     eager::StatsArgs st;
     std::memset(&st, 0, sizeof st);
     stats_layout(ctx, workspace, stats, st);
-    st.largest = largest_records(ctx, b0, b1);
     st.e0 = a.e0;
     st.b_lo = b0;
     st.b_hi = b1;
@@ -635,6 +636,7 @@ int sgd_step_lars(eager_ctx *ctx, int b0, int b1, const float *update, const eag
     }
     st.want_rate = eager::rate_by_bucket(largest, ends, a.n, b1 - b0) ? eager::kRateByBucket : eager::kRate;
     if (st.want_rate == eager::kRateByBucket) st.n_records = largest;
+    else stats_slices(ctx, st);
     st.trust = trust;
     st.wd = ctx->weight_decay;
     st.eps = eps;

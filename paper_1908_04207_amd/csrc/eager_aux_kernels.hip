@@ -782,13 +782,12 @@ int views_average_waves(int n_views)
 
 }  // namespace
 
-hipError_t launch_stats_finish(const StatsArgs &args, hipStream_t stream)
+hipError_t launch_stats_finish(const StatsArgs &a, hipStream_t stream)
 {
-    const int n = args.b_hi - args.b_lo;
-    if (n <= 0 || args.want_rate == kRateByBucket) return hipSuccess;
-    StatsArgs a = args;
+    const int n = a.b_hi - a.b_lo;
+    if (n <= 0 || a.want_rate == kRateByBucket) return hipSuccess;
+    if (a.slices > kStatsMaxSlices || a.slices < 1) return hipErrorInvalidValue;
     const bool grouped = a.want_rate && norms_grouped(a.n_records, n), wide = finish_threads(n) == 1024;
-    finish_slices(a, n, grouped);
     const dim3 grid(static_cast<unsigned>(n), static_cast<unsigned>(a.slices)), threads(wide ? 1024 : 256);
     switch ((a.slices > 1 ? 4 : 0) | (grouped ? 2 : 0) | (wide ? 1 : 0)) {
     case 0: return launch(stats_finish_kernel<false, 256, false>, grid, threads, 0, stream, a);

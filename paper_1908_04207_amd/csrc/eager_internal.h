@@ -57,8 +57,8 @@ struct StatsArgs {
     // trust * |w| / (|u| + wd * |w| + eps), or 1 where a norm is zero
     int want_rate;               // kRateByBucket: by the update kernel itself, which takes a bucket per workgroup
     float trust, wd, eps;
-    // A bucket with many records is added up by several workgroups, at most `slices`, of `per_slice` records each, which
-    // the launcher works out from the records of the largest bucket (finish_slices): one
+    // A bucket with many records is added up by several workgroups, at most `slices`, of `per_slice` records each, worked out
+    // from the records of the largest bucket (finish_slices): one
     // partial each (partials[bucket * kStatsMaxSlices + slice]), and the last of them to arrive adds these.  The bucket's
     // first partial counts the arrivals in its `flag`, zero between launches.
     StatsRecord *partials;
