@@ -761,25 +761,6 @@ __global__ __launch_bounds__(THREADS) void lars_bucket_kernel(const SgdArgs a, c
     }
 }
 
-// Resident wavefronts per CU of the weight-view kernels when the caller leaves it open: what
-// counts is the KiB of loads in flight per CU, about 38 for the update (1 + 2 per view loads
-// per lane, views in chunks of 8) and 26 for the average (one load per view).  25.6 M elements, update: 8 views 553 us
-// with 2, 538 with 3, 559 with 4, uncapped 612; 10 views 725, 710, 704, 759; 16 views 1093, 1144, 1185, 1261; average: 4 views
-// 127.4 with 8, 124.7 with 6, 130.4 with 5, uncapped 139; 6 views 191.0 with 5, 187.9 with 4, 211 with 3; 8 views 255.6 with 4,
-// 257.6 with 3; 12 views 393 and 388; 2 views 62 with 16, 65 with 12.
-int views_sgd_waves(int n_views)
-{
-    const int loads = 1 + 2 * (n_views < 8 ? n_views : 8);
-    const int w = (38 + loads / 2) / loads, least = n_views > 12 ? 2 : 3;
-    return w < least ? least : w;
-}
-int views_average_waves(int n_views)
-{
-    if (n_views < 4) return n_views == 1 ? -1 : 32 / n_views;
-    const int w = 26 / n_views, least = n_views < 12 ? 4 : 3;
-    return w < least ? least : w;
-}
-
 }  // namespace
 
 hipError_t launch_stats_finish(const StatsArgs &a, hipStream_t stream)
@@ -820,14 +801,11 @@ namespace {
 template <typename A>
 hipError_t launch_views(void (*kernel)(A), const A &a, const Launch &cfg, int auto_waves, hipStream_t stream)
 {
-    long long g = (a.n / 4 + 63) / 64;
-    if (g < 1) g = 1;
+    const long long g = views_tiles(a.n);
     if (g * 64 > kMaxGridThreads) return hipErrorInvalidValue;    // these kernels do not stride
     Launch l = cfg;
     l.block = 64;
-    // half of the traffic is stores: few wavefronts per CU, as for the rounds (but 8 views of 200 k elements, 3 tiles per
-    // CU, 5.7 us with 3 at a time and 5.3 without a cap)
-    const int bpc = cfg.blocks_per_cu != 0 ? cfg.blocks_per_cu : g <= 6 * kCus ? -1 : auto_waves;
+    const int bpc = cfg.blocks_per_cu == 0 ? auto_waves : cfg.blocks_per_cu;
     return launch_capped(kernel, a, bpc, l, static_cast<unsigned>(g), stream);
 }
 template <int N, bool MOMENTUM>
@@ -864,7 +842,7 @@ hipError_t launch_few_average(const ViewsArgs &a, bool nt, const Launch &cfg, in
 hipError_t launch_views_sgd(const ViewsArgs &a, bool fast, const Launch &cfg, hipStream_t stream)
 {
     if (a.n <= 0 || a.n_views <= 0) return hipSuccess;
-    const int waves = views_sgd_waves(a.n_views);
+    const int waves = views_sgd_waves(a.n_views, a.n);
     const bool nt = a.n * (4 + 16ll * a.n_views) > kPlainRoundBytes;
     if (a.n_views <= 4)
         return fast ? launch_few_sgd<true, 4>(a, nt, cfg, waves, stream) : launch_few_sgd<false, 4>(a, nt, cfg, waves, stream);
@@ -880,7 +858,7 @@ hipError_t launch_views_sgd(const ViewsArgs &a, bool fast, const Launch &cfg, hi
 hipError_t launch_views_average(const ViewsArgs &a, const Launch &cfg, hipStream_t stream)
 {
     if (a.n <= 0 || a.n_views <= 0) return hipSuccess;
-    const int waves = views_average_waves(a.n_views);
+    const int waves = views_average_waves(a.n_views, a.n);
     const bool nt = a.n * 8ll * a.n_views > kPlainRoundBytes;
     if (a.n_views <= 4) return launch_few_average<4>(a, nt, cfg, waves, stream);
     if (a.n_views <= 8) return launch_few_average<8>(a, nt, cfg, waves, stream);

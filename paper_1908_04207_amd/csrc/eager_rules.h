@@ -183,6 +183,32 @@ inline bool small_round(const SlotArgs &s, long long bytes_per_element)
 // 9.9 and 10.6 at 40 MiB, 14.1 and 13.6 at 64.
 constexpr long long kPlainRoundBytes = 56ll << 20;
 
+// Resident wavefronts per CU of the weight-view kernels when the caller leaves it open, -1: no cap.  Half of the traffic is
+// stores: few, as for the rounds.  What
+// counts is the KiB of loads in flight per CU, about 38 for the update (1 + 2 per view loads
+// per lane, views in chunks of 8) and 26 for the average (one load per view).  25.6 M elements, update: 8 views 553 us
+// with 2, 538 with 3, 559 with 4, uncapped 612; 10 views 725, 710, 704, 759; 16 views 1093, 1144, 1185, 1261; average: 4 views
+// 127.4 with 8, 124.7 with 6, 130.4 with 5, uncapped 139; 6 views 191.0 with 5, 187.9 with 4, 211 with 3; 8 views 255.6 with 4,
+// 257.6 with 3; 12 views 393 and 388; 2 views 62 with 16, 65 with 12.
+// The average of more than 16 views, whose kernel has 16 loads in flight: 17 views of 0.4, 1 and 25.6 M elements 10.6 26.7 561 us
+// with 4, 11.7 27.6 595 with 3; 40 of 0.4, 1 and 4 M 23.6 60.4 239 and 24.6 59.2 213.
+// Up to 6 tiles per CU there is no cap (update of 8 views of 200 k elements 5.7 us with 3 and 5.3 without; average of 64 of 390 k 36.8
+// and 31.6), but for updates of more than 24 views (48 and 64 of 390 k 51 and 70 us with 2, 55 and 75 without).
+inline long long views_tiles(long long n) { return std::max((n / 4 + 63) / 64, 1ll); }
+inline int views_sgd_waves(int n_views, long long n)
+{
+    if (n_views <= 24 && views_tiles(n) <= 6 * kCus) return -1;
+    const int loads = 1 + 2 * (n_views < 8 ? n_views : 8);
+    return std::max((38 + loads / 2) / loads, n_views > 12 ? 2 : 3);
+}
+inline int views_average_waves(int n_views, long long n)
+{
+    if (n_views == 1 || views_tiles(n) <= 6 * kCus) return -1;
+    if (n_views < 4) return 32 / n_views;
+    const bool three = n_views > 16 ? n_views >= 24 && n >= 1 << 20 : n_views >= 12;
+    return std::max(26 / n_views, three ? 3 : 4);
+}
+
 // Slots of the sum without what fills them up.
 inline int sum_terms(const SlotArgs &s)
 {

@@ -255,9 +255,29 @@ static int paced()
     return 0;
 }
 
+// Weight views: a cap from 6 tiles per CU on (updates of more than 24 views: always).
+static int views()
+{
+    const long long line = 6ll * 256 * 256;
+    for (int n_views = 1; n_views <= 64; ++n_views)
+        for (long long n : {1ll, 255ll, line, line + 4, 1ll << 20, 1ll << 33}) {
+            const int update = views_sgd_waves(n_views, n), average = views_average_waves(n_views, n);
+            CHECK((update == -1) == (n <= line && n_views <= 24) && (average == -1) == (n <= line || n_views == 1));
+            for (int w : {update, average}) CHECK(w == -1 || (w >= 2 && w <= 16));
+        }
+    CHECK(views_tiles(1) == 1 && views_tiles(256) == 1 && views_tiles(260) == 2);
+    for (int n_views : {17, 23, 24, 64}) {
+        CHECK(views_average_waves(n_views, (1 << 20) - 1) == 4 && views_average_waves(n_views, 1 << 20) == (n_views < 24 ? 4 : 3));
+        CHECK(views_sgd_waves(n_views, 1 << 20) == 2);
+    }
+    CHECK(views_average_waves(12, 1 << 25) == 3 && views_average_waves(16, 1 << 25) == 3 && views_average_waves(11, 1 << 25) == 4);
+    CHECK(views_sgd_waves(8, 1 << 25) == 3 && views_sgd_waves(9, 1 << 25) == 3 && views_sgd_waves(12, 1 << 25) == 3 && views_sgd_waves(13, 1 << 25) == 2);
+    return 0;
+}
+
 int main()
 {
-    if (lanes() || back() || paced() || narrow() || grids() || finishing() || slices() || norms() || by_bucket() || bytes() || occupancy()) return 1;
+    if (views() || lanes() || back() || paced() || narrow() || grids() || finishing() || slices() || norms() || by_bucket() || bytes() || occupancy()) return 1;
     std::printf("ok\n");
     return 0;
 }
