@@ -859,7 +859,7 @@ hipError_t launch_views_average(const ViewsArgs &a, const Launch &cfg, hipStream
 {
     if (a.n <= 0 || a.n_views <= 0) return hipSuccess;
     const int waves = views_average_waves(a.n_views, a.n);
-    const bool nt = a.n * 8ll * a.n_views > kPlainRoundBytes;
+    const bool nt = views_average_streamed(a.n_views, a.n);
     if (a.n_views <= 4) return launch_few_average<4>(a, nt, cfg, waves, stream);
     if (a.n_views <= 8) return launch_few_average<8>(a, nt, cfg, waves, stream);
     if (a.n_views <= 16) return launch_few_average<16>(a, nt, cfg, waves, stream);

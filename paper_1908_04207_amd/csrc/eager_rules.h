@@ -209,6 +209,16 @@ inline int views_average_waves(int n_views, long long n)
     return std::max(26 / n_views, three ? 3 : 4);
 }
 
+// Whether the average streams its views past the caches.  Up to 56 MiB plain accesses are faster (see kPlainRoundBytes) from 4 views on,
+// of 4 to 8 not below 28 MiB (4: 32), where the views just fit the second-level caches: 1 and 2 views streamed and plain, 18 to 30 MB 4.2
+// to 5.5 and 4.5 to 6.6 us, 34 MB 4.6 and 5.5 (2 views); 4 views of 24 MB 4.4 and 4.5, of 52 MB 7.7 and 6.7; 8 views 4.1 4.4 and 8.1 6.7;
+// 16 views 4.5 4.6 and 9.1 6.9.
+inline bool views_average_streamed(int n_views, long long n)
+{
+    const long long bytes = n * 8 * n_views;
+    return bytes > kPlainRoundBytes || n_views < 4 || (n_views <= 8 && bytes < (n_views == 4 ? 32ll : 28ll) << 20);
+}
+
 // Slots of the sum without what fills them up.
 inline int sum_terms(const SlotArgs &s)
 {
