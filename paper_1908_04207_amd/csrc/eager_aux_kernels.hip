@@ -387,7 +387,8 @@ __global__ __launch_bounds__(64) void views_average_kernel(const ViewsArgs)
 // The two for up to 16 views, whose pointers every wavefront has in registers before it asks for the first of them: read where
 // they are used, line after line of an argument block for 64, they are trips of their own, and the host copies the block with
 // every launch.  Average and update, pointers as they come and this: 20 k elements, 8 views 3.0 3.5 and 2.6 3.3 us, 200 k 3.8 6.3
-// and 3.7 5.3, 10 views 4.0 8.1 and 4.2 6.2; 25.6 M, 6 views 214 417 and 186 411, 8 views 260 557 and 255 550.
+// and 3.7 5.3, 10 views 4.0 8.1 and 4.2 6.2; 25.6 M, 6 views 214 417 and 186 411 (which views are updated
+// with the pointers as they come: launch_views_sgd).
 // An access is a view's base with the tile's first element, uniform, and the lane's offset.  NT: the views are streamed.
 template <bool NT>
 __device__ __forceinline__ f32x4 ld_view(const float *view, long long first, unsigned off)
@@ -846,10 +847,11 @@ hipError_t launch_views_sgd(const ViewsArgs &a, bool fast, const Launch &cfg, hi
     const bool nt = a.n * (4 + 16ll * a.n_views) > kPlainRoundBytes;
     if (a.n_views <= 4)
         return fast ? launch_few_sgd<true, 4>(a, nt, cfg, waves, stream) : launch_few_sgd<false, 4>(a, nt, cfg, waves, stream);
-    if (a.n_views <= 8)
+    // (streamed, 7, 8 and 16 views are faster with the pointers read as they come: 25.6 M elements 471 541 1104 us, with all at once
+    // 479 562 1123; 6, 9 and 12 views 413 620 844 and 408 616 830)
+    if (a.n_views <= (nt ? 6 : 8))
         return fast ? launch_few_sgd<true, 8>(a, nt, cfg, waves, stream) : launch_few_sgd<false, 8>(a, nt, cfg, waves, stream);
-    // (streamed, 16 views are 2 % faster with the pointers read as they come: 25.6 M elements 1104 and 1123 us)
-    if (a.n_views <= (nt ? 12 : 16))
+    if (a.n_views > 8 && a.n_views <= (nt ? 12 : 16))
         return fast ? launch_few_sgd<true, 16>(a, nt, cfg, waves, stream) : launch_few_sgd<false, 16>(a, nt, cfg, waves, stream);
     return fast ? launch_views(views_sgd_kernel<true>, a, cfg, waves, stream)
                 : launch_views(views_sgd_kernel<false>, a, cfg, waves, stream);

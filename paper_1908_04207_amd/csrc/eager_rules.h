@@ -186,8 +186,8 @@ constexpr long long kPlainRoundBytes = 56ll << 20;
 // Resident wavefronts per CU of the weight-view kernels when the caller leaves it open, -1: no cap.  Half of the traffic is
 // stores: few, as for the rounds.  What
 // counts is the KiB of loads in flight per CU, about 38 for the update (1 + 2 per view loads
-// per lane, views in chunks of 8) and 26 for the average (one load per view).  25.6 M elements, update: 8 views 553 us
-// with 2, 538 with 3, 559 with 4, uncapped 612; 10 views 725, 710, 704, 759; 16 views 1093, 1144, 1185, 1261; average: 4 views
+// per lane, views in chunks of 8) and 26 for the average (one load per view).  25.6 M elements, update: 8 views 550 us
+// with 2, 540 with 3, but 4 M 87 and 95; 10 views 708 with 2, 686 with 3, 688 with 4, uncapped 776; 16 views 1093, 1144, 1185, 1261; average: 4 views
 // 127.4 with 8, 124.7 with 6, 130.4 with 5, uncapped 139; 6 views 191.0 with 5, 187.9 with 4, 211 with 3; 8 views 255.6 with 4,
 // 257.6 with 3; 12 views 393 and 388; 2 views 62 with 16, 65 with 12.
 // The average of more than 16 views, whose kernel has 16 loads in flight: 17 views of 0.4, 1 and 25.6 M elements 10.6 26.7 561 us
@@ -199,7 +199,7 @@ inline int views_sgd_waves(int n_views, long long n)
 {
     if (n_views <= 24 && views_tiles(n) <= 6 * kCus) return -1;
     const int loads = 1 + 2 * (n_views < 8 ? n_views : 8);
-    return std::max((38 + loads / 2) / loads, n_views > 12 ? 2 : 3);
+    return std::max((38 + loads / 2) / loads, n_views > 8 && n_views <= 12 ? 3 : 2);
 }
 inline int views_average_waves(int n_views, long long n)
 {

@@ -272,7 +272,7 @@ static int views()
         CHECK(views_sgd_waves(n_views, 1 << 20) == 2);
     }
     CHECK(views_average_waves(12, 1 << 25) == 3 && views_average_waves(16, 1 << 25) == 3 && views_average_waves(11, 1 << 25) == 4);
-    CHECK(views_sgd_waves(8, 1 << 25) == 3 && views_sgd_waves(9, 1 << 25) == 3 && views_sgd_waves(12, 1 << 25) == 3 && views_sgd_waves(13, 1 << 25) == 2);
+    CHECK(views_sgd_waves(8, 1 << 25) == 2 && views_sgd_waves(9, 1 << 25) == 3 && views_sgd_waves(12, 1 << 25) == 3 && views_sgd_waves(13, 1 << 25) == 2);
     for (int n_views : {1, 3, 4, 8, 9, 64}) {
         const long long most = kPlainRoundBytes / 8 / n_views, held = (((n_views == 4 ? 32ll : 28ll) << 20) - 1) / 8 / n_views;
         CHECK(views_average_streamed(n_views, most + 1) && views_average_streamed(n_views, most) == (n_views < 4));
