@@ -457,7 +457,8 @@ hipError_t launch_slots(SlotArgs &s, long long model, const Launch &cfg, hipStre
         return stats ? launch_capped(burst_kernel<BF16, FAST, NTS, OPT, true>, s, bpc, cfg, grid, st)
                      : launch_capped(burst_kernel<BF16, FAST, NTS, OPT, false>, s, bpc, cfg, grid, st);
     // (launch options are for the general kernel)
-    if (cfg.chunk == 0 && small && cfg.block == 64 && !cfg.xcd_map && bpc < 0 && !NTS && short_round(s)) {
+    if (cfg.chunk == 0 && small && cfg.block == 64 && !cfg.xcd_map && bpc < 0 && !NTS && short_round(s) &&
+        short_pays(s, BF16, FAST, !plain, OPT)) {
         ShortLauncher *const f = BF16 ? (FAST ? launch_short_bf16_fast : launch_short_bf16)
                                       : (FAST ? launch_short_f32_fast : launch_short_f32);
         return f(s, !plain, st);

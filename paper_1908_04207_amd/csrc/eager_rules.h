@@ -281,8 +281,8 @@ void fill_chunk(const SlotArgs &s, bool any_order, long long first, long long n,
     a.h.first = a.bits[0];
 }
 
-// Whether a small run goes to the kernel of short lists: it was ahead of chunk_kernel wherever both can take the list
-// (eager_short.h has the times).  (Statistics have arguments of their own; a launch is within 32-bit offsets.)
+// Whether the kernel of short lists can take a small run.  (Statistics have arguments of their own; a launch is within
+// 32-bit offsets.)
 inline bool short_round(const SlotArgs &s)
 {
     return !s.stats.stats && sum_terms(s) + s.h.n_copy <= 16 && s.h.n_copy <= kShortCopies && s.h.n <= kChunkElements;
@@ -368,6 +368,25 @@ inline bool chunk_paced(const SlotArgs &s, int slots, bool bf16, bool update, in
 {
     return slots <= 16 && s.h.n_copy >= (bf16 ? 5 : 6) && s.h.n <= static_cast<long long>(resident) * kCus * 256 &&
            s.h.n * round_bytes(s, update) > kPlainRoundBytes;
+}
+
+// Whether a run that the kernel of short lists can take (short_round) is its: where it is ahead of chunk_kernel, which is
+// nearly everywhere (eager_short.h has the times).  Not so, short_kernel and chunk_kernel:
+//   * where copies are stored one at a time (chunk_paced), which takes the wavefronts that chunk_kernel has registers for: 8
+//     processes, 7 late, 1.06 M elements, fp32 fused 15.9 and 14.6 us, bf16 13.8 and 12.1
+//   * bf16 in any order, beyond the 128 k elements up to which a lane may have one, from 8 streams on: 12 processes with 4 send buffers 262 k 4.76 and 4.43 us, 8
+//     processes 3.06 and 2.93 (4 processes 2.79 and 2.79)
+//   * bf16 in fixed order, one element to a lane, 4 or more send buffers among many streams: 8 processes with 8 send
+//     buffers 1024 elements 3.16 and 2.86 us, 131 k 4.52 and 3.70; with 4, 4 late 2.96 and 2.87; with 4, on time, 2.68 and 2.74
+inline bool short_pays(const SlotArgs &s, bool bf16, bool fast, bool nt, bool update)
+{
+    const int terms = sum_terms(s), slots = terms + s.h.n_copy;
+    if (nt && chunk_paced(s, slots, bf16, update, 32)) return false;
+    if (!bf16) return true;
+    if (fast) return s.h.n <= 1 << 17 || slots < 8;
+    int fp32 = 0;
+    for (int j = 0; j < terms; ++j) fp32 += !(s.slot[j] & kSlotBf16);
+    return fp32 < 4 || slots + s.h.n_copy <= 12 || !chunk_narrow(s.h.n, slots, s.h.n_copy, bf16, false, 0);
 }
 
 // Resident wavefronts per CU of the burst kernel, -1: no cap.

@@ -92,11 +92,7 @@ __device__ __forceinline__ void short_body(const ShortArgs<CH> &h, unsigned at0,
     if (copies && in) {
 #pragma unroll
         for (int j = kHalf; j < CH; ++j)
-            if (copies >> j & 1u) {
-                st_vec<W, NT>(h.dst[j - kHalf], off, x[j]);
-                if (NT && W == 4 && CH == 16 && (h.shape >> kShortForm & 3u) == kPaced)
-                    __builtin_amdgcn_s_waitcnt(kStoresArrived);
-            }
+            if (copies >> j & 1u) st_vec<W, NT>(h.dst[j - kHalf], off, x[j]);
     }
     if constexpr (FAST) s = s + s2;
     if constexpr (FAST && BF16) s = s + (s3 + s4);
@@ -144,15 +140,8 @@ template <bool BF16, bool FAST, bool NT, bool OPT, int CH>
 hipError_t launch_short_sized(const SlotArgs &s, int slots, hipStream_t st)
 {
     const bool narrow = chunk_narrow(s.h.n, slots, s.h.n_copy, BF16, false, 0);
-    int form = narrow ? kNarrow : kWide;
-    if constexpr (NT && CH == 16)
-        if (!narrow && chunk_paced(s, slots, BF16, OPT, 32)) {
-            // (the kernel is asked for its registers once, and only where all else speaks for it)
-            static const int resident = kernel_waves(short_kernel<BF16, FAST, NT, OPT, CH>);
-            if (chunk_paced(s, slots, BF16, OPT, resident)) form = kPaced;
-        }
     ShortArgs<CH> a;
-    fill_short(s, FAST, form, a);
+    fill_short(s, FAST, narrow ? kNarrow : kWide, a);
     const long long g = narrow ? (s.h.n + 63) / 64 : round_workgroups(s.h.n, BF16, 64);
     return launch(short_kernel<BF16, FAST, NT, OPT, CH>, dim3(static_cast<unsigned>(g)), dim3(64), 0, st, a);
 }

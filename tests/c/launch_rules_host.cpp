@@ -281,9 +281,43 @@ static int views()
     return 0;
 }
 
+// Short lists that chunk_kernel keeps: copies stored one at a time, bf16 in any order with 8 streams and four elements to a lane,
+// bf16 in fixed order with 4 send buffers among many streams and one element to a lane.
+static int short_lists()
+{
+    auto is = [](int pending, int grads, int copies, bool bf16, bool fast, long long n, bool nt = false, bool update = true) {
+        SlotArgs s{};
+        s.h.n = n;
+        int k = 0;
+        auto push = [&](unsigned long long tag) {
+            s.slot[k] = 0x10000ull * (k + 1) | tag;
+            ++k;
+        };
+        const unsigned long long type = bf16 ? kSlotBf16 + 0ull : 0ull;
+        for (int j = 0; j < pending; ++j) push(kAdd);
+        for (int j = 0; j < grads; ++j) push(kAdd | type);
+        if (k % kBurst) push(kSkip);
+        s.h.n_sum = k;
+        s.h.n_copy = copies;
+        for (int j = 0; j < copies; ++j) push(kSkip | kSlotCopy | type);
+        return short_round(s) && short_pays(s, bf16, fast, nt, update);
+    };
+    const long long wide = (1 << 17) + 1;
+    for (bool fast : {false, true}) {
+        CHECK(is(8, 8, 0, false, fast, 64) && is(8, 8, 0, false, fast, wide) && is(0, 1, 7, false, fast, 1 << 20));
+        CHECK(!is(0, 1, 7, false, fast, 1'060'000, true) && is(0, 3, 5, false, fast, 1'060'000, true));
+        CHECK(!is(0, 1, 7, true, fast, 1'300'000, true) && is(0, 1, 8, true, fast, 64) && !is(0, 1, 9, true, fast, 64));
+        CHECK(is(2, 4, 5, true, fast, 64) && is(4, 4, 0, true, fast, 64) && is(4, 8, 0, true, fast, 64));
+    }
+    CHECK(!is(8, 8, 0, true, false, 64) && !is(4, 12, 0, true, false, 1 << 17) && !is(4, 4, 4, true, false, 64) && !is(4, 1, 8, true, false, 64));
+    CHECK(is(3, 13, 0, true, false, 64) && is(8, 8, 0, true, false, wide) && is(8, 8, 0, true, true, 64));
+    CHECK(!is(0, 8, 0, true, true, wide) && is(0, 7, 0, true, true, wide) && is(0, 8, 0, true, false, wide));
+    return 0;
+}
+
 int main()
 {
-    if (views() || lanes() || back() || paced() || narrow() || grids() || finishing() || slices() || norms() || by_bucket() || bytes() || occupancy()) return 1;
+    if (short_lists() || views() || lanes() || back() || paced() || narrow() || grids() || finishing() || slices() || norms() || by_bucket() || bytes() || occupancy()) return 1;
     std::printf("ok\n");
     return 0;
 }
