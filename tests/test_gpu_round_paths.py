@@ -88,16 +88,19 @@ def test_short_lists_of_every_length(eb, dtype, order, n):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("form", ["narrow", "chunks of 8", "chunks of 16", "bursts"])
-def test_signed_zeros_and_infinities_in_every_form(eb, dtype, form):
+@pytest.mark.parametrize("form,P,n", [
+    ("short, 8 streams", 4, 523), ("short, 16 streams, one element to a lane", 9, 523),
+    ("short, 16 streams, four", 8, 131_072 + 523), ("long, one element to a lane", 17, 523),
+    ("chunks of 8", 9, 523), ("chunks of 16", 9, 523), ("bursts", 4, 0)])
+def test_signed_zeros_and_infinities_in_every_form(eb, dtype, form, P, n):
     """Late, late again with a pending buffer, on time with one (a pair), everybody on time: gradients, pending
     buffers, parameters and momentum of -0.0, and infinities and NaN that meet in a sum, a pair or not at all, bit
-    for bit in fixed order - with branches (chunk_kernel, one element to a lane and four) and with the masks of
-    burst_kernel, where what is masked out is +0.0.  In the ragged tail too."""
-    P = 4 if form == "bursts" else 9
+    for bit in fixed order - with branches (short_kernel with up to 8 and up to 16 streams, chunk_kernel with longer
+    lists and where a launch option asks for it, one element to a lane and four) and with the masks of burst_kernel,
+    where what is masked out is +0.0.  In the ragged tail too."""
     # every mask moves at least all gradients, w and v, the latter two read and written
     per = P * (2 if dtype == "bf16" else 4) + 16
-    n = LINE // per + 303 if form == "bursts" else 523
+    n = n or LINE // per + 303
     assert (n * per > LINE) == (form == "bursts")
     pair = Pair(eb, P, [0], [n], (n + 7) // 8 * 8, dtype, 0, seed=6)
     if form.startswith("chunks"):
