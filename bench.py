@@ -421,7 +421,7 @@ def measure(k: int, steps: int, warmup: int, order: str, calib: Calibration | No
         "llc_resident_bytes_per_step": resident,
         "hbm_frac": round((total_b - resident * steps) / kern_s / 1e9 / HBM_PEAK_GBS, 4),
         "cache_resident": resident >= step_b,
-        "kernels_per_round": ("chunk_kernel (a small model: everything at once)" if resident >= step_b else
+        "kernels_per_round": ("short_kernel, chunk_kernel for long lists (a small model: everything at once)" if resident >= step_b else
                               "burst_kernel; in rounds the library splits, burst_kernel (reduction + "
                               "update) then carry_kernel (late gradients into the send buffers)"),
     }

@@ -320,15 +320,17 @@ typedef struct {
  *   stats      device array of n_buckets entries, 16-byte aligned, caller-owned; NULL detaches
  *   workspace  device memory, 16-byte aligned, caller-owned, at least
  *              eager_stats_workspace_bytes() bytes; the library keeps the bucket table, one
- *              32-byte record per 256 elements and 129 per bucket there.  It
- *              must stay allocated while attached, and is shared by all calls of this context: with
+ *              32-byte record per 256 elements and 129 per bucket there, among them a count per
+ *              bucket that is zero between calls.  It must stay allocated while attached, nobody
+ *              else may write to it (a count that is not zero spoils the bucket's later totals until
+ *              the next attach), and it is shared by all calls of this context: with
  *              statistics attached, the calls of a context must be ordered (one stream, or
  *              events), and no other context may use the same workspace concurrently
- *   stream     the bucket table is written into the workspace by a small kernel on this stream
+ *   stream     the bucket table is written and the counts are cleared by a small kernel on this stream
  *              (rounds that use the statistics must be ordered after it, e.g. on the same
  *              stream)
  * Needs the launch key "chunk" of eager_tuning.h at 0 (default) or 16; otherwise the next round
- * fails with ESTATE.  One or two extra small kernels run per launch.
+ * fails with ESTATE.  One extra small kernel runs per launch.
  * Errors: EINVAL (NULL ctx, workspace too small or misaligned), ENOMEM, EDEVICE.
  */
 int eager_stats_workspace_bytes(const eager_ctx *ctx, int64_t *bytes);
@@ -347,7 +349,8 @@ int eager_stats_attach(eager_ctx *ctx, eager_bucket_stats *stats, void *workspac
  * eager_set_update_rule:
  *     g = rate_b * (u + weight_decay * w);  v' = mu * v + g;
  *     w' = w - lr * (nesterov ? g + mu * v' : v')
- * Two passes over the buckets (norms, then update: 8 + 20 bytes per element); padding between
+ * Two passes over the buckets (norms, then update: 8 + 20 bytes per element), or one (20) where no
+ * bucket of the range is large; padding between
  * buckets takes the rate of the bucket before it.
  * Needs eager_stats_attach: the workspace holds the partial sums, and stats[b] of every bucket
  * in [b0, b1) is overwritten with sumsq_update, sumsq_params (before the step), nonfinite and
@@ -375,7 +378,7 @@ int eager_sgd_step_lars(eager_ctx *ctx, int b0, int b1, const float *update, con
  * EAGER_STATIC_MAX_ELEMENTS elements (first bucket start to last bucket end); beyond that the
  * call returns EAGER_ELIMIT and launches nothing.
  * All calls on one GPU share the array and it keeps the last call's contents (every record that
- * is read has been written by the same call before, so nothing needs clearing): calls that
+ * is read has been written by the same call before, and the call clears the counts it uses): calls that
  * overlap in time on one GPU - two streams, two contexts, two threads - race; order them.
  * Errors: as eager_sgd_step_lars without ESTATE; EINVAL also for a NULL or misaligned stats;
  * ELIMIT; EDEVICE.

@@ -1,4 +1,4 @@
-// gfx950 kernels around the round: the second stage of the per-bucket statistics, the update
+// gfx950 kernels around the round: the finishing of the per-bucket statistics, the update
 // rule alone on a receive buffer (plain, or with a layer-wise rate per bucket: norms pass, rate,
 // update pass), and what processes that lag by more than one round need - a late gradient
 // stashed into a send buffer, the update of several weight views from one read of the result, the
@@ -540,7 +540,8 @@ __global__ __launch_bounds__(256) void sgd_kernel(const SgdArgs a)
 }
 
 // ---- update rule with a rate per bucket (layer-wise adaptive rate scaling) ------------------
-// Two passes, because the norms of a bucket must be complete before its first element moves:
+// Two passes, because the norms of a bucket must be complete before its first element moves (or one, where a
+// workgroup holds its bucket: lars_bucket_kernel):
 // norms_kernel leaves the same per-wavefront records as a round with statistics (finished by
 // stats_finish_kernel, which also forms the rate), lars_kernel applies
 //     g = rate_b * (u + wd*w);  v' = mu*v + g;  step = nesterov ? g + mu*v' : v';  w' = w - lr*step

@@ -68,7 +68,7 @@ struct StatsArgs {
 constexpr int kRate = 1, kRateByBucket = 2;
 constexpr int kStatsMaxSlices = 64;
 // The workspace: bucket table (16 bytes each), a record for each of `stats_tiles` tiles, (n_buckets + 1) blocks of 64 lane
-// records, kStatsMaxSlices partials per bucket.
+// records, kStatsMaxSlices partials per bucket, the first of which counts arrivals.
 inline long long stats_tiles(long long first, long long end) { return (end - first) / 256 + 8; }
 constexpr long long kStatsRecordsPerSlice = 4096;
 

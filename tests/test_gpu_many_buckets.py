@@ -1,5 +1,5 @@
 """Per-bucket statistics and the layer-wise rule of models with many buckets: both sizes of the
-finishing workgroup, with and without a first stage, next to buckets of one element; and of a model
+finishing workgroup, with and without slices, next to buckets of one element; and of a model
 large enough for the norms pass in groups of tiles.  Against plain 64-bit sums."""
 import numpy as np
 import pytest
@@ -85,7 +85,7 @@ def test_sums_and_rates(eb, count, large):
     [52_001, 60_000, 2048 * 20, 7, 90_002] * 240])
 def test_norms_in_groups_of_tiles(eb, num):
     """More than 50 M elements: groups of 8 tiles that lie inside one bucket, that buckets share, that
-    end with the run; enough records for the first stage; a range of buckets for which groups are too
+    end with the run; enough records for slices; a range of buckets for which groups are too
     few; more buckets than the large finishing workgroups are for."""
     off, n = [], 0
     for m in num:

@@ -274,7 +274,7 @@ def test_layerwise_rate_update(eb, k, clip, order, wd, nesterov):
 
 
 def test_bucket_statistics_are_reproducible(eb):
-    """No atomics, fixed trees: two runs of the same rounds give the same bits."""
+    """Fixed trees, whoever arrives last: two runs of the same rounds give the same bits."""
     cfg = shapes.scaled(shapes.config(2), 5000)
     bt = cfg.buckets
     outs = []
@@ -956,7 +956,7 @@ def test_seeded_random_cases_bitwise(eb, seed):
 
 def test_bucket_statistics_of_a_bucket_with_many_records(eb):
     """A bucket of 4.4 M elements between small ones: its 17 k wavefront records are added up in
-    slices by the first-stage kernel (more than 4096 records), the small buckets' directly; sums
+    slices by several workgroups (more than 12 k records), the small buckets' by one each; sums
     against the oracle's numpy sums, fused round and layer-wise step, a range that starts inside
     the run."""
     from oracle import eager_oracle as eo

@@ -227,7 +227,7 @@ def test_statistics_of_a_streamed_round(eb, dtype):
 @pytest.mark.parametrize("num", [
     [2048 * 3, 100, 2047, 2049, 5, 256, 2048],            # groups of 8 tiles begin and end everywhere
     [3], [255, 4096, 1], [2048 * 40 + 3, 1_400_001, 9],
-    [13_000_001, 40, 2_000_000]])                         # enough records for the first stage
+    [13_000_001, 40, 2_000_000]])                         # enough records for slices
 def test_layerwise_norms_by_groups_of_tiles(eb, num):
     """Norms, rates and the layer-wise step over buckets that begin and end anywhere in groups of 8
     tiles (the norms pass itself works in groups from 50 M elements only), in a workspace that a round
