@@ -1,6 +1,6 @@
 // gfx950 kernel of the round for small runs, whose time is the one from launch to the last store:
 // a launch, one trip to the arguments, one trip to the streams.  Lists of up to 16 streams have a kernel of their own
-// (eager_short.h); this one takes the longer ones, rounds with by-products and the launch options.  Included by the files that
+// (eager_short.h); this one takes the longer ones, those that short_pays leaves to it, rounds with by-products and the launch options.  Included by the files that
 // instantiate it, one per gradient type and order, with and without by-products (compiled side by side).
 #pragma once
 

@@ -86,17 +86,8 @@ inline bool norms_grouped(long long tiles, int n_buckets)
     return tiles >= 3 << 16 && tiles >= 128ll * n_buckets;
 }
 
-// The slices of the finishing kernel, for the largest of the launch's `buckets`: 4096 records to a workgroup - one in 8 where
-// they come in groups - which is one trip to memory for 1024 threads and two for 256, or as many more as 64 slices come to.
-// Half or a quarter as many are faster while that makes no more workgroups than CUs, most of which have nothing to do where
-// the other buckets are small (1 bucket of 12 k
-// records 5.4 us with 4096, 5.0 with 1024; but up to 4 k in slices, 1.5 M elements in 22 buckets, norms and layer-wise step
-// 27.6 us, 26.0 with one workgroup to a bucket; 5 of up to 50 k 6.3 and 5.7; but 48 of up to 20 k 6.4 and 11.0).  A first launch for
-// the slices and a second for the totals, which this was, took 8.9, 9.6 and 9.7; and 7.8 for 161 of up to 9 k, 6.7 now.
-// Two or three slices are a trip less and a count of arrivals more: see few_slices.
-// Groups: 800 buckets of 10 k elements and one of 70 M 26.6 us in 64 slices, 14.5 in 9.  Slices of the largest bucket's
-// records, not of the run's: 8 buckets of 273 k each 19.8 us in 8 slices, 13.6 in 64 (two launches 16.9).
 constexpr int kNormsTiles = 8;         // records of norms_kernel come in groups of so many
+
 // Whether 2 or 3 slices are worth it.  Not where one workgroup has the records in about a trip, nor where those of the other
 // buckets that have nothing to do (n slices are n workgroups to every bucket) do not all fit the chip beside them; of
 // 256 threads, which take more trips, up to 1536 buckets.  Two processes with norms, one bucket of 1.1, 2 and 3.1 M elements among
@@ -108,6 +99,16 @@ inline bool few_slices(long long records, long long slices, int buckets)
     if (finish_threads(buckets) < 1024) return records > 5632 && buckets <= 1536;
     return records > (buckets <= 64 ? 5632 : 7168) && slices * buckets < 2 * kCus;
 }
+
+// The slices of the finishing kernel, for the largest of the launch's `buckets`: 4096 records to a workgroup - one in 8 where
+// they come in groups - which is one trip to memory for 1024 threads and two for 256, or as many more as 64 slices come to.
+// Half or a quarter as many are faster while that makes no more workgroups than CUs, most of which have nothing to do where
+// the other buckets are small (1 bucket of 12 k records 5.4 us with 4096, 5.0 with 1024; but up to 4 k in slices, 1.5 M elements in 22 buckets, norms and layer-wise step
+// 27.6 us, 26.0 with one workgroup to a bucket; 5 of up to 50 k 6.3 and 5.7; but 48 of up to 20 k 6.4 and 11.0).  A first launch for
+// the slices and a second for the totals, which this was, took 8.9, 9.6 and 9.7; and 7.8 for 161 of up to 9 k, 6.7 now.
+// Two or three slices are a trip less and a count of arrivals more: see few_slices.
+// Groups: 800 buckets of 10 k elements and one of 70 M 26.6 us in 64 slices, 14.5 in 9.  Slices of the largest bucket's
+// records, not of the run's: 8 buckets of 273 k each 19.8 us in 8 slices, 13.6 in 64 (two launches 16.9).
 inline void finish_slices(StatsArgs &a, int buckets, bool grouped)
 {
     const long long unit = grouped ? kNormsTiles : 1, most = (a.largest + unit - 1) / unit;
@@ -184,11 +185,10 @@ inline bool small_round(const SlotArgs &s, long long bytes_per_element)
 constexpr long long kPlainRoundBytes = 56ll << 20;
 
 // Resident wavefronts per CU of the weight-view kernels when the caller leaves it open, -1: no cap.  Half of the traffic is
-// stores: few, as for the rounds.  What
-// counts is the KiB of loads in flight per CU, about 38 for the update (1 + 2 per view loads
-// per lane, views in chunks of 8) and 26 for the average (one load per view).  25.6 M elements, update: 8 views 550 us
-// with 2, 540 with 3, but 4 M 87 and 95; 10 views 708 with 2, 686 with 3, 688 with 4, uncapped 776; 16 views 1093, 1144, 1185, 1261; average: 4 views
-// 127.4 with 8, 124.7 with 6, 130.4 with 5, uncapped 139; 6 views 191.0 with 5, 187.9 with 4, 211 with 3; 8 views 255.6 with 4,
+// stores: few, as for the rounds.  What counts is the KiB of loads in flight per CU, about 38 for the update (1 + 2 per
+// view loads per lane, views in chunks of 8) and 26 for the average (one load per view).  25.6 M elements, update: 8 views
+// 550 us with 2, 540 with 3, but 4 M 87 and 95; 10 views 708 with 2, 686 with 3, 688 with 4, uncapped 776; 16 views 1093,
+// 1144, 1185, 1261; average: 4 views 127.4 with 8, 124.7 with 6, 130.4 with 5, uncapped 139; 6 views 191.0 with 5, 187.9 with 4, 211 with 3; 8 views 255.6 with 4,
 // 257.6 with 3; 12 views 393 and 388; 2 views 62 with 16, 65 with 12.
 // The average of more than 16 views, whose kernel has 16 loads in flight: 17 views of 0.4, 1 and 25.6 M elements 10.6 26.7 561 us
 // with 4, 11.7 27.6 595 with 3; 40 of 0.4, 1 and 4 M 23.6 60.4 239 and 24.6 59.2 213.
@@ -374,8 +374,8 @@ inline bool chunk_paced(const SlotArgs &s, int slots, bool bf16, bool update, in
 // nearly everywhere (eager_short.h has the times).  Not so, short_kernel and chunk_kernel:
 //   * where copies are stored one at a time (chunk_paced), which takes the wavefronts that chunk_kernel has registers for: 8
 //     processes, 7 late, 1.06 M elements, fp32 fused 15.9 and 14.6 us, bf16 13.8 and 12.1
-//   * bf16 in any order, beyond the 128 k elements up to which a lane may have one, from 8 streams on: 12 processes with 4 send buffers 262 k 4.76 and 4.43 us, 8
-//     processes 3.06 and 2.93 (4 processes 2.79 and 2.79)
+//   * bf16 in any order, beyond the 128 k elements up to which a lane may have one, from 8 streams on: 12 processes with
+//     4 send buffers, 262 k 4.76 and 4.43 us, 8 processes 3.06 and 2.93 (4 processes 2.79 and 2.79)
 //   * bf16 in fixed order, one element to a lane, 4 or more send buffers among many streams: 8 processes with 8 send
 //     buffers 1024 elements 3.16 and 2.86 us, 131 k 4.52 and 3.70; with 4, 4 late 2.96 and 2.87; with 4, on time, 2.68 and 2.74
 inline bool short_pays(const SlotArgs &s, bool bf16, bool fast, bool nt, bool update)
