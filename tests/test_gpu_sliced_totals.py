@@ -57,3 +57,36 @@ def test_totals(num):
             rate = torch.where((su > 0) & (sw > 0), rate, torch.ones_like(rate))
             assert ((first.view(torch.float32).view(-1, 8)[:, 6].double() - rate).abs() <= 1.2e-7 * rate).all()
     ctx.close()
+
+
+def test_totals_in_a_graph():
+    """A captured round with norms, replayed between eager ones of the same context: the count of arrivals is left at
+    zero by both."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1908_04207_amd import binding as eb
+    dev, off, num = torch.device("cuda:0"), [0, 3_200_004, 3_200_008], [3_200_001, 4, 2_900_003]
+    n = off[-1] + num[-1]
+    G, u, unread = torch.empty(n, device=dev).normal_(0.0, 1e-3), torch.empty(n, device=dev), torch.zeros(4, device=dev)
+    ctx = eb.Context(1, off, num)
+    raw = torch.empty(len(num) * 32, dtype=torch.uint8, device=dev)
+    need = ctx.eager_stats_workspace_bytes()
+    ws = torch.full((need,), 0x5A, dtype=torch.uint8, device=dev)
+    ctx.eager_stats_attach(raw, ws, need)
+
+    def call(k):
+        ctx.eager_partial_allreduce(eb.make_plan(eb.MAJORITY, 1, k, 1), [G], [unread], recv=u)
+
+    call(0)
+    torch.cuda.synchronize()
+    want = raw.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(1)
+    for k in range(2, 5):
+        for again in (graph.replay, lambda: call(k)):
+            raw.fill_(0x5A)
+            again()
+            torch.cuda.synchronize()
+            assert torch.equal(raw, want), k
+    ctx.close()
